@@ -164,6 +164,33 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
+// A buffer descriptor over `bytes` bytes at p: loads through it return zero behind the end.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, int bytes) {
+  const uint64_t u = reinterpret_cast<uint64_t>(p);  // the same for all lanes, in scalar registers
+  const uint64_t lo = uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(u)))),
+                 hi = uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(u >> 32))));
+  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(lo | (hi << 32)), 0,
+                                           __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
+}
+// 16 bytes per lane from memory straight into LDS: the wavefront's 64 chunks land at `dst` (the same
+// for all lanes) one after the other, each lane choosing what it reads (`lane_off`; `off` is the
+// same for all lanes).  Arrival is waited for with wait_vm<younger loads that may still be on
+// their way>().
+__device__ __forceinline__ void load_lds16(__amdgpu_buffer_rsrc_t src, int lane_off, int off, uint16_t* dst) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (__attribute__((address_space(3))) void*)dst, 16, lane_off, off, 0, 0);
+}
+template <int N>
+__device__ __forceinline__ void wait_vm() {
+  static_assert(N >= 0 && N < 64, "six bits");
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+// All LDS traffic of the wavefront done (as the intrinsic, so that the compiler knows it: vmcnt 63,
+// expcnt 7, lgkmcnt 0).
+__device__ __forceinline__ void wait_lgkm0() {
+  __builtin_amdgcn_s_waitcnt(0xC07F);
+  asm volatile("" ::: "memory");
+}
+
 // Deterministic block-wide sum (fixed tree): every thread gets the total.
 // `buf` holds one double per wave; blockDim.x must be a multiple of 64 and <= 1024.
 __device__ __forceinline__ double block_sum(double v, double* buf) {

@@ -8,13 +8,14 @@
 // operands of v_mfma_f32_32x32x16_bf16 want (lane l: row l % 32, eight consecutive k from
 // 8 * (l / 32)).
 //
-// A workgroup (8 wavefronts) computes 256 tokens x 256 features = two heads; a wavefront owns 64
-// tokens x one head's 128 features (2 x 4 accumulator blocks: six LDS operand reads feed eight
-// matrix instructions).  The feature pair (c, c + 64) that the rotary embedding mixes lives in the same
-// lane and register of accumulator blocks j and j + 2, so the rotation needs no exchange.  The
+// A workgroup (4 wavefronts) computes 256 tokens x 256 features = two heads; a wavefront owns 128
+// tokens x one head's 128 features (4 x 4 accumulator blocks: eight LDS operand reads feed sixteen
+// matrix instructions).  The feature pair (c, c + 64) that the rotary embedding mixes lives in the
+// same lane and register of accumulator blocks j and j + 2, so the rotation needs no exchange.  The
 // rotated tile goes through LDS once so that every lane stores 16 contiguous bytes of a token's
 // head vector.
 #include <algorithm>
+#include <type_traits>
 
 #include "d2o_internal.h"
 #include "device_utils.h"
@@ -22,17 +23,19 @@
 namespace d2o {
 namespace {
 
-constexpr int kBM = 256, kBN = 128, kBK = 32;  // kBN: one head; a workgroup's tile holds kHeadsPerWg of them
-constexpr int kHeadsPerWg = 2, kThreads = 512;
-constexpr int kLd = kBK;                     // LDS pitch (elements) of the operand tiles: 64 bytes = four 16-byte chunks,
-                                             // chunk k of row r stored at position k ^ ((r >> 2) & 3): the 16 lanes of a
-                                             // 128-bit access phase then cover all 64 banks once, for the staging stores
-                                             // (four consecutive rows x four chunks) and for the operand reads (sixteen
-                                             // consecutive rows, one chunk)
-constexpr int kLdC = kBN + 8;                // LDS pitch of the result tile
-constexpr int kOperandElems = 2 * (kBM + kHeadsPerWg * kBN) * kLd;  // two stages
-constexpr int kResultElems = kBM / 2 * kLdC;          // the result tile passes through LDS in two halves
-constexpr int kSmemElems = kOperandElems > kResultElems ? kOperandElems : kResultElems;
+constexpr int kBM = 256, kBN = 128, kBK = 64;  // kBN: one head; a workgroup's tile holds kHeadsPerWg of them
+constexpr int kHeadsPerWg = 2, kThreads = 256;
+constexpr int kLd = kBK;                     // LDS pitch (elements) of the operand tiles: 128 bytes = eight 16-byte chunks,
+                                             // chunk k of row r stored at position k ^ ((r >> 1) & 7): the 16 lanes of a
+                                             // 128-bit access phase then cover all 64 banks once
+constexpr int kTokenStages = 3, kWeightStages = 2;  // k-tiles of the two operands in LDS
+constexpr int kStageElems = kBM * kLd;       // (kBM = kHeadsPerWg * kBN)
+constexpr int kSmemBytes = (kTokenStages + kWeightStages) * kStageElems * 2;  // all 160 KB of a CU
+constexpr int kCus = 256;                    // workgroups that run at a time, one per CU
+
+enum Loads { kNothing, kTokens, kWeights };
+template <Loads W>
+using LoadsOf = std::integral_constant<Loads, W>;
 
 struct QkvArgs {
   const uint16_t* X;
@@ -42,183 +45,263 @@ struct QkvArgs {
   double log2_base;
 };
 
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void qkv_rope_bf16(QkvArgs a) {
-  __shared__ __attribute__((aligned(16))) uint16_t smem[kSmemElems];
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, m = lane & 31, h = lane >> 5;
+// What bounds it: the matrix core, which on operands that toggle like these runs at the clock the
+// power limit leaves (a bare loop of these instructions on random data reaches 1.7 PFLOP/s).  One
+// wavefront per SIMD with 256 accumulator registers reads 8 KB of operands per 16 instructions
+// (half of what LDS delivers in their time); with two wavefronts of 64 x 128 it was 12 KB per 16.
+// k-tiles go from memory to LDS without passing through registers (the swizzle applied to the
+// addresses the lanes read from) and hold whole 128-byte lines of a row: with k-tiles of 32
+// every line was fetched twice.  The operand reads of the next quarter tile and the loads are placed between the
+// matrix instructions of the current one, so the matrix core only waits at the barrier, once
+// per tile.  The workgroups are persistent (one per CU): the first k-tiles of the next output
+// tile arrive during the epilogue, and the workgroups of an XCD stay close enough to each other
+// that a line one of them fetched is still in the XCD's L2 when the others ask for it.
+// 32768 tokens x 4096 -> 96 heads: 2.5-2.6 ms = 1.27-1.3 PFLOP/s (8 wavefronts, k-tiles of 32
+// through registers, one output tile per workgroup: 3.3-3.4 ms).  A k-tile takes 2250 cycles of
+// which 2048 are matrix instructions; an output tile's epilogue (6 us of a 100 us tile) is not
+// overlapped.
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void qkv_rope_bf16(QkvArgs a, int nft, int ntiles, int nwg) {
+  extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, m = lane & 31, h = lane >> 5;
+  const int nheads = a.Hq + 2 * a.Hkv;
+  const int wm = w & 1, wn = w >> 1;      // the wavefront's 128 tokens, and which head of the pair
+  const int row_bytes = a.hidden * 2;
+  const bool half = a.hidden % kBK != 0;  // the last k-tile has 32 columns
+  const int nfull = a.hidden / kBK, nkt = nfull + (half ? 1 : 0);
   // Workgroups go to the eight XCDs round-robin in launch order.  Each XCD takes one eighth of
   // the heads (its slice of W stays close to it) and walks the token tiles with its heads as
   // the fast index, so the workgroups that run together share a few token tiles and that slice.
-  int ftile = blockIdx.x;  // feature tile = a pair of heads out of [Q heads | K heads | V heads]
-  int rt = blockIdx.y;     // token tile
-  if (gridDim.x % 8 == 0) {
-    const int lin = blockIdx.x + gridDim.x * blockIdx.y, xcd = lin & 7, s_ = lin >> 3, fpx = gridDim.x / 8;
-    ftile = xcd * fpx + s_ % fpx;
-    rt = s_ / fpx;
+  auto tile_of = [&](int lin, int& ftile, int& rt) {  // ftile: a pair of heads out of [Q heads | K heads | V heads]
+    if (nft % 8 == 0) {
+      const int xcd = lin & 7, s_ = lin >> 3, fpx = nft / 8;
+      ftile = xcd * fpx + s_ % fpx;
+      rt = s_ / fpx;
+    } else {
+      ftile = lin % nft;
+      rt = lin / nft;
+    }
+  };
+  // ---- loads.  One instruction fills 8 rows of a k-tile (64 lanes x 16 bytes, consecutive in LDS); a
+  // wavefront issues eight for the tokens and eight for the weights.  The buffers end with the
+  // output tile's last row: what lies behind it (rows of a last tile, and columns of the last k-tile
+  // in the last row) reads as zero and is never used.  k-tiles form one sequence over all output
+  // tiles of the workgroup; `next` is the place two of them ahead of the one being multiplied.
+  // The tokens of a k-tile are requested seven quarters of a tile before they are needed, its
+  // weights four (LDS holds five half k-tiles): two and two left the matrix core waiting for a
+  // fifth of the time.
+  struct Cursor {
+    __amdgpu_buffer_rsrc_t x, w;
+    int lin, kt;
+  } next;
+  auto open = [&](int lin) {
+    int ftile, rt;
+    tile_of(min(lin, ntiles - 1), ftile, rt);
+    const int xrows = lin < ntiles ? min(kBM, a.M - rt * kBM) : 0;  // past the last output tile: empty buffers
+    const int wrows = lin < ntiles ? min(kHeadsPerWg, nheads - ftile * kHeadsPerWg) * kBN : 0;
+    next.x = buffer_of(a.X + int64_t(rt) * kBM * a.hidden, xrows * row_bytes);
+    next.w = buffer_of(a.W + int64_t(ftile) * kHeadsPerWg * kBN * a.hidden, wrows * row_bytes);
+    next.lin = lin;
+    next.kt = 0;
+  };
+  auto advance = [&]() {
+    if (++next.kt == nkt) open(next.lin + nwg);
+  };
+  const int lane_off = (w * 64 + (lane >> 3)) * row_bytes;           // this lane's row in load 0 (and 8)
+  const int off_even = lane_off + (((lane & 7) ^ (lane >> 4)) << 4);  // with its chunk in even loads,
+  const int off_odd = lane_off + (((lane & 7) ^ (lane >> 4) ^ 4) << 4);  // and in odd ones (rows 8 further on)
+  auto tokens = [&](int sa) { return smem + sa * kStageElems; };
+  auto weights = [&](int sb) { return smem + (kTokenStages + sb) * kStageElems; };
+  auto load = [&](int i, bool tok, uint16_t* stage) {  // load i (0..7) of the k-tile `next`
+    load_lds16(tok ? next.x : next.w, (i & 1) ? off_odd : off_even, next.kt * (kBK * 2) + i * 8 * row_bytes,
+               stage + (w * 8 + i) * 8 * kLd);
+  };
+  // operand i (0..3: token blocks, 4..7: feature blocks) of quarter ks of the k-tile in these stages
+  const int swz = (m >> 1) & 7;
+  auto operand = [&](int i, int ks, int sa, int sb) -> bf16x8 {
+    const uint16_t* row = i < 4 ? tokens(sa) + (wm * 128 + i * 32 + m) * kLd : weights(sb) + (wn * kBN + (i - 4) * 32 + m) * kLd;
+    return *reinterpret_cast<const bf16x8*>(row + (((ks * 2 + h) ^ swz) << 3));
+  };
+  f32x16 acc[4][4];
+  bf16x8 S0[8], S1[8];
+  auto mma2 = [&](const bf16x8 (&S)[8], int q) {  // two of the sixteen matrix instructions of a quarter tile
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 2 * q; u < 2 * q + 2; ++u)
+      acc[u >> 2][u & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(S[u >> 2], S[4 + (u & 3)], acc[u >> 2][u & 3], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // the operands in the order in which the matrix instructions need them
+  constexpr int kOrder[8] = {0, 4, 5, 6, 7, 1, 2, 3};
+  // One quarter: multiplies Sa while the operands of quarter ks of stages (sa, sb) arrive in Sb, spread
+  // out so that the four wavefronts do not queue at the LDS; the loads of the tokens or weights of `next` into `dst`
+  // go out in between.
+  auto quarter = [&](const bf16x8 (&Sa)[8], bf16x8 (&Sb)[8], int ks, int sa, int sb, auto what, uint16_t* dst) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      mma2(Sa, q);
+      if (ks != 3) {
+        Sb[kOrder[q]] = operand(kOrder[q], ks, sa, sb);
+      } else if (q < 4) {  // the barrier that follows waits for them
+        Sb[kOrder[2 * q]] = operand(kOrder[2 * q], ks, sa, sb);
+        Sb[kOrder[2 * q + 1]] = operand(kOrder[2 * q + 1], ks, sa, sb);
+      }
+      if constexpr (decltype(what)::value != kNothing) load(q, decltype(what)::value == kTokens, dst);
+    }
+  };
+  // Behind this barrier every wavefront has its last operands of the current k-tile in registers
+  // and its loads of the following one in LDS (the tokens of the one after that may be on their
+  // way): the current stages are free and the following k-tile complete.
+  auto turn = [&]() {
+    wait_lgkm0();
+    wait_vm<8>();
+    __builtin_amdgcn_s_barrier();
+  };
+  open(blockIdx.x);
+#pragma unroll
+  for (int kt = 0; kt < 2; ++kt) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) load(i, true, tokens(kt));
+#pragma unroll
+    for (int i = 0; i < 8; ++i) load(i, false, weights(kt));
+    advance();
   }
-  const int nheads = a.Hq + 2 * a.Hkv;
-  const int wm = w & 3, wn = w >> 2;      // the wavefront's 64 tokens, and which head of the pair
-  const int ft = ftile * kHeadsPerWg + wn;  // this wavefront's head (an odd head count leaves the last tile's second half idle)
-  const bool live = ft < nheads;
-  const int row0 = rt * kBM;  // first token (flattened over sequences) of the tile
-  const uint16_t* Xb = a.X;
-  const uint16_t* Wb = a.W + int64_t(ftile) * kHeadsPerWg * kBN * a.hidden;
-  const int wrows = min(kHeadsPerWg * kBN, (nheads - ftile * kHeadsPerWg) * kBN);  // weight rows this tile has
-  constexpr int kStageElems = (kBM + kHeadsPerWg * kBN) * kLd;
-  auto As = [&](int st) { return smem + st * kStageElems; };
-  auto Bs = [&](int st) { return smem + st * kStageElems + kBM * kLd; };
-
-  f32x16 acc[2][4];
+  wait_vm<16>();
+  __builtin_amdgcn_s_barrier();
+  int sa = 0, sb = 0;  // stages of the current k-tile
+#pragma unroll 1
+  for (int lin = blockIdx.x; lin < ntiles; lin += nwg) {
+    int ftile, rt;
+    tile_of(lin, ftile, rt);
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  // staging: a tile row holds 64 bytes = four 16-byte chunks; 1024 chunks of X and 512 of W.
-  // Two register sets: the loads of k-tile t + 2 are issued while tile t is multiplied, and a
-  // tile moves from its registers to LDS one iteration after that, so a load has two
-  // iterations (and the other resident workgroup's) to arrive; one iteration is shorter than
-  // an L2 round trip under load.
-  auto swz = [](int row, int col) { return col ^ (((row >> 2) & 3) << 3); };  // col: element offset of a 16-byte chunk
-  constexpr int NA = kBM * 4 / kThreads, NB = kHeadsPerWg * kBN * 4 / kThreads;  // 16-byte chunks per thread
-  struct Regs {
-    u32x4 a[NA], b[NB];
-  } R0, R1;
-  auto issue = [&](int kt, Regs& R) {
-    const int k0 = kt * kBK;
-#pragma unroll
-    for (int i = 0; i < NA; ++i) {
-      const int c = tid + kThreads * i, row = c >> 2, col = (c & 3) * 8;
-      R.a[i] = *reinterpret_cast<const u32x4*>(Xb + int64_t(min(row0 + row, a.M - 1)) * a.hidden + k0 + col);
-    }
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      const int c = tid + kThreads * i, row = c >> 2, col = (c & 3) * 8;
-      R.b[i] = *reinterpret_cast<const u32x4*>(Wb + int64_t(min(row, wrows - 1)) * a.hidden + k0 + col);
-    }
-  };
-  auto stage = [&](int st, const Regs& R) {
-#pragma unroll
-    for (int i = 0; i < NA; ++i) {
-      const int c = tid + kThreads * i, row = c >> 2, col = (c & 3) * 8;
-      *reinterpret_cast<u32x4*>(As(st) + row * kLd + swz(row, col)) = R.a[i];
-    }
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      const int c = tid + kThreads * i, row = c >> 2, col = (c & 3) * 8;
-      *reinterpret_cast<u32x4*>(Bs(st) + row * kLd + swz(row, col)) = R.b[i];
-    }
-  };
-  // all operand reads of a stage first, then its sixteen matrix instructions back to back
-  auto multiply = [&](int st) {
-    bf16x8 av[kBK / 16][2], bv[kBK / 16][4];
-#pragma unroll
-    for (int ks = 0; ks < kBK / 16; ++ks) {
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-        av[ks][i] = *reinterpret_cast<const bf16x8*>(As(st) + (wm * 64 + i * 32 + m) * kLd + swz(m, ks * 16 + h * 8));
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-        bv[ks][j] = *reinterpret_cast<const bf16x8*>(Bs(st) + (wn * kBN + j * 32 + m) * kLd + swz(m, ks * 16 + h * 8));
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) S0[i] = operand(i, 0, sa, sb);
+#pragma unroll 1
+    for (int t = 0; t < nfull; ++t) {
+      const int sa1 = sa == 2 ? 0 : sa + 1, sa2 = sa == 0 ? 2 : sa - 1;
+      quarter(S0, S1, 1, sa, sb, LoadsOf<kTokens>{}, tokens(sa2));
+      quarter(S1, S0, 2, sa, sb, LoadsOf<kNothing>{}, nullptr);
+      quarter(S0, S1, 3, sa, sb, LoadsOf<kNothing>{}, nullptr);
+      turn();
+      quarter(S1, S0, 0, sa1, sb ^ 1, LoadsOf<kWeights>{}, weights(sb));
+      advance();
+      sa = sa1;
+      sb ^= 1;
     }
+    if (half) {  // 32 more columns
+      const int sa1 = sa == 2 ? 0 : sa + 1, sa2 = sa == 0 ? 2 : sa - 1;
+      quarter(S0, S1, 1, sa, sb, LoadsOf<kTokens>{}, tokens(sa2));
 #pragma unroll
-    for (int ks = 0; ks < kBK / 16; ++ks)
+      for (int q = 0; q < 8; ++q) mma2(S1, q);
+      turn();
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < 8; ++i) load(i, false, weights(sb));
+      advance();
+      sa = sa1;
+      sb ^= 1;
+    }
+    // ---- rotary embedding on queries and keys.  Accumulator layout: acc[i][j][r] is token
+    //      wm*128 + i*32 + (r/4)*8 + 4h + r%4 of the tile, feature j*32 + m of the wavefront's head.
+    //      Features c < 64 pair with c + 64: blocks (0, 2) and (1, 3) of the same lane and register.
+    int eln = lane;  // (opaque: address arithmetic hoisted out of the tile loop would not fit the registers)
+    asm volatile("" : "+v"(eln));
+    const int em = eln & 31, eh = eln >> 5;
+    const int ft = ftile * kHeadsPerWg + wn;  // this wavefront's head (an odd head count leaves the last tile's second half idle)
+    const int row0 = rt * kBM;                // first token (flattened over sequences) of the tile
+    // Token of the flattened row row0 + r (0 <= r < kBM) and its sequence: the tile starts inside
+    // sequence seq0 at token tok0; a sequence shorter than a tile can end several times in it.
+    const int seq0 = row0 / a.n, tok0 = row0 - seq0 * a.n, first = a.n - tok0;
+    const float inv_n = 1.0f / float(a.n);
+    auto place = [&](int r, int& seq, int& tok) {
+      // sequences that end before the row (exact: r - first < 256, n >= 1; -1 stands for all rows before the first end)
+      const int q = int(floorf((float(max(r - first, -1)) + 0.5f) * inv_n)) + 1;
+      seq = seq0 + q;
+      tok = tok0 + r - q * a.n;
+    };
+    const bool rotate = ft < a.Hq + a.Hkv, whole = first >= kBM;  // whole: the tile's tokens are of one sequence
+    double turns_per_pos[2];  // turns (angle / 2 pi) per position step of this lane's two feature pairs
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      turns_per_pos[j] = exp2(-(2.0 * double(j * 32 + em) / double(kBN)) * a.log2_base) * 0.15915494309189535;
+    // ---- rotated and through LDS, 32 tokens of the wavefront at a time: [token][feature] in bf16, then
+    //      16 contiguous bytes per lane.  The token stage that is free until the next k-tile's loads has room
+    //      for it, every wavefront in the part that its own loads fill.
+    View dst = a.q;
+    int head = ft;
+    if (ft >= a.Hq + a.Hkv) {
+      dst = a.v;
+      head = ft - a.Hq - a.Hkv;
+    } else if (ft >= a.Hq) {
+      dst = a.k;
+      head = ft - a.Hq;
+    }
+    uint16_t* out = static_cast<uint16_t*>(dst.ptr) + head * dst.sh;
+    uint16_t* Cs = tokens(sa == 0 ? 2 : sa - 1) + w * 64 * kLd;
+    // the block's values of register r, and their place in the staged rows (rows 4 h apart are
+    // written together: the half row's offset puts them on different banks)
+    auto put = [&](int r, int j, float v) {
+      Cs[((r >> 2) * 8 + eh * 4 + (r & 3)) * kBN + ((j * 32 + em) ^ (eh << 5))] = Elem<uint16_t>::from_f32(v);
+    };
+    auto put_rotated = [&](int i, int r, int j, float frac) {
+      // the hardware sine and cosine take their argument in turns
+      const float sn = __builtin_amdgcn_sinf(frac), cs = __builtin_amdgcn_cosf(frac);
+      const float x0 = acc[i][j][r], x1 = acc[i][j + 2][r];
+      put(r, j, x0 * cs - x1 * sn);
+      put(r, j + 2, x1 * cs + x0 * sn);
+    };
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      // the angle in fp64, reduced to a fraction of a turn before the fp32 sine and cosine
+      // (positions reach 10^5: an fp32 product would be off by a hundredth of a radian)
+      if (!rotate) {
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[ks][i], bv[ks][j], acc[i][j], 0, 0, 0);
-  };
-  const int nk = a.hidden / kBK;
-  issue(0, R0);
-  if (nk > 1) issue(1, R1);
-  stage(0, R0);
-  __syncthreads();
-  for (int kt = 0; kt < nk; kt += 2) {
-    // LDS stage 0 holds tile kt, R1 tile kt + 1
-    if (kt + 2 < nk) issue(kt + 2, R0);
-    multiply(0);
-    if (kt + 1 < nk) stage(1, R1);
-    __syncthreads();
-    if (kt + 1 >= nk) break;
-    // LDS stage 1 holds tile kt + 1, R0 tile kt + 2
-    if (kt + 3 < nk) issue(kt + 3, R1);
-    multiply(1);
-    if (kt + 2 < nk) stage(0, R0);
-    __syncthreads();
-  }
-  // ---- rotary embedding on queries and keys.  Accumulator layout: acc[i][j][r] is token
-  //      wm*64 + i*32 + (r/4)*8 + 4h + r%4 of the tile, feature j*32 + m of the wavefront's head.  Features c < 64 pair with
-  //      c + 64: blocks (0, 2) and (1, 3) of the same lane and register.
-  const bool rotate = live && ft < a.Hq + a.Hkv;
-  if (rotate) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int c = j * 32 + m;
-      // turns (angle / 2 pi) per position step of this feature pair
-      const double turns_per_pos = exp2(-(2.0 * double(c) / double(kBN)) * a.log2_base) * 0.15915494309189535;
+          for (int r = 0; r < 16; ++r) put(r, j, acc[i][j][r]);
+      } else if (whole) {  // four consecutive tokens: one reduction
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            const double turns = double(a.pos0 + tok0 + wm * 128 + i * 32 + g * 8 + eh * 4) * turns_per_pos[j];
+            const double frac = turns - rint(turns);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) put_rotated(i, 4 * g + e, j, float(fma(double(e), turns_per_pos[j], frac)));
+            __builtin_amdgcn_sched_barrier(0);  // one group after the other: interleaving them costs registers
+          }
+      } else {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int t = row0 + wm * 64 + i * 32 + (r >> 2) * 8 + h * 4 + (r & 3);
-          const int pos = a.pos0 + (t % a.n);
-          // the angle in fp64, reduced to a fraction of a turn before the fp32 sine and cosine
-          // (positions reach 10^5: an fp32 product would be off by a hundredth of a radian); the
-          // hardware sine and cosine take their argument in turns
-          const double turns = double(pos) * turns_per_pos;
-          const float frac = float(turns - rint(turns));
-          const float sn = __builtin_amdgcn_sinf(frac), cs = __builtin_amdgcn_cosf(frac);
-          const float x0 = acc[i][j][r], x1 = acc[i][j + 2][r];
-          acc[i][j][r] = x0 * cs - x1 * sn;
-          acc[i][j + 2][r] = x1 * cs + x0 * sn;
-        }
-    }
-  }
-  // ---- through LDS (the operand tiles are no longer needed; the loop's last barrier has passed),
-  //      one head and 128 tokens at a time: [token][feature] in bf16, then 16 contiguous bytes per lane
-  uint16_t* Cs = smem;
-#pragma unroll 1
-  for (int pass = 0; pass < 2 * kHeadsPerWg; ++pass) {
-    const int half = pass & 1, hsel = pass >> 1;
-    if (wn == hsel && (wm >> 1) == half) {
+          int seq, tok;
+          place(wm * 128 + i * 32 + (r >> 2) * 8 + eh * 4 + (r & 3), seq, tok);
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int row = (wm & 1) * 64 + i * 32 + (r >> 2) * 8 + h * 4 + (r & 3);
-            Cs[row * kLdC + j * 32 + m] = Elem<uint16_t>::from_f32(acc[i][j][r]);
+          for (int j = 0; j < 2; ++j) {
+            const double turns = double(a.pos0 + tok) * turns_per_pos[j];
+            put_rotated(i, r, j, float(turns - rint(turns)));
           }
-    }
-    __syncthreads();
-    // which tensor and head this pass writes
-    const int fh = ftile * kHeadsPerWg + hsel;
-    if (fh < nheads) {
-      View dst = a.q;
-      int head = fh;
-      if (fh >= a.Hq + a.Hkv) {
-        dst = a.v;
-        head = fh - a.Hq - a.Hkv;
-      } else if (fh >= a.Hq) {
-        dst = a.k;
-        head = fh - a.Hq;
+          __builtin_amdgcn_sched_barrier(0);
+        }
       }
-      uint16_t* out = static_cast<uint16_t*>(dst.ptr);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
 #pragma unroll
-      for (int i = 0; i < kBM / 2 * kBN / 8 / kThreads; ++i) {
-        const int c = tid + kThreads * i, row = c >> 4, col = (c & 15) * 8;
-        const int t = row0 + half * (kBM / 2) + row;
-        if (t < a.M) {
-          const int b = t / a.n, tok = t % a.n;
-          *reinterpret_cast<u32x4*>(out + b * dst.sb + head * dst.sh + int64_t(tok) * dst.sn + col) =
-              *reinterpret_cast<const u32x4*>(Cs + row * kLdC + col);
+      for (int c = 0; c < 8; ++c) {
+        const int row = c * 4 + (eln >> 4), col = (eln & 15) * 8;
+        const int tile_row = wm * 128 + i * 32 + row;
+        if (row0 + tile_row < a.M && ft < nheads) {
+          int b, tok;
+          place(tile_row, b, tok);
+          *reinterpret_cast<u32x4*>(out + b * dst.sb + int64_t(tok) * dst.sn + col) =
+              *reinterpret_cast<const u32x4*>(Cs + row * kBN + (col ^ (((row >> 2) & 1) << 5)));
         }
       }
     }
-    __syncthreads();
   }
 }
 
@@ -234,7 +317,7 @@ extern "C" int d2o_qkv_project(int32_t batch, int32_t n, int32_t hidden, int32_t
       !(rope_base > 1.0))
     return D2O_ERR_INVALID_ARG;
   if (dtype != D2O_BF16 || head_dim != kBN) return D2O_ERR_UNSUPPORTED;
-  if (hidden % kBK) return D2O_ERR_UNSUPPORTED;
+  if (hidden % (kBK / 2) || hidden > (1 << 22) - kBK) return D2O_ERR_UNSUPPORTED;  // (a tile's rows are addressed with 31 bits)
   if (int64_t(batch) * n > 0x7FFFFFFF) return D2O_ERR_INVALID_ARG;
   for (const d2o_view* v : {&Q, &K, &V}) {
     if (!v->ptr || (reinterpret_cast<uintptr_t>(v->ptr) & 15) || v->stride_b % 8 || v->stride_h % 8 ||
@@ -255,7 +338,11 @@ extern "C" int d2o_qkv_project(int32_t batch, int32_t n, int32_t hidden, int32_t
   a.Hkv = n_kv_heads;
   a.pos0 = pos0;
   a.log2_base = std::log2(rope_base);
-  const dim3 grid((n_q_heads + 2 * n_kv_heads + kHeadsPerWg - 1) / kHeadsPerWg, (a.M + kBM - 1) / kBM);
-  qkv_rope_bf16<<<grid, kThreads, 0, static_cast<hipStream_t>(stream)>>>(a);
+  const int nft = (n_q_heads + 2 * n_kv_heads + kHeadsPerWg - 1) / kHeadsPerWg, ntiles = nft * ((a.M + kBM - 1) / kBM);
+  if (hipFuncSetAttribute(reinterpret_cast<const void*>(qkv_rope_bf16), hipFuncAttributeMaxDynamicSharedMemorySize,
+                          kSmemBytes) != hipSuccess)
+    return D2O_ERR_HIP;
+  const int nwg = std::min(ntiles, kCus);
+  qkv_rope_bf16<<<nwg, kThreads, kSmemBytes, static_cast<hipStream_t>(stream)>>>(a, nft, ntiles, nwg);
   return hipGetLastError() == hipSuccess ? D2O_OK : D2O_ERR_HIP;
 }

@@ -1,0 +1,36 @@
+"""Edges of the tiles and of the dispatch rules of single kernels, against the oracle: sizes at
+which a kernel's loop, remainder or variant changes.  (What the calls do as a whole is in
+test_gpu_parity.py.)"""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import d2o_ref as ref
+from paper_2406_13035_amd import binding
+from tests import helpers as H
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,n,hidden,Hq,Hkv", [
+    (1, 1, 32, 2, 1),        # one token, half of a 64-column k-tile
+    (5, 37, 96, 3, 1),       # five sequences inside one 256-token tile, an odd head count, a k-tile and a half
+    (1, 257, 64, 1, 1),      # one token past the tile, one k-tile
+    (3, 200, 160, 4, 2),     # tiles that hold the end of a sequence
+    (1, 1600, 96, 32, 32),   # more output tiles than workgroups, the k-tile sequence odd in each
+])
+def test_projection_tile_edges(B, n, hidden, Hq, Hkv):
+    """|got - want| <= 2e-3 |row|_inf + 2^-8 |want|: the oracle's fp64 product and rotation against
+    fp32 accumulation and one rounding to bf16, as in test_qkv_projection_with_rotary_embedding."""
+    g = torch.Generator().manual_seed(n + hidden)
+    X = torch.randn(B, n, hidden, generator=g).to(torch.bfloat16)
+    W = (torch.randn((Hq + 2 * Hkv) * 128, hidden, generator=g) / hidden ** 0.5).to(torch.bfloat16)
+    out = binding.d2o_qkv_project(X.cuda(), W.cuda(), Hq, Hkv, 128, 7, 10000.0)
+    Xd, Wd = binding.tensor_to_f64(X), binding.tensor_to_f64(W)
+    for b in range(B):
+        for got, want in zip(out, ref.qkv_project(Xd[b], Wd, Hq, Hkv, 128, 7, 10000.0)):
+            got = binding.tensor_to_f64(got[b])
+            assert np.all(np.abs(got - want) <= H.FLOAT_TOL * np.abs(want).max(axis=-1, keepdims=True)
+                          + 2.0 ** -8 * np.abs(want))
