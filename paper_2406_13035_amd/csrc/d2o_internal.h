@@ -16,6 +16,7 @@ constexpr int kMaxQuerySlices = 16;  // block append: workgroups that share the 
 constexpr int kMinAutoSplitRows = 6144, kMaxAutoSplitRows = 16384;  // bounds of the automatic split_rows (below the lower one the two extra launches cost more than a single closing workgroup)
 constexpr int kChunk = 256;        // cache slots handled by one workgroup in the decode kernels
 constexpr int kColBN = 256;        // keys per workgroup, column-sum pass (bf16)
+constexpr int kF32BN = 32;         // the same, fp32
 
 // A strided [b][head][token][d] (or [layer][b][head][d]) tensor, strides in elements.
 struct View {
@@ -94,7 +95,7 @@ struct d2o_ctx {
   void* vt = nullptr;            // [B][Hkv][npad/64][d][64] transposed values, tile by tile, as scaled fp16 (bf16 path)
   uint32_t* vmax_bits = nullptr; // [B][Hkv] bit pattern of max |v|
   float* vt_unscale = nullptr;   // [B][Hkv] power of two that undoes the fp16 scaling
-  double* varpart = nullptr;     // [B][Hq][npad/128][2] partial sums of s and s^2
+  double* varpart = nullptr;     // [B][Hq][npad/128 (fp32: npad/kF32BN)][2] partial sums of s and s^2
   // token-level prefill stages, all [B][Hkv][npad] unless noted
   int32_t* sel_ret = nullptr;    // retained positions, ascending
   int32_t* sel_evi = nullptr;    // evicted positions, ascending

@@ -34,3 +34,29 @@ def test_projection_tile_edges(B, n, hidden, Hq, Hkv):
             got = binding.tensor_to_f64(got[b])
             assert np.all(np.abs(got - want) <= H.FLOAT_TOL * np.abs(want).max(axis=-1, keepdims=True)
                           + 2.0 ** -8 * np.abs(want))
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 31, 32, 33, 255, 257, 300])
+@pytest.mark.parametrize("d,Hq,Hkv", [(64, 4, 2), (128, 2, 2)])
+def test_fp32_prompt_attention_tile_edges(n, d, Hq, Hkv):
+    """16 query rows and 32 keys per tile, 8 wavefronts (256 keys) per round, 32 keys per column-sum
+    block.  A logit of magnitude s carries at most (d / 16 + 4) roundings of 2^-24 s (four chains of d / 16
+    products of four, added pairwise and scaled), which a probability shows as a relative error; the
+    sums behind it add a few units of 2^-24 each.  |s| <= 20 here: 20 * 12 * 6e-8 = 1.4e-5, and twice
+    that for the normaliser."""
+    rng = np.random.RandomState(n + d)
+    Q, K, V = (rng.randn(h, n, d).astype(np.float32) for h in (Hq, Hkv, Hkv))
+    ctx = binding.D2O(1, 1, Hq, Hkv, d, n, n + 2, dtype="f32")
+    Qg, Kg, Vg = (torch.from_numpy(x)[None].cuda() for x in (Q, K, V))
+    O = torch.empty(1, Hq, n, d, device="cuda:0")
+    ctx.d2o_prefill_attend(0, Qg, Kg, Vg, O)
+    score, F = ctx.d2o_scores_export(0, n), ctx.d2o_get_density()
+    got, G, var = O[0].double().cpu().numpy(), Hq // Hkv, []
+    for h in range(Hkv):
+        o, s, v = ref.prefill_kv_head(Q[h * G:(h + 1) * G].astype(np.float64), K[h].astype(np.float64),
+                                         V[h].astype(np.float64))
+        assert np.abs(got[h * G:(h + 1) * G] - o).max() <= 3e-5 * np.abs(V[h]).max()
+        assert np.abs(score[0, h] - s).max() <= 3e-5 * s.max()
+        var += list(v)
+    assert abs(F[0, 0] - np.mean(var)) <= 1e-4 * max(np.mean(var), 1e-3)
+    ctx.close()
