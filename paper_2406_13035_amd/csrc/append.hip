@@ -185,18 +185,32 @@ struct BlockRows {
     }
     __syncthreads();
   }
-  // element k of staged row `row` (0..255) as fp64 (fp8: the code, without the row's power of two)
-  static __device__ __forceinline__ double elem(const unsigned char* smem, int row, int k) {
-    const unsigned char* p = smem + row * kPitch + k * int(sizeof(T));
-    if constexpr (sizeof(T) == 1) return double(__builtin_amdgcn_cvt_f32_fp8(int(*p), 0));
-    else if constexpr (sizeof(T) == 2) return double(__uint_as_float(uint32_t(*reinterpret_cast<const uint16_t*>(p)) << 16));
-    else return double(*reinterpret_cast<const float*>(p));
+  // element e of 16 bytes of a staged row as fp64 (fp8: the code, without the row's power of two)
+  static constexpr int EL = 16 / sizeof(T);
+  static __device__ __forceinline__ double elem(const u32x4& raw, int e) {
+    if constexpr (sizeof(T) == 1) {
+      const int wd = int(raw[e / 4]);
+      return double(e % 4 == 0   ? __builtin_amdgcn_cvt_f32_fp8(wd, 0)
+                    : e % 4 == 1 ? __builtin_amdgcn_cvt_f32_fp8(wd, 1)
+                    : e % 4 == 2 ? __builtin_amdgcn_cvt_f32_fp8(wd, 2)
+                                 : __builtin_amdgcn_cvt_f32_fp8(wd, 3));
+    } else if constexpr (sizeof(T) == 2) {
+      return double(__uint_as_float(e & 1 ? raw[e / 2] & 0xFFFF0000u : raw[e / 2] << 16));
+    } else {
+      return double(__uint_as_float(raw[e]));
+    }
   }
-  // The query tile's B operands: bq[s] = element 4 s + kq of query q0 + c.
+  // The contraction takes a row's quarters side by side: step s multiplies element (D / 4) kq + s in
+  // lane group kq, so that a lane reads its quarter of a row 16 bytes at a time.
+  // The query tile's B operands: bq[s] = that element of query q0 + c.
   static __device__ __forceinline__ void load_queries(const double* aq_head, int q0, int lane, double (&bq)[KS]) {
-    const double* qp = aq_head + int64_t(q0 + (lane & 15)) * D + (lane >> 4);
+    const double* qp = aq_head + int64_t(q0 + (lane & 15)) * D + (lane >> 4) * KS;
 #pragma unroll
-    for (int s = 0; s < KS; ++s) bq[s] = qp[4 * s];
+    for (int s = 0; s < KS; s += 2) {
+      const double2 v = *reinterpret_cast<const double2*>(qp + s);
+      bq[s] = v.x;
+      bq[s + 1] = v.y;
+    }
   }
   // Logits of the tile's 16 queries against the rows [64 g, 64 g + 64) of the chunk:
   // S[t][r] = (row 64 g + 16 t + 4 r + kq) . (query c) / sqrt(d) (fp8: times the row's power of two, exactly).
@@ -206,10 +220,16 @@ struct BlockRows {
 #pragma unroll
     for (int t = 0; t < 4; ++t) S[t] = f64x4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int s = 0; s < KS; ++s)
+    for (int s = 0; s < KS; s += EL) {
+      u32x4 raw[4];
 #pragma unroll
       for (int t = 0; t < 4; ++t)
-        S[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(elem(smem, g * 64 + t * 16 + c, 4 * s + kq), bq[s], S[t], 0, 0, 0);
+        raw[t] = *reinterpret_cast<const u32x4*>(smem + (g * 64 + t * 16 + c) * kPitch + kq * (RB / 4) + s * int(sizeof(T)));
+#pragma unroll
+      for (int e = 0; e < EL; ++e)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) S[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(elem(raw[t], e), bq[s + e], S[t], 0, 0, 0);
+    }
     // (times the rounded reciprocal of sqrt(d), exact for d = 64: a block's logits are compared
     // within the float tolerance, and a division per element would cost a tenth of the pass)
     const double inv_root_d = 1.0 / sqrt(double(D));
@@ -232,6 +252,34 @@ __device__ __forceinline__ double kq_max(double v) {
 __device__ __forceinline__ double kq_sum(double v) {
   v += __shfl_xor(v, 16, 64);
   return v + __shfl_xor(v, 32, 64);
+}
+
+// Sums of sixteen values per lane over the sixteen lanes c of a lane group: every exchange also halves the
+// number of values a lane still adds up, and lane c ends with the sum of value
+// c / 8 + 2 (c % 2) + 4 (c / 2 % 2) + 8 (c / 4 % 2) (seven instructions per exchange; sixteen butterflies
+// through the LDS permutation cost eight LDS instructions each).
+__device__ __forceinline__ int row16_sums_owner(int c) { return (c >> 3 & 1) | (c & 1) << 1 | (c >> 1 & 1) << 2 | (c >> 2 & 1) << 3; }
+__device__ __forceinline__ double row16_sums(const double (&v)[16], int c) {
+  constexpr int kRor8 = 0x128, kShl4 = 0x104, kShr4 = 0x114;  // rotation by 8 lanes, shifts by 4, inside a row of 16
+  double a[8], b[4], d[2];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const double keep = c & 8 ? v[2 * i + 1] : v[2 * i], send = c & 8 ? v[2 * i] : v[2 * i + 1];
+    a[i] = keep + dpp_f64<kRor8>(send);
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const double keep = c & 1 ? a[2 * i + 1] : a[2 * i], send = c & 1 ? a[2 * i] : a[2 * i + 1];
+    b[i] = keep + dpp_f64<kDppXor1>(send);
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const double keep = c & 2 ? b[2 * i + 1] : b[2 * i], send = c & 2 ? b[2 * i] : b[2 * i + 1];
+    d[i] = keep + dpp_f64<kDppXor2>(send);
+  }
+  const double keep = c & 4 ? d[1] : d[0], send = c & 4 ? d[0] : d[1];
+  const double up = dpp_f64<kShl4>(send), down = dpp_f64<kShr4>(send);  // from lane c + 4 and from lane c - 4
+  return keep + (c & 4 ? down : up);
 }
 
 template <typename T, int D>
@@ -348,6 +396,7 @@ __global__ __launch_bounds__(256) void block_apply(const int32_t* __restrict__ c
       f64x4 S[4];
       BR::logits(smem, g, lane, bq, S);
       const int j0 = chunk * kChunk + g * 64 + kq;
+      double pr[16];  // the probabilities, value 4 t + r
 #pragma unroll
       for (int t = 0; t < 4; ++t)
 #pragma unroll
@@ -356,13 +405,7 @@ __global__ __launch_bounds__(256) void block_apply(const int32_t* __restrict__ c
           // (the division by the normaliser is a multiplication by its reciprocal here: the
           // probabilities are compared within the float tolerance, never bit for bit)
           const double p = (j < N && j <= seen) ? exp(S[t][r] - M) * Linv : 0.0;
-          // Eq. 6: the row's sum over the tile's queries, then over the wavefront's tiles
-          double ps = p;
-          ps += __shfl_xor(ps, 1, 64);
-          ps += __shfl_xor(ps, 2, 64);
-          ps += __shfl_xor(ps, 4, 64);
-          ps += __shfl_xor(ps, 8, 64);
-          if (c == 0) rs[w * 256 + row] += ps;
+          pr[4 * t + r] = p;
           // P V: this (t, r) is one contraction step over the rows 16 t + 4 r + kq
           float pa = float(p);
           if constexpr (sizeof(T) == 1) pa *= reinterpret_cast<const float*>(smem + BR::kRowsBytes + 256 * 8)[row];
@@ -397,6 +440,10 @@ __global__ __launch_bounds__(256) void block_apply(const int32_t* __restrict__ c
 #pragma unroll
           for (int ct = 0; ct < CT; ++ct) O[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(pa, vb[ct], O[ct], 0, 0, 0);
         }
+      // Eq. 6: the rows' sums over the tile's queries, one row per lane, then over the wavefront's tiles
+      const double ps = row16_sums(pr, c);
+      const int own = row16_sums_owner(c);
+      rs[w * 256 + g * 64 + (own >> 2) * 16 + 4 * (own & 3) + kq] += ps;
     }
     // O[ct][r]: query q0 + 4 kq + r, column CT c + ct
 #pragma unroll
