@@ -204,16 +204,34 @@ hipError_t fill32(void* p, uint32_t v, size_t bytes, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Several such fills in one launch: a reset is a dozen arrays of a few kilobytes, and as a dozen
+// launches it took 45 us of every prompt.
+constexpr int kMaxFills = 12;
+struct Fills {
+  uint32_t* p[kMaxFills];
+  uint32_t v[kMaxFills];
+  size_t n[kMaxFills];
+};
+__global__ void fill_many(Fills f) {
+  uint32_t* p = f.p[blockIdx.y];
+  const uint32_t v = f.v[blockIdx.y];
+  const size_t n = f.n[blockIdx.y];
+  for (size_t i = size_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += size_t(gridDim.x) * blockDim.x) p[i] = v;
+}
+
 // The per-sequence geometry of one layer travels to the device as kernel arguments (up to
-// kMetaPerLaunch sequences per launch): no host buffer has to outlive the call, so the caller's
+// kMetaPerLaunch heads per launch): no host buffer has to outlive the call, so the caller's
 // stream is neither synchronised nor fed from pageable memory.
-constexpr int kMetaPerLaunch = 16;
+constexpr int kMetaPerLaunch = 64;
 struct MetaPack {
   int32_t v[kMetaPerLaunch * 4];
 };
-__global__ void write_meta_kernel(int32_t* dst, MetaPack m, int n_words) {
+// `stage`, when given, is the copy for the staging rows of an fp8 cache: a head's start at row 0.
+__global__ void write_meta_kernel(int32_t* dst, int32_t* stage, MetaPack m, int n_words) {
   const int i = threadIdx.x;
-  if (i < n_words) dst[i] = m.v[i];
+  if (i >= n_words) return;
+  dst[i] = m.v[i];
+  if (stage) stage[i] = i % 4 == 0 ? 0 : m.v[i];
 }
 
 }  // namespace
@@ -231,14 +249,10 @@ hipError_t launch_write_meta(d2o_ctx* x, int layer, hipStream_t s) {
       m.v[4 * i + 2] = t.recent;
       m.v[4 * i + 3] = t.chunk_base;
     }
-    write_meta_kernel<<<1, kMetaPerLaunch * 4, 0, s>>>(x->meta + (size_t(layer) * B + b0) * 4, m, nb * 4);
-    hipError_t e = hipGetLastError();
+    const size_t off = (size_t(layer) * B + b0) * 4;
+    write_meta_kernel<<<1, kMetaPerLaunch * 4, 0, s>>>(x->meta + off, x->cfg.cache_fp8 ? x->meta_stage + off : nullptr, m, nb * 4);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (x->cfg.cache_fp8) {  // the staging rows of a head start at row 0
-      for (int i = 0; i < nb; ++i) m.v[4 * i + 0] = 0;
-      write_meta_kernel<<<1, kMetaPerLaunch * 4, 0, s>>>(x->meta_stage + (size_t(layer) * B + b0) * 4, m, nb * 4);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
   }
   return hipSuccess;
 }
@@ -312,18 +326,29 @@ int d2o_reset(d2o_ctx* x, void* stream) {
   const d2o_config& c = x->cfg;
   const size_t lbh = size_t(c.n_layers) * c.batch * c.n_kv_heads;
   // Only the small per-head state needs defined contents; 0xFF bytes read as NaN / -1.
-  D2O_HIP_CHECK(x, fill32(x->layer_F, 0xFFFFFFFFu, sizeof(double) * c.n_layers * c.batch, s));
-  D2O_HIP_CHECK(x, fill32(x->head_var, 0xFFFFFFFFu, sizeof(double) * c.n_layers * c.batch * c.n_q_heads, s));
-  D2O_HIP_CHECK(x, fill32(x->ccount, 0u, sizeof(int32_t) * lbh, s));
-  D2O_HIP_CHECK(x, fill32(x->ctotal, 0u, sizeof(int32_t) * lbh, s));
-  D2O_HIP_CHECK(x, fill32(x->ctau, 0xFFFFFFFFu, sizeof(double) * lbh, s));
-  D2O_HIP_CHECK(x, fill32(x->meta, 0u, sizeof(int32_t) * 4 * lbh, s));
-  D2O_HIP_CHECK(x, fill32(x->ev_evicted, 0xFFFFFFFFu, sizeof(int32_t) * lbh, s));
-  D2O_HIP_CHECK(x, fill32(x->ev_target, 0xFFFFFFFFu, sizeof(int32_t) * lbh, s));
-  D2O_HIP_CHECK(x, fill32(x->ev_ustar, 0xFFFFFFFFu, sizeof(double) * lbh, s));
-  D2O_HIP_CHECK(x, fill32(x->ccand, 0xFFFFFFFFu, sizeof(int32_t) * lbh * decode_candidates(), s));
-  D2O_HIP_CHECK(x, fill32(x->cticket, 0u, sizeof(uint32_t) * lbh, s));
-  D2O_HIP_CHECK(x, fill32(x->cmiss, 0u, sizeof(uint32_t) * lbh, s));
+  Fills f{};
+  int nf = 0;
+  size_t most = 1;
+  auto fill = [&](void* p, uint32_t v, size_t bytes) {
+    f.p[nf] = static_cast<uint32_t*>(p);
+    f.v[nf] = v;
+    f.n[nf++] = bytes / 4;
+    most = std::max(most, bytes / 4);
+  };
+  fill(x->layer_F, 0xFFFFFFFFu, sizeof(double) * c.n_layers * c.batch);
+  fill(x->head_var, 0xFFFFFFFFu, sizeof(double) * c.n_layers * c.batch * c.n_q_heads);
+  fill(x->ccount, 0u, sizeof(int32_t) * lbh);
+  fill(x->ctotal, 0u, sizeof(int32_t) * lbh);
+  fill(x->ctau, 0xFFFFFFFFu, sizeof(double) * lbh);
+  fill(x->meta, 0u, sizeof(int32_t) * 4 * lbh);
+  fill(x->ev_evicted, 0xFFFFFFFFu, sizeof(int32_t) * lbh);
+  fill(x->ev_target, 0xFFFFFFFFu, sizeof(int32_t) * lbh);
+  fill(x->ev_ustar, 0xFFFFFFFFu, sizeof(double) * lbh);
+  fill(x->ccand, 0xFFFFFFFFu, sizeof(int32_t) * lbh * decode_candidates());
+  fill(x->cticket, 0u, sizeof(uint32_t) * lbh);
+  fill(x->cmiss, 0u, sizeof(uint32_t) * lbh);
+  fill_many<<<dim3(unsigned(std::min<size_t>((most + 255) / 256, 64)), nf), 256, 0, s>>>(f);
+  D2O_HIP_CHECK(x, hipGetLastError());
   for (auto& l : x->layers) l = LayerState{};
   std::fill(x->used_slots.begin(), x->used_slots.end(), 0);
   std::fill(x->used_chunks.begin(), x->used_chunks.end(), 0);
