@@ -91,7 +91,7 @@ void layout(d2o_ctx* x, char* persistent, char* scratch, size_t* pbytes, size_t*
   Carver s{scratch};
   s.take(x->lse, B * Hq * np);
   s.take_raw(x->vt, c.dtype == D2O_BF16 ? B * Hkv * d * np * es : 0);
-  s.take(x->vmax_bits, B * Hkv);
+  s.take(x->vmax_bits, B * Hkv * kVmaxShares);
   s.take(x->vt_unscale, B * Hkv);
   s.take(x->varpart, B * Hq * (np / (c.dtype == D2O_F32 ? kF32BN : 128)) * 2);
   const size_t bh = B * Hkv;

@@ -17,6 +17,7 @@ constexpr int kMinAutoSplitRows = 6144, kMaxAutoSplitRows = 16384;  // bounds of
 constexpr int kChunk = 256;        // cache slots handled by one workgroup in the decode kernels
 constexpr int kColBN = 256;        // keys per workgroup, column-sum pass (bf16)
 constexpr int kF32BN = 32;         // the same, fp32
+constexpr int kVmaxShares = 64;    // workgroups per head that look for the largest value of V (bf16)
 
 // A strided [b][head][token][d] (or [layer][b][head][d]) tensor, strides in elements.
 struct View {
@@ -93,7 +94,7 @@ struct d2o_ctx {
   // prefill attention
   float* lse = nullptr;          // [B][Hq][npad]   row log-sum-exp (natural log, scaled logits)
   void* vt = nullptr;            // [B][Hkv][npad/64][d][64] transposed values, tile by tile, as scaled fp16 (bf16 path)
-  uint32_t* vmax_bits = nullptr; // [B][Hkv] bit pattern of max |v|
+  uint32_t* vmax_bits = nullptr; // [B][Hkv][kVmaxShares] bit pattern of max |v| of the workgroups' shares
   float* vt_unscale = nullptr;   // [B][Hkv] power of two that undoes the fp16 scaling
   double* varpart = nullptr;     // [B][Hq][npad/128 (fp32: npad/kF32BN)][2] partial sums of s and s^2
   // token-level prefill stages, all [B][Hkv][npad] unless noted

@@ -37,32 +37,35 @@ constexpr int kLdV = 64 + 8;   // LDS row pitch of the [d][key] tile
 constexpr float kPShift = 12.f;  // probabilities are formed as 2^12 * p before the fp16 rounding
 constexpr float kLazy = 3.f;     // log2 of the growth the exponent reference tolerates before it moves
 
-__global__ void zero_u32(uint32_t* p, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0u;
-}
-
-// max |v| per (sequence, KV head), as the bit pattern of the non-negative float.
+// max |v| of a share of a (sequence, KV head)'s values, as the bit pattern of the non-negative float:
+// vmax[head][share].  (Combined by atomics on one word per head, the words of all heads in a line or
+// two of memory, 2048 workgroups queued for 15 us on them: 21.6 us at 32 heads x 4096 tokens, and
+// the words had to be cleared by a launch of their own.)
 __global__ __launch_bounds__(256) void vabsmax_kernel(const uint16_t* __restrict__ V, View vv, uint32_t* __restrict__ vmax,
                                                       int n) {
   __shared__ uint32_t red[4];
   const int h = blockIdx.y, b = blockIdx.z, Hkv = gridDim.y;
   const uint16_t* src = V + b * vv.sb + h * vv.sh;
   uint32_t m = 0;
-  for (int c = blockIdx.x * 256 + threadIdx.x; c < n * 16; c += gridDim.x * 256) {
-    const int row = c >> 4, col = (c & 15) * 8;
-    const u32x4 v = *reinterpret_cast<const u32x4*>(src + int64_t(row) * vv.sn + col);
+  const int step = gridDim.x * 256, col = (threadIdx.x & 15) * 8;
+  for (int c0 = blockIdx.x * 256 + threadIdx.x; c0 < n * 16; c0 += 4 * step) {
+    u32x4 v[4];  // four loads in flight (past the end: the last row again)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      m = max(m, (v[i] << 16) & 0x7FFFFFFFu);
-      m = max(m, v[i] & 0x7FFF0000u);
-    }
+    for (int u = 0; u < 4; ++u)
+      v[u] = *reinterpret_cast<const u32x4*>(src + int64_t(min((c0 + u * step) >> 4, n - 1)) * vv.sn + col);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        m = max(m, (v[u][i] << 16) & 0x7FFFFFFFu);
+        m = max(m, v[u][i] & 0x7FFF0000u);
+      }
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o, 64));
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
   __syncthreads();
-  if (threadIdx.x == 0) atomicMax(&vmax[b * Hkv + h], max(max(red[0], red[1]), max(red[2], red[3])));
+  if (threadIdx.x == 0) vmax[(b * Hkv + h) * kVmaxShares + blockIdx.x] = max(max(red[0], red[1]), max(red[2], red[3]));
 }
 
 // Power-of-two factor that maps max|v| into [2^13, 2^14) (1 when the head is all zero).
@@ -78,10 +81,14 @@ __device__ __forceinline__ float v_scale_from_max(uint32_t maxbits) {
 // rows a power-of-two stride apart, all on one memory channel).
 __global__ __launch_bounds__(256) void transpose_v(const uint16_t* __restrict__ V, View vv, uint16_t* __restrict__ VT,
                                                    const uint32_t* __restrict__ vmax, float* __restrict__ unscale,
-                                                   int n, int npad) {
+                                                   int n, int npad, int shares) {
   __shared__ uint16_t t[64][kD + 2];
-  const int k0 = blockIdx.x * 64, h = blockIdx.y, b = blockIdx.z, Hkv = gridDim.y;
-  const float mul = v_scale_from_max(vmax[b * Hkv + h]);
+  const int k0 = blockIdx.x * 64, h = blockIdx.y, b = blockIdx.z, Hkv = gridDim.y, lane = threadIdx.x & 63;
+  static_assert(kVmaxShares == 64, "a share per lane");
+  uint32_t vm = lane < shares ? vmax[(b * Hkv + h) * kVmaxShares + lane] : 0u;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) vm = max(vm, (uint32_t)__shfl_xor((int)vm, o, 64));
+  const float mul = v_scale_from_max(vm);
   if (blockIdx.x == 0 && threadIdx.x == 0) unscale[b * Hkv + h] = 1.0f / mul;
   const uint16_t* src = V + b * vv.sb + h * vv.sh;
   for (int c = threadIdx.x; c < 64 * 16; c += 256) {
@@ -600,12 +607,10 @@ hipError_t launch_prefill_bf16(d2o_ctx* c, int layer, View Q, View K, View V, Vi
                                        hipFuncAttributeMaxDynamicSharedMemorySize, kAttnSmemBytes);
     if (e != hipSuccess) return e;
   }
-  const int nbh = cf.batch * cf.n_kv_heads;
-  zero_u32<<<(nbh + 255) / 256, 256, 0, s>>>(c->vmax_bits, nbh);
-  vabsmax_kernel<<<dim3(std::min(64, (n * 16 + 255) / 256), cf.n_kv_heads, cf.batch), 256, 0, s>>>(
-      (const uint16_t*)V.ptr, V, c->vmax_bits, n);
+  const int shares = std::min(kVmaxShares, (n * 16 + 255) / 256);
+  vabsmax_kernel<<<dim3(shares, cf.n_kv_heads, cf.batch), 256, 0, s>>>((const uint16_t*)V.ptr, V, c->vmax_bits, n);
   transpose_v<<<dim3(c->npad / 64, cf.n_kv_heads, cf.batch), 256, 0, s>>>((const uint16_t*)V.ptr, V, (uint16_t*)c->vt,
-                                                                         c->vmax_bits, c->vt_unscale, n, c->npad);
+                                                                         c->vmax_bits, c->vt_unscale, n, c->npad, shares);
   {
   KernelTimer kt(c, D2O_K_ATTN_FWD, s);
   attn_fwd_bf16<kAttnRW, kAttnNW><<<dim3((nblk + 1) / 2, cf.n_q_heads, cf.batch), 64 * kAttnNW, kAttnSmemBytes, s>>>(
