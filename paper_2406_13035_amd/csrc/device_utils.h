@@ -179,6 +179,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, int b
 __device__ __forceinline__ void load_lds16(__amdgpu_buffer_rsrc_t src, int lane_off, int off, uint16_t* dst) {
   __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (__attribute__((address_space(3))) void*)dst, 16, lane_off, off, 0, 0);
 }
+// The same from an address of each lane's own.
+__device__ __forceinline__ void load_lds16(const void* src, uint16_t* dst) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                   (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+}
 template <int N>
 __device__ __forceinline__ void wait_vm() {
   static_assert(N >= 0 && N < 64, "six bits");
