@@ -641,7 +641,11 @@ __global__ __launch_bounds__(256) void match_refine(const T* __restrict__ K, Vie
 // ------------------------------------------------------------------------------------------
 // Threshold (Eq. 10, t = 0) and grouping of the passing tokens by target.  One workgroup per
 // (sequence, KV head).  Group members are stored unordered; merge_kernel visits them in
-// ascending evicted order.
+// ascending evicted order.  One workgroup per head is a chain of memory round trips: the slots'
+// counters live in LDS up to kGroupSlots retained tokens (as words in memory beyond), and a thread has
+// four tokens in flight.  (One token at a time and counters in memory: 16.9 us at 32 heads x 4096
+// tokens, 112 us at 32768; now 8.5 and 41 us.)
+constexpr int kGroupSlots = 15360;  // 60 KB
 __global__ __launch_bounds__(1024) void threshold_group_kernel(const double* __restrict__ ustar,
                                                                const int32_t* __restrict__ tgt,
                                                                const int32_t* __restrict__ cnt, uint8_t* __restrict__ pass,
@@ -650,11 +654,13 @@ __global__ __launch_bounds__(1024) void threshold_group_kernel(const double* __r
                                                                double* __restrict__ tau_out, int npad, double tau_force,
                                                                int ema, double beta) {
   __shared__ double red[16];
-  __shared__ int wa[16], wb[16];
+  __shared__ int wa[16];
+  __shared__ int slot_lds[kGroupSlots];  // counts of the slots' sources, then the places of their next ones
   const int hk = blockIdx.x, b = blockIdx.y, Hkv = gridDim.x;
   const int64_t bh = int64_t(b) * Hkv + hk;
   const int nret = cnt[bh * 2], nevi = cnt[bh * 2 + 1];
   const int tid = threadIdx.x;
+  const bool in_lds = nret < kGroupSlots;
   const double* us = ustar + bh * npad;
   const int32_t* tg = tgt + bh * npad;
   uint8_t* ps = pass + bh * npad;
@@ -671,7 +677,8 @@ __global__ __launch_bounds__(1024) void threshold_group_kernel(const double* __r
     return;  // tau keeps its value (unset, NaN, after prompt encoding)
   }
   double part = 0.0;
-  for (int i = tid; i < nevi; i += blockDim.x) part += us[i];
+#pragma unroll 4
+  for (int i = tid; i < nevi; i += 1024) part += us[i];
   double tau = block_sum(part, red) / double(nevi);
   if (ema) {  // a step that evicts several tokens at once: Eq. 10 on their mean best similarity
     const double prev = tau_out[bh];
@@ -680,22 +687,40 @@ __global__ __launch_bounds__(1024) void threshold_group_kernel(const double* __r
   }
   if (tid == 0 && !(ema && !isnan(tau_force))) tau_out[bh] = tau;  // (a forced threshold leaves the EMA state alone)
   const double thr = isnan(tau_force) ? tau : tau_force;
-  for (int j = tid; j <= nret; j += blockDim.x) {
-    gc[j] = 0;
-    gu[j] = 0;
+  for (int j = tid; j <= nret; j += 1024) {
+    if (in_lds) {
+      slot_lds[j] = 0;
+    } else {
+      gc[j] = 0;
+      gu[j] = 0;
+    }
   }
   __syncthreads();
-  for (int i = tid; i < nevi; i += blockDim.x) {
-    const bool ok = us[i] >= thr;
+  // four tokens in flight per thread: the loop waits for memory once for them
+  auto each_token = [&](auto f) {
+    for (int i0 = tid; i0 < nevi; i0 += 4 * 1024) {
+      double u[4];
+      int t[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        u[k] = us[min(i0 + k * 1024, nevi - 1)];
+        t[k] = tg[min(i0 + k * 1024, nevi - 1)];
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (i0 + k * 1024 < nevi) f(i0 + k * 1024, u[k] >= thr, t[k]);
+    }
+  };
+  each_token([&](int i, bool ok, int t) {
     ps[i] = ok ? 1 : 0;
-    if (ok) atomicAdd(&gc[tg[i]], 1);
-  }
+    if (ok) atomicAdd(in_lds ? &slot_lds[t] : &gc[t], 1);
+  });
   __syncthreads();
-  // exclusive prefix of gc over [0, nret]
+  // exclusive prefix of the counts over [0, nret]
   int base = 0;
   for (int j0 = 0; j0 <= nret; j0 += blockDim.x) {
     const int j = j0 + tid;
-    const int v = (j < nret) ? gc[j] : 0;
+    const int v = j < nret ? (in_lds ? slot_lds[j] : gc[j]) : 0;
     // inclusive scan within the wavefront
     int inc = v;
 #pragma unroll
@@ -711,31 +736,45 @@ __global__ __launch_bounds__(1024) void threshold_group_kernel(const double* __r
       if (i < (tid >> 6)) woff += wa[i];
       tot += wa[i];
     }
-    if (j <= nret) go[j] = base + woff + inc - v;
+    if (j <= nret) {
+      go[j] = base + woff + inc - v;
+      if (in_lds) slot_lds[j] = base + woff + inc - v;
+    }
     base += tot;
   }
   __syncthreads();
-  for (int i = tid; i < nevi; i += blockDim.x) {
-    if (ps[i]) {
-      const int t = tg[i];
-      const int k = atomicAdd(&gu[t], 1);
-      gs[go[t] + k] = i;
-    }
-  }
-  (void)wb;
+  each_token([&](int i, bool ok, int t) {
+    if (!ok) return;
+    if (in_lds)
+      gs[atomicAdd(&slot_lds[t], 1)] = i;
+    else
+      gs[go[t] + atomicAdd(&gu[t], 1)] = i;
+  });
 }
 
 // PER consecutive elements of a row as one load / one store.
 template <typename T, int PER>
-__device__ __forceinline__ void load_elems(const T* p, double* out) {
+struct RowBits {
   static_assert(PER * sizeof(T) == 4 || PER * sizeof(T) == 8, "one 4- or 8-byte access");
-  T tmp[PER];
-  if constexpr (PER * sizeof(T) == 4)
-    *reinterpret_cast<uint32_t*>(tmp) = *reinterpret_cast<const uint32_t*>(p);
-  else
-    *reinterpret_cast<uint64_t*>(tmp) = *reinterpret_cast<const uint64_t*>(p);
+  typedef typename std::conditional<PER * sizeof(T) == 4, uint32_t, uint64_t>::type type;
+};
+template <typename T, int PER>
+__device__ __forceinline__ typename RowBits<T, PER>::type load_row_bits(const T* p) {
+  return *reinterpret_cast<const typename RowBits<T, PER>::type*>(p);
+}
+template <typename T, int PER>
+__device__ __forceinline__ void widen(typename RowBits<T, PER>::type raw, double* out) {
 #pragma unroll
-  for (int i = 0; i < PER; ++i) out[i] = Elem<T>::to_f64(tmp[i]);
+  for (int i = 0; i < PER; ++i) {
+    if constexpr (sizeof(T) == 2)
+      out[i] = Elem<T>::to_f64(T(raw >> (16 * i)));
+    else
+      out[i] = Elem<T>::to_f64(__uint_as_float(uint32_t(raw >> (32 * i))));
+  }
+}
+template <typename T, int PER>
+__device__ __forceinline__ void load_elems(const T* p, double* out) {
+  widen<T, PER>(load_row_bits<T, PER>(p), out);
 }
 template <typename T, int PER>
 __device__ __forceinline__ void store_elems(T* p, const double* v, double z) {
@@ -757,9 +796,13 @@ __device__ __forceinline__ void store_elems(T* p, const double* v, double z) {
 // cluster centre collect hundreds of sources; a small budget lengthens every list).
 //   up to 64 sources      one source per lane: the lanes rank their sources (count the smaller
 //                         ones), fetch weight and position in parallel;
-//   up to kMergeCap       the same ranking through LDS, weight and position stored at the rank;
+//   up to kMergeCap       the same ranking through LDS, the sources stored at their ranks, and then
+//                         64 of them at a time as above;
 //   beyond                the next source is extracted by a scan per step.
-// The rows are then read kMergeBatch sources at a time in rank order.
+// The rows are then read kMergeBatch sources at a time in rank order.  A list is a chain of dependent
+// loads, so what counts is how many lists are in flight: 16 KB of LDS per workgroup and rows held as
+// they were loaded (with weights and positions in LDS and rows widened on arrival it was 32 KB and
+// five workgroups per CU: 34.7 us at 32 heads x 4096 tokens, now 24.6 us; 174 -> 114 us at 32768).
 constexpr int kMergeCap = 512;
 constexpr int kMergeBatch = 8;
 template <typename T, int D, bool AVERAGE>
@@ -768,9 +811,7 @@ __global__ __launch_bounds__(256) void merge_kernel(const T* __restrict__ K, Vie
                                                     const double* __restrict__ ustar, const int32_t* __restrict__ goff,
                                                     const int32_t* __restrict__ gsrc, const int32_t* __restrict__ meta,
                                                     T* __restrict__ cK, T* __restrict__ cV, int npad, int64_t slots) {
-  __shared__ int s_src[4][kMergeCap];
-  __shared__ int s_pos[4][kMergeCap];
-  __shared__ double s_w[4][kMergeCap];
+  __shared__ int s_src[4][kMergeCap], s_sorted[4][kMergeCap];
   const int hk = blockIdx.y, b = blockIdx.z, Hkv = gridDim.y;
   const int64_t bh = int64_t(b) * Hkv + hk;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -808,20 +849,27 @@ __global__ __launch_bounds__(256) void merge_kernel(const T* __restrict__ K, Vie
       av[p] = __dadd_rn(av[p], __dmul_rn(wgt, xv[p]));
     }
   };
-  // rows of kMergeBatch sources in flight; weight and position of source s come from `at`
-  auto stream = [&](auto at) {
-    for (int s0 = 0; s0 < ns; s0 += kMergeBatch) {
-      double wq[kMergeBatch], xk[kMergeBatch][PER], xv[kMergeBatch][PER];
+  // `count` sources, kMergeBatch rows in flight; the weight and position of source s are in lane at(s)
+  auto stream = [&](int count, double wl, int pl, auto at) {
+    for (int s0 = 0; s0 < count; s0 += kMergeBatch) {
+      double wq[kMergeBatch];
+      typename RowBits<T, PER>::type xk[kMergeBatch], xv[kMergeBatch];
 #pragma unroll
       for (int u = 0; u < kMergeBatch; ++u) {
-        int pos;
-        at(min(s0 + u, ns - 1), wq[u], pos);
-        load_elems<T, PER>(kb + int64_t(pos) * kv.sn + lane * PER, xk[u]);
-        load_elems<T, PER>(vb + int64_t(pos) * vv.sn + lane * PER, xv[u]);
+        const int owner = at(min(s0 + u, count - 1));
+        wq[u] = lane_f64(wl, owner);
+        const int pos = __builtin_amdgcn_readlane(pl, owner);
+        xk[u] = load_row_bits<T, PER>(kb + int64_t(pos) * kv.sn + lane * PER);
+        xv[u] = load_row_bits<T, PER>(vb + int64_t(pos) * vv.sn + lane * PER);
       }
 #pragma unroll
       for (int u = 0; u < kMergeBatch; ++u)
-        if (s0 + u < ns) add_source(wq[u], xk[u], xv[u]);
+        if (s0 + u < count) {
+          double fk[PER], fv[PER];
+          widen<T, PER>(xk[u], fk);
+          widen<T, PER>(xv[u], fv);
+          add_source(wq[u], fk, fv);
+        }
     }
   };
   if (ns <= 64) {
@@ -831,30 +879,23 @@ __global__ __launch_bounds__(256) void merge_kernel(const T* __restrict__ K, Vie
     const int pmine = have ? el[mine] : 0;
     int rank = 0;  // sources are distinct: the ranks are a permutation of 0 .. ns-1
     for (int i = 0; i < ns; ++i) rank += __builtin_amdgcn_readlane(mine, i) < mine ? 1 : 0;
-    stream([&](int s, double& wgt, int& pos) {
-      const int owner = __ffsll((long long)__ballot(have && rank == s)) - 1;
-      wgt = lane_f64(wmine, owner);
-      pos = __builtin_amdgcn_readlane(pmine, owner);
-    });
+    stream(ns, wmine, pmine, [&](int s) { return __ffsll((long long)__ballot(have && rank == s)) - 1; });
   } else if (ns <= kMergeCap) {
     for (int t = lane; t < ns; t += 64) s_src[w][t] = src[t];
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     for (int t = lane; t < ns; t += 64) {
       const int mine = s_src[w][t];
-      const double wm = weight(us[mine]);
-      const int pm = el[mine];
       int rank = 0;
       for (int i = 0; i < ns; ++i) rank += s_src[w][i] < mine ? 1 : 0;
-      s_w[w][rank] = wm;
-      s_pos[w][rank] = pm;
+      s_sorted[w][rank] = mine;
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    stream([&](int s, double& wgt, int& pos) {
-      wgt = s_w[w][s];
-      pos = s_pos[w][s];
-    });
+    for (int t0 = 0; t0 < ns; t0 += 64) {
+      const int mine = s_sorted[w][min(t0 + lane, ns - 1)];
+      stream(min(64, ns - t0), weight(us[mine]), el[mine], [](int s) { return s; });
+    }
   } else {
     int prev = -1;
     for (int s = 0; s < ns; ++s) {
