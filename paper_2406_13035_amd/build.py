@@ -9,11 +9,12 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 SOURCES = ["d2o_host.hip", "prefill_f32.hip", "prefill_bf16.hip", "tokens.hip", "decode.hip", "decode_split.hip", "append.hip", "qkv.hip", "fp8.hip"]
 LIB = os.environ.get("D2O_LIB", os.path.join(HERE, "libd2o.so"))
-# Matrix-core results straight into vector registers: the kernels of these files post-process
+# Matrix-core results straight into vector registers: the kernels of tokens.hip post-process
 # every accumulator element on the vector ALU, and a copy out of the accumulation registers per
-# element is a sizeable part of their instruction count.
+# element is a sizeable part of their instruction count; those of decode.hip have few accumulators
+# and 128 registers for everything (separate accumulation registers cost them a wavefront per SIMD).
 VGPR_FORM = ["-mllvm", "-amdgpu-mfma-vgpr-form"]
-EXTRA_FLAGS = {"tokens.hip": VGPR_FORM}
+EXTRA_FLAGS = {"tokens.hip": VGPR_FORM, "decode.hip": VGPR_FORM}
 
 
 def build(verbose: bool = False) -> str:

@@ -123,10 +123,11 @@ __global__ __launch_bounds__(128) void decode_prepare(DecodeArgs a, const IT* __
     // must still see the count the step began with.
     a.ctotal[lbh] = count + 1;
   }
-  double* vec = a.vecs + lbh * (G + kCand) * D;
+  constexpr int NV = G + kCand;
+  double* vec = a.vecs + lbh * NV * D;
 #pragma unroll
   for (int g = 0; g < G; ++g)
-    if (c < D) vec[g * D + c] = Elem<IT>::to_f64(q[li * qv.sn + b * qv.sb + (hk * G + g) * qv.sh + c]);
+    if (c < D) vec[operand_index<T, NV>(g, c)] = Elem<IT>::to_f64(q[li * qv.sn + b * qv.sb + (hk * G + g) * qv.sh + c]);
   // the candidates' keys: all slot numbers first, then all rows, then one exchange for the
   // norms (one memory round trip each instead of one per candidate)
   int cs[kCand];
@@ -140,7 +141,7 @@ __global__ __launch_bounds__(128) void decode_prepare(DecodeArgs a, const IT* __
   }
 #pragma unroll
   for (int i = 0; i < kCand; ++i) {
-    if (c < D) vec[(G + i) * D + c] = x[i];
+    if (c < D) vec[operand_index<T, NV>(G + i, c)] = x[i];
     part[i] = wave_sum(x[i] * x[i]);
   }
   if ((c & 63) == 0) {
@@ -450,24 +451,24 @@ __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ 
   close_head<T, D>(a, lbh, slot0, total, evict, ev, low, cl, told, sred, ired, dred, wcm_u, wcm_ps, park_kv);
 }
 
+// (second launch bound: wavefronts per SIMD)
 template <typename T, typename OT, int D, int G>
-__global__ __launch_bounds__(256) void decode_attend(DecodeArgs a, OT* __restrict__ out, View ov) {
+__global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 3) void decode_attend(DecodeArgs a, OT* __restrict__ out, View ov) {
   constexpr int VB = sizeof(T) == 1 ? 8 : 16;   // V pass: bytes per lane and load (fp8: 8, which keeps the
                                                 // partial sums at eight per lane and query head)
   constexpr int kVec = VB / sizeof(T);          // elements per load
   typedef typename RawBits<VB>::type VRaw;
   constexpr int RB = D * sizeof(T);             // bytes of a cache row
   constexpr int NP = RB / kPiece;               // row pieces staged through LDS
-  constexpr int EP = kPiece / sizeof(T);        // elements of a piece
+  constexpr int EL = 16 / sizeof(T);            // elements of a lane's 16 bytes of a piece
   constexpr int TPR = RB / VB;                  // V pass: lanes per row
   constexpr int RPI = 64 / TPR;                 // V pass: rows per load instruction
   constexpr int NVL = kSub / RPI;               // V pass: loads per lane
   constexpr int NV = G + kCand;
+  constexpr int CG = (NV + 1) / 4, NR = NV > 4 * CG ? NV - 4 * CG : 0;  // K pass: groups of four operand vectors, and vectors left over
   constexpr int kRec = rec_doubles(G);
-  constexpr int ES = NV <= 4 ? 4 : 2;           // elements per K-pass step (scalar register budget)
-  constexpr int NST = EP / ES;                  // steps per piece (even)
-  typedef typename RawBits<ES * sizeof(T)>::type Raw;
   __shared__ __attribute__((aligned(16))) unsigned char stage[kStageBytes];
+  __shared__ __attribute__((aligned(16))) double opnd[NV * D];
   __shared__ float ps[4][G][kSub];
   __shared__ double wmax[4][G];  // per wavefront: softmax maximum of its sub-chunk (-inf: no rows)
   __shared__ int sh_last;
@@ -494,20 +495,23 @@ __global__ __launch_bounds__(256) void decode_attend(DecodeArgs a, OT* __restric
     cs[c] = ((ciptr)a.cand)[lbh * kCand + c];
     cn[c] = ((cptr)a.cnorm)[lbh * kCand + c];
   }
-  asm volatile("" ::"s"(total), "s"(mt0), "s"(mt3));  // all of them are on their way before the first wait
-  if (grp * kGroup * kChunk >= total) return;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  // the head's operand vectors, 16 bytes per thread and load
+  constexpr int kOpnd16 = NV * D / 2, kOpndLoads = (kOpnd16 + 255) / 256;
+  u32x4 opr[kOpndLoads];
+#pragma unroll
+  for (int i = 0; i < kOpndLoads; ++i)
+    opr[i] = reinterpret_cast<const u32x4*>(a.vecs + lbh * NV * D)[min(tid + i * 256, kOpnd16 - 1)];
+  asm volatile("" ::"s"(total), "s"(mt0), "s"(mt3));  // all of them are on their way before the first wait
+  if (grp * kChunk >= total) return;
   const int64_t bh = int64_t(b) * a.Hkv + hk;
   const int64_t slot0 = bh * a.slots + mt0;
   const unsigned char* Kh = static_cast<const unsigned char*>(a.cK) + slot0 * RB;
   const unsigned char* Vh = static_cast<const unsigned char*>(a.cV) + slot0 * RB;
-  // A workgroup owns kGroup consecutive chunks of 256 slots; each wavefront works alone on 64
-  // rows ("sub-chunk") of each of them, in a software pipeline: while it computes on one
-  // sub-chunk, the V rows of that sub-chunk and the K rows of its next one are in flight.
-  // There is no workgroup barrier until the ticket.
-  cptr S = (cptr)(a.vecs + lbh * NV * D);
-  unsigned char* mine = stage + w * 64 * kPitch;
-  int ln = lane;  // the lane number as the loop body sees it
+  // A workgroup owns a chunk of 256 slots; each wavefront works alone on 64 rows ("sub-chunk") of it:
+  // while it computes on its keys, its V rows are in flight.
+  unsigned char* mine = stage + w * kWaveStage;
+  const int ln = lane;
   const double root_d = sqrt(double(D));
   // K loads of a sub-chunk.  The K pass takes a row's bytes in pieces of 64 (one LDS staging round
   // each); the loads fetch two pieces at a time as whole 128-byte lines: 8 lanes per row, 8 rows
@@ -527,45 +531,42 @@ __global__ __launch_bounds__(256) void decode_attend(DecodeArgs a, OT* __restric
       kreg[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(Kc + int64_t(r) * RB + p0 * kPiece + (ln & 7) * 16));
     }
   };
-  const int sub0 = grp * kGroup * (kChunk / kSub) + w;
+  const int sub = grp * (kChunk / kSub) + w;
+  const int rows = min(kSub, total - sub * kSub);  // <= 0: nothing for this wavefront
+  if (rows > 0) load_pair(sub, rows, 0);
 #pragma unroll
-  for (int it = 0; it < kGroup; ++it) {
-    const int sub = sub0 + it * (kChunk / kSub);
-    const int rows = min(kSub, total - sub * kSub);  // <= 0: nothing (more) for this wavefront
-    if (rows <= 0) {  // nothing (more) for this wavefront: it only takes part in the combination
-      if (ln < G) wmax[w][ln] = -INFINITY;
-      break;
-    }
-    // With more than one pass, address arithmetic hoisted out of the loop would cost more
-    // registers than the occupancy allows; an opaque lane number keeps it inside.
-    if (kGroup > 1) asm volatile("" : "+v"(ln));
+  for (int i = 0; i < kOpndLoads; ++i)
+    if (tid + i * 256 < kOpnd16) reinterpret_cast<u32x4*>(opnd)[tid + i * 256] = opr[i];
+  lds_barrier();  // the operands are in LDS; the K rows may still be on their way
+  if (rows <= 0) {  // this wavefront only takes part in the combination
+    if (ln < G) wmax[w][ln] = -INFINITY;
+  } else {
     const int tr = ln / TPR, tc = ln % TPR;
-    load_pair(sub, rows, 0);
     const unsigned char* Vc = Vh + int64_t(sub) * kSub * RB;
-    // ---- K pass: lane = row.  The queries and candidate keys arrive through scalar loads.
-    double acc[NV];
+    // ---- K pass in the layout of v_mfma_f64_4x4x4_4b: D[i][j] += A[i][k] B[k][j] in four blocks b,
+    // where lane i + 4 b + 16 k holds A, lane j + 4 b + 16 k holds B and lane j + 4 b + 16 i holds D.
+    // i is one of four cache rows, j one of four operand vectors (queries, candidate keys), and k one
+    // of the four 16-byte parts of a row piece: a lane takes its part's elements one after the other,
+    // for four rows (set s of the staged rows holds rows s + 4 b + 16 i), so that an operand read
+    // from LDS serves four products.  Four vectors go through the matrix instruction, which adds the parts
+    // up; it does 16 products per cycle, like the vector ALU, so one or two
+    // vectors, which would leave its columns empty, are multiplied there (with the squared norm) and
+    // only added up by it, as products with ones.
+    // Either way the lane's own row (its lane number) is one transposition inside a quad of lanes away.
+    double acc[4][CG > 0 ? CG : 1], part[4][NR + 1];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) acc[v] = 0.0;
-    double nr = 0.0;
-    Raw rawA, rawB;
-    double sA[NV][ES], sB[NV][ES];
-    auto fetch = [&](int e0, int st, Raw& raw, double (&sv)[NV][ES]) {  // e0: first element of the piece
-      raw = *reinterpret_cast<const Raw*>(mine + ln * kPitch + st * ES * int(sizeof(T)));
+    for (int s = 0; s < 4; ++s) {
 #pragma unroll
-      for (int v = 0; v < NV; ++v)
+      for (int c = 0; c < CG; ++c) acc[s][c] = 0.0;
 #pragma unroll
-        for (int e = 0; e < ES; ++e) sv[v][e] = S[v * D + e0 + st * ES + e];
-    };
-    auto step = [&](const Raw& raw, const double (&sv)[NV][ES]) {
-      double x[ES];
-      raw_to_f64<T, ES>(raw, x);
-#pragma unroll
-      for (int e = 0; e < ES; ++e) nr = fma(x[e], x[e], nr);
-#pragma unroll
-      for (int v = 0; v < NV; ++v)
-#pragma unroll
-        for (int e = 0; e < ES; ++e) acc[v] = fma(x[e], sv[v][e], acc[v]);
-    };
+      for (int c = 0; c <= NR; ++c) part[s][c] = 0.0;
+    }
+    const unsigned char* arow = mine + (((ln >> 2) & 3) * 4 + (ln & 3)) * kPitch + (ln >> 4) * 16;
+    const double* bcol = opnd + (min(ln & 3, NV - 1) * 4 + (ln >> 4)) * 2;  // vector ln % 4 of a group (three: the last one twice)
+    const double* ball = opnd + (CG * 16 + (ln >> 4)) * 2;       // first of the left-over vectors
+    // the staging lanes' rows: i * 8 + t
+    const int t = ln >> 3;
+    unsigned char* srow = mine + (t & 3) * kSetBytes + (t >> 2) * 4 * kPitch + (ln & 3) * 16;
     // V rows travel in quarters of the sub-chunk through two register sets: two quarters are on
     // their way while the lanes finish the K pass, the others follow as the sets are consumed
     // (a whole sub-chunk in registers would cost the kernel a quarter of its occupancy).
@@ -588,8 +589,7 @@ __global__ __launch_bounds__(256) void decode_attend(DecodeArgs a, OT* __restric
       rek = valid ? a.cKe[slot0 + j] : 0;
       rev = valid ? a.cVe[slot0 + j] : 0;
     }
-#pragma unroll
-    for (int p = 0; p < NP; ++p) {
+    auto stage_piece = [&](int p) {
       // The staging area is private to the wavefront and LDS serves a wavefront's requests in
       // order, so the piece hand-over needs compiler ordering only.
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -597,39 +597,87 @@ __global__ __launch_bounds__(256) void decode_attend(DecodeArgs a, OT* __restric
       if (((ln >> 2) & 1) == (p & 1)) {  // the lanes that hold this piece's half of the lines
 #pragma unroll
         for (int i = 0; i < 8; ++i)
-          *reinterpret_cast<u32x4*>(mine + (i * 8 + (ln >> 3)) * kPitch + (ln & 3) * 16) = kreg[i];
+          *reinterpret_cast<u32x4*>(srow + (((2 * i) & 3) * 4 + (i >> 1)) * kPitch) = kreg[i];
       }
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
-      if ((p & 1) && p + 1 < NP) load_pair(sub, rows, p + 1);
-      if (p == NP - 1) {  // the first half of this sub-chunk's V rows
-        load_vq(0, 0);
-        load_vq(1, 1);
+    };
+    auto multiply_piece = [&](int p) {
+      u32x4 ar[4];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) ar[s] = *reinterpret_cast<const u32x4*>(arow + s * kSetBytes);
+#pragma unroll
+      for (int e = 0; e < EL / 2; ++e) {
+        double2 bg[CG > 0 ? CG : 1], br[NR > 0 ? NR : 1];
+#pragma unroll
+        for (int c = 0; c < CG; ++c) bg[c] = *reinterpret_cast<const double2*>(bcol + (p * (EL / 2) + e) * NV * 8 + c * 32);
+#pragma unroll
+        for (int c = 0; c < NR; ++c) br[c] = *reinterpret_cast<const double2*>(ball + (p * (EL / 2) + e) * NV * 8 + c * 8);
+#pragma unroll
+        for (int s0 = 0; s0 < 4; s0 += 2) {  // two sets at a time: independent products, few registers
+          double x0[2], x1[2];
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            pair_f64<T>(ar[s0 + i], e, x0[i], x1[i]);
+#pragma unroll
+            for (int c = 0; c < CG; ++c)
+              acc[s0 + i][c] = __builtin_amdgcn_mfma_f64_4x4x4f64(x0[i], bg[c].x, acc[s0 + i][c], 0, 0, 0);
+          }
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            double(&ps)[NR + 1] = part[s0 + i];
+#pragma unroll
+            for (int c = 0; c < CG; ++c)
+              acc[s0 + i][c] = __builtin_amdgcn_mfma_f64_4x4x4f64(x1[i], bg[c].y, acc[s0 + i][c], 0, 0, 0);
+#pragma unroll
+            for (int c = 0; c < NR; ++c) ps[c] = fma(x1[i], br[c].y, fma(x0[i], br[c].x, ps[c]));
+            ps[NR] = fma(x1[i], x1[i], fma(x0[i], x0[i], ps[NR]));
+          }
+          __builtin_amdgcn_sched_barrier(0);  // interleaving more of them costs registers
+        }
       }
-      // ES elements per step.  The row's bits and the scalar operands of a step are fetched one
-      // step ahead (two register sets), so their latency hides behind the previous step's FMAs.
-      const int e0 = p * EP;
-      fetch(e0, 0, rawA, sA);
+    };
 #pragma unroll 1
-      for (int st = 0; st < NST; st += 2) {
-        // the wait for a set comes before the other set's fetches are issued (scalar loads
-        // return out of order, so a wait after them would cover them too)
-        arrived(sA[0][0]);
-        fetch(e0, st + 1, rawB, sB);
-        __builtin_amdgcn_sched_barrier(0);  // the fetches go out before the FMAs, not among them
-        step(rawA, sA);
-        arrived(sB[0][0]);
-        fetch(e0, min(st + 2, NST - 1), rawA, sA);
-        __builtin_amdgcn_sched_barrier(0);
-        step(rawB, sB);
-      }
+    for (int p = 0; p < NP - 1; ++p) {
+      stage_piece(p);
+      if (p & 1) load_pair(sub, rows, p + 1);
+      multiply_piece(p);
+    }
+    stage_piece(NP - 1);
+    load_vq(0, 0);  // the first half of this sub-chunk's V rows
+    load_vq(1, 1);
+    multiply_piece(NP - 1);
+    // every lane takes its own row's products
+    auto own = [&](double v0, double v1, double v2, double v3) {
+      const double lo = (ln & 1) ? v1 : v0, hi = (ln & 1) ? v3 : v2;
+      return (ln & 2) ? hi : lo;
+    };
+    double dot[NV], nr;
+#pragma unroll
+    for (int c = 0; c <= NR; ++c) {
+      double t4[4];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) t4[s] = __builtin_amdgcn_mfma_f64_4x4x4f64(part[s][c], 1.0, 0.0, 0, 0, 0);
+      (c == NR ? nr : dot[CG * 4 + c]) = own(t4[0], t4[1], t4[2], t4[3]);
+    }
+#pragma unroll
+    for (int c = 0; c < CG; ++c) {
+      auto column = [&](auto jc) {  // operand vector 4 c + jc: lane jc of every quad holds its results
+        constexpr int j = decltype(jc)::value, bcast = j * 0x55;
+        if (4 * c + j < NV) dot[4 * c + j] = own(dpp_f64<bcast>(acc[0][c]), dpp_f64<bcast>(acc[1][c]),
+                                                 dpp_f64<bcast>(acc[2][c]), dpp_f64<bcast>(acc[3][c]));
+      };
+      column(std::integral_constant<int, 0>{});
+      column(std::integral_constant<int, 1>{});
+      column(std::integral_constant<int, 2>{});
+      column(std::integral_constant<int, 3>{});
     }
     if constexpr (sizeof(T) == 1) {
       // the K pass worked on the codes: the row's power of two scales its dot products and its
       // squared norm (exactly: the sums are exact, see the precision notes of the file header)
       const double sk = pow2_f64(rek);
 #pragma unroll
-      for (int v = 0; v < NV; ++v) acc[v] *= sk;
+      for (int v = 0; v < NV; ++v) dot[v] *= sk;
       nr *= sk * sk;
     }
     // ---- softmax statistics of the sub-chunk; the lane owns cache row sub*kSub + lane
@@ -637,7 +685,7 @@ __global__ __launch_bounds__(256) void decode_attend(DecodeArgs a, OT* __restric
     double recv = 0.0;  // this lane's element of the sub-chunk record
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-      const double sg = acc[g] / root_d;
+      const double sg = dot[g] / root_d;
       const double mx = fast_wave_max(valid ? sg : -INFINITY);
       const double e = valid ? exp(sg - mx) : 0.0;
       // (fp8 cache: the V pass works on the codes, so the row's power of two rides on its probability)
@@ -655,7 +703,7 @@ __global__ __launch_bounds__(256) void decode_attend(DecodeArgs a, OT* __restric
 #pragma unroll
     for (int c = 0; c < kCand; ++c) {
       const double den = cn[c] * nrow;
-      const double u = den > 0.0 ? acc[G + c] / den : 0.0;
+      const double u = den > 0.0 ? dot[G + c] / den : 0.0;
       const Best m = fast_wave_best_match(u, pos, (valid && cs[c] >= 0 && j != cs[c]) ? j : -1);
       if (ln == 2 * G + c) recv = m.u;
       if (ln == 2 * G + kCand + c) recv = double(m.slot);
@@ -721,7 +769,6 @@ __global__ __launch_bounds__(256) void decode_attend(DecodeArgs a, OT* __restric
   //      rescaled from its sub-chunk's maximum to the chunk's (fp32, like the rows themselves).
   //      A quarter of the partial-output bytes of a row per sub-chunk: on this chip a written
   //      byte costs the stream of K and V rows several read bytes.
-  static_assert(kGroup == 1, "one chunk per workgroup");
   lds_barrier();
   for (int g = w; g < G; g += 4) {
     double mc = wmax[0][g];
@@ -734,7 +781,7 @@ __global__ __launch_bounds__(256) void decode_attend(DecodeArgs a, OT* __restric
         const double mw = wmax[i][g];
         if (mw != -INFINITY) {
           const float f = expf(float(mw - mc));
-          const float* xr = reinterpret_cast<const float*>(stage + i * 64 * kPitch) + g * D + lane * 2;
+          const float* xr = reinterpret_cast<const float*>(stage + i * kWaveStage) + g * D + lane * 2;
           o0 = fmaf(f, xr[0], o0);
           o1 = fmaf(f, xr[1], o1);
         }
@@ -750,7 +797,7 @@ __global__ __launch_bounds__(256) void decode_attend(DecodeArgs a, OT* __restric
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   if (tid == 0) {
-    const int ngroup = (total + kGroup * kChunk - 1) / (kGroup * kChunk);
+    const int ngroup = (total + kChunk - 1) / kChunk;
     sh_last = (__hip_atomic_fetch_add(&a.ticket[lbh], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
                unsigned(ngroup - 1)) ? 1 : 0;
   }
@@ -977,7 +1024,7 @@ hipError_t launch_decode(d2o_ctx* c, int layer0, int nl_all, View q, View k, Vie
       chunk_id[i] = i;
       mc[i] = 1;
       for (const auto& mt : c->layers[a.layer0 + i].meta) {
-        mc[i] = std::max(mc[i], (mt.budget + 1 + kGroup * kChunk - 1) / (kGroup * kChunk));
+        mc[i] = std::max(mc[i], (mt.budget + 1 + kChunk - 1) / kChunk);
         rows += mt.budget + 1;
       }
     }

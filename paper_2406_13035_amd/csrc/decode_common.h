@@ -22,10 +22,14 @@ constexpr int kMaxLayersPerCall = 64;
 // best cosine and that key's slot; rounded up to a multiple of eight (64 bytes).
 __host__ __device__ constexpr int rec_doubles(int G) { return (2 * G + 2 * kCand + 7) / 8 * 8; }
 constexpr int kPiece = 64;              // bytes of a cache row staged per LDS round
-constexpr int kPitch = kPiece + 16;     // LDS pitch of a staged row piece (20 words: the lanes' reads spread over all banks)
-constexpr int kStageBytes = 4 * 64 * kPitch;
+constexpr int kPitch = kPiece + 16;     // LDS pitch of a staged row piece (20 words: sixteen lanes that read sixteen
+                                        // consecutive rows, and four lanes that write a row, meet all banks once)
+// A wavefront's 64 rows are staged in four sets of sixteen, row s + 4 b + 16 i as row 4 b + i of set s; 16 words
+// between the sets put consecutive rows on different banks for the writing lanes.
+constexpr int kSetBytes = 16 * kPitch + 64;
+constexpr int kWaveStage = 4 * kSetBytes;
+constexpr int kStageBytes = 4 * kWaveStage;
 constexpr int kSub = 64;                // rows one wavefront handles at a time (lane = row)
-constexpr int kGroup = 1;               // chunks of 256 slots per workgroup
 
 struct DecodeArgs {
   int32_t* ccount;
@@ -46,7 +50,7 @@ struct DecodeArgs {
                       // query heads, [G..2G) exp-sums relative to them, [2G..2G+kCand) the candidates' best
                       // cosine, [2G+kCand..2G+2kCand) its slot (-1 none); written with one store
   float* pacc;        // [chunk][B][Hkv][G][d] partial outputs, relative to the chunk's softmax maximum
-  double* vecs;       // [L][B][Hkv][G + kCand][d] queries and candidate keys as fp64
+  double* vecs;       // [L][B][Hkv][(G + kCand) * d] queries and candidate keys as fp64, in the order of operand_index
   double* cnorm;      // [L][B][Hkv][kCand] |k| of the candidates
   int32_t* ev_evicted;
   int32_t* ev_target;
@@ -113,7 +117,7 @@ __device__ __forceinline__ void cvt16f<uint8_t>(const u32x4& v, float* out) {
   }
 }
 
-// N consecutive elements (4, 8 or 16 bytes) held as raw bits, and their conversion to doubles.
+// Consecutive elements (2 to 16 bytes) held as raw bits.
 template <int BYTES> struct RawBits;
 template <> struct RawBits<16> { typedef u32x4 type; };
 template <> struct RawBits<8> { typedef u32x2 type; };
@@ -123,29 +127,6 @@ __device__ __forceinline__ uint32_t raw_word(const uint16_t& r, int) { return r;
 __device__ __forceinline__ uint32_t raw_word(const u32x4& r, int i) { return r[i]; }
 __device__ __forceinline__ uint32_t raw_word(const u32x2& r, int i) { return r[i]; }
 __device__ __forceinline__ uint32_t raw_word(const uint32_t& r, int) { return r; }
-template <typename T, int N, typename R>
-__device__ __forceinline__ void raw_to_f64(const R& r, double* out) {
-  if constexpr (sizeof(T) == 1) {  // two or four fp8 codes in one word, without the row's power of two
-    static_assert(N == 2 || N == 4, "fp8 codes come two or four at a time");
-    const int wd = int(raw_word(r, 0));
-    out[0] = double(__builtin_amdgcn_cvt_f32_fp8(wd, 0));
-    out[1] = double(__builtin_amdgcn_cvt_f32_fp8(wd, 1));
-    if constexpr (N == 4) {
-      out[2] = double(__builtin_amdgcn_cvt_f32_fp8(wd, 2));
-      out[3] = double(__builtin_amdgcn_cvt_f32_fp8(wd, 3));
-    }
-  } else if constexpr (sizeof(T) == 2) {
-#pragma unroll
-    for (int i = 0; i < N / 2; ++i) {
-      out[2 * i] = double(__uint_as_float(raw_word(r, i) << 16));
-      out[2 * i + 1] = double(__uint_as_float(raw_word(r, i) & 0xFFFF0000u));
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < N; ++i) out[i] = double(__uint_as_float(raw_word(r, i)));
-  }
-}
-
 // The partial results of a step are laid out chunk-major: [layer's chunk offset + chunk]
 // [sequence][KV head]...  Workgroups are dispatched head-fastest, so the results that are written
 // at about the same time are neighbours in memory (per-head contiguous arrays scatter them; a
@@ -161,10 +142,29 @@ __device__ __forceinline__ int64_t elog_index(const DecodeArgs& a, int64_t bh, i
   return (((int64_t(chunk0) + (j >> 8)) * (a.B * a.Hkv) + bh) * G + g) * kChunk + (j & (kChunk - 1));
 }
 
-// Pins the point where a scalar-loaded value must have arrived; nothing is scheduled across it.
-__device__ __forceinline__ void arrived(double v) {
-  asm volatile("" ::"s"(v));
-  __builtin_amdgcn_sched_barrier(0);
+// Place of element c of operand vector v (queries, then candidate keys) in a head's table: the order in
+// which the lanes of the K pass's matrix instructions fetch it.  A row piece of 64 bytes is four
+// parts of 16 (k = 0..3); two consecutive elements of every part and vector form a step.
+template <typename T, int NV>
+__host__ __device__ constexpr int operand_index(int v, int c) {
+  constexpr int EP = kPiece / int(sizeof(T)), EL = 16 / int(sizeof(T));
+  const int p = c / EP, k = c % EP / EL, e = c % EL;
+  return (((p * (EL / 2) + e / 2) * NV + v) * 4 + k) * 2 + (e & 1);
+}
+// Elements 2 i and 2 i + 1 of 16 bytes of a row (fp8 codes: without the row's power of two).
+template <typename T>
+__device__ __forceinline__ void pair_f64(const u32x4& r, int i, double& x0, double& x1) {
+  if constexpr (sizeof(T) == 1) {
+    const int wd = int(r[i / 2]);
+    x0 = double(i & 1 ? __builtin_amdgcn_cvt_f32_fp8(wd, 2) : __builtin_amdgcn_cvt_f32_fp8(wd, 0));
+    x1 = double(i & 1 ? __builtin_amdgcn_cvt_f32_fp8(wd, 3) : __builtin_amdgcn_cvt_f32_fp8(wd, 1));
+  } else if constexpr (sizeof(T) == 2) {
+    x0 = double(__uint_as_float(r[i] << 16));
+    x1 = double(__uint_as_float(r[i] & 0xFFFF0000u));
+  } else {
+    x0 = double(__uint_as_float(r[2 * i]));
+    x1 = double(__uint_as_float(r[2 * i + 1]));
+  }
 }
 
 // Data that one workgroup of decode_attend hands to another (the head's last workgroup) goes

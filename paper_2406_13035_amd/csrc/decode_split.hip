@@ -56,7 +56,6 @@ __global__ __launch_bounds__(256) void decode_close_part(DecodeArgs a) {
   constexpr int U = G >= 8 ? 2 : 4;  // slots per thread and batch of the score pass
   constexpr int C4 = D / 4;          // threads across an output row (four columns each)
   constexpr int RG = 256 / C4;       // groups of threads that share the part's chunks
-  static_assert(kGroup == 1, "a flat index is one chunk");
   __shared__ double em[kMaxPartChunks * 4 * G];  // exp(m_sub - max) / normaliser of the part's sub-chunks
   __shared__ float fred[4 * 256];
   __shared__ double sred[8];
