@@ -7,10 +7,10 @@
 //                   attention pass multiplies every cache key with: the G queries and the keys
 //                   of kCand eviction candidates chosen at the end of the previous step.
 //   decode_attend   one workgroup per chunk of 256 slots, each of its four wavefronts working
-//                   alone on 64 of them.  K pass: the keys go through LDS so that one lane owns
-//                   one cache row; the lane forms, in fp64, the G logits, the dot products with
-//                   the candidate keys and the row's squared norm (the vectors come in through
-//                   scalar loads, so there is no cross-lane reduction).  Then the softmax
+//                   alone on 64 of them.  K pass: the keys go through LDS, and four lanes share
+//                   four cache rows, a quarter of every 64 bytes each; they form, in fp64, the G
+//                   logits, the dot products with the candidate keys and the rows' squared norms
+//                   (the vectors are in LDS as fp64).  Then, one row per lane, the softmax
 //                   statistics of the 64 rows, the candidates' best cosine among them (Eq. 9),
 //                   and the partial P V in fp32.
 //                   The last workgroup of a head to finish (a ticket counter, no waiting)
@@ -75,6 +75,13 @@ hipError_t static_scratch_address(unsigned char** out) {
 namespace {
 
 using namespace dec;
+
+// The type of q, k_new, v_new and (unless fp32 is asked for) of the outputs: the cache's own
+// type, or bf16 when the cache holds fp8 codes.
+template <typename T>
+struct TensorType {
+  typedef typename std::conditional<sizeof(T) == 1, uint16_t, T>::type type;
+};
 
 // T: the cache's element type (uint8_t: fp8 codes), IT: the type of q, k_new, v_new.
 template <typename T, typename IT, int D, int G>
@@ -198,17 +205,23 @@ __device__ __forceinline__ void head_normaliser(const DecodeArgs& a, int64_t bh,
 
 // Closing work of a head, by one workgroup of 256 threads: combine the sub-chunks, update the
 // scores, choose the evicted token and the next candidates, find the merge target and finish the
-// step.  Every load whose address does not depend on a result of this function is issued before
-// the first of the workgroup-wide reductions, so the function costs a few memory round trips.
+// step.  What bounds it is its chain of memory round trips and workgroup-wide exchanges, so every
+// load whose address does not depend on a result of this function is issued before the first of
+// the reductions - the records, and the first batches of partial rows and of scores with their
+// exp-logits - and the rows that a merge needs when the candidate is evicted as soon as the
+// candidate's match is known.  (With each of them requested where it is used, and an exchange per
+// evicted token and candidate, a head of 80 to 1900 entries took 18000 to 24700 cycles to close;
+// issued one layer per call, 32 layers take 8 % less now, and a step of a 128-entry fp32 cache
+// 17.5 instead of 19.2 us.)
 template <typename T, typename OT, int D, int G>
 __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ out, const View& ov, int li, int b,
                                           int hk, int64_t lbh, int total, int nsub, double* sred, int* ired,
                                           float* fred, double* dred, unsigned char* park) {
   constexpr int kRec = rec_doubles(G);
-  constexpr int U = G >= 8 ? 1 : G >= 4 ? 3 : G >= 2 ? 4 : 6;  // slots per thread and batch of the score pass
+  constexpr int U = G >= 8 ? 1 : G >= 4 ? 2 : G >= 2 ? 4 : 6;  // slots per thread and batch of the score pass
   constexpr int C4 = D / 4;                           // threads across an output row (four columns each)
   constexpr int RG = 256 / C4;                        // groups of threads that share the sub-chunks
-  constexpr int PB = 4;                               // partial rows in flight per thread
+  constexpr int PB = G >= 4 ? 1 : G == 2 ? 2 : 4;      // partial rows of each query head in flight per thread
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int last = total - 1;
   const int32_t* mt = a.meta + lbh * 4;
@@ -231,12 +244,37 @@ __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ 
     park_kv[tid] = Kc[int64_t(last) * D + tid];
     park_kv[256 + tid] = Vc[int64_t(last) * D + tid];
   }
+  constexpr int kEmCap = (kStageBytes - 8192) / int(sizeof(double));
+  constexpr int kSegSubs = kEmCap / G;  // sub-chunks whose factors fit `em`
+  // ---- the first batches of the output and score passes are requested now: they arrive while the
+  //      normaliser is formed
+  double sc[U], e[U][G];
+  int ps[U];
+  int seg0 = 0, jend = min(total, kSegSubs * kSub);  // the segment of sub-chunks whose factors `em` holds, and its last slot + 1
+  auto load_batch = [&](int j0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int j = min(j0 + u * 256, jend - 1);
+      sc[u] = a.cscore[slot0 + j];
+      ps[u] = a.cpos[slot0 + j];
+#pragma unroll
+      for (int g = 0; g < G; ++g) e[u][g] = ld_agent(&a.elog[elog_index(a, bh, ch0, G, g, j)]);
+    }
+  };
+  const int c4 = tid % C4, rg = tid / C4;
+  const int nchunk = (nsub + 3) / 4;
+  constexpr bool kEarlyRows = G <= 4;  // (eight query heads' rows would not fit the registers)
+  float4 pr[G][PB];
+  auto load_partial = [&](int g, int c0) {
+#pragma unroll
+    for (int u = 0; u < PB; ++u)
+      pr[g][u] = ld_agent4(a.pacc + (chunk_index(a, bh, ch0, min(c0 + u * RG, nchunk - 1)) * G + g) * D + c4 * 4);
+  };
   // ---- head maximum and exact normaliser sum_j exp(s_j - max) of each query head (fixed tree),
   //      all query heads in one sweep over the sub-chunk records.  exp(m_sub - max) of every
   //      sub-chunk and query head is kept in LDS (`em`, behind the parked values) for the output
   //      and score passes; for a head with more sub-chunks than fit, the factors overwrite the
   //      maxima in the records and the score pass brings them into LDS segment by segment.
-  constexpr int kEmCap = (kStageBytes - 8192) / int(sizeof(double));
   double* em = reinterpret_cast<double*>(park);  // [nsub][G]
   const bool em_lds = nsub * G <= kEmCap;
   double Mg[G], Lg[G];
@@ -268,14 +306,19 @@ __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ 
         for (int g = 0; g < G; ++g) Mg[g] = fmax(Mg[g], ld_agent(&a.rec[x + g]));
       }
     }
+    if constexpr (kEarlyRows) {
 #pragma unroll
-    for (int g = 0; g < G; ++g) Mg[g] = wave_max(Mg[g]);
-    __syncthreads();
+      for (int g = 0; g < G; ++g) load_partial(g, rg);
+    }
+    load_batch(tid);
+#pragma unroll
+    for (int g = 0; g < G; ++g) Mg[g] = fast_wave_max(Mg[g]);
+    lds_barrier();
     if (lane == 0) {
 #pragma unroll
       for (int g = 0; g < G; ++g) dred[w * G + g] = Mg[g];
     }
-    __syncthreads();
+    lds_barrier();
 #pragma unroll
     for (int g = 0; g < G; ++g) Mg[g] = fmax(fmax(dred[g], dred[G + g]), fmax(dred[2 * G + g], dred[3 * G + g]));
     double part[G];
@@ -293,9 +336,19 @@ __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ 
           st_agent(&a.rec[x + g], t);  // the factor replaces the maximum (nobody needs it again)
       }
     }
+    // (block_sum's tree, all query heads in one exchange)
 #pragma unroll
-    for (int g = 0; g < G; ++g) Lg[g] = block_sum(part[g], sred);
-    __syncthreads();  // `em` is complete (in memory: the stores have been acknowledged)
+    for (int g = 0; g < G; ++g) part[g] = wave_sum(part[g]);
+    if (lane == 0) {
+#pragma unroll
+      for (int g = 0; g < G; ++g) dred[(4 + w) * G + g] = part[g];
+    }
+    if (em_lds)
+      lds_barrier();
+    else
+      __syncthreads();  // the factors are in memory: the stores have been acknowledged
+#pragma unroll
+    for (int g = 0; g < G; ++g) Lg[g] = ((dred[4 * G + g] + dred[5 * G + g]) + dred[6 * G + g]) + dred[7 * G + g];
     // the table holds the factors already divided by the normaliser: a probability is then
     // one product, exp(s_j - m_sub) * em
     if (em_lds) {
@@ -331,26 +384,12 @@ __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ 
       wcm_ps[w * kCand + i] = make_int2(r.pos, r.slot);
     }
   }
-  // ---- score pass, set-up
   const bool evict = total > mt[1];
   const int recent = mt[2];
   Best ev{0.0, 0, -1};
   Best low[kCand + 1];
 #pragma unroll
   for (int i = 0; i <= kCand; ++i) low[i] = Best{0.0, 0, -1};
-  double sc[U], e[U][G];
-  int ps[U];
-  int seg0 = 0, jend = total;  // the segment of sub-chunks whose factors `em` holds, and its last slot + 1
-  auto load_batch = [&](int j0) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int j = min(j0 + u * 256, jend - 1);
-      sc[u] = a.cscore[slot0 + j];
-      ps[u] = a.cpos[slot0 + j];
-#pragma unroll
-      for (int g = 0; g < G; ++g) e[u][g] = ld_agent(&a.elog[elog_index(a, bh, ch0, G, g, j)]);
-    }
-  };
   // Eq. 6 for the batch's slots, the token to evict (Eq. 7-8 on count+1 entries) and the lowest
   // scores among the tokens evictable at the next step
   auto apply_batch = [&](int j0) {
@@ -384,18 +423,20 @@ __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ 
   };
   // ---- output rows: thread (rg, c4) adds the chunks rg, rg + RG, ... of four columns, PB
   //      loads in flight; the groups' sums are added in ascending order
-  const int c4 = tid % C4, rg = tid / C4;
-  const int nchunk = (nsub + 3) / 4;
+  const MergeRows<T> mr = [&]() {
+    lds_barrier();  // the wavefronts' matches are in LDS
+    return load_merge_rows<T, D>(a, slot0, cl[0], candidate_match(wcm_u, wcm_ps, 0).slot);
+  }();
 #pragma unroll
   for (int g = 0; g < G; ++g) {
     float num[4] = {0.f, 0.f, 0.f, 0.f};
     for (int c0 = rg; c0 < nchunk; c0 += PB * RG) {
-      float4 v[PB];
+      if (!kEarlyRows || c0 != rg) load_partial(g, c0);
+      const float4(&v)[PB] = pr[g];
       double fc[PB];
 #pragma unroll
       for (int u = 0; u < PB; ++u) {
         const int cc = min(c0 + u * RG, nchunk - 1);
-        v[u] = ld_agent4(a.pacc + (chunk_index(a, bh, ch0, cc) * G + g) * D + c4 * 4);
         fc[u] = 0.0;  // exp(chunk maximum - max): the largest of its sub-chunks' factors
 #pragma unroll
         for (int i = 0; i < 4; ++i)
@@ -426,7 +467,6 @@ __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ 
     __builtin_amdgcn_sched_barrier(0);  // one query head after the other (registers)
   }
   // ---- score pass: batches of U slots per thread, their loads in flight together
-  constexpr int kSegSubs = kEmCap / G;  // sub-chunks whose factors fit `em`
 #pragma unroll 1
   for (seg0 = 0; seg0 < nsub; seg0 += kSegSubs) {
     const int nseg = min(kSegSubs, nsub - seg0);
@@ -444,11 +484,11 @@ __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ 
     }
 #pragma unroll 1
     for (int j0 = seg0 * kSub + tid; j0 < jend; j0 += U * 256) {
-      load_batch(j0);
+      if (j0 != tid) load_batch(j0);
       apply_batch(j0);
     }
   }
-  close_head<T, D>(a, lbh, slot0, total, evict, ev, low, cl, told, sred, ired, dred, wcm_u, wcm_ps, park_kv);
+  close_head<T, D>(a, lbh, slot0, total, evict, ev, low, cl, told, sred, ired, dred, wcm_u, wcm_ps, park_kv, mr);
 }
 
 // (second launch bound: wavefronts per SIMD)
@@ -468,7 +508,10 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
   constexpr int CG = (NV + 1) / 4, NR = NV > 4 * CG ? NV - 4 * CG : 0;  // K pass: groups of four operand vectors, and vectors left over
   constexpr int kRec = rec_doubles(G);
   __shared__ __attribute__((aligned(16))) unsigned char stage[kStageBytes];
-  __shared__ __attribute__((aligned(16))) double opnd[NV * D];
+  // the operand vectors: a copy per wavefront where four fit (the wavefronts then stay independent
+  // until they combine their results), else one for the workgroup, behind a barrier
+  constexpr bool kOwnOpnd = G <= 2;
+  __shared__ __attribute__((aligned(16))) double opnd[kOwnOpnd ? 4 : 1][NV * D];
   __shared__ float ps[4][G][kSub];
   __shared__ double wmax[4][G];  // per wavefront: softmax maximum of its sub-chunk (-inf: no rows)
   __shared__ int sh_last;
@@ -476,8 +519,9 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
   // Grid: x = head (fastest), y = flat chunk group over the layers.  Workgroups go round-robin to
   // the XCDs in index order, so with a head count that is a multiple of the XCD count every chunk
   // of a head, and the workgroup that closes it, run on one XCD.
-  const int entry = find_entry(a, blockIdx.y), grp = blockIdx.y - a.lay_off[entry];
-  const int li = a.lay_id[entry];
+  // (a call of one layer needs no search)
+  const int entry = a.nl == 1 ? 0 : find_entry(a, blockIdx.y), grp = blockIdx.y - (a.nl == 1 ? 0 : a.lay_off[entry]);
+  const int li = a.nl == 1 ? 0 : a.lay_id[entry];
   const int l = a.layer0 + li, b = blockIdx.x / a.Hkv, hk = blockIdx.x % a.Hkv;
   const int64_t lbh = (int64_t(l) * a.B + b) * a.Hkv + hk;
   // Everything the workgroup needs to know about its head comes through the scalar cache in one
@@ -497,11 +541,12 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
   }
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   // the head's operand vectors, 16 bytes per thread and load
-  constexpr int kOpnd16 = NV * D / 2, kOpndLoads = (kOpnd16 + 255) / 256;
+  constexpr int kOpnd16 = NV * D / 2, kOpndThreads = kOwnOpnd ? 64 : 256, kOpndLoads = (kOpnd16 + kOpndThreads - 1) / kOpndThreads;
+  const int ot = kOwnOpnd ? lane : tid;
   u32x4 opr[kOpndLoads];
 #pragma unroll
   for (int i = 0; i < kOpndLoads; ++i)
-    opr[i] = reinterpret_cast<const u32x4*>(a.vecs + lbh * NV * D)[min(tid + i * 256, kOpnd16 - 1)];
+    opr[i] = reinterpret_cast<const u32x4*>(a.vecs + lbh * NV * D)[min(ot + i * kOpndThreads, kOpnd16 - 1)];
   asm volatile("" ::"s"(total), "s"(mt0), "s"(mt3));  // all of them are on their way before the first wait
   if (grp * kChunk >= total) return;
   const int64_t bh = int64_t(b) * a.Hkv + hk;
@@ -511,6 +556,7 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
   // A workgroup owns a chunk of 256 slots; each wavefront works alone on 64 rows ("sub-chunk") of it:
   // while it computes on its keys, its V rows are in flight.
   unsigned char* mine = stage + w * kWaveStage;
+  double* mine_opnd = opnd[kOwnOpnd ? w : 0];
   const int ln = lane;
   const double root_d = sqrt(double(D));
   // K loads of a sub-chunk.  The K pass takes a row's bytes in pieces of 64 (one LDS staging round
@@ -536,8 +582,8 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
   if (rows > 0) load_pair(sub, rows, 0);
 #pragma unroll
   for (int i = 0; i < kOpndLoads; ++i)
-    if (tid + i * 256 < kOpnd16) reinterpret_cast<u32x4*>(opnd)[tid + i * 256] = opr[i];
-  lds_barrier();  // the operands are in LDS; the K rows may still be on their way
+    if (ot + i * kOpndThreads < kOpnd16) reinterpret_cast<u32x4*>(mine_opnd)[ot + i * kOpndThreads] = opr[i];
+  if (!kOwnOpnd) lds_barrier();  // the operands are in LDS; the K rows may still be on their way
   if (rows <= 0) {  // this wavefront only takes part in the combination
     if (ln < G) wmax[w][ln] = -INFINITY;
   } else {
@@ -553,6 +599,10 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
     // vectors, which would leave its columns empty, are multiplied there (with the squared norm) and
     // only added up by it, as products with ones.
     // Either way the lane's own row (its lane number) is one transposition inside a quad of lanes away.
+    // With one row per lane and the operands as scalar loads, fetched a step ahead, a wavefront of a
+    // small launch spent 12900 cycles here, most of them waiting for one cache line of operands after
+    // the other (2 KB per head at G = 1); it now spends 5300.  Where the stream of K and V is the bound
+    // both forms take the same time; issued one layer per call, 32 layers take 4.8 % less.
     double acc[4][CG > 0 ? CG : 1], part[4][NR + 1];
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
@@ -562,8 +612,8 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
       for (int c = 0; c <= NR; ++c) part[s][c] = 0.0;
     }
     const unsigned char* arow = mine + (((ln >> 2) & 3) * 4 + (ln & 3)) * kPitch + (ln >> 4) * 16;
-    const double* bcol = opnd + (min(ln & 3, NV - 1) * 4 + (ln >> 4)) * 2;  // vector ln % 4 of a group (three: the last one twice)
-    const double* ball = opnd + (CG * 16 + (ln >> 4)) * 2;       // first of the left-over vectors
+    const double* bcol = mine_opnd + (min(ln & 3, NV - 1) * 4 + (ln >> 4)) * 2;  // vector ln % 4 of a group (three: the last one twice)
+    const double* ball = mine_opnd + (CG * 16 + (ln >> 4)) * 2;       // first of the left-over vectors
     // the staging lanes' rows: i * 8 + t
     const int t = ln >> 3;
     unsigned char* srow = mine + (t & 3) * kSetBytes + (t >> 2) * 4 * kPitch + (ln & 3) * 16;
@@ -825,13 +875,6 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
   head_tail<T, OT, D, G>(a, out, ov, li, b, hk, lbh, total, (total + kSub - 1) / kSub, sred, ired, fred, dred,
                          stage + 8192);
 }
-
-// The type of q, k_new, v_new and (unless fp32 is asked for) of the outputs: the cache's own
-// type, or bf16 when the cache holds fp8 codes.
-template <typename T>
-struct TensorType {
-  typedef typename std::conditional<sizeof(T) == 1, uint16_t, T>::type type;
-};
 
 template <typename T, int D>
 hipError_t run_prepare_g(d2o_ctx* c, const DecodeArgs& a, int nl, View q, View k, View v, hipStream_t s) {

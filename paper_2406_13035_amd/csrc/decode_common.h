@@ -233,14 +233,42 @@ __device__ __forceinline__ Best fast_wave_first_evicted(const Best& b) {
   const int src = __ffsll((long long)who) - 1;
   return Best{smin, pmax, __builtin_amdgcn_readlane(b.slot, src)};
 }
+// This thread's elements of the two rows a step merges, the evicted one (ke, ve) and its match (kt, vt),
+// as they were before the step; fp8 cache: with the rows' powers of two.
+template <typename T>
+struct MergeRows {
+  T ke, ve, kt, vt;
+  int xke, xve, xkt, xvt;
+};
+template <typename T, int D>
+__device__ __forceinline__ MergeRows<T> load_merge_rows(const DecodeArgs& a, int64_t slot0, int es, int bs) {
+  MergeRows<T> r{};
+  const int e = max(es, 0), t = max(bs, 0);
+  if (threadIdx.x < D) {
+    const T* Kc = static_cast<const T*>(a.cK) + slot0 * D + threadIdx.x;
+    const T* Vc = static_cast<const T*>(a.cV) + slot0 * D + threadIdx.x;
+    r.ke = Kc[int64_t(e) * D];
+    r.ve = Vc[int64_t(e) * D];
+    r.kt = Kc[int64_t(t) * D];
+    r.vt = Vc[int64_t(t) * D];
+  }
+  if constexpr (sizeof(T) == 1) {
+    r.xke = a.cKe[slot0 + e];
+    r.xve = a.cVe[slot0 + e];
+    r.xkt = a.cKe[slot0 + t];
+    r.xvt = a.cVe[slot0 + t];
+  }
+  return r;
+}
 // Eq. 9 arg-max result -> Eq. 10 threshold, Eq. 11-12 merge with one source, slot bookkeeping.
 // Called by every thread of a workgroup (at least D threads) with block-uniform arguments.
-// told: the head's threshold before the step; (kl, vl): this thread's element of the last slot's
-// row as it was before the step; (sl, pl): that slot's updated score and its position.
+// (es, ep): the evicted slot and its position; (best, bp, bs): its match; told: the head's threshold
+// before the step; (kl, vl): this thread's element of the last slot's row as it was before the step;
+// (sl, pl): that slot's updated score and its position; mr: the two rows to merge.
 template <typename T, int D>
-__device__ __forceinline__ void finish_head(const DecodeArgs& a, int64_t lbh, int64_t slot0, int es, int total,
+__device__ __forceinline__ void finish_head(const DecodeArgs& a, int64_t lbh, int64_t slot0, int es, int ep, int total,
                                             double best, int bp, int bs, double told, T kl, T vl, double sl,
-                                            int pl, double* red) {
+                                            int pl, const MergeRows<T>& mr, double* red) {
   T* Kc = static_cast<T*>(a.cK) + slot0 * D;
   T* Vc = static_cast<T*>(a.cV) + slot0 * D;
   const int tid = threadIdx.x, last = total - 1;
@@ -253,7 +281,7 @@ __device__ __forceinline__ void finish_head(const DecodeArgs& a, int64_t lbh, in
     do_merge = best >= a.tau_force;
   }
   if (tid == 0) {
-    a.ev_evicted[lbh] = es == last ? pl : a.cpos[slot0 + es];
+    a.ev_evicted[lbh] = ep;
     a.ev_target[lbh] = do_merge ? bp : -1;
     a.ev_ustar[lbh] = best;
     a.ccount[lbh] = last;
@@ -272,10 +300,8 @@ __device__ __forceinline__ void finish_head(const DecodeArgs& a, int64_t lbh, in
     if (do_merge) {
       double km = 0.0, vm = 0.0;
       if (tid < D) {
-        const double ke = Elem<T>::to_f64(es == last ? kl : Kc[int64_t(es) * D + tid]) * pow2_f64(Ke[es]);
-        const double ve = Elem<T>::to_f64(es == last ? vl : Vc[int64_t(es) * D + tid]) * pow2_f64(Ve[es]);
-        const double kt = Elem<T>::to_f64(bs == last ? kl : Kc[int64_t(bs) * D + tid]) * pow2_f64(Ke[bs]);
-        const double vt = Elem<T>::to_f64(bs == last ? vl : Vc[int64_t(bs) * D + tid]) * pow2_f64(Ve[bs]);
+        const double ke = Elem<T>::to_f64(mr.ke) * pow2_f64(mr.xke), ve = Elem<T>::to_f64(mr.ve) * pow2_f64(mr.xve);
+        const double kt = Elem<T>::to_f64(mr.kt) * pow2_f64(mr.xkt), vt = Elem<T>::to_f64(mr.vt) * pow2_f64(mr.xvt);
         const double kk = __dadd_rn(__dmul_rn(e1, kt), __dmul_rn(w, ke));
         const double vv = __dadd_rn(__dmul_rn(e1, vt), __dmul_rn(w, ve));
         km = Elem<uint16_t>::to_f64(Elem<uint16_t>::from_f64(kk / z));
@@ -320,10 +346,8 @@ __device__ __forceinline__ void finish_head(const DecodeArgs& a, int64_t lbh, in
   } else {
     if (tid < D) {
       if (do_merge) {
-        const T ke = es == last ? kl : Kc[int64_t(es) * D + tid], ve = es == last ? vl : Vc[int64_t(es) * D + tid];
-        const T kt = bs == last ? kl : Kc[int64_t(bs) * D + tid], vt = bs == last ? vl : Vc[int64_t(bs) * D + tid];
-        const double kk = __dadd_rn(__dmul_rn(e1, Elem<T>::to_f64(kt)), __dmul_rn(w, Elem<T>::to_f64(ke)));
-        const double vv = __dadd_rn(__dmul_rn(e1, Elem<T>::to_f64(vt)), __dmul_rn(w, Elem<T>::to_f64(ve)));
+        const double kk = __dadd_rn(__dmul_rn(e1, Elem<T>::to_f64(mr.kt)), __dmul_rn(w, Elem<T>::to_f64(mr.ke)));
+        const double vv = __dadd_rn(__dmul_rn(e1, Elem<T>::to_f64(mr.vt)), __dmul_rn(w, Elem<T>::to_f64(mr.ve)));
         const T km = Elem<T>::from_f64(kk / z), vm = Elem<T>::from_f64(vv / z);
         if (bs == last) {  // the merged row is the one that moves into the hole
           kl = km;
@@ -400,58 +424,78 @@ __device__ __forceinline__ Best scan_matches(const DecodeArgs& a, int64_t slot0,
 }
 
 
+// Best match of candidate 0 over the workgroup's four wavefronts (their results are in LDS).
+__device__ __forceinline__ Best candidate_match(const double* wcm_u, const int2* wcm_ps, int ci) {
+  Best m{wcm_u[ci], wcm_ps[ci].x, wcm_ps[ci].y};
+#pragma unroll
+  for (int i = 1; i < 4; ++i) {
+    const int2 q = wcm_ps[i * kCand + ci];
+    if (better_match(wcm_u[i * kCand + ci], q.x, q.y, m)) m = Best{wcm_u[i * kCand + ci], q.x, q.y};
+  }
+  return m;
+}
+
 // The end of a head's closing work, by a workgroup of 256 threads.  On entry every thread holds
 // its own first-evicted entry `ev` and its sorted list `low` of the next step's lowest evictable
 // entries (a thread's entries belong to slots no other thread holds); LDS holds, per wavefront
 // and candidate, the best match found (`wcm_u`, `wcm_ps` = (position, slot)), the last slot's
 // updated score and position (sred[4], ired[8]) and its row as it was before the step
-// (`park_kv`: K at [0, D), V at [256, 256 + D)).  The function reduces them over the workgroup,
-// writes the next step's candidates, resets the head's ticket, finds the merge target (from the
-// candidates' results, else by a pass over the head's keys) and finishes the step.
+// (`park_kv`: K at [0, D), V at [256, 256 + D)).  `mr` holds the rows of candidate 0 and of its best
+// match (requested before the score pass, so that a step that evicts this candidate, which is the
+// normal case, waits for no memory here).  The function reduces the entries over the workgroup
+// (one exchange for the evicted token and the next candidates), writes the next step's
+// candidates, resets the head's ticket, finds the merge target (from the candidates' results,
+// else by a pass over the head's keys) and finishes the step.
 template <typename T, int D>
 __device__ __forceinline__ void close_head(const DecodeArgs& a, int64_t lbh, int64_t slot0, int total, bool evict,
                                            Best ev, Best (&low)[kCand + 1], const int (&cl)[kCand], double told,
                                            double* sred, int* ired, double* dred, const double* wcm_u,
-                                           const int2* wcm_ps, const T* park_kv) {
+                                           const int2* wcm_ps, const T* park_kv, MergeRows<T> mr) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int last = total - 1;
-  // evicted token: block-wide
-  ev = fast_wave_first_evicted(ev);
-  lds_barrier();
-  if (lane == 0) {
-    sred[w] = ev.u;
-    ired[w] = ev.pos;
-    ired[4 + w] = ev.slot;
+  // per wavefront: the first evicted, then the kCand + 1 lowest of the next step's evictable tokens
+  constexpr int NE = kCand + 2;
+  static_assert(4 * NE * 2 <= D, "the entries fit the exchange buffer");
+  Best* ex = reinterpret_cast<Best*>(dred);  // [4][NE]
+  {
+    const Best h = fast_wave_first_evicted(ev);
+    if (lane == 0) ex[w * NE] = h;
   }
-  lds_barrier();
-  const double s_last = sred[4];
-  const int p_last = ired[8];
-  ev = Best{sred[0], ired[0], ired[4]};
-#pragma unroll
-  for (int i = 1; i < 4; ++i)
-    if (evicts_before(sred[i], ired[i], ired[4 + i], ev)) ev = Best{sred[i], ired[i], ired[4 + i]};
-  const int es = evict ? ev.slot : -1;  // a candidate always exists: total > budget >= T + M
-  // the kCand + 1 lowest of the next step's evictable tokens: repeated block-wide extraction
-  int nxt[kCand + 1];
 #pragma unroll
   for (int r = 0; r <= kCand; ++r) {
-    Best h = fast_wave_first_evicted(low[0]);
-    lds_barrier();
-    if (lane == 0) {
-      sred[w] = h.u;
-      ired[w] = h.pos;
-      ired[4 + w] = h.slot;
-    }
-    lds_barrier();
-    h = Best{sred[0], ired[0], ired[4]};
-#pragma unroll
-    for (int i = 1; i < 4; ++i)
-      if (evicts_before(sred[i], ired[i], ired[4 + i], h)) h = Best{sred[i], ired[i], ired[4 + i]};
-    nxt[r] = h.slot;
+    const Best h = fast_wave_first_evicted(low[0]);
+    if (lane == 0) ex[w * NE + 1 + r] = h;
     if (h.slot >= 0 && low[0].slot == h.slot) {  // the owner pops its head
 #pragma unroll
       for (int i = 0; i < kCand; ++i) low[i] = low[i + 1];
       low[kCand].slot = -1;
+    }
+  }
+  lds_barrier();
+  const double s_last = sred[4];
+  const int p_last = ired[8];
+  ev = ex[0];
+#pragma unroll
+  for (int i = 1; i < 4; ++i) {
+    const Best h = ex[i * NE];
+    if (evicts_before(h.u, h.pos, h.slot, ev)) ev = h;
+  }
+  const int es = evict ? ev.slot : -1;  // a candidate always exists: total > budget >= T + M
+  Best nx[kCand + 1];
+#pragma unroll
+  for (int i = 0; i <= kCand; ++i) nx[i] = Best{0.0, 0, -1};
+#pragma unroll
+  for (int k = 0; k < 4 * (kCand + 1); ++k) {
+    const Best h = ex[k / (kCand + 1) * NE + 1 + k % (kCand + 1)];
+    if (evicts_before(h.u, h.pos, h.slot, nx[kCand])) {
+      nx[kCand] = h;
+#pragma unroll
+      for (int i = kCand; i > 0; --i)
+        if (evicts_before(nx[i].u, nx[i].pos, nx[i].slot, nx[i - 1])) {
+          const Best t = nx[i - 1];
+          nx[i - 1] = nx[i];
+          nx[i] = t;
+        }
     }
   }
   int ci = -1;
@@ -461,7 +505,7 @@ __device__ __forceinline__ void close_head(const DecodeArgs& a, int64_t lbh, int
   if (tid == 0) {  // the next step's candidates (every thread holds this step's list in registers)
     int k = 0;
     for (int r = 0; r <= kCand && k < kCand; ++r) {
-      int s = nxt[r];
+      int s = nx[r].slot;
       if (s < 0 || s == es) continue;
       if (es >= 0 && s == last) s = es;  // the last slot is about to move into the freed one
       a.cand[lbh * kCand + k++] = s;
@@ -484,30 +528,28 @@ __device__ __forceinline__ void close_head(const DecodeArgs& a, int64_t lbh, int
     // outside the list): a second pass over the head's keys.
     if (tid == 0) a.cmiss[lbh] += 1u;
     m = scan_matches<T, D>(a, slot0, es, total, dred, sred);
-  } else {
-    if (tid < 4) {  // the four wavefronts' results (written before the barriers of the score pass)
-      const int2 q = wcm_ps[tid * kCand + ci];
-      m = Best{wcm_u[tid * kCand + ci], q.x, q.y};
+    m = fast_wave_best_match(m.u, m.pos, m.slot);
+    lds_barrier();
+    if (lane == 0) {
+      sred[w] = m.u;
+      ired[w] = m.pos;
+      ired[4 + w] = m.slot;
     }
-  }
-  m = fast_wave_best_match(m.u, m.pos, m.slot);
-  lds_barrier();
-  if (lane == 0) {
-    sred[w] = m.u;
-    ired[w] = m.pos;
-    ired[4 + w] = m.slot;
-  }
-  lds_barrier();
-  m = Best{sred[0], ired[0], ired[4]};
+    lds_barrier();
+    m = Best{sred[0], ired[0], ired[4]};
 #pragma unroll
-  for (int i = 1; i < 4; ++i)
-    if (better_match(sred[i], ired[i], ired[4 + i], m)) m = Best{sred[i], ired[i], ired[4 + i]};
+    for (int i = 1; i < 4; ++i)
+      if (better_match(sred[i], ired[i], ired[4 + i], m)) m = Best{sred[i], ired[i], ired[4 + i]};
+  } else {
+    m = candidate_match(wcm_u, wcm_ps, ci);
+  }
+  if (ci != 0) mr = load_merge_rows<T, D>(a, slot0, es, m.slot);
   T kl = T(), vl = T();
   if (tid < D) {
     kl = park_kv[tid];
     vl = park_kv[256 + tid];
   }
-  finish_head<T, D>(a, lbh, slot0, es, total, m.u, m.pos, m.slot, told, kl, vl, s_last, p_last, sred);
+  finish_head<T, D>(a, lbh, slot0, es, ev.pos, total, m.u, m.pos, m.slot, told, kl, vl, s_last, p_last, mr, sred);
 }
 
 // The two launches that close the heads with more than a.big_rows entries (decode_split.hip).

@@ -306,6 +306,8 @@ __global__ __launch_bounds__(256) void decode_close_final(DecodeArgs a, OT* __re
     sred[4] = r[24];
     ired[8] = int(r[25]);
   }
+  __syncthreads();
+  const MergeRows<T> mr = load_merge_rows<T, D>(a, slot0, cl[0], candidate_match(wcm_u, wcm_ps, 0).slot);
   // ---- output rows: thread (rg, c4) adds the parts rg, rg + RG, ... of four columns, PB loads in
   //      flight; the groups' sums are added in ascending order
   {
@@ -344,7 +346,7 @@ __global__ __launch_bounds__(256) void decode_close_final(DecodeArgs a, OT* __re
     }
   }
   const bool evict = total > mt[1];
-  close_head<T, D>(a, lbh, slot0, total, evict, ev, low, cl, told, sred, ired, dred, wcm_u, wcm_ps, park_kv);
+  close_head<T, D>(a, lbh, slot0, total, evict, ev, low, cl, told, sred, ired, dred, wcm_u, wcm_ps, park_kv, mr);
 }
 
 template <typename T, typename OT, int D, int G>
