@@ -48,7 +48,8 @@ __global__ __launch_bounds__(256) void rank_by_position(const int32_t* __restric
       const int lim = min(kRankTile, (n - t0 + 7) & ~7);  // the padding compares as "not smaller"
       for (int i = tid; i < lim; i += 256) tile[i] = t0 + i < n ? cpos[slot0 + t0 + i] : 0x7FFFFFFF;
       __syncthreads();
-      for (int i = 0; i < lim; i += 8) {
+#pragma unroll 4
+      for (int i = 0; i < lim; i += 8) {  // (unrolled: several LDS reads in flight)
         const int4 pa = *reinterpret_cast<const int4*>(&tile[i]), pb = *reinterpret_cast<const int4*>(&tile[i + 4]);
 #pragma unroll
         for (int u = 0; u < U; ++u)
