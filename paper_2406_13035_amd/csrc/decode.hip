@@ -941,18 +941,27 @@ __global__ __launch_bounds__(256) void init_candidates(const int32_t* __restrict
   Best low[kCand + 1];
 #pragma unroll
   for (int i = 0; i <= kCand; ++i) low[i] = Best{0.0, 0, -1};
-  for (int j = tid; j < total; j += 256) {
-    const double sc = cscore[slot0 + j];
-    const int p = cpos[slot0 + j];
-    if (p >= n_sink && p <= new_pos - recent && evicts_before(sc, p, j, low[kCand - 1])) {
-      low[kCand - 1] = Best{sc, p, j};
+  for (int j0 = tid; j0 < total; j0 += 8 * 256) {  // eight entries in flight per thread
+    double sc[8];
+    int ps[8];
 #pragma unroll
-      for (int i = kCand - 1; i > 0; --i)
-        if (evicts_before(low[i].u, low[i].pos, low[i].slot, low[i - 1])) {
-          const Best t = low[i - 1];
-          low[i - 1] = low[i];
-          low[i] = t;
-        }
+    for (int u = 0; u < 8; ++u) {
+      sc[u] = cscore[slot0 + min(j0 + u * 256, total - 1)];
+      ps[u] = cpos[slot0 + min(j0 + u * 256, total - 1)];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int j = j0 + u * 256, p = ps[u];
+      if (j < total && p >= n_sink && p <= new_pos - recent && evicts_before(sc[u], p, j, low[kCand - 1])) {
+        low[kCand - 1] = Best{sc[u], p, j};
+#pragma unroll
+        for (int i = kCand - 1; i > 0; --i)
+          if (evicts_before(low[i].u, low[i].pos, low[i].slot, low[i - 1])) {
+            const Best t = low[i - 1];
+            low[i - 1] = low[i];
+            low[i] = t;
+          }
+      }
     }
   }
 #pragma unroll

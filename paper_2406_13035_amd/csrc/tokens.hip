@@ -28,35 +28,6 @@ __device__ __forceinline__ uint64_t order_key(double x) {
   return (b & 0x8000000000000000ull) ? ~b : (b | 0x8000000000000000ull);
 }
 
-// Exclusive prefix sums of two 0/1 flags over the block, in thread order.  Returns the
-// exclusive counts and adds the block totals to *tot_a / *tot_b (read by all threads).
-__device__ __forceinline__ void block_scan2(bool fa, bool fb, int& ex_a, int& ex_b, int& tot_a, int& tot_b,
-                                            int* wa, int* wb) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  const unsigned long long ma = __ballot(fa), mb = __ballot(fb);
-  const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  const int pa = __popcll(ma & below), pb = __popcll(mb & below);
-  __syncthreads();
-  if (lane == 0) {
-    wa[w] = __popcll(ma);
-    wb[w] = __popcll(mb);
-  }
-  __syncthreads();
-  int oa = 0, ob = 0, ta = 0, tb = 0;
-  for (int i = 0; i < nw; ++i) {
-    if (i < w) {
-      oa += wa[i];
-      ob += wb[i];
-    }
-    ta += wa[i];
-    tb += wb[i];
-  }
-  ex_a = oa + pa;
-  ex_b = ob + pb;
-  tot_a = ta;
-  tot_b = tb;
-}
-
 // Exclusive prefix sums of one integer per thread over the block, in thread order, and the
 // block total (read by all threads).
 __device__ __forceinline__ void block_scan_int(int v, int& ex, int& tot, int* wa) {
@@ -466,18 +437,28 @@ __global__ __launch_bounds__(256) void match_filter_bf16(const uint16_t* __restr
 __global__ __launch_bounds__(1024) void amb_compact_kernel(const int32_t* __restrict__ cand, const int32_t* __restrict__ cnt,
                                                            int32_t* __restrict__ amb_list, int32_t* __restrict__ amb_cnt,
                                                            int32_t* __restrict__ ncand, int npad) {
-  __shared__ int wa[16], wb[16];
+  __shared__ int wa[16];
   const int hk = blockIdx.x, b = blockIdx.y, Hkv = gridDim.x;
   const int64_t bh = int64_t(b) * Hkv + hk;
   const int nevi = cnt[bh * 2 + 1];
+  constexpr int PT = 4;  // consecutive rows per thread and block-wide scan
   int base = 0;
-  for (int i0 = 0; i0 < nevi; i0 += blockDim.x) {
-    const int i = i0 + threadIdx.x;
-    const bool amb = i < nevi && cand[bh * npad + i] < 0;
-    if (i < nevi) ncand[bh * npad + i] = 0;
-    int ex, exd, tot, totd;
-    block_scan2(amb, false, ex, exd, tot, totd, wa, wb);
-    if (amb) amb_list[bh * npad + base + ex] = i;
+  for (int i0 = 0; i0 < nevi; i0 += PT * 1024) {
+    const int it = i0 + PT * int(threadIdx.x);
+    bool amb[PT];
+    int n = 0;
+#pragma unroll
+    for (int u = 0; u < PT; ++u) {
+      amb[u] = it + u < nevi && cand[bh * npad + it + u] < 0;
+      if (it + u < nevi) ncand[bh * npad + it + u] = 0;
+      n += amb[u] ? 1 : 0;
+    }
+    int ex, tot;
+    block_scan_int(n, ex, tot, wa);
+    int at = base + ex;
+#pragma unroll
+    for (int u = 0; u < PT; ++u)
+      if (amb[u]) amb_list[bh * npad + at++] = it + u;
     base += tot;
   }
   if (threadIdx.x == 0) amb_cnt[bh] = base;
@@ -602,6 +583,10 @@ __global__ __launch_bounds__(256) void match_refine(const T* __restrict__ K, Vie
     for (int j = lane; j < nret; j += 64) {
       const T* rr = kb + int64_t(rl[j]) * kv.sn;
       double dot = 0.0, nr = 0.0;
+      constexpr int kUnroll = sizeof(T) == 2 ? 1 : 4;
+      // (bf16 rows come here as exceptions: unrolled, this loop's registers would halve the wavefronts
+      // that the listed candidates above need in flight; fp32 rows always do)
+#pragma unroll kUnroll
       for (int c = 0; c < D; c += kVec) {
         double y[kVec];
         load8<T>(rr + c, y);

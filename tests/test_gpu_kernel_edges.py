@@ -8,7 +8,7 @@ import pytest
 import torch
 
 from oracle import d2o_ref as ref
-from paper_2406_13035_amd import binding
+from paper_2406_13035_amd import binding, synth
 from tests import helpers as H
 
 pytestmark = pytest.mark.gpu
@@ -59,4 +59,21 @@ def test_fp32_prompt_attention_tile_edges(n, d, Hq, Hkv):
         assert np.abs(score[0, h] - s).max() <= 3e-5 * s.max()
         var += list(v)
     assert abs(F[0, 0] - np.mean(var)) <= 1e-4 * max(np.mean(var), 1e-3)
+    ctx.close()
+
+
+@pytest.mark.parametrize("budget", [15359, 15360])
+def test_grouping_counters_in_lds_and_in_memory(budget):
+    """Merge groups of a head with as many retained tokens as the grouping kernel has counters in
+    LDS, and one more (counters in memory): selections, targets and flags identical, merged rows
+    within the float bar (check_compress_against_oracle)."""
+    w = synth.WORKLOADS[3].scaled(n_q_heads=1, n_kv_heads=1, n_clusters=32)
+    n, recent = 16500, 4000
+    _, K, V = H.make_inputs(w, 1, 5, n)
+    score32 = np.random.default_rng(budget).random((1, 1, n), dtype=np.float32)
+    ctx = H.new_ctx(w, 1, 1, n, budget + 8)
+    ctx.d2o_scores_import(0, score32)
+    ctx.d2o_compress_layer(0, K, V, budget, recent)
+    stats, _ = H.check_compress_against_oracle(ctx, 0, K, V, score32, budget, recent, 0, w.dtype)
+    assert stats["evicted"] == n - budget and 0 < stats["passed"] < n - budget
     ctx.close()
