@@ -349,6 +349,7 @@ __global__ __launch_bounds__(256) void block_norm(const int32_t* __restrict__ ct
   if (threadIdx.x == 0) ccount[bh] = N;
   for (int q = threadIdx.x; q < nq; q += 256) {
     double M = -INFINITY;
+#pragma unroll 4
     for (int c = 0; c < nch; ++c) M = fmax(M, stat[((int64_t(c) * bhN + bh) * maxq + q) * 2]);
     double L = 0.0;
     for (int c = 0; c < nch; ++c) {
@@ -361,7 +362,7 @@ __global__ __launch_bounds__(256) void block_norm(const int32_t* __restrict__ ct
 }
 
 template <typename T, int D>
-__global__ __launch_bounds__(256) void block_apply(const int32_t* __restrict__ ctotal, const int32_t* __restrict__ meta,
+__global__ __launch_bounds__(256, 2) void block_apply(const int32_t* __restrict__ ctotal, const int32_t* __restrict__ meta,
                                                    const T* __restrict__ cK, const T* __restrict__ cV,
                                                    const int8_t* __restrict__ cKe, const int8_t* __restrict__ cVe,
                                                    double* __restrict__ spart, const double* __restrict__ aq,
@@ -369,6 +370,10 @@ __global__ __launch_bounds__(256) void block_apply(const int32_t* __restrict__ c
                                                    int G, int maxq, int64_t slots, int rows_cap, int tiles_per_slice) {
   typedef BlockRows<T, D> BR;
   constexpr int CT = BR::CT;
+  constexpr int VW = CT * int(sizeof(T)) / 4;
+  struct alignas(VW >= 4 ? 16 : 8) VRow {  // this lane's columns of a V row, as stored
+    uint32_t w[VW];
+  };
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   // behind the rows (and the fp8 scales): per wavefront and row, the sum of its queries' probabilities
   double* rs = reinterpret_cast<double*>(smem + BR::kRowsBytes + BR::kScaleBytes);
@@ -395,11 +400,24 @@ __global__ __launch_bounds__(256) void block_apply(const int32_t* __restrict__ c
 #pragma unroll 1
     for (int g = 0; g < ngroup; ++g) {
       f64x4 S[4];
-      BR::logits(smem, g, lane, bq, S);
       const int j0 = chunk * kChunk + g * 64 + kq;
+      // V rows come from memory four steps at a time, requested before the arithmetic that precedes them
+      // (read where they are multiplied, the compiler waited for each row in turn: 210 us for 256 tokens on 2048-entry caches, 32
+      // heads, instead of 184)
+      VRow vr[2][4];
+      auto load_v = [&](int t) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          vr[t & 1][r] = *reinterpret_cast<const VRow*>(cV + (slot0 + min(j0 + t * 16 + 4 * r, N - 1)) * D + c * CT);
+      };
+      load_v(0);
+      BR::logits(smem, g, lane, bq, S);
       double pr[16];  // the probabilities, value 4 t + r
 #pragma unroll
-      for (int t = 0; t < 4; ++t)
+      for (int t = 0; t < 4; ++t) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (t < 3) load_v(t + 1);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int row = g * 64 + t * 16 + 4 * r + kq, j = j0 + t * 16 + 4 * r;
@@ -410,37 +428,26 @@ __global__ __launch_bounds__(256) void block_apply(const int32_t* __restrict__ c
           // P V: this (t, r) is one contraction step over the rows 16 t + 4 r + kq
           float pa = float(p);
           if constexpr (sizeof(T) == 1) pa *= reinterpret_cast<const float*>(smem + BR::kRowsBytes + 256 * 8)[row];
-          const T* vrow = cV + (slot0 + min(j, N - 1)) * D + c * CT;
           float vb[CT];
-          if constexpr (sizeof(T) == 1) {
-            static_assert(sizeof(T) != 1 || CT == 8, "eight codes per lane");
-            const u32x2 raw = *reinterpret_cast<const u32x2*>(vrow);
 #pragma unroll
-            for (int wd = 0; wd < 2; ++wd) {
-              vb[4 * wd] = __builtin_amdgcn_cvt_f32_fp8(int(raw[wd]), 0);
-              vb[4 * wd + 1] = __builtin_amdgcn_cvt_f32_fp8(int(raw[wd]), 1);
-              vb[4 * wd + 2] = __builtin_amdgcn_cvt_f32_fp8(int(raw[wd]), 2);
-              vb[4 * wd + 3] = __builtin_amdgcn_cvt_f32_fp8(int(raw[wd]), 3);
-            }
-          } else if constexpr (sizeof(T) == 2) {
-            static_assert(sizeof(T) != 2 || CT == 8, "eight bf16 columns per lane");
-            const u32x4 raw = *reinterpret_cast<const u32x4*>(vrow);
-#pragma unroll
-            for (int wd = 0; wd < 4; ++wd) {
-              vb[2 * wd] = __uint_as_float(raw[wd] << 16);
-              vb[2 * wd + 1] = __uint_as_float(raw[wd] & 0xFFFF0000u);
-            }
-          } else {
-#pragma unroll
-            for (int x = 0; x < CT; x += 4) {
-              const u32x4 raw = *reinterpret_cast<const u32x4*>(vrow + x);
-#pragma unroll
-              for (int e = 0; e < 4; ++e) vb[x + e] = __uint_as_float(raw[e]);
+          for (int wd = 0; wd < VW; ++wd) {
+            const uint32_t raw = vr[t & 1][r].w[wd];
+            if constexpr (sizeof(T) == 1) {
+              vb[4 * wd] = __builtin_amdgcn_cvt_f32_fp8(int(raw), 0);
+              vb[4 * wd + 1] = __builtin_amdgcn_cvt_f32_fp8(int(raw), 1);
+              vb[4 * wd + 2] = __builtin_amdgcn_cvt_f32_fp8(int(raw), 2);
+              vb[4 * wd + 3] = __builtin_amdgcn_cvt_f32_fp8(int(raw), 3);
+            } else if constexpr (sizeof(T) == 2) {
+              vb[2 * wd] = __uint_as_float(raw << 16);
+              vb[2 * wd + 1] = __uint_as_float(raw & 0xFFFF0000u);
+            } else {
+              vb[wd] = __uint_as_float(raw);
             }
           }
 #pragma unroll
           for (int ct = 0; ct < CT; ++ct) O[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(pa, vb[ct], O[ct], 0, 0, 0);
         }
+      }
       // Eq. 6: the rows' sums over the tile's queries, one row per lane, then over the wavefront's tiles
       const double ps = row16_sums(pr, c);
       const int own = row16_sums_owner(c);
@@ -481,6 +488,7 @@ __global__ __launch_bounds__(D) void block_finish(const int32_t* __restrict__ ct
   const int bhN = gridDim.x, bh = blockIdx.x, q = blockIdx.y, c = threadIdx.x;
   const int N = ctotal[bh], nch = (N + kChunk - 1) / kChunk;
   float t = 0.f;
+#pragma unroll 8
   for (int ch = 0; ch < nch; ++ch) t += pout[((int64_t(ch) * bhN + bh) * maxq + q) * D + c];
   const int b = bh / Hkv, hk = bh % Hkv;
   out[b * ov.sb + (hk * G + q % G) * ov.sh + int64_t(q / G) * ov.sn + c] = Elem<OT>::from_f32(t);
@@ -553,7 +561,7 @@ hipError_t run_block_attend(d2o_ctx* c, int layer, View q, View k, View v, View 
   const int want = std::max(1, std::min(kMaxQuerySlices, 2048 / std::max(1, bh * nch)));
   const int tiles_per_slice = 4 * ((ntile + 4 * want - 1) / (4 * want));
   const int nslice = (ntile + tiles_per_slice - 1) / tiles_per_slice;
-  block_begin<T, IT, D><<<dim3(cf.n_kv_heads, cf.batch, 8), 256, 0, s>>>(ccount, ctotal, meta, (T*)c->cacheK, (T*)c->cacheV, c->cscore,
+  block_begin<T, IT, D><<<dim3(cf.n_kv_heads, cf.batch, 32), 256, 0, s>>>(ccount, ctotal, meta, (T*)c->cacheK, (T*)c->cacheV, c->cscore,
                                                                          c->cpos, (const IT*)q.ptr, q, (const IT*)k.ptr, k,
                                                                          (const IT*)v.ptr, v, c->ap_q, m, G, maxq, first_pos,
                                                                          cf.slots_per_seq);
