@@ -391,33 +391,43 @@ __device__ __forceinline__ Best scan_matches(const DecodeArgs& a, int64_t slot0,
   const double sne = sqrt(block_sum(part, red));
   const int tr = tid / TPR, tc = (tid % TPR) * kVec;
   Best m{0.0, 0, -1};
-  for (int r0 = 0; r0 < total; r0 += RPP) {
-    const int j = r0 + tr;
-    double dot = 0.0, nr = 0.0;
-    if (j < total) {
-      double x[kVec];
-      cvt16<T>(*reinterpret_cast<const u32x4*>(Kc + int64_t(j) * D + tc), x);
+  constexpr int U = 4;  // rows in flight per thread (one at a time, 10000 rows took 0.5 ms)
+#pragma unroll 1
+  for (int r0 = 0; r0 < total; r0 += U * RPP) {
+    u32x4 raw[U];
 #pragma unroll
-      for (int e = 0; e < kVec; ++e) {
-        dot = fma(x[e], ke[tc + e], dot);
-        nr = fma(x[e], x[e], nr);
+    for (int k = 0; k < U; ++k)
+      raw[k] = *reinterpret_cast<const u32x4*>(Kc + int64_t(min(r0 + k * RPP + tr, total - 1)) * D + tc);
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const int j = r0 + k * RPP + tr;
+      double dot = 0.0, nr = 0.0;
+      {
+        double x[kVec];
+        cvt16<T>(raw[k], x);
+#pragma unroll
+        for (int e = 0; e < kVec; ++e) {
+          dot = fma(x[e], ke[tc + e], dot);
+          nr = fma(x[e], x[e], nr);
+        }
       }
-    }
 #pragma unroll
-    for (int o = TPR / 2; o > 0; o >>= 1) {
-      dot += __shfl_xor(dot, o, 64);
-      nr += __shfl_xor(nr, o, 64);
-    }
-    if constexpr (sizeof(T) == 1) {  // the row's power of two: exact on sums that are exact
-      const double sc = pow2_f64(a.cKe[slot0 + min(j, total - 1)]);
-      dot *= sc;
-      nr *= sc * sc;
-    }
-    if (j < total && j != es && (tid % TPR) == 0) {
-      const double den = sne * sqrt(nr);
-      const double u = den > 0.0 ? dot / den : 0.0;
-      const int p = a.cpos[slot0 + j];
-      if (better_match(u, p, j, m)) m = Best{u, p, j};
+      for (int o = TPR / 2; o > 0; o >>= 1) {
+        dot += __shfl_xor(dot, o, 64);
+        nr += __shfl_xor(nr, o, 64);
+      }
+      if constexpr (sizeof(T) == 1) {  // the row's power of two: exact on sums that are exact
+        const double sc = pow2_f64(a.cKe[slot0 + min(j, total - 1)]);
+        dot *= sc;
+        nr *= sc * sc;
+      }
+      if (j < total && j != es && (tid % TPR) == 0) {
+        const double den = sne * sqrt(nr);
+        const double u = den > 0.0 ? dot / den : 0.0;
+        const int p = a.cpos[slot0 + j];
+        if (better_match(u, p, j, m)) m = Best{u, p, j};
+      }
+      __builtin_amdgcn_sched_barrier(0);  // one row after the other (registers)
     }
   }
   return m;
