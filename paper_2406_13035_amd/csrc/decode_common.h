@@ -369,6 +369,17 @@ __device__ __forceinline__ void finish_head(const DecodeArgs& a, int64_t lbh, in
   }
 }
 
+// Sum over each group of N consecutive lanes (8, 16 or 32); every lane of the group gets it.
+template <int N>
+__device__ __forceinline__ double lane_group_sum(double v) {
+  static_assert(N == 8 || N == 16 || N == 32, "lanes that share a row");
+  v += dpp_f64<kDppXor1>(v);
+  v += dpp_f64<kDppXor2>(v);
+  v += dpp_f64<kDppHalfMirror>(v);
+  if constexpr (N >= 16) v += dpp_f64<kDppMirror>(v);
+  if constexpr (N == 32) v += __shfl_xor(v, 16, 64);
+  return v;
+}
 // Cosine of the evicted key against every other row of the head (Eq. 9) by the whole workgroup;
 // returns the arg-max per wavefront-reduced lane (the caller reduces over the wavefronts).
 // ke: D doubles of shared memory, red: one double per wavefront.  NT = threads of the workgroup.
@@ -391,44 +402,43 @@ __device__ __forceinline__ Best scan_matches(const DecodeArgs& a, int64_t slot0,
   const double sne = sqrt(block_sum(part, red));
   const int tr = tid / TPR, tc = (tid % TPR) * kVec;
   Best m{0.0, 0, -1};
-  constexpr int U = 4;  // rows in flight per thread (one at a time, 10000 rows took 0.5 ms)
+  // Four rows per group of TPR lanes are in flight (one at a time, 10000 rows took 0.5 ms); lane k of a
+  // group then takes row k to its cosine, so that the square root and the division serve four rows.
+  constexpr int U = 4;
+  static_assert(TPR >= U, "a lane per row");
+  const int own = min(tid % TPR, U - 1);
 #pragma unroll 1
   for (int r0 = 0; r0 < total; r0 += U * RPP) {
     u32x4 raw[U];
 #pragma unroll
     for (int k = 0; k < U; ++k)
       raw[k] = *reinterpret_cast<const u32x4*>(Kc + int64_t(min(r0 + k * RPP + tr, total - 1)) * D + tc);
+    const int j = r0 + own * RPP + tr, jc = min(j, total - 1);
+    const int p = a.cpos[slot0 + jc];
+    double dot = 0.0, nr = 0.0;
 #pragma unroll
     for (int k = 0; k < U; ++k) {
-      const int j = r0 + k * RPP + tr;
-      double dot = 0.0, nr = 0.0;
-      {
-        double x[kVec];
-        cvt16<T>(raw[k], x);
+      double x[kVec], dk = 0.0, nk = 0.0;
+      cvt16<T>(raw[k], x);
 #pragma unroll
-        for (int e = 0; e < kVec; ++e) {
-          dot = fma(x[e], ke[tc + e], dot);
-          nr = fma(x[e], x[e], nr);
-        }
+      for (int e = 0; e < kVec; ++e) {
+        dk = fma(x[e], ke[tc + e], dk);
+        nk = fma(x[e], x[e], nk);
       }
-#pragma unroll
-      for (int o = TPR / 2; o > 0; o >>= 1) {
-        dot += __shfl_xor(dot, o, 64);
-        nr += __shfl_xor(nr, o, 64);
-      }
-      if constexpr (sizeof(T) == 1) {  // the row's power of two: exact on sums that are exact
-        const double sc = pow2_f64(a.cKe[slot0 + min(j, total - 1)]);
-        dot *= sc;
-        nr *= sc * sc;
-      }
-      if (j < total && j != es && (tid % TPR) == 0) {
-        const double den = sne * sqrt(nr);
-        const double u = den > 0.0 ? dot / den : 0.0;
-        const int p = a.cpos[slot0 + j];
-        if (better_match(u, p, j, m)) m = Best{u, p, j};
-      }
+      dk = lane_group_sum<TPR>(dk);
+      nk = lane_group_sum<TPR>(nk);
+      dot = own == k ? dk : dot;
+      nr = own == k ? nk : nr;
       __builtin_amdgcn_sched_barrier(0);  // one row after the other (registers)
     }
+    if constexpr (sizeof(T) == 1) {  // the row's power of two: exact on sums that are exact
+      const double sc = pow2_f64(a.cKe[slot0 + jc]);
+      dot *= sc;
+      nr *= sc * sc;
+    }
+    const double den = sne * sqrt(nr);
+    const double u = den > 0.0 ? dot / den : 0.0;
+    if (j < total && j != es && (tid % TPR) < U && better_match(u, p, j, m)) m = Best{u, p, j};
   }
   return m;
 }
