@@ -164,20 +164,21 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-// A buffer descriptor over `bytes` bytes at p: loads through it return zero behind the end.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, int bytes) {
+// A buffer descriptor over `bytes` bytes at p: a load through it whose lane offset is not below `bytes`
+// touches no memory and returns zero.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, uint32_t bytes) {
   const uint64_t u = reinterpret_cast<uint64_t>(p);  // the same for all lanes, in scalar registers
   const uint64_t lo = uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(u)))),
                  hi = uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(u >> 32))));
   return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(lo | (hi << 32)), 0,
-                                           __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
+                                           __builtin_amdgcn_readfirstlane(int(bytes)), 0x00020000);
 }
 // 16 bytes per lane from memory straight into LDS: the wavefront's 64 chunks land at `dst` (the same
-// for all lanes) one after the other, each lane choosing what it reads (`lane_off`; `off` is the
-// same for all lanes).  Arrival is waited for with wait_vm<younger loads that may still be on
-// their way>().
-__device__ __forceinline__ void load_lds16(__amdgpu_buffer_rsrc_t src, int lane_off, int off, uint16_t* dst) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (__attribute__((address_space(3))) void*)dst, 16, lane_off, off, 0, 0);
+// for all lanes) one after the other, each lane choosing what it reads.  The whole displacement is
+// the lane's: the instruction's scalar offset takes no part in the comparison with the buffer's size.
+// Arrival is waited for with wait_vm<younger loads that may still be on their way>().
+__device__ __forceinline__ void load_lds16(__amdgpu_buffer_rsrc_t src, uint32_t lane_off, uint16_t* dst) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (__attribute__((address_space(3))) void*)dst, 16, int(lane_off), 0, 0, 0);
 }
 // The same from an address of each lane's own.
 __device__ __forceinline__ void load_lds16(const void* src, uint16_t* dst) {

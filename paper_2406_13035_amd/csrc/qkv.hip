@@ -19,15 +19,13 @@
 
 #include "d2o_internal.h"
 #include "device_utils.h"
+#include "qkv_tile.h"
 
 namespace d2o {
 namespace {
 
-constexpr int kBM = 256, kBN = 128, kBK = 64;  // kBN: one head; a workgroup's tile holds kHeadsPerWg of them
-constexpr int kHeadsPerWg = 2, kThreads = 256;
-constexpr int kLd = kBK;                     // LDS pitch (elements) of the operand tiles: 128 bytes = eight 16-byte chunks,
-                                             // chunk k of row r stored at position k ^ ((r >> 1) & 7): the 16 lanes of a
-                                             // 128-bit access phase then cover all 64 banks once
+using namespace qkv;
+
 constexpr int kTokenStages = 3, kWeightStages = 2;  // k-tiles of the two operands in LDS
 constexpr int kStageElems = kBM * kLd;       // (kBM = kHeadsPerWg * kBN)
 constexpr int kSmemBytes = (kTokenStages + kWeightStages) * kStageElems * 2;  // all 160 KB of a CU
@@ -65,7 +63,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, m = lane & 31, h = lane >> 5;
   const int nheads = a.Hq + 2 * a.Hkv;
   const int wm = w & 1, wn = w >> 1;      // the wavefront's 128 tokens, and which head of the pair
-  const int row_bytes = a.hidden * 2;
+  const uint32_t row_bytes = uint32_t(a.hidden) * 2;
   const bool half = a.hidden % kBK != 0;  // the last k-tile has 32 columns
   const int nfull = a.hidden / kBK, nkt = nfull + (half ? 1 : 0);
   // Workgroups go to the eight XCDs round-robin in launch order.  Each XCD takes one eighth of
@@ -84,7 +82,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
   // ---- loads.  One instruction fills 8 rows of a k-tile (64 lanes x 16 bytes, consecutive in LDS); a
   // wavefront issues eight for the tokens and eight for the weights.  The buffers end with the
   // output tile's last row: what lies behind it (rows of a last tile, and columns of the last k-tile
-  // in the last row) reads as zero and is never used.  k-tiles form one sequence over all output
+  // in the last row) is not read, arrives as zero and is never used.  k-tiles form one sequence over all output
   // tiles of the workgroup; `next` is the place two of them ahead of the one being multiplied.
   // The tokens of a k-tile are requested seven quarters of a tile before they are needed, its
   // weights four (LDS holds five half k-tiles): two and two left the matrix core waiting for a
@@ -98,22 +96,19 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
     tile_of(min(lin, ntiles - 1), ftile, rt);
     const int xrows = lin < ntiles ? min(kBM, a.M - rt * kBM) : 0;  // past the last output tile: empty buffers
     const int wrows = lin < ntiles ? min(kHeadsPerWg, nheads - ftile * kHeadsPerWg) * kBN : 0;
-    next.x = buffer_of(a.X + int64_t(rt) * kBM * a.hidden, xrows * row_bytes);
-    next.w = buffer_of(a.W + int64_t(ftile) * kHeadsPerWg * kBN * a.hidden, wrows * row_bytes);
+    next.x = buffer_of(a.X + int64_t(rt) * kBM * a.hidden, buffer_bytes(xrows, row_bytes));
+    next.w = buffer_of(a.W + int64_t(ftile) * kHeadsPerWg * kBN * a.hidden, buffer_bytes(wrows, row_bytes));
     next.lin = lin;
     next.kt = 0;
   };
   auto advance = [&]() {
     if (++next.kt == nkt) open(next.lin + nwg);
   };
-  const int lane_off = (w * 64 + (lane >> 3)) * row_bytes;           // this lane's row in load 0 (and 8)
-  const int off_even = lane_off + (((lane & 7) ^ (lane >> 4)) << 4);  // with its chunk in even loads,
-  const int off_odd = lane_off + (((lane & 7) ^ (lane >> 4) ^ 4) << 4);  // and in odd ones (rows 8 further on)
+  const uint32_t off_even = lane_offset(w, lane, false, row_bytes), off_odd = lane_offset(w, lane, true, row_bytes);
   auto tokens = [&](int sa) { return smem + sa * kStageElems; };
   auto weights = [&](int sb) { return smem + (kTokenStages + sb) * kStageElems; };
   auto load = [&](int i, bool tok, uint16_t* stage) {  // load i (0..7) of the k-tile `next`
-    load_lds16(tok ? next.x : next.w, (i & 1) ? off_odd : off_even, next.kt * (kBK * 2) + i * 8 * row_bytes,
-               stage + (w * 8 + i) * 8 * kLd);
+    load_lds16(tok ? next.x : next.w, ((i & 1) ? off_odd : off_even) + load_step(i, next.kt, row_bytes), stage + lds_start(w, i));
   };
   // operand i (0..3: token blocks, 4..7: feature blocks) of quarter ks of the k-tile in these stages
   const int swz = (m >> 1) & 7;
