@@ -259,7 +259,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
         for (int j = 0; j < 4; ++j)
 #pragma unroll
           for (int r = 0; r < 16; ++r) put(r, j, acc[i][j][r]);
-      } else if (whole) {  // four consecutive tokens: one reduction
+      } else if (whole) {  // four consecutive tokens: one product; each angle is reduced before it is rounded
 #pragma unroll
         for (int g = 0; g < 4; ++g)
 #pragma unroll
@@ -267,7 +267,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
             const double turns = double(a.pos0 + tok0 + wm * 128 + i * 32 + g * 8 + eh * 4) * turns_per_pos[j];
             const double frac = turns - rint(turns);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) put_rotated(i, 4 * g + e, j, float(fma(double(e), turns_per_pos[j], frac)));
+            for (int e = 0; e < 4; ++e) {
+              const double t = fma(double(e), turns_per_pos[j], frac);
+              put_rotated(i, 4 * g + e, j, float(t - rint(t)));
+            }
             __builtin_amdgcn_sched_barrier(0);  // one group after the other: interleaving them costs registers
           }
       } else {

@@ -36,6 +36,22 @@ def test_projection_tile_edges(B, n, hidden, Hq, Hkv):
                           + 2.0 ** -8 * np.abs(want))
 
 
+def test_projection_rotates_a_token_alike_in_every_tile():
+    """A tile inside one sequence forms its angles four tokens at a time, a tile with a sequence's end one by
+    one; both reduce every token's angle to half a turn before its one rounding to fp32, so the same
+    tokens give the same bits.  (The two fp64 angles differ by about 2^-53 * 10^3 turns, which changes one fp32
+    rounding in 10^5, of which one in 10^4 shows in a bf16 result: 10^-9 per element, 10^7 elements.  An angle
+    rounded at up to a turn changes about a hundred of them.)"""
+    n, part, pos0, Hq, Hkv = 4096, 128, 3, 16, 8
+    g = torch.Generator().manual_seed(4)
+    X = torch.randn(1, n, 32, generator=g).to(torch.bfloat16).cuda()
+    W = (torch.randn((Hq + 2 * Hkv) * 128, 32, generator=g) / 32 ** 0.5).to(torch.bfloat16).cuda()
+    whole = binding.d2o_qkv_project(X, W, Hq, Hkv, 128, pos0)
+    for s in range(0, n, part):
+        for got, want in zip(binding.d2o_qkv_project(X[:, s:s + part].contiguous(), W, Hq, Hkv, 128, pos0 + s), whole):
+            assert torch.equal(got, want[:, :, s:s + part])
+
+
 @pytest.mark.parametrize("n", [1, 15, 16, 17, 31, 32, 33, 255, 257, 300])
 @pytest.mark.parametrize("d,Hq,Hkv", [(64, 4, 2), (128, 2, 2)])
 def test_fp32_prompt_attention_tile_edges(n, d, Hq, Hkv):
