@@ -58,6 +58,9 @@ struct QkvArgs {
 // through registers, one output tile per workgroup: 3.3-3.4 ms).  A k-tile takes 2250 cycles of
 // which 2048 are matrix instructions; an output tile's epilogue (6 us of a 100 us tile) is not
 // overlapped.
+// Wide: rows of more than kMaxBufferHidden columns, whose offsets inside a tile pass 31 bits; loaded by 64-bit
+// address with the rows clamped (more address arithmetic per load, so not for the others).
+template <bool Wide>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void qkv_rope_bf16(QkvArgs a, int nft, int ntiles, int nwg) {
   extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, m = lane & 31, h = lane >> 5;
@@ -89,15 +92,21 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
   // fifth of the time.
   struct Cursor {
     __amdgpu_buffer_rsrc_t x, w;
+    const uint16_t *xp, *wp;  // Wide: instead of the buffers
+    int xrows, wrows;
     int lin, kt;
   } next;
   auto open = [&](int lin) {
     int ftile, rt;
     tile_of(min(lin, ntiles - 1), ftile, rt);
-    const int xrows = lin < ntiles ? min(kBM, a.M - rt * kBM) : 0;  // past the last output tile: empty buffers
-    const int wrows = lin < ntiles ? min(kHeadsPerWg, nheads - ftile * kHeadsPerWg) * kBN : 0;
-    next.x = buffer_of(a.X + int64_t(rt) * kBM * a.hidden, buffer_bytes(xrows, row_bytes));
-    next.w = buffer_of(a.W + int64_t(ftile) * kHeadsPerWg * kBN * a.hidden, buffer_bytes(wrows, row_bytes));
+    next.xp = a.X + int64_t(rt) * kBM * a.hidden;
+    next.wp = a.W + int64_t(ftile) * kHeadsPerWg * kBN * a.hidden;
+    next.xrows = min(kBM, a.M - rt * kBM);
+    next.wrows = min(kHeadsPerWg, nheads - ftile * kHeadsPerWg) * kBN;
+    if constexpr (!Wide) {  // past the last output tile: empty buffers
+      next.x = buffer_of(next.xp, lin < ntiles ? buffer_bytes(next.xrows, row_bytes) : 0u);
+      next.w = buffer_of(next.wp, lin < ntiles ? buffer_bytes(next.wrows, row_bytes) : 0u);
+    }
     next.lin = lin;
     next.kt = 0;
   };
@@ -108,7 +117,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
   auto tokens = [&](int sa) { return smem + sa * kStageElems; };
   auto weights = [&](int sb) { return smem + (kTokenStages + sb) * kStageElems; };
   auto load = [&](int i, bool tok, uint16_t* stage) {  // load i (0..7) of the k-tile `next`
-    load_lds16(tok ? next.x : next.w, ((i & 1) ? off_odd : off_even) + load_step(i, next.kt, row_bytes), stage + lds_start(w, i));
+    uint16_t* dst = stage + lds_start(w, i);
+    if constexpr (Wide)
+      load_lds16((tok ? next.xp : next.wp) + wide_offset(w, lane, i, next.kt, tok ? next.xrows : next.wrows, int64_t(a.hidden) * 2) / 2, dst);
+    else
+      load_lds16(tok ? next.x : next.w, ((i & 1) ? off_odd : off_even) + load_step(i, next.kt, row_bytes), dst);
   };
   // operand i (0..3: token blocks, 4..7: feature blocks) of quarter ks of the k-tile in these stages
   const int swz = (m >> 1) & 7;
@@ -315,7 +328,7 @@ extern "C" int d2o_qkv_project(int32_t batch, int32_t n, int32_t hidden, int32_t
       !(rope_base > 1.0))
     return D2O_ERR_INVALID_ARG;
   if (dtype != D2O_BF16 || head_dim != kBN) return D2O_ERR_UNSUPPORTED;
-  if (hidden % (kBK / 2) || hidden > (1 << 22) - kBK) return D2O_ERR_UNSUPPORTED;  // (a tile's rows are addressed with 31 bits)
+  if (hidden % (kBK / 2)) return D2O_ERR_UNSUPPORTED;
   if (int64_t(batch) * n > 0x7FFFFFFF) return D2O_ERR_INVALID_ARG;
   for (const d2o_view* v : {&Q, &K, &V}) {
     if (!v->ptr || (reinterpret_cast<uintptr_t>(v->ptr) & 15) || v->stride_b % 8 || v->stride_h % 8 ||
@@ -337,10 +350,10 @@ extern "C" int d2o_qkv_project(int32_t batch, int32_t n, int32_t hidden, int32_t
   a.pos0 = pos0;
   a.log2_base = std::log2(rope_base);
   const int nft = (n_q_heads + 2 * n_kv_heads + kHeadsPerWg - 1) / kHeadsPerWg, ntiles = nft * ((a.M + kBM - 1) / kBM);
-  if (hipFuncSetAttribute(reinterpret_cast<const void*>(qkv_rope_bf16), hipFuncAttributeMaxDynamicSharedMemorySize,
-                          kSmemBytes) != hipSuccess)
+  const auto kernel = hidden > kMaxBufferHidden ? qkv_rope_bf16<true> : qkv_rope_bf16<false>;
+  if (hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kSmemBytes) != hipSuccess)
     return D2O_ERR_HIP;
   const int nwg = std::min(ntiles, kCus);
-  qkv_rope_bf16<<<nwg, kThreads, kSmemBytes, static_cast<hipStream_t>(stream)>>>(a, nft, ntiles, nwg);
+  kernel<<<nwg, kThreads, kSmemBytes, static_cast<hipStream_t>(stream)>>>(a, nft, ntiles, nwg);
   return hipGetLastError() == hipSuccess ? D2O_OK : D2O_ERR_HIP;
 }

@@ -28,6 +28,15 @@ constexpr uint32_t load_step(int i, int kt, uint32_t row_bytes) {
 constexpr int lds_start(int w, int i) { return (w * kLoads + i) * 8 * kLd; }
 // Bytes of a buffer over `rows` rows.
 constexpr uint32_t buffer_bytes(int rows, uint32_t row_bytes) { return uint32_t(rows) * row_bytes; }
+// Rows up to this wide keep a tile's offsets within 31 bits.
+constexpr int kMaxBufferHidden = (1 << 22) - kBK;
+// Wider ones: the same load's byte from the tile's first row on, held inside the tile's `rows` rows (a row or column
+// behind them is replaced by the last one and never used).
+constexpr int64_t wide_offset(int w, int lane, int i, int kt, int rows, int64_t row_bytes) {
+  const int row = w * 64 + i * 8 + (lane >> 3), last = rows - 1;
+  const int64_t col = int64_t(kt) * (kBK * 2) + ((((lane & 7) ^ (lane >> 4)) ^ (i & 1 ? 4 : 0)) << 4);
+  return (row < last ? row : last) * row_bytes + (col < row_bytes - 16 ? col : row_bytes - 16);
+}
 
 }  // namespace qkv
 }  // namespace d2o

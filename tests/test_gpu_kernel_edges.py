@@ -52,6 +52,27 @@ def test_projection_rotates_a_token_alike_in_every_tile():
             assert torch.equal(got, want[:, :, s:s + part])
 
 
+@pytest.mark.parametrize("hidden", [(1 << 22) - 64, (1 << 22) - 32, 1 << 22])
+def test_projection_of_very_wide_rows(hidden):
+    """Rows so wide that a tile's offsets pass 31 bits, and the last width below: two sequences of
+    two tokens against a product in 64 bits; the bar of test_projection_tile_edges plus the fp32 sum's own
+    error (hidden / 16 steps whose roundings add like a random walk: 2^-24 * 500 of the row's norm, below 2e-4)."""
+    B, n, Hq, Hkv = 2, 2, 1, 1
+    g = torch.Generator(device="cuda").manual_seed(hidden)
+    X = torch.randn(B, n, hidden, generator=g, device="cuda").to(torch.bfloat16)
+    W = torch.empty((Hq + 2 * Hkv) * 128, hidden, dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    W *= hidden ** -0.5
+    got = binding.d2o_qkv_project(X, W, Hq, Hkv, 128, 5)
+    Y = torch.zeros(B * n, W.shape[0], dtype=torch.float64, device="cuda")
+    for c in range(0, hidden, 1 << 18):
+        Y += X.view(B * n, hidden)[:, c:c + (1 << 18)].double() @ W[:, c:c + (1 << 18)].double().t()
+    Y = Y.view(B, n, -1).cpu().numpy()
+    for b in range(B):
+        for t, want in zip(got, ref.qkv_project(Y[b], np.eye(W.shape[0]), Hq, Hkv, 128, 5)):
+            err = np.abs(binding.tensor_to_f64(t[b]) - want)
+            assert np.all(err <= (H.FLOAT_TOL + 2e-4) * np.abs(want).max(axis=-1, keepdims=True) + 2.0 ** -8 * np.abs(want))
+
+
 @pytest.mark.parametrize("n", [1, 15, 16, 17, 31, 32, 33, 255, 257, 300])
 @pytest.mark.parametrize("d,Hq,Hkv", [(64, 4, 2), (128, 2, 2)])
 def test_fp32_prompt_attention_tile_edges(n, d, Hq, Hkv):
