@@ -70,7 +70,8 @@ __global__ __launch_bounds__(64 * kWaves) void attn_rows_f32(const float* __rest
   f32x4 acc[DT];  // acc[c][r]: column (4q + r) * DT + c of the row
 #pragma unroll
   for (int c = 0; c < DT; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float mx = -INFINITY, l = 0.f;
+  float mx = -INFINITY, l = 0.f, p[2][4];
+  bool special = false;  // the last tile holds infinite or NaN values
   const int nkt = min(row0 + 15, n - 1) / 32 + 1;  // 32-key tiles that any row of the block sees
   f32x4 k0[D / 16], k1[D / 16];
   auto load_keys = [&](int t) {
@@ -104,7 +105,7 @@ __global__ __launch_bounds__(64 * kWaves) void attn_rows_f32(const float* __rest
     tm = fmaxf(tm, __shfl_xor(tm, 32, 64));  // a row of the block that sees no key of the tile: -inf
     const float mn = fmaxf(mx, tm * scale2), ref = mn == -INFINITY ? 0.f : mn;
     const float a = exp2f(mx - ref);
-    float p[2][4], ps = 0.f;
+    float ps = 0.f;
 #pragma unroll
     for (int u = 0; u < 2; ++u)
 #pragma unroll
@@ -114,6 +115,28 @@ __global__ __launch_bounds__(64 * kWaves) void attn_rows_f32(const float* __rest
       }
     l = l * a + ps;
     mx = mn;
+    // Keys that a row does not see enter the products with probability 0, and 0 times an infinite or NaN value is
+    // NaN.  All of them are in the row block's last tile (the rows behind the end too): there such values are set
+    // to 0 in the operands and added afterwards, one by one, to the rows that see them.
+    if (t == nkt - 1) {
+      uint32_t top = 0;
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int c = 0; c < DT; ++c) top = max(top, __float_as_uint(v[u][r][c / 4][c % 4]) << 1);
+      special = __any(top >= 0xFF000000u);
+      if (special) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int c = 0; c < DT; ++c)
+              if (!isfinite(v[u][r][c / 4][c % 4])) v[u][r][c / 4][c % 4] = 0.f;
+      }
+    }
 #pragma unroll
     for (int c = 0; c < DT; ++c) {
 #pragma unroll
@@ -124,6 +147,25 @@ __global__ __launch_bounds__(64 * kWaves) void attn_rows_f32(const float* __rest
         for (int r = 0; r < 4; ++r)
           acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[u][r][c / 4][c % 4], p[u][r], acc[c], 0, 0, 0);
     }
+  }
+  if (special) {
+    const int t = nkt - 1;
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll 1
+        for (int kq = 0; kq < 4; ++kq) {
+          const int key = t * 32 + u * 16 + 4 * kq + r;
+          const float pk = __shfl(p[u][r], 16 * kq + m, 64);
+          if (key >= n) continue;  // (the same for all lanes)
+          const float* x = vb + int64_t(key) * vv.sn + 4 * q * DT;
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int c = 0; c < DT; ++c)
+              if (key <= row && !isfinite(x[e * DT + c])) acc[c][e] = fmaf(pk, x[e * DT + c], acc[c][e]);
+        }
   }
   l += __shfl_xor(l, 16, 64);
   l += __shfl_xor(l, 32, 64);

@@ -114,3 +114,39 @@ def test_grouping_counters_in_lds_and_in_memory(budget):
     stats, _ = H.check_compress_against_oracle(ctx, 0, K, V, score32, budget, recent, 0, w.dtype)
     assert stats["evicted"] == n - budget and 0 < stats["passed"] < n - budget
     ctx.close()
+
+
+@pytest.mark.parametrize("n,row,bad", [
+    (1, 0, float("inf")),
+    (40, 39, float("nan")),      # the last row, which also stands in for the rows behind the end
+    (300, 0, float("inf")),
+    (300, 17, float("-inf")),    # the second row of a 16-row block, inside a 32-key tile
+    (300, 31, float("nan")),
+    (300, 160, float("inf")),
+])
+@pytest.mark.parametrize("d,Hq,Hkv", [(64, 4, 2), (128, 2, 2)])
+def test_fp32_prompt_attention_keeps_later_non_finite_values_out(n, row, bad, d, Hq, Hkv):
+    """An infinite or NaN element in V row `row` of KV head 0 reaches that column of the rows from `row` on and
+    nothing else: every other element has the bits of the run without it, and those columns hold
+    what one term of that kind gives."""
+    rng = np.random.RandomState(n + d + row)
+    Q, K, V = (torch.from_numpy(rng.randn(1, h, n, d).astype(np.float32)).cuda() for h in (Hq, Hkv, Hkv))
+    cols = [3, d - 1]
+    ctx = binding.D2O(1, 1, Hq, Hkv, d, n, n + 2, dtype="f32")
+    out = []
+    for value in (None, bad):
+        Vv = V.clone()
+        if value is not None:
+            Vv[0, 0, row, cols] = value
+        O = torch.empty(1, Hq, n, d, device="cuda:0")
+        ctx.d2o_reset()
+        ctx.d2o_prefill_attend(0, Q, K, Vv, O)
+        out.append(O[0].cpu())
+    ctx.close()
+    clean, got = out
+    assert torch.isfinite(clean).all()
+    hit = torch.zeros(Hq, n, d, dtype=torch.bool)
+    hit[:Hq // Hkv, row:, cols] = True
+    want = torch.full_like(got, bad)     # every softmax weight of these inputs is positive
+    assert torch.equal(got[~hit], clean[~hit])
+    assert torch.equal(got[hit].nan_to_num(7.0), want[hit].nan_to_num(7.0))
