@@ -111,9 +111,9 @@ struct d2o_ctx {
   double* m_ustar = nullptr;     // exact best similarity per evicted row
   int32_t* m_tgt = nullptr;      // exact match (retained rank)
   uint8_t* m_pass = nullptr;     // threshold test
-  int32_t* g_cnt = nullptr;      // [..][npad+1] sources per retained slot
-  int32_t* g_off = nullptr;      // [..][npad+1] exclusive prefix of g_cnt
-  int32_t* g_cur = nullptr;      // [..][npad+1] fill cursors
+  int32_t* g_cnt = nullptr;      // [..][npad+1] sources per retained slot (of heads whose counters do not fit LDS)
+  int32_t* g_off = nullptr;      // [..][npad+1] exclusive prefix of the slots' sources
+  int32_t* g_cur = nullptr;      // [..][npad+1] fill cursors (of the same heads)
   int32_t* g_src = nullptr;      // evicted ranks grouped by target (unordered inside a group)
   // fp8 cache: the bf16 rows of the layer being compressed (the prompt-phase kernels work on
   // them; encode_layer then writes the cache) and of a head being imported or exported

@@ -777,7 +777,7 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
           static_assert(sizeof(T) != 1 || kVec == 8, "two words of codes");
 #pragma unroll
           for (int wd = 0; wd < 2; ++wd) {
-            const int bits = int(raw_word(vbuf[q & 1][i], wd));
+            const int bits = int(vbuf[q & 1][i][wd]);
             x[4 * wd] = __builtin_amdgcn_cvt_f32_fp8(bits, 0);
             x[4 * wd + 1] = __builtin_amdgcn_cvt_f32_fp8(bits, 1);
             x[4 * wd + 2] = __builtin_amdgcn_cvt_f32_fp8(bits, 2);

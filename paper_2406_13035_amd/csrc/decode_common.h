@@ -117,16 +117,10 @@ __device__ __forceinline__ void cvt16f<uint8_t>(const u32x4& v, float* out) {
   }
 }
 
-// Consecutive elements (2 to 16 bytes) held as raw bits.
+// 8 or 16 bytes of consecutive elements held as raw bits.
 template <int BYTES> struct RawBits;
 template <> struct RawBits<16> { typedef u32x4 type; };
 template <> struct RawBits<8> { typedef u32x2 type; };
-template <> struct RawBits<4> { typedef uint32_t type; };
-template <> struct RawBits<2> { typedef uint16_t type; };
-__device__ __forceinline__ uint32_t raw_word(const uint16_t& r, int) { return r; }
-__device__ __forceinline__ uint32_t raw_word(const u32x4& r, int i) { return r[i]; }
-__device__ __forceinline__ uint32_t raw_word(const u32x2& r, int i) { return r[i]; }
-__device__ __forceinline__ uint32_t raw_word(const uint32_t& r, int) { return r; }
 // The partial results of a step are laid out chunk-major: [layer's chunk offset + chunk]
 // [sequence][KV head]...  Workgroups are dispatched head-fastest, so the results that are written
 // at about the same time are neighbours in memory (per-head contiguous arrays scatter them; a

@@ -661,10 +661,7 @@ __global__ __launch_bounds__(1024) void threshold_group_kernel(const double* __r
   int32_t* gs = gsrc + bh * npad;
   if (nevi == 0) {
     // no sources anywhere: merge_kernel reads the offsets of every slot, so they must say so
-    for (int j = tid; j <= nret; j += blockDim.x) {
-      gc[j] = 0;
-      go[j] = 0;
-    }
+    for (int j = tid; j <= nret; j += blockDim.x) go[j] = 0;
     return;  // tau keeps its value (unset, NaN, after prompt encoding)
   }
   double part = 0.0;
