@@ -19,7 +19,11 @@ pytestmark = pytest.mark.gpu
     (5, 37, 96, 3, 1),       # five sequences inside one 256-token tile, an odd head count, a k-tile and a half
     (1, 257, 64, 1, 1),      # one token past the tile, one k-tile
     (3, 200, 160, 4, 2),     # tiles that hold the end of a sequence
-    (1, 1600, 96, 32, 32),   # more output tiles than workgroups, the k-tile sequence odd in each
+    (1, 1600, 96, 32, 32),   # more output tiles than workgroups, two k-tiles in each (the last one half)
+    (1, 1600, 32, 32, 32),   # the same with a single half k-tile: every load opens another output tile
+    (1, 1600, 64, 32, 32),   # ... a single whole one
+    (1, 1600, 192, 32, 32),  # ... three: a workgroup's second output tile starts in the other weight stage
+    (3, 1000, 160, 31, 6),   # ... two and a half; 22 head pairs (no XCD order), the last half empty, sequence ends in tiles
 ])
 def test_projection_tile_edges(B, n, hidden, Hq, Hkv):
     """|got - want| <= 2e-3 |row|_inf + 2^-8 |want|: the oracle's fp64 product and rotation against
@@ -150,3 +154,52 @@ def test_fp32_prompt_attention_keeps_later_non_finite_values_out(n, row, bad, d,
     want = torch.full_like(got, bad)     # every softmax weight of these inputs is positive
     assert torch.equal(got[~hit], clean[~hit])
     assert torch.equal(got[hit].nan_to_num(7.0), want[hit].nan_to_num(7.0))
+
+
+def _imported_state(ctx, g, dtype, storage, Hkv, d, count, n0):
+    """`count` survivors of an n0-token prompt in every head of layer 0, and the oracle's copies."""
+    caches = []
+    for h in range(Hkv):
+        K, V = (ref.round_storage(g.standard_normal((count, d)), dtype) for _ in range(2))
+        score = 1.0 + g.random(count)
+        pos = np.sort(g.choice(n0, count, replace=False)).astype(np.int32)
+        ctx.d2o_cache_import(0, 0, h, K, V, score, pos, 0.1, n0)
+        K, V = ref.round_storage(K, storage), ref.round_storage(V, storage)
+        caches.append(ref.HeadCache(K, V, score.copy(), pos.astype(np.int64), 0.1, storage))
+    return caches
+
+
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+@pytest.mark.parametrize("dtype,d,fp8", [("bf16", 128, False), ("bf16", 128, True), ("f32", 64, False), ("f32", 128, False)])
+def test_generation_step_at_the_edges_of_its_tiles(dtype, d, fp8, G):
+    """Every form of the K pass (operand vectors in groups of four and left over, an operand copy per wavefront
+    or per workgroup, every element type), at entry counts around its wavefront (64) and chunk (256) and around
+    the rows that the second pass over the keys takes per round (32 to 128).  An imported cache has
+    no candidates, so the first step makes that second pass; the next two do not."""
+    storage, Hkv, beta, steps = ("fp8" if fp8 else dtype), 2, 0.7, 3
+    for total in (2, 31, 32, 33, 63, 64, 65, 127, 128, 129, 255, 256, 257, 321):
+        budget, n0 = total - 1, 400
+        g = np.random.default_rng(1000 * G + total)
+        ctx = binding.D2O(1, 1, G * Hkv, Hkv, d, n0, budget + 8, dtype=dtype, beta=beta, out_f32=True, cache_fp8=fp8)
+        ctx.d2o_layer_reserve(0, n0, budget, 0)
+        caches = _imported_state(ctx, g, dtype, storage, Hkv, d, budget, n0)
+        x = [ref.round_storage(g.standard_normal((steps, 1, 1, h, d)), dtype) for h in (G * Hkv, Hkv, Hkv)]
+        q, k, v = (torch.from_numpy(a).to(torch.float32 if dtype == "f32" else torch.bfloat16).cuda() for a in x)
+        out = torch.empty(1, 1, G * Hkv, d, device="cuda:0")
+        for t in range(steps):
+            ctx.d2o_decode_step(0, 1, q[t], k[t], v[t], out)
+            ev, tg, us = ctx.d2o_last_events(0)
+            got = out[0, 0].double().cpu().numpy()
+            for h in range(Hkv):
+                want, e = ref.decode_step_head(caches[h], x[0][t, 0, 0, h * G:(h + 1) * G], x[1][t, 0, 0, h], x[2][t, 0, 0, h],
+                                               n0 + t, budget, 0, 0, beta)
+                assert (ev[0, h], tg[0, h]) == (e.evicted_pos, e.target_pos), f"total {total} step {t} head {h}"
+                assert e.evicted_pos >= 0 and abs(us[0, h] - e.u_star) < 1e-13
+                assert H.rownorm_err(got[h * G:(h + 1) * G], want) <= H.FLOAT_TOL, f"total {total} step {t} head {h}"
+        assert ctx.d2o_candidate_misses() >= Hkv
+        for h, cache in enumerate(caches):
+            gK, gV, gs, gp, gtau = ctx.d2o_cache_export(0, 0, h, budget + 1)
+            assert np.array_equal(gp, cache.pos) and np.array_equal(gK, cache.K) and np.array_equal(gV, cache.V)
+            np.testing.assert_allclose(gs, cache.score, rtol=1e-12)
+            assert abs(gtau - cache.tau) < 1e-13
+        ctx.close()
