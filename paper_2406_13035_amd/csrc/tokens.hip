@@ -624,8 +624,9 @@ __global__ __launch_bounds__(256) void match_refine(const T* __restrict__ K, Vie
     }
   }
   if (tc == 0 && valid) {
-    ustar[bh * npad + erank] = best;
-    tgt[bh * npad + erank] = bj;
+    const bool none = bj == 0x7FFFFFFF;  // a non-finite key: no cosine compares above the start, and no threshold is reached
+    ustar[bh * npad + erank] = none ? __longlong_as_double(0x7FF8000000000000ll) : best;
+    tgt[bh * npad + erank] = none ? 0 : bj;
   }
 }
 

@@ -203,3 +203,29 @@ def test_generation_step_at_the_edges_of_its_tiles(dtype, d, fp8, G):
             np.testing.assert_allclose(gs, cache.score, rtol=1e-12)
             assert abs(gtau - cache.tau) < 1e-13
         ctx.close()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("tau_force", [float("nan"), float("-inf")])
+def test_an_evicted_key_that_is_not_finite_merges_into_nothing(dtype, tau_force):
+    """Its cosines are NaN (inf / inf), which no threshold admits, also where everything is to be merged: the
+    oracle's targets and flags, and the other evicted tokens' merges unchanged."""
+    n, budget, recent, d, bad = 300, 100, 20, 128, 57
+    g = np.random.default_rng(9)
+    K, V = (ref.round_storage(g.standard_normal((n, d)), dtype) for _ in range(2))
+    score = g.random(n).astype(np.float32)
+    score[bad] = 0.0
+    K[bad, 5] = np.inf
+    ctx = binding.D2O(1, 1, 1, 1, d, n, budget + 8, dtype=dtype, tau_force=tau_force)
+    Kg, Vg = (torch.from_numpy(x)[None, None].to(torch.float32 if dtype == "f32" else torch.bfloat16).cuda() for x in (K, V))
+    ctx.d2o_scores_import(0, score[None, None])
+    ctx.d2o_compress_layer(0, Kg, Vg, budget, recent)
+    with np.errstate(invalid="ignore"):
+        cache, want = ref.compress_head(K, V, score.astype(np.float64), budget, recent, 0, dtype, tau_force)
+    ret, evi, tgt, us, ps = ctx.d2o_prefill_events(0, 0, 0, n)
+    row = int(np.flatnonzero(evi == bad)[0])
+    assert np.isnan(us[row]) and not ps[row] and ps.any() == (tau_force == float("-inf"))
+    assert np.array_equal(ret, want.retained) and np.array_equal(tgt, want.target) and np.array_equal(ps, want.passed)
+    gK, gV = ctx.d2o_cache_export(0, 0, 0, budget + 1)[:2]
+    assert H.rownorm_err(gK, cache.K) <= H.FLOAT_TOL and H.rownorm_err(gV, cache.V) <= H.FLOAT_TOL
+    ctx.close()
