@@ -266,13 +266,13 @@ __device__ __forceinline__ void finish_head(const DecodeArgs& a, int64_t lbh, in
   T* Kc = static_cast<T*>(a.cK) + slot0 * D;
   T* Vc = static_cast<T*>(a.cV) + slot0 * D;
   const int tid = threadIdx.x, last = total - 1;
-  bool do_merge;
+  bool do_merge;  // (never without a match: no cosine of a non-finite key compares above another)
   if (isnan(a.tau_force)) {
     const double tnew = isnan(told) ? best : __dadd_rn(__dmul_rn(a.beta, best), __dmul_rn(1.0 - a.beta, told));
-    do_merge = best >= tnew;
+    do_merge = bs >= 0 && best >= tnew;
     if (tid == 0) a.ctau[lbh] = tnew;
   } else {
-    do_merge = best >= a.tau_force;
+    do_merge = bs >= 0 && best >= a.tau_force;
   }
   if (tid == 0) {
     a.ev_evicted[lbh] = ep;
@@ -494,7 +494,13 @@ __device__ __forceinline__ void close_head(const DecodeArgs& a, int64_t lbh, int
     const Best h = ex[i * NE];
     if (evicts_before(h.u, h.pos, h.slot, ev)) ev = h;
   }
-  const int es = evict ? ev.slot : -1;  // a candidate always exists: total > budget >= T + M
+  // (a candidate always exists: total > budget >= T + M; but where every score is NaN none compares below
+  // another and the slot is -1: the new token leaves then)
+  if (ev.slot < 0) {
+    ev.slot = last;
+    ev.pos = p_last;
+  }
+  const int es = evict ? ev.slot : -1;
   Best nx[kCand + 1];
 #pragma unroll
   for (int i = 0; i <= kCand; ++i) nx[i] = Best{0.0, 0, -1};

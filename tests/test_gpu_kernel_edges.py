@@ -229,3 +229,45 @@ def test_an_evicted_key_that_is_not_finite_merges_into_nothing(dtype, tau_force)
     gK, gV = ctx.d2o_cache_export(0, 0, 0, budget + 1)[:2]
     assert H.rownorm_err(gK, cache.K) <= H.FLOAT_TOL and H.rownorm_err(gV, cache.V) <= H.FLOAT_TOL
     ctx.close()
+
+
+@pytest.mark.parametrize("split_rows", [0, 256])
+@pytest.mark.parametrize("cache_fp8", [False, True])
+def test_a_head_whose_scores_are_nan_stays_inside_its_cache(cache_fp8, split_rows):
+    """A NaN in one query makes every score of its KV head NaN; no entry then compares as the lowest, and every
+    step drops the token it brought.  Everything beside that head has the bytes of the run without the NaN: the
+    layer before it (whose last slot precedes the head's first), the other heads, the densities."""
+    L, Hkv, d, budget, n0, steps = 2, 2, 128, 600, 700, 4
+    res = []
+    for poison in (False, True):
+        g = np.random.default_rng(3)
+        ctx = binding.D2O(1, L, Hkv, Hkv, d, n0, L * (budget + 8), dtype="bf16", tau_force=float("-inf"), out_f32=True,
+                          cache_fp8=cache_fp8, split_rows=split_rows)
+        for l in range(L):
+            ctx.d2o_layer_reserve(l, n0, budget, 0)
+            for h in range(Hkv):
+                K, V = (ref.round_storage(g.standard_normal((budget, d)), "bf16") for _ in range(2))
+                ctx.d2o_cache_import(l, 0, h, K, V, 1.0 + g.random(budget), np.arange(budget, dtype=np.int32), 0.1, n0)
+        q, k, v = (torch.from_numpy(g.standard_normal((steps, L, 1, Hkv, d))).to(torch.bfloat16).cuda() for _ in range(3))
+        if poison:
+            q[0, 1, 0, 0, 7] = float("nan")
+        out = torch.empty(L, 1, Hkv, d, device="cuda:0")
+        outs, events = [], []
+        for t in range(steps):
+            ctx.d2o_decode_step(0, L, q[t], k[t], v[t], out)
+            outs.append(out.cpu().clone())
+            events.append([ctx.d2o_last_events(l) for l in range(L)])
+        caches = {(l, h): ctx.d2o_cache_export(l, 0, h, budget + 1) for l in range(L) for h in range(Hkv)}
+        res.append((outs, events, caches, ctx.d2o_get_density()))
+        ctx.close()
+    (o0, e0, c0, f0), (o1, e1, c1, f1) = res
+    assert np.array_equal(f0, f1, equal_nan=True)
+    for t in range(steps):
+        assert e1[t][1][0][0, 0] == n0 + t                      # the poisoned head evicts the new token
+        for l, h in ((0, 0), (0, 1), (1, 1)):
+            assert torch.equal(o0[t][l, 0, h], o1[t][l, 0, h])
+            assert all(np.array_equal(x[0, h], y[0, h]) for x, y in zip(e0[t][l], e1[t][l]))
+    for lh in ((0, 0), (0, 1), (1, 1)):
+        assert all(np.array_equal(x, y, equal_nan=True) for x, y in zip(c0[lh], c1[lh]))
+    K, V, s, p, _ = c1[(1, 0)]
+    assert np.isnan(s).all() and np.array_equal(np.sort(p), np.arange(budget)) and np.isfinite(K).all() and np.isfinite(V).all()
