@@ -129,9 +129,8 @@ void layout(d2o_ctx* x, char* persistent, char* scratch, size_t* pbytes, size_t*
   s.take(x->ap_out, ap * x->ap_nch * bh * x->ap_maxq * d);
   s.take(x->ap_spart, ap * kMaxQuerySlices * bh * x->ap_nch * kChunk);
   s.take(x->d_logit, nch * B * Hq * kChunk);
-  const size_t nsub = nch * 4;  // partial results are kept per 64 slots, a quarter of a chunk
-  s.take(x->d_rec, bh * nsub * 32);
-  s.take(x->d_pacc, bh * nsub * G * d);
+  s.take(x->d_rec, bh * nch * 4 * 32);  // per 64 slots, a quarter of a chunk
+  s.take(x->d_pacc, bh * nch * G * d);
   s.take(x->d_part, bh * nch * kPartRecDoubles + L * bh * 16);  // part records, then 16 doubles per head
   s.take(x->d_vecs, L * bh * (G + nc) * d);
   s.take(x->d_cnorm, L * bh * nc);

@@ -135,9 +135,9 @@ struct d2o_ctx {
   double* ap_spart = nullptr;    // [kMaxQuerySlices][B][Hkv][ap_nch * 256] per row: sum of the slice's probabilities
   // decode
   double* d_logit = nullptr;     // [nchunk][B][Hkv][G][256] exp(logit - sub-chunk max), chunk-major
-  double* d_rec = nullptr;       // [nchunk][B][Hkv][4][32] per 64 slots: softmax maxima and sums, candidates' best cosine and slot
+  double* d_rec = nullptr;       // [nchunk][B][Hkv][4][at most 32] per 64 slots: softmax maxima and sums, candidates' best cosine and slot
   double* d_part = nullptr;      // [nchunk][B][Hkv][kPartRecDoubles] records of the split closing kernels (one per part, at its first chunk)
-  float* d_pacc = nullptr;       // [nchunk][B][Hkv][4][G][d] partial outputs
+  float* d_pacc = nullptr;       // [nchunk][B][Hkv][G][d] partial outputs
   double* d_vecs = nullptr;      // [L][B][Hkv][G + candidates][d] queries and candidate keys, fp64
   double* d_cnorm = nullptr;     // [L][B][Hkv][candidates] norms of the candidate keys
 };
