@@ -221,7 +221,10 @@ __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ 
   constexpr int U = G >= 8 ? 1 : G >= 4 ? 2 : G >= 2 ? 4 : 6;  // slots per thread and batch of the score pass
   constexpr int C4 = D / 4;                           // threads across an output row (four columns each)
   constexpr int RG = 256 / C4;                        // groups of threads that share the sub-chunks
-  constexpr int PB = G >= 4 ? 1 : G == 2 ? 2 : 4;      // partial rows of each query head in flight per thread
+  // partial rows of each query head in flight per thread: four in all, or one each (eight query heads with
+  // four rows each, one layer: 48.0 instead of 40.3 us at 1500 entries per head, 60.5 instead of 58.5 at 6000; 32 layers,
+  // four sequences: 1093 instead of 1074 for two steps)
+  constexpr int PB = G >= 4 ? 1 : G == 2 ? 2 : 4;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int last = total - 1;
   const int32_t* mt = a.meta + lbh * 4;

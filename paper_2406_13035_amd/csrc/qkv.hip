@@ -54,7 +54,7 @@ struct QkvArgs {
 // per tile.  The workgroups are persistent (one per CU): the first k-tiles of the next output
 // tile arrive during the epilogue, and the workgroups of an XCD stay close enough to each other
 // that a line one of them fetched is still in the XCD's L2 when the others ask for it.
-// 32768 tokens x 4096 -> 96 heads: 2.5-2.6 ms = 1.27-1.3 PFLOP/s (8 wavefronts, k-tiles of 32
+// 32768 tokens x 4096 -> 96 heads: 2.49-2.67 ms = 1.24-1.32 PFLOP/s (8 wavefronts, k-tiles of 32
 // through registers, one output tile per workgroup: 3.3-3.4 ms).  A k-tile takes 2250 cycles of
 // which 2048 are matrix instructions; an output tile's epilogue (6 us of a 100 us tile) is not
 // overlapped.
