@@ -523,8 +523,8 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
   // the XCDs in index order, so with a head count that is a multiple of the XCD count every chunk
   // of a head, and the workgroup that closes it, run on one XCD.
   // (a call of one layer needs no search)
-  const int entry = a.nl == 1 ? 0 : find_entry(a, blockIdx.y), grp = blockIdx.y - (a.nl == 1 ? 0 : a.lay_off[entry]);
-  const int li = a.nl == 1 ? 0 : a.lay_id[entry];
+  const LayerEntry entry = a.nl == 1 ? LayerEntry{0, 0} : find_entry(a, blockIdx.y);
+  const int li = entry.layer, grp = blockIdx.y - entry.first;
   const int l = a.layer0 + li, b = blockIdx.x / a.Hkv, hk = blockIdx.x % a.Hkv;
   const int64_t lbh = (int64_t(l) * a.B + b) * a.Hkv + hk;
   // Everything the workgroup needs to know about its head comes through the scalar cache in one

@@ -181,15 +181,20 @@ __device__ __forceinline__ float4 ld_agent4(const float* p) {  // 16 bytes as tw
                      __uint_as_float(uint32_t(hi)), __uint_as_float(uint32_t(hi >> 32)));
 }
 
-// Which entry of the call's layer list a flat chunk index belongs to (block-uniform).  The
-// list is sorted by size, so the workgroups dispatched last belong to the smallest caches.
-// Unused entries of lay_off hold INT_MAX, so the search is a fixed chain of scalar compares on
-// kernel arguments: no memory round trip precedes the loads that depend on the layer.
-__device__ __forceinline__ int find_entry(const DecodeArgs& a, int x) {
-  int entry = 0;
-#pragma unroll
-  for (int i = 1; i < kMaxLayersPerCall; ++i) entry += x >= a.lay_off[i] ? 1 : 0;
-  return entry;
+// Which entry of the call's layer list a flat chunk index belongs to (block-uniform), that entry's
+// layer and first index.  The list is sorted by size, so the workgroups dispatched last belong to the
+// smallest caches.  Unused entries of lay_off hold INT_MAX.  Every lane looks at one entry: two vector
+// loads of the kernel arguments and a count of the lanes whose entry starts at or before x.  (As
+// 63 scalar compares this was 186 vector and 300 scalar instructions per wavefront, a twelfth of
+// the vector instructions of a chunk of the fp8 cache, whose launch is bound by their issue.)
+struct LayerEntry {
+  int first, layer;
+};
+__device__ __forceinline__ LayerEntry find_entry(const DecodeArgs& a, int x) {
+  static_assert(kMaxLayersPerCall == 64, "an entry per lane");
+  const int lane = threadIdx.x & 63, off = a.lay_off[lane], id = a.lay_id[lane];
+  const int e = __popcll(__ballot(x >= off)) - 1;  // (lay_off[0] is 0)
+  return LayerEntry{__builtin_amdgcn_readlane(off, e), __builtin_amdgcn_readlane(id, e)};
 }
 
 // (u larger, then position smaller) wins; slot < 0 means "no entry".

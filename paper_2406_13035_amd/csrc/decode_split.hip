@@ -61,8 +61,8 @@ __global__ __launch_bounds__(256) void decode_close_part(DecodeArgs a) {
   __shared__ double sred[8];
   __shared__ int ired[8];
   // grid: x = head, y = flat part index over the layers that can hold large heads (lay_off counts parts here)
-  const int entry = find_entry(a, blockIdx.y), grp = (blockIdx.y - a.lay_off[entry]) * a.part_chunks;
-  const int li = a.lay_id[entry];
+  const LayerEntry entry = find_entry(a, blockIdx.y);
+  const int li = entry.layer, grp = (blockIdx.y - entry.first) * a.part_chunks;
   const int l = a.layer0 + li, b = blockIdx.x / a.Hkv, hk = blockIdx.x % a.Hkv;
   const int64_t lbh = (int64_t(l) * a.B + b) * a.Hkv + hk;
   const int total = a.ctotal[lbh];
