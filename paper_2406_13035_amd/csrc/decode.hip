@@ -507,6 +507,7 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
   constexpr int TPR = RB / VB;                  // V pass: lanes per row
   constexpr int RPI = 64 / TPR;                 // V pass: rows per load instruction
   constexpr int NVL = kSub / RPI;               // V pass: loads per lane
+  constexpr bool kMmaV = sizeof(T) <= 2;        // V pass on the matrix core
   constexpr int NV = G + kCand;
   constexpr int CG = (NV + 1) / 4, NR = NV > 4 * CG ? NV - 4 * CG : 0;  // K pass: groups of four operand vectors, and vectors left over
   constexpr int kRec = rec_doubles(G);
@@ -515,7 +516,6 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
   // until they combine their results), else one for the workgroup, behind a barrier
   constexpr bool kOwnOpnd = G <= 2;
   __shared__ __attribute__((aligned(16))) double opnd[kOwnOpnd ? 4 : 1][NV * D];
-  __shared__ float ps[4][G][kSub];
   __shared__ double wmax[4][G];  // per wavefront: softmax maximum of its sub-chunk (-inf: no rows)
   __shared__ int sh_last;
 
@@ -571,18 +571,20 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
   // of a line then comes from memory again).  The next pair is requested as soon as this one
   // sits in LDS.
   static_assert(NP % 2 == 0, "pieces are loaded in pairs");
-  u32x4 kreg[8];
-  auto load_pair = [&](int sub, int rows, int p0) {
-    const unsigned char* Kc = Kh + int64_t(sub) * kSub * RB;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int r = min(i * 8 + (ln >> 3), rows - 1);  // rows past the end repeat the last one
-      kreg[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(Kc + int64_t(r) * RB + p0 * kPiece + (ln & 7) * 16));
-    }
-  };
-  const int sub = grp * (kChunk / kSub) + w;
+  // Both streams go through buffer descriptors that end with the wavefront's last row: rows past it
+  // read as zero, and a load costs at most one address instruction (64-bit addresses of clamped rows
+  // cost six, 190 of a bf16 chunk's 2300 vector instructions per wavefront).
+  const int sub = __builtin_amdgcn_readfirstlane(grp * (kChunk / kSub) + w);
   const int rows = min(kSub, total - sub * kSub);  // <= 0: nothing for this wavefront
-  if (rows > 0) load_pair(sub, rows, 0);
+  const __amdgpu_buffer_rsrc_t Kb = buffer_of(Kh + int64_t(sub) * kSub * RB, uint32_t(max(rows, 0) * RB));
+  const __amdgpu_buffer_rsrc_t Vb = buffer_of(Vh + int64_t(sub) * kSub * RB, uint32_t(max(rows, 0) * RB));
+  u32x4 kreg[8];
+  const uint32_t koff = (ln >> 3) * RB + (ln & 7) * 16;
+  auto load_pair = [&](int p0) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) kreg[i] = stream16(Kb, koff + p0 * kPiece + i * 8 * RB);
+  };
+  if (rows > 0) load_pair(0);
 #pragma unroll
   for (int i = 0; i < kOpndLoads; ++i)
     if (ot + i * kOpndThreads < kOpnd16) reinterpret_cast<u32x4*>(mine_opnd)[ot + i * kOpndThreads] = opr[i];
@@ -591,7 +593,6 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
     if (ln < G) wmax[w][ln] = -INFINITY;
   } else {
     const int tr = ln / TPR, tc = ln % TPR;
-    const unsigned char* Vc = Vh + int64_t(sub) * kSub * RB;
     // ---- K pass in the layout of v_mfma_f64_4x4x4_4b: D[i][j] += A[i][k] B[k][j] in four blocks b,
     // where lane i + 4 b + 16 k holds A, lane j + 4 b + 16 k holds B and lane j + 4 b + 16 i holds D.
     // i is one of four cache rows, j one of four operand vectors (queries, candidate keys), and k one
@@ -620,18 +621,14 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
     // the staging lanes' rows: i * 8 + t
     const int t = ln >> 3;
     unsigned char* srow = mine + (t & 3) * kSetBytes + (t >> 2) * 4 * kPitch + (ln & 3) * 16;
-    // V rows travel in quarters of the sub-chunk through two register sets: two quarters are on
-    // their way while the lanes finish the K pass, the others follow as the sets are consumed
-    // (a whole sub-chunk in registers would cost the kernel a quarter of its occupancy).
+    // V rows (load i: rows i * RPI + tr): a bf16 or fp8 sub-chunk is requested whole, as far as the
+    // registers allow during the last piece of the K pass (fp8 all of it, bf16 half) and the rest right after;
+    // fp32 rows travel in quarters through two register sets.
+    constexpr int VE = kMmaV ? (sizeof(T) == 1 ? NVL : NVL / 2) : NVL / 2;  // loads requested during the K pass
     constexpr int VQ = NVL / 4;
-    VRaw vbuf[2][VQ];
-    auto load_vq = [&](int q, int set) {
-#pragma unroll
-      for (int i = 0; i < VQ; ++i) {
-        const int r = min((q * VQ + i) * RPI + tr, rows - 1);  // repeated rows meet a zero probability
-        vbuf[set][i] = __builtin_nontemporal_load(reinterpret_cast<const VRaw*>(Vc + int64_t(r) * RB + tc * VB));
-      }
-    };
+    VRaw vbuf[kMmaV ? NVL : NVL / 2];
+    const uint32_t voff = tr * RB + tc * VB;
+    auto load_v = [&](int i, int slot) { vbuf[slot] = stream_raw<VB>(Vb, voff + i * RPI * RB); };
     // this lane's score-side loads ride along
     const bool valid = ln < rows;
     const int j = sub * kSub + ln;
@@ -693,13 +690,19 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
 #pragma unroll 1
     for (int p = 0; p < NP - 1; ++p) {
       stage_piece(p);
-      if (p & 1) load_pair(sub, rows, p + 1);
+      if (p & 1) load_pair(p + 1);
       multiply_piece(p);
     }
     stage_piece(NP - 1);
-    load_vq(0, 0);  // the first half of this sub-chunk's V rows
-    load_vq(1, 1);
+#pragma unroll
+    for (int i = 0; i < VE; ++i) load_v(i, i);
     multiply_piece(NP - 1);
+    if constexpr (kMmaV) {
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = VE; i < NVL; ++i) load_v(i, i);
+      __builtin_amdgcn_sched_barrier(0);
+    }
     // every lane takes its own row's products
     auto own = [&](double v0, double v1, double v2, double v3) {
       const double lo = (ln & 1) ? v1 : v0, hi = (ln & 1) ? v3 : v2;
@@ -736,13 +739,34 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
     // ---- softmax statistics of the sub-chunk; the lane owns cache row sub*kSub + lane
     const int64_t pidx = sub_index(a, bh, mt3, sub) * G;
     double recv = 0.0;  // this lane's element of the sub-chunk record
+    // The probabilities go to the staging area (the K pass is done with it) for the V pass: as fp32, or, for
+    // its matrix products, each as three bf16 terms that add up to it exactly (an fp32 value has three times
+    // eight significant bits), in the order of their A operand: term t of query head g is row 3 g + t of
+    // kTermPitch bytes, cache row r its element 16 (r % 4) + r / 4.
+    constexpr int kTermPitch = 128 + 16;
+    static_assert(!kMmaV || (RPI == 4 && 3 * G * kTermPitch <= kWaveStage), "the terms fit the staging area");
+    float* psf = reinterpret_cast<float*>(mine);  // [G][kSub]
+    unsigned char* const term = mine + ((ln & 3) * 16 + (ln >> 2)) * 2;
+    // fp8 cache: the V pass works on the codes, so a row's power of two rides on its probability, taken
+    // relative to the largest of the sub-chunk (which multiplies the sums: the terms keep their range)
+    const int rev_max = sizeof(T) == 1 ? -fast_wave_min(valid ? -rev : 128) : 0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (int g = 0; g < G; ++g) {
       const double sg = dot[g] / root_d;
       const double mx = fast_wave_max(valid ? sg : -INFINITY);
       const double e = valid ? exp(sg - mx) : 0.0;
-      // (fp8 cache: the V pass works on the codes, so the row's power of two rides on its probability)
-      ps[w][g][ln] = sizeof(T) == 1 ? float(e) * pow2_f32(rev) : float(e);
+      if constexpr (kMmaV) {
+        const float p1 = sizeof(T) == 1 ? ldexpf(float(e), rev - rev_max) : float(e);
+        const float p2 = p1 - __uint_as_float(__float_as_uint(p1) & 0xFFFF0000u);
+        const float p3 = p2 - __uint_as_float(__float_as_uint(p2) & 0xFFFF0000u);
+        *reinterpret_cast<uint16_t*>(term + (3 * g) * kTermPitch) = uint16_t(__float_as_uint(p1) >> 16);
+        *reinterpret_cast<uint16_t*>(term + (3 * g + 1) * kTermPitch) = uint16_t(__float_as_uint(p2) >> 16);
+        *reinterpret_cast<uint16_t*>(term + (3 * g + 2) * kTermPitch) = uint16_t(__float_as_uint(p3) >> 16);
+      } else {
+        psf[g * kSub + ln] = float(e);
+      }
       if (valid) st_agent(&a.elog[elog_index(a, bh, mt3, G, g, j)], e);
       const double sm = fast_wave_sum(e);
       if (ln == g) {
@@ -762,59 +786,115 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
       if (ln == 2 * G + kCand + c) recv = double(m.slot);
     }
     if (ln < kRec) st_agent(&a.rec[(pidx / G) * kRec + ln], recv);  // the record in one store
-    // ---- partial P V, fp32: TPR lanes per row, RPI rows per load, then a sum over the row groups
+    // ---- partial P V.  The wavefront's partial rows (one per query head) go to its staging area for the
+    // combination over the workgroup.
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    float pv[G][kVec];
-#pragma unroll
-    for (int g = 0; g < G; ++g)
-#pragma unroll
-      for (int e = 0; e < kVec; ++e) pv[g][e] = 0.f;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-#pragma unroll
-      for (int i = 0; i < VQ; ++i) {
-        const int r = (q * VQ + i) * RPI + tr;
-        float x[kVec];
-        if constexpr (sizeof(T) == 1) {  // eight codes in two words (the byte selector is an immediate)
-          static_assert(sizeof(T) != 1 || kVec == 8, "two words of codes");
-#pragma unroll
-          for (int wd = 0; wd < 2; ++wd) {
-            const int bits = int(vbuf[q & 1][i][wd]);
-            x[4 * wd] = __builtin_amdgcn_cvt_f32_fp8(bits, 0);
-            x[4 * wd + 1] = __builtin_amdgcn_cvt_f32_fp8(bits, 1);
-            x[4 * wd + 2] = __builtin_amdgcn_cvt_f32_fp8(bits, 2);
-            x[4 * wd + 3] = __builtin_amdgcn_cvt_f32_fp8(bits, 3);
-          }
-        } else {
-          cvt16f<T>(vbuf[q & 1][i], x);
-        }
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-          const float p = ps[w][g][r];  // 0 for rows beyond the end
-#pragma unroll
-          for (int e = 0; e < kVec; ++e) pv[g][e] = fmaf(p, x[e], pv[g][e]);
-        }
-      }
-      if (q + 2 < 4) load_vq(q + 2, q & 1);
-    }
-    // sum over the row groups; the wavefront's partial rows (one per query head) go to its
-    // staging area, which is free again, for the combination over the workgroup
     float* xch = reinterpret_cast<float*>(mine);
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
+    if constexpr (kMmaV) {
+      // On the matrix core, in fp32: v_mfma_f32_16x16x32_bf16 (lane l: A[l % 16][8 (l / 16) ..], B[8 (l / 16) ..][l % 16],
+      // D[4 (l / 16) + r][l % 16]) multiplies the probabilities' terms, query head g's as its rows
+      // 4 g .. 4 g + 2, with 32 V rows.  A lane holds eight columns of every fourth row, so instruction
+      // j takes column j of every lane, and two rows' elements are one permutation away from a word
+      // of its B operand.  The products are exact, the sums over the rows need no exchange between lanes.
+      // (One multiply-add per element, query head and lane, and the sums over the row groups through
+      // LDS: 780 vector instructions per wavefront with four query heads, 328 with an fp8 cache; now 100 and 120.)
+      constexpr int GB = (G + 3) / 4;  // blocks of four query heads
+      bf16x8 pa[GB][2];
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
+      for (int gb = 0; gb < GB; ++gb)
 #pragma unroll
-      for (int e = 0; e < kVec; ++e) {
-        float t = pv[g][e];
+        for (int hf = 0; hf < 2; ++hf) {
+          const int g = min(gb * 4 + (tc >> 2), G - 1), t = min(tc & 3, 2);  // (rows without a term repeat another; their sums are not used)
+          pa[gb][hf] = *reinterpret_cast<const bf16x8*>(mine + (3 * g + t) * kTermPitch + tr * 32 + hf * 16);
+        }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      f32x4 o[GB][8];
 #pragma unroll
-        for (int o = TPR; o < 64; o <<= 1) t += __shfl_xor(t, o, 64);
-        pv[g][e] = t;
+      for (int j2 = 0; j2 < 4; ++j2) {  // columns 2 j2 and 2 j2 + 1 of the lane's eight
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+          u32x4 b0, b1;
+#pragma unroll
+          for (int x = 0; x < 4; ++x) {  // rows 2 x and 2 x + 1 of the lane's eight
+            const VRaw &r0 = vbuf[hf * 8 + 2 * x], &r1 = vbuf[hf * 8 + 2 * x + 1];
+            uint32_t lo, hi;  // the two rows' columns, as bf16 pairs
+            if constexpr (sizeof(T) == 1) {
+              // (codes have four significant bits: exact in bf16)
+              const uint32_t pair = __builtin_amdgcn_perm(r1[j2 / 2], r0[j2 / 2], j2 & 1 ? 0x07030602u : 0x05010400u);
+              lo = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(pair, 1.0f, false));
+              hi = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(pair, 1.0f, true));
+            } else {
+              lo = __builtin_amdgcn_perm(r1[j2], r0[j2], 0x05040100u);
+              hi = __builtin_amdgcn_perm(r1[j2], r0[j2], 0x07060302u);
+            }
+            b0[x] = lo;
+            b1[x] = hi;
+          }
+#pragma unroll
+          for (int gb = 0; gb < GB; ++gb) {
+            const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+            o[gb][2 * j2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa[gb][hf], __builtin_bit_cast(bf16x8, b0),
+                                                                    hf ? o[gb][2 * j2] : zero, 0, 0, 0);
+            o[gb][2 * j2 + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa[gb][hf], __builtin_bit_cast(bf16x8, b1),
+                                                                        hf ? o[gb][2 * j2 + 1] : zero, 0, 0, 0);
+          }
+        }
       }
-      if (tr == 0) {
+      const float back = sizeof(T) == 1 ? pow2_f32(rev_max) : 1.f;
 #pragma unroll
-        for (int e = 0; e < kVec; ++e) xch[g * D + tc * kVec + e] = pv[g][e];
+      for (int gb = 0; gb < GB; ++gb) {
+        const int g = gb * 4 + tr;
+        if (g < G) {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            const f32x4 d = o[gb][j];
+            xch[g * D + tc * 8 + j] = ((d[2] + d[1]) + d[0]) * back;
+          }
+        }
+      }
+    } else {
+      // fp32 rows: TPR lanes per row, RPI rows per load, then a sum over the row groups
+      float pv[G][kVec];
+#pragma unroll
+      for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int e = 0; e < kVec; ++e) pv[g][e] = 0.f;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+#pragma unroll
+        for (int i = 0; i < VQ; ++i) {
+          const int r = (q * VQ + i) * RPI + tr;
+          float x[kVec];
+          cvt16f<T>(vbuf[(q & 1) * VQ + i], x);
+#pragma unroll
+          for (int g = 0; g < G; ++g) {
+            const float p = psf[g * kSub + r];  // 0 for rows beyond the end
+#pragma unroll
+            for (int e = 0; e < kVec; ++e) pv[g][e] = fmaf(p, x[e], pv[g][e]);
+          }
+        }
+        if (q + 2 < 4) {
+#pragma unroll
+          for (int i = 0; i < VQ; ++i) load_v((q + 2) * VQ + i, (q & 1) * VQ + i);
+        }
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+#pragma unroll
+        for (int e = 0; e < kVec; ++e) {
+          float t = pv[g][e];
+#pragma unroll
+          for (int o = TPR; o < 64; o <<= 1) t += __shfl_xor(t, o, 64);
+          pv[g][e] = t;
+        }
+        if (tr == 0) {
+#pragma unroll
+          for (int e = 0; e < kVec; ++e) xch[g * D + tc * kVec + e] = pv[g][e];
+        }
       }
     }
   }

@@ -121,6 +121,16 @@ __device__ __forceinline__ void cvt16f<uint8_t>(const u32x4& v, float* out) {
 template <int BYTES> struct RawBits;
 template <> struct RawBits<16> { typedef u32x4 type; };
 template <> struct RawBits<8> { typedef u32x2 type; };
+// 16, or BYTES, bytes per lane of a stream that is read once (non-temporal), `off` bytes into the buffer; zero past its end.
+constexpr int kStreamPolicy = 2;
+__device__ __forceinline__ u32x4 stream16(__amdgpu_buffer_rsrc_t src, uint32_t off) {
+  return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(src, int(off), 0, kStreamPolicy));
+}
+template <int BYTES>
+__device__ __forceinline__ typename RawBits<BYTES>::type stream_raw(__amdgpu_buffer_rsrc_t src, uint32_t off) {
+  if constexpr (BYTES == 16) return stream16(src, off);
+  else return __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(src, int(off), 0, kStreamPolicy));
+}
 // The partial results of a step are laid out chunk-major: [layer's chunk offset + chunk]
 // [sequence][KV head]...  Workgroups are dispatched head-fastest, so the results that are written
 // at about the same time are neighbours in memory (per-head contiguous arrays scatter them; a
@@ -150,8 +160,9 @@ template <typename T>
 __device__ __forceinline__ void pair_f64(const u32x4& r, int i, double& x0, double& x1) {
   if constexpr (sizeof(T) == 1) {
     const int wd = int(r[i / 2]);
-    x0 = double(i & 1 ? __builtin_amdgcn_cvt_f32_fp8(wd, 2) : __builtin_amdgcn_cvt_f32_fp8(wd, 0));
-    x1 = double(i & 1 ? __builtin_amdgcn_cvt_f32_fp8(wd, 3) : __builtin_amdgcn_cvt_f32_fp8(wd, 1));
+    const auto two = i & 1 ? __builtin_amdgcn_cvt_pk_f32_fp8(wd, true) : __builtin_amdgcn_cvt_pk_f32_fp8(wd, false);
+    x0 = double(two[0]);
+    x1 = double(two[1]);
   } else if constexpr (sizeof(T) == 2) {
     x0 = double(__uint_as_float(r[i] << 16));
     x1 = double(__uint_as_float(r[i] & 0xFFFF0000u));
