@@ -332,7 +332,7 @@ typedef enum {
   D2O_K_MATCH_REFINE = 4,  /* exact fp64 cosine / arg-max                                  */
   D2O_K_MERGE = 5,
   D2O_K_DECODE_ATTEND = 6,  /* attention over the cache + score update + evict/merge         */
-  D2O_K_DECODE_PREPARE = 7, /* append of the new token, operand set-up                      */
+  D2O_K_DECODE_PREPARE = 7, /* append of the new token, operand set-up: part of the launch of D2O_K_DECODE_ATTEND, whose time it repeats */
   D2O_K_DECODE_CLOSE = 8,   /* closing work of very large heads, split over workgroups        */
   D2O_K_COUNT = 9
 } d2o_kernel_id;

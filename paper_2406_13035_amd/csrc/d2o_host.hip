@@ -132,8 +132,6 @@ void layout(d2o_ctx* x, char* persistent, char* scratch, size_t* pbytes, size_t*
   s.take(x->d_rec, bh * nch * 4 * 32);  // per 64 slots, a quarter of a chunk
   s.take(x->d_pacc, bh * nch * G * d);
   s.take(x->d_part, bh * nch * kPartRecDoubles + L * bh * 16);  // part records, then 16 doubles per head
-  s.take(x->d_vecs, L * bh * (G + nc) * d);
-  s.take(x->d_cnorm, L * bh * nc);
 
   *sbytes = (s.off + 255) & ~size_t(255);
 }

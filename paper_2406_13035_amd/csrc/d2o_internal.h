@@ -80,7 +80,7 @@ struct d2o_ctx {
   double* cscore = nullptr;      // [B][Hkv][slots]
   int32_t* cpos = nullptr;       // [B][Hkv][slots]
   int32_t* ccount = nullptr;     // [L][B][Hkv]
-  int32_t* ctotal = nullptr;     // [L][B][Hkv] entries of the running decode step (count + 1), fixed for the whole step
+  int32_t* ctotal = nullptr;     // [L][B][Hkv] entries of a head the running decode step leaves to its split kernels (else 0); block append: entries with the block
   double* ctau = nullptr;        // [L][B][Hkv]
   int32_t* meta = nullptr;       // [L][B][Hkv][4]
   int32_t* ev_evicted = nullptr; // [L][B][Hkv]
@@ -138,8 +138,6 @@ struct d2o_ctx {
   double* d_rec = nullptr;       // [nchunk][B][Hkv][4][at most 32] per 64 slots: softmax maxima and sums, candidates' best cosine and slot
   double* d_part = nullptr;      // [nchunk][B][Hkv][kPartRecDoubles] records of the split closing kernels (one per part, at its first chunk)
   float* d_pacc = nullptr;       // [nchunk][B][Hkv][G][d] partial outputs
-  double* d_vecs = nullptr;      // [L][B][Hkv][G + candidates][d] queries and candidate keys, fp64
-  double* d_cnorm = nullptr;     // [L][B][Hkv][candidates] norms of the candidate keys
 };
 
 namespace d2o {

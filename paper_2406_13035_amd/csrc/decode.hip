@@ -1,18 +1,20 @@
 // One generation step over the compressed cache (Sec. 3 Eq. 2-3; Sec. 4.2 Eq. 6-12), for a
-// range of layers in one set of launches.  The step is bound by HBM traffic, so the design
-// reads every K and V row of every layer exactly once per step:
+// range of layers in one launch (two more for very large heads).  The step reads every K and V row of
+// every layer exactly once:
 //
-//   decode_prepare  per (layer, sequence, KV head): writes the new token's k, v into the free
-//                   slot (score 0, its position) and lays out, in fp64, the vectors the
-//                   attention pass multiplies every cache key with: the G queries and the keys
-//                   of kCand eviction candidates chosen at the end of the previous step.
 //   decode_attend   one workgroup per chunk of 256 slots, each of its four wavefronts working
-//                   alone on 64 of them.  K pass: the keys go through LDS, and four lanes share
+//                   alone on 64 of them.  It lays out, in fp64 in LDS, the vectors that every cache key is
+//                   multiplied with: the G queries and the keys of kCand eviction candidates chosen at the
+//                   end of the previous step; the wavefront whose rows the new token's k, v fall among
+//                   writes them into the free slot (score 0, its position).  (A launch of its own for
+//                   both, before this one, cost a step 5 to 12 us: one layer per call, 32 layers took
+//                   984 us instead of 875, a step of a 128-entry fp32 cache 17.1 instead of 15.1.)
+//                   K pass: the keys go through LDS, and four lanes share
 //                   four cache rows, a quarter of every 64 bytes each; they form, in fp64, the G
-//                   logits, the dot products with the candidate keys and the rows' squared norms
-//                   (the vectors are in LDS as fp64).  Then, one row per lane, the softmax
+//                   logits, the dot products with the candidate keys and the rows' squared norms.
+//                   Then, one row per lane, the softmax
 //                   statistics of the 64 rows, the candidates' best cosine among them (Eq. 9),
-//                   and the partial P V in fp32.
+//                   and the partial P V in fp32 on the matrix core.
 //                   The last workgroup of a head to finish (a ticket counter, no waiting)
 //                   closes the head: output rows, exact fp64 normaliser, score update (Eq. 6,
 //                   generation case), the token to evict (Eq. 7-8: lowest score outside sinks
@@ -37,8 +39,7 @@
 
 namespace d2o {
 
-// Scratch memory of d2o_decode_step_static: the partial results and operand vectors of one
-// generation step, for callers that cannot hand over (or allocate) a scratch workspace.  One
+// Scratch memory of d2o_decode_step_static: the partial results of one generation step, for callers that cannot hand over (or allocate) a scratch workspace.  One
 // copy per GPU, held from the moment the library's code is loaded on it until the process ends.
 // In host code the array's name is only a handle: the device address comes from
 // hipGetSymbolAddress, once per device, and is what kernels and launchers are given.
@@ -83,81 +84,22 @@ struct TensorType {
   typedef typename std::conditional<sizeof(T) == 1, uint16_t, T>::type type;
 };
 
-// T: the cache's element type (uint8_t: fp8 codes), IT: the type of q, k_new, v_new.
-template <typename T, typename IT, int D, int G>
-__global__ __launch_bounds__(128) void decode_prepare(DecodeArgs a, const IT* __restrict__ q, View qv,
-                                                      const IT* __restrict__ kn, View kv, const IT* __restrict__ vn,
-                                                      View vv) {
-  __shared__ double red[2 * kCand > 4 ? 2 * kCand : 4];
-  const int li = blockIdx.y, l = a.layer0 + li, b = blockIdx.x / a.Hkv, hk = blockIdx.x % a.Hkv;
-  const int64_t lbh = (int64_t(l) * a.B + b) * a.Hkv + hk;
-  const int count = a.ccount[lbh];
-  const int64_t slot0 = (int64_t(b) * a.Hkv + hk) * a.slots + a.meta[lbh * 4 + 0];
-  const int c = threadIdx.x;
-  T* Kc = static_cast<T*>(a.cK) + slot0 * D;
-  T* Vc = static_cast<T*>(a.cV) + slot0 * D;
-  if constexpr (sizeof(T) == 1) {
-    // fp8 cache: the new row is encoded as it enters the cache (its largest magnitude decides
-    // the row's power of two: a reduction over the two wavefronts)
-    static_assert(D == 128, "one element per thread");
-    const double kx = Elem<IT>::to_f64(kn[li * kv.sn + b * kv.sb + hk * kv.sh + c]);
-    const double vx = Elem<IT>::to_f64(vn[li * vv.sn + b * vv.sb + hk * vv.sh + c]);
-    const double ak = wave_max(fabs(kx)), av = wave_max(fabs(vx));
-    if ((c & 63) == 0) {
-      red[c >> 6] = ak;
-      red[2 + (c >> 6)] = av;
-    }
-    __syncthreads();
-    const int ek = fp8_row_exponent(fmax(red[0], red[1])), ev = fp8_row_exponent(fmax(red[2], red[3]));
-    Kc[int64_t(count) * D + c] = fp8_encode(ldexp(kx, -ek));
-    Vc[int64_t(count) * D + c] = fp8_encode(ldexp(vx, -ev));
-    if (c == 0) {
-      a.cKe[slot0 + count] = int8_t(ek);
-      a.cVe[slot0 + count] = int8_t(ev);
-    }
-    __syncthreads();  // `red` is used again below
-  } else {
-    if (c < D) {
-      Kc[int64_t(count) * D + c] = kn[li * kv.sn + b * kv.sb + hk * kv.sh + c];
-      Vc[int64_t(count) * D + c] = vn[li * vv.sn + b * vv.sb + hk * vv.sh + c];
+// This lane's share of a vector of D elements (elements E lane .. E lane + E - 1, E = D / 64) as loaded and as fp64.
+template <typename U, int D>
+struct LaneShare {
+  static constexpr int E = D / 64;
+  typedef typename std::conditional<E * sizeof(U) == 2, uint16_t, typename std::conditional<E * sizeof(U) == 4, uint32_t, uint64_t>::type>::type Bits;
+  static __device__ __forceinline__ Bits load(const U* p, int lane) { return *reinterpret_cast<const Bits*>(p + E * lane); }
+  static __device__ __forceinline__ void widen(Bits b, double (&x)[E]) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      if constexpr (sizeof(U) == 4)
+        x[e] = double(__uint_as_float(uint32_t(b >> (32 * e))));
+      else
+        x[e] = Elem<U>::to_f64(U(b >> (8 * int(sizeof(U)) * e)));
     }
   }
-  if (c == 0) {
-    a.cscore[slot0 + count] = 0.0;
-    a.cpos[slot0 + count] = a.new_pos;
-    // The step's entry count gets a word of its own: the head's closing workgroup overwrites
-    // ccount while other workgroups of the same launch may not have started yet, and those
-    // must still see the count the step began with.
-    a.ctotal[lbh] = count + 1;
-  }
-  constexpr int NV = G + kCand;
-  double* vec = a.vecs + lbh * NV * D;
-#pragma unroll
-  for (int g = 0; g < G; ++g)
-    if (c < D) vec[operand_index<T, NV>(g, c)] = Elem<IT>::to_f64(q[li * qv.sn + b * qv.sb + (hk * G + g) * qv.sh + c]);
-  // the candidates' keys: all slot numbers first, then all rows, then one exchange for the
-  // norms (one memory round trip each instead of one per candidate)
-  int cs[kCand];
-#pragma unroll
-  for (int i = 0; i < kCand; ++i) cs[i] = a.cand[lbh * kCand + i];  // older slots: never the one just written
-  double x[kCand], part[kCand];
-#pragma unroll
-  for (int i = 0; i < kCand; ++i) {
-    x[i] = (cs[i] >= 0 && c < D) ? Elem<T>::to_f64(Kc[int64_t(cs[i]) * D + c]) : 0.0;
-    if constexpr (sizeof(T) == 1) x[i] *= pow2_f64(a.cKe[slot0 + max(cs[i], 0)]);
-  }
-#pragma unroll
-  for (int i = 0; i < kCand; ++i) {
-    if (c < D) vec[operand_index<T, NV>(G + i, c)] = x[i];
-    part[i] = wave_sum(x[i] * x[i]);
-  }
-  if ((c & 63) == 0) {
-#pragma unroll
-    for (int i = 0; i < kCand; ++i) red[(c >> 6) * kCand + i] = part[i];
-  }
-  __syncthreads();
-  if (c < kCand) a.cnorm[lbh * kCand + c] = sqrt(red[c] + red[kCand + c]);  // wavefront 0's sum first
-}
+};
 
 // Softmax maximum and exact normaliser sum_j exp(s_j - max) of each query head of one head, from
 // its sub-chunk records (fixed summation tree), by one workgroup of 256 threads of the launch
@@ -243,9 +185,9 @@ __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ 
   double* wcm_u = sred + 8 + 8;                            // [4][kCand], behind sred and ired
   int2* wcm_ps = reinterpret_cast<int2*>(wcm_u + 4 * kCand);  // [4][kCand] (position, slot)
   T* park_kv = reinterpret_cast<T*>(wcm_ps + 4 * kCand);
-  if (tid < D) {
-    park_kv[tid] = Kc[int64_t(last) * D + tid];
-    park_kv[256 + tid] = Vc[int64_t(last) * D + tid];
+  if (tid < D) {  // (the new token's row, written by another workgroup of this launch)
+    park_kv[tid] = ld_agent(Kc + int64_t(last) * D + tid);
+    park_kv[256 + tid] = ld_agent(Vc + int64_t(last) * D + tid);
   }
   constexpr int kEmCap = (kStageBytes - 8192) / int(sizeof(double));
   constexpr int kSegSubs = kEmCap / G;  // sub-chunks whose factors fit `em`
@@ -258,7 +200,7 @@ __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ 
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int j = min(j0 + u * 256, jend - 1);
-      sc[u] = a.cscore[slot0 + j];
+      sc[u] = a.cscore[slot0 + j];  // (the last slot's score and position are known without memory: see below)
       ps[u] = a.cpos[slot0 + j];
 #pragma unroll
       for (int g = 0; g < G; ++g) e[u][g] = ld_agent(&a.elog[elog_index(a, bh, ch0, G, g, j)]);
@@ -374,7 +316,7 @@ __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ 
       const int s = c == tid ? own_s[i] : int(ld_agent(&a.rec[x + 2 * G + kCand + i]));
       if (s >= 0) {
         const double u = c == tid ? own_u[i] : ld_agent(&a.rec[x + 2 * G + i]);
-        const int p = a.cpos[slot0 + s];
+        const int p = s == last ? a.new_pos : a.cpos[slot0 + s];
         if (better_match(u, p, s, cm[i])) cm[i] = Best{u, p, s};
       }
     }
@@ -400,11 +342,11 @@ __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ 
     for (int u = 0; u < U; ++u) {
       const int j = j0 + u * 256;
       if (j < jend) {
-        double s2 = sc[u];
+        double s2 = j == last ? 0.0 : sc[u];
 #pragma unroll
         for (int g = 0; g < G; ++g) s2 = fma(e[u][g], em[(j / kSub - seg0) * G + g], s2);
         a.cscore[slot0 + j] = s2;
-        const int p = ps[u];
+        const int p = j == last ? a.new_pos : ps[u];
         if (j == last) {  // kept for the move into the freed slot
           sred[4] = s2;
           ired[8] = p;
@@ -494,9 +436,15 @@ __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ 
   close_head<T, D>(a, lbh, slot0, total, evict, ev, low, cl, told, sred, ired, dred, wcm_u, wcm_ps, park_kv, mr);
 }
 
-// (second launch bound: wavefronts per SIMD)
+// T: the cache's element type (uint8_t: fp8 codes).  (second launch bound: wavefronts per SIMD)
 template <typename T, typename OT, int D, int G>
-__global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 3) void decode_attend(DecodeArgs a, OT* __restrict__ out, View ov) {
+__global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 3) void decode_attend(
+    DecodeArgs a, const typename TensorType<T>::type* __restrict__ q, View qv, const typename TensorType<T>::type* __restrict__ kn,
+    View kv, const typename TensorType<T>::type* __restrict__ vn, View vv, OT* __restrict__ out, View ov) {
+  typedef typename TensorType<T>::type IT;  // of q, k_new, v_new
+  typedef LaneShare<IT, D> Share;
+  typedef LaneShare<T, D> RowShare;
+  constexpr int E = Share::E;
   constexpr int VB = sizeof(T) == 1 ? 8 : 16;   // V pass: bytes per lane and load (fp8: 8, which keeps the
                                                 // partial sums at eight per lane and query head)
   constexpr int kVec = VB / sizeof(T);          // elements per load
@@ -523,35 +471,32 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
   // the XCDs in index order, so with a head count that is a multiple of the XCD count every chunk
   // of a head, and the workgroup that closes it, run on one XCD.
   // (a call of one layer needs no search)
-  const LayerEntry entry = a.nl == 1 ? LayerEntry{0, 0} : find_entry(a, blockIdx.y);
+  const LayerEntry entry = a.nl == 1 ? LayerEntry{0, 0, int(gridDim.y)} : find_entry(a, blockIdx.y);
   const int li = entry.layer, grp = blockIdx.y - entry.first;
   const int l = a.layer0 + li, b = blockIdx.x / a.Hkv, hk = blockIdx.x % a.Hkv;
   const int64_t lbh = (int64_t(l) * a.B + b) * a.Hkv + hk;
   // Everything the workgroup needs to know about its head comes through the scalar cache in one
   // round trip (the loads are independent of each other): the fill level, the layer's slot and
-  // sub-chunk offsets, the candidates.  The kernel that wrote them has completed.
+  // sub-chunk offsets, the candidates.  The fill level changes when the head is closed, after every
+  // workgroup of the head, the idle ones beyond its last row too, has drawn its ticket.
   typedef const int32_t __attribute__((address_space(4))) * ciptr;
-  typedef const double __attribute__((address_space(4))) * cptr;
   const ciptr mt = (ciptr)a.meta + lbh * 4;
-  const int total = ((ciptr)a.ctotal)[lbh];  // the new token has been appended; constant during this launch
+  int count = ((ciptr)a.ccount)[lbh];
   const int mt0 = mt[0], mt3 = mt[3];
   int cs[kCand];
-  double cn[kCand];
 #pragma unroll
-  for (int c = 0; c < kCand; ++c) {
-    cs[c] = ((ciptr)a.cand)[lbh * kCand + c];
-    cn[c] = ((cptr)a.cnorm)[lbh * kCand + c];
-  }
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  // the head's operand vectors, 16 bytes per thread and load
-  constexpr int kOpnd16 = NV * D / 2, kOpndThreads = kOwnOpnd ? 64 : 256, kOpndLoads = (kOpnd16 + kOpndThreads - 1) / kOpndThreads;
-  const int ot = kOwnOpnd ? lane : tid;
-  u32x4 opr[kOpndLoads];
+  for (int c = 0; c < kCand; ++c) cs[c] = ((ciptr)a.cand)[lbh * kCand + c];
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // the query heads whose operands this wavefront lays out: all of them, or every fourth
+  constexpr int NQ = kOwnOpnd ? G : (G + 3) / 4;
+  auto head_of = [&](int i) { return kOwnOpnd ? i : i * 4 + w; };
+  const IT* const qh = q + li * qv.sn + b * qv.sb + int64_t(hk) * G * qv.sh;
+  typename Share::Bits qraw[NQ];
 #pragma unroll
-  for (int i = 0; i < kOpndLoads; ++i)
-    opr[i] = reinterpret_cast<const u32x4*>(a.vecs + lbh * NV * D)[min(ot + i * kOpndThreads, kOpnd16 - 1)];
-  asm volatile("" ::"s"(total), "s"(mt0), "s"(mt3));  // all of them are on their way before the first wait
-  if (grp * kChunk >= total) return;
+  for (int i = 0; i < NQ; ++i) qraw[i] = Share::load(qh + min(head_of(i), G - 1) * qv.sh, lane);
+  asm volatile("" : "+s"(count) : "s"(mt0), "s"(mt3));  // all of them are on their way before the first wait; count is read once
+  const int total = count + 1;  // with the new token
+  if (grp * kChunk < total) {
   const int64_t bh = int64_t(b) * a.Hkv + hk;
   const int64_t slot0 = bh * a.slots + mt0;
   const unsigned char* Kh = static_cast<const unsigned char*>(a.cK) + slot0 * RB;
@@ -576,19 +521,105 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
   // cost six, 190 of a bf16 chunk's 2300 vector instructions per wavefront).
   const int sub = __builtin_amdgcn_readfirstlane(grp * (kChunk / kSub) + w);
   const int rows = min(kSub, total - sub * kSub);  // <= 0: nothing for this wavefront
-  const __amdgpu_buffer_rsrc_t Kb = buffer_of(Kh + int64_t(sub) * kSub * RB, uint32_t(max(rows, 0) * RB));
-  const __amdgpu_buffer_rsrc_t Vb = buffer_of(Vh + int64_t(sub) * kSub * RB, uint32_t(max(rows, 0) * RB));
+  // The new token's row: its wavefront (at most one of the head) writes it to the cache, and takes its
+  // products and its term of P V from registers; the streams end before it.
+  const int jnew = count - sub * kSub;
+  const bool owner = jnew >= 0 && jnew < kSub;
+  const uint32_t cached = uint32_t(max(min(kSub, jnew), 0) * RB);
+  const __amdgpu_buffer_rsrc_t Kb = buffer_of(Kh + int64_t(sub) * kSub * RB, cached);
+  const __amdgpu_buffer_rsrc_t Vb = buffer_of(Vh + int64_t(sub) * kSub * RB, cached);
   u32x4 kreg[8];
   const uint32_t koff = (ln >> 3) * RB + (ln & 7) * 16;
   auto load_pair = [&](int p0) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) kreg[i] = stream16(Kb, koff + p0 * kPiece + i * 8 * RB);
   };
-  if (rows > 0) load_pair(0);
+  // (the candidate's row is needed first, and loads arrive in order)
+  typename RowShare::Bits craw[kCand];
+  int cexp[kCand];
 #pragma unroll
-  for (int i = 0; i < kOpndLoads; ++i)
-    if (ot + i * kOpndThreads < kOpnd16) reinterpret_cast<u32x4*>(mine_opnd)[ot + i * kOpndThreads] = opr[i];
+  for (int c = 0; c < kCand; ++c) {
+    craw[c] = RowShare::load(static_cast<const T*>(a.cK) + (slot0 + max(cs[c], 0)) * D, lane);
+    cexp[c] = sizeof(T) == 1 ? int(a.cKe[slot0 + max(cs[c], 0)]) : 0;
+  }
+  typename Share::Bits kraw = 0, vraw = 0;
+  if (owner) {
+    kraw = Share::load(kn + li * kv.sn + b * kv.sb + hk * kv.sh, lane);
+    vraw = Share::load(vn + li * vv.sn + b * vv.sb + hk * vv.sh, lane);
+  }
+  if (rows > 0) load_pair(0);
+  // ---- operands to LDS: queries, and the keys of the eviction candidates with their norms
+  auto lay_out = [&](int v, const double (&x)[E]) {
+    if constexpr (E == 2)
+      *reinterpret_cast<double2*>(mine_opnd + operand_index<T, NV>(v, 2 * lane)) = make_double2(x[0], x[1]);
+    else
+      mine_opnd[operand_index<T, NV>(v, lane)] = x[0];
+  };
+#pragma unroll
+  for (int i = 0; i < NQ; ++i) {
+    double x[E];
+    Share::widen(qraw[i], x);
+    if (head_of(i) < G) lay_out(head_of(i), x);
+  }
+  double cn[kCand];
+#pragma unroll
+  for (int c = 0; c < kCand; ++c) {
+    double x[E], part = 0.0;
+    RowShare::widen(craw[c], x);
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      x[e] = cs[c] < 0 ? 0.0 : sizeof(T) == 1 ? x[e] * pow2_f64(cexp[c]) : x[e];
+      part = fma(x[e], x[e], part);
+    }
+    if (kOwnOpnd || w == c % 4) lay_out(G + c, x);
+    cn[c] = sqrt(fast_wave_sum(part));
+  }
   if (!kOwnOpnd) lds_barrier();  // the operands are in LDS; the K rows may still be on their way
+  // the new row's K and V as they enter the cache
+  double knew[E];
+  float vnew[E];
+  if (owner) {
+    double x[E], y[E];
+    Share::widen(kraw, x);
+    Share::widen(vraw, y);
+    T* Kc = static_cast<T*>(a.cK) + (slot0 + count) * D;
+    T* Vc = static_cast<T*>(a.cV) + (slot0 + count) * D;
+    typename RowShare::Bits kst, vst;
+    if constexpr (sizeof(T) == 1) {
+      // fp8 cache: encoded; the row's largest magnitude decides its power of two
+      static_assert(E == 2, "two elements per lane");
+      const int ek = fp8_row_exponent(fast_wave_max(fmax(fabs(x[0]), fabs(x[1]))));
+      const int ev = fp8_row_exponent(fast_wave_max(fmax(fabs(y[0]), fabs(y[1]))));
+      kst = vst = 0;
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const uint8_t ck = fp8_encode(ldexp(x[e], -ek)), cv = fp8_encode(ldexp(y[e], -ev));
+        kst |= typename RowShare::Bits(ck) << (8 * e);
+        vst |= typename RowShare::Bits(cv) << (8 * e);
+        knew[e] = Elem<T>::to_f64(ck) * pow2_f64(ek);
+        vnew[e] = Elem<T>::to_f32(cv) * pow2_f32(ev);
+      }
+      if (lane == 0) {
+        st_agent(a.cKe + slot0 + count, int8_t(ek));
+        st_agent(a.cVe + slot0 + count, int8_t(ev));
+      }
+    } else {
+      kst = kraw;
+      vst = vraw;
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        knew[e] = x[e];
+        vnew[e] = float(y[e]);
+      }
+    }
+    // (write-through: the head's closing workgroup may read the row in this launch, and stores the score again)
+    st_agent(reinterpret_cast<typename RowShare::Bits*>(Kc) + lane, kst);
+    st_agent(reinterpret_cast<typename RowShare::Bits*>(Vc) + lane, vst);
+    if (lane == 0) {
+      st_agent(a.cscore + slot0 + count, 0.0);
+      st_agent(a.cpos + slot0 + count, a.new_pos);
+    }
+  }
   if (rows <= 0) {  // this wavefront only takes part in the combination
     if (ln < G) wmax[w][ln] = -INFINITY;
   } else {
@@ -632,12 +663,13 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
     // this lane's score-side loads ride along
     const bool valid = ln < rows;
     const int j = sub * kSub + ln;
-    const int pos = valid ? a.cpos[slot0 + j] : 0;
+    const bool fresh = ln == jnew;  // (only in the new row's wavefront)
+    const int pos = fresh ? a.new_pos : valid ? a.cpos[slot0 + j] : 0;
     // fp8 cache: the powers of two of this lane's K and V row
     int rek = 0, rev = 0;
     if constexpr (sizeof(T) == 1) {
-      rek = valid ? a.cKe[slot0 + j] : 0;
-      rev = valid ? a.cVe[slot0 + j] : 0;
+      rek = valid && !fresh ? a.cKe[slot0 + j] : 0;
+      rev = valid && !fresh ? a.cVe[slot0 + j] : -120;
     }
     auto stage_piece = [&](int p) {
       // The staging area is private to the wavefront and LDS serves a wavefront's requests in
@@ -736,6 +768,21 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
       for (int v = 0; v < NV; ++v) dot[v] *= sk;
       nr *= sk * sk;
     }
+    if (owner) {  // the new row's products: E of its elements per lane, summed over the wavefront
+      double nn = 0.0;
+#pragma unroll
+      for (int e = 0; e < E; ++e) nn = fma(knew[e], knew[e], nn);
+      nn = fast_wave_sum(nn);
+      nr = fresh ? nn : nr;
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {
+        double dv = 0.0;
+#pragma unroll
+        for (int e = 0; e < E; ++e) dv = fma(knew[e], mine_opnd[operand_index<T, NV>(v, E * lane + e)], dv);
+        dv = fast_wave_sum(dv);
+        dot[v] = fresh ? dv : dot[v];
+      }
+    }
     // ---- softmax statistics of the sub-chunk; the lane owns cache row sub*kSub + lane
     const int64_t pidx = sub_index(a, bh, mt3, sub) * G;
     double recv = 0.0;  // this lane's element of the sub-chunk record
@@ -749,7 +796,8 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
     unsigned char* const term = mine + ((ln & 3) * 16 + (ln >> 2)) * 2;
     // fp8 cache: the V pass works on the codes, so a row's power of two rides on its probability, taken
     // relative to the largest of the sub-chunk (which multiplies the sums: the terms keep their range)
-    const int rev_max = sizeof(T) == 1 ? -fast_wave_min(valid ? -rev : 128) : 0;
+    const int rev_max = sizeof(T) == 1 ? -fast_wave_min(-rev) : 0;  // (-120, the smallest there is, in lanes without a cached row)
+    float pnew[G];  // the new row's probabilities
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
@@ -767,6 +815,7 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
       } else {
         psf[g * kSub + ln] = float(e);
       }
+      if (owner) pnew[g] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(float(e)), jnew));
       if (valid) st_agent(&a.elog[elog_index(a, bh, mt3, G, g, j)], e);
       const double sm = fast_wave_sum(e);
       if (ln == g) {
@@ -897,6 +946,14 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
         }
       }
     }
+    if (owner) {  // the new row's term
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int e = 0; e < E; ++e) xch[g * D + E * lane + e] = fmaf(pnew[g], vnew[e], xch[g * D + E * lane + e]);
+    }
   }
   // ---- one partial output row per chunk and query head: the four wavefronts' rows, each
   //      rescaled from its sub-chunk's maximum to the chunk's (fp32, like the rows themselves).
@@ -923,30 +980,30 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
       st_agent(reinterpret_cast<uint64_t*>(a.pacc + (chunk_index(a, bh, mt3, grp) * G + g) * D + lane * 2), two);
     }
   }
+  }  // (the workgroup has rows)
   // ---- ticket: the last workgroup of the head to arrive closes the head.  Every store above
   //      that it will read is a write-through store; they have completed once the memory
   //      counters are zero, before the barrier that precedes the ticket.
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  if (tid == 0) {
-    const int ngroup = (total + kChunk - 1) / kChunk;
+  if (tid == 0)
     sh_last = (__hip_atomic_fetch_add(&a.ticket[lbh], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
-               unsigned(ngroup - 1)) ? 1 : 0;
-  }
+               unsigned(entry.chunks - 1)) ? 1 : 0;
   __syncthreads();
   if (!sh_last) return;
   // Consumer side of the hand-over.  The other workgroups' results (rec, elog, pacc) are read
   // below through ld_agent only, which goes around this XCD's L2 whatever the compiler does
   // with plain loads; this fence keeps the compiler from moving any load of the closing code
   // above the ticket.  Plain loads in the closing code are limited to data that no other
-  // workgroup of this launch writes: cscore, cpos, cK, cV, ctau, cand, meta of this head.
+  // workgroup of this launch writes: ctau, cand, meta of this head, and cscore and cpos of its older slots.
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
   // the staging area is free: it holds the closing code's exchange buffers
   float* fred = reinterpret_cast<float*>(stage);
   double* dred = reinterpret_cast<double*>(stage + 4 * 256 * sizeof(float));
   double* sred = dred + D;
   int* ired = reinterpret_cast<int*>(sred + 8);
+  if (tid == 0) a.ctotal[lbh] = total > a.big_rows ? total : 0;
   if (total > a.big_rows) {
     // A very large head: two more launches close it (decode_close_part / _final).  All its
     // sub-chunk records are there now, so this workgroup leaves them the head's softmax
@@ -959,42 +1016,32 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
                          stage + 8192);
 }
 
-template <typename T, int D>
-hipError_t run_prepare_g(d2o_ctx* c, const DecodeArgs& a, int nl, View q, View k, View v, hipStream_t s) {
-  typedef typename TensorType<T>::type IT;
-  const int bh = a.B * a.Hkv;
-  KernelTimer kt(c, D2O_K_DECODE_PREPARE, s);
-  const dim3 grid(bh, nl);
-  switch (a.G) {
-    case 1: decode_prepare<T, IT, D, 1><<<grid, 128, 0, s>>>(a, (const IT*)q.ptr, q, (const IT*)k.ptr, k, (const IT*)v.ptr, v); break;
-    case 2: decode_prepare<T, IT, D, 2><<<grid, 128, 0, s>>>(a, (const IT*)q.ptr, q, (const IT*)k.ptr, k, (const IT*)v.ptr, v); break;
-    case 4: decode_prepare<T, IT, D, 4><<<grid, 128, 0, s>>>(a, (const IT*)q.ptr, q, (const IT*)k.ptr, k, (const IT*)v.ptr, v); break;
-    case 8: decode_prepare<T, IT, D, 8><<<grid, 128, 0, s>>>(a, (const IT*)q.ptr, q, (const IT*)k.ptr, k, (const IT*)v.ptr, v); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
+struct StepViews {
+  View q, k, v, out;
+};
 
 template <typename T, typename OT, int D, int G>
-hipError_t run_attend(d2o_ctx* c, const DecodeArgs& a, int flat_chunks, View out, hipStream_t s) {
-  KernelTimer kt(c, D2O_K_DECODE_ATTEND, s);
-  decode_attend<T, OT, D, G><<<dim3(a.B * a.Hkv, flat_chunks), 256, 0, s>>>(a, (OT*)out.ptr, out);
+hipError_t run_attend(d2o_ctx* c, const DecodeArgs& a, int flat_chunks, const StepViews& t, hipStream_t s) {
+  typedef typename TensorType<T>::type IT;
+  KernelTimer kt(c, D2O_K_DECODE_ATTEND, s), kp(c, D2O_K_DECODE_PREPARE, s);
+  decode_attend<T, OT, D, G><<<dim3(a.B * a.Hkv, flat_chunks), 256, 0, s>>>(a, (const IT*)t.q.ptr, t.q, (const IT*)t.k.ptr, t.k,
+                                                                           (const IT*)t.v.ptr, t.v, (OT*)t.out.ptr, t.out);
   return hipGetLastError();
 }
 
 template <typename T, int D, int G>
-hipError_t run_decode(d2o_ctx* c, const DecodeArgs& a, int fc, View out, hipStream_t s) {
-  if (a.out_f32) return run_attend<T, float, D, G>(c, a, fc, out, s);
-  return run_attend<T, typename TensorType<T>::type, D, G>(c, a, fc, out, s);
+hipError_t run_decode(d2o_ctx* c, const DecodeArgs& a, int fc, const StepViews& t, hipStream_t s) {
+  if (a.out_f32) return run_attend<T, float, D, G>(c, a, fc, t, s);
+  return run_attend<T, typename TensorType<T>::type, D, G>(c, a, fc, t, s);
 }
 
 template <typename T, int D>
-hipError_t run_decode_g(d2o_ctx* c, const DecodeArgs& a, int fc, View out, hipStream_t s) {
+hipError_t run_decode_g(d2o_ctx* c, const DecodeArgs& a, int fc, const StepViews& t, hipStream_t s) {
   switch (a.G) {
-    case 1: return run_decode<T, D, 1>(c, a, fc, out, s);
-    case 2: return run_decode<T, D, 2>(c, a, fc, out, s);
-    case 4: return run_decode<T, D, 4>(c, a, fc, out, s);
-    case 8: return run_decode<T, D, 8>(c, a, fc, out, s);
+    case 1: return run_decode<T, D, 1>(c, a, fc, t, s);
+    case 2: return run_decode<T, D, 2>(c, a, fc, t, s);
+    case 4: return run_decode<T, D, 4>(c, a, fc, t, s);
+    case 8: return run_decode<T, D, 8>(c, a, fc, t, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -1077,25 +1124,23 @@ hipError_t launch_init_candidates(d2o_ctx* c, int layer, int new_pos, hipStream_
   return hipGetLastError();
 }
 
-// Sizes (in bytes, each rounded up to 256) of the six scratch arrays of a decode step, in the
-// order elog, rec, pacc, vecs, cnorm, part.
-static void decode_scratch_sizes(const d2o_ctx* c, size_t (&sz)[6]) {
+// Sizes (in bytes, each rounded up to 256) of the four scratch arrays of a decode step, in the
+// order elog, rec, pacc, part.
+static void decode_scratch_sizes(const d2o_ctx* c, size_t (&sz)[4]) {
   const d2o_config& cf = c->cfg;
   const size_t B = cf.batch, L = cf.n_layers, Hq = cf.n_q_heads, Hkv = cf.n_kv_heads, d = cf.head_dim;
   const size_t G = Hq / Hkv, bh = B * Hkv, nch = c->nchunk_cap, nsub = nch * 4;
   sz[0] = nch * B * Hq * kChunk * sizeof(double);
   sz[1] = bh * nsub * rec_doubles(int(G)) * sizeof(double);  // one record per 64 slots
   sz[2] = bh * nch * G * d * sizeof(float);                  // one partial output row per chunk and query head
-  sz[3] = L * bh * (G + kCand) * d * sizeof(double);
-  sz[4] = L * bh * kCand * sizeof(double);
-  sz[5] = (bh * nch * kPartRecDoubles + L * bh * 16) * sizeof(double);  // part records, then 16 doubles per head
+  sz[3] = (bh * nch * kPartRecDoubles + L * bh * 16) * sizeof(double);  // part records, then 16 doubles per head
   for (size_t& x : sz) x = (x + 255) & ~size_t(255);
 }
 
 size_t decode_static_scratch_need(const d2o_ctx* c) {
-  size_t sz[6];
+  size_t sz[4];
   decode_scratch_sizes(c, sz);
-  return sz[0] + sz[1] + sz[2] + sz[3] + sz[4] + sz[5];
+  return sz[0] + sz[1] + sz[2] + sz[3];
 }
 size_t decode_static_scratch_capacity() { return kStaticScratchBytes; }
 
@@ -1119,19 +1164,15 @@ hipError_t launch_decode(d2o_ctx* c, int layer0, int nl_all, View q, View k, Vie
   a.elog = c->d_logit;
   a.rec = c->d_rec;
   a.pacc = c->d_pacc;
-  a.vecs = c->d_vecs;
-  a.cnorm = c->d_cnorm;
   a.part = c->d_part;
-  if (static_scratch) {  // the same six arrays, carved from the library's static device array
-    size_t sz[6];
+  if (static_scratch) {  // the same four arrays, carved from the library's static device array
+    size_t sz[4];
     decode_scratch_sizes(c, sz);
     unsigned char* p = static_scratch;
     a.elog = reinterpret_cast<double*>(p);
     a.rec = reinterpret_cast<double*>(p += sz[0]);
     a.pacc = reinterpret_cast<float*>(p += sz[1]);
-    a.vecs = reinterpret_cast<double*>(p += sz[2]);
-    a.cnorm = reinterpret_cast<double*>(p += sz[3]);
-    a.part = reinterpret_cast<double*>(p += sz[4]);
+    a.part = reinterpret_cast<double*>(p += sz[2]);
   }
   a.ev_evicted = c->ev_evicted;
   a.ev_target = c->ev_target;
@@ -1176,18 +1217,8 @@ hipError_t launch_decode(d2o_ctx* c, int layer0, int nl_all, View q, View k, Vie
       return x;
     };
     const int es = c->esize, os = cf.out_f32 ? 4 : c->esize;
-    const View qg = shift(q, es), kg = shift(k, es), vg = shift(v, es), og = shift(out, os);
+    const StepViews tg{shift(q, es), shift(k, es), shift(v, es), shift(out, os)};
     hipError_t e;
-    // ---- append + operand set-up for every layer of the group
-    if (cf.cache_fp8)
-      e = run_prepare_g<uint8_t, 128>(c, a, nl, qg, kg, vg, s);
-    else if (cf.dtype == D2O_BF16)
-      e = run_prepare_g<uint16_t, 128>(c, a, nl, qg, kg, vg, s);
-    else if (cf.head_dim == 64)
-      e = run_prepare_g<float, 64>(c, a, nl, qg, kg, vg, s);
-    else
-      e = run_prepare_g<float, 128>(c, a, nl, qg, kg, vg, s);
-    if (e != hipSuccess) return e;
     // ---- attention over the caches, one workgroup per 256 slots; the layers with most chunks first
     {
       std::stable_sort(chunk_id, chunk_id + nc, [&](int x, int y) { return mc[x] > mc[y]; });
@@ -1199,20 +1230,20 @@ hipError_t launch_decode(d2o_ctx* c, int layer0, int nl_all, View q, View k, Vie
       }
       for (int i = nc; i <= kMaxLayersPerCall; ++i) a.lay_off[i] = i == nc ? flat : 0x7FFFFFFF;
       if (cf.cache_fp8)
-        e = run_decode_g<uint8_t, 128>(c, a, flat, og, s);
+        e = run_decode_g<uint8_t, 128>(c, a, flat, tg, s);
       else if (cf.dtype == D2O_BF16)
-        e = run_decode_g<uint16_t, 128>(c, a, flat, og, s);
+        e = run_decode_g<uint16_t, 128>(c, a, flat, tg, s);
       else if (cf.head_dim == 64)
-        e = run_decode_g<float, 64>(c, a, flat, og, s);
+        e = run_decode_g<float, 64>(c, a, flat, tg, s);
       else
-        e = run_decode_g<float, 128>(c, a, flat, og, s);
+        e = run_decode_g<float, 128>(c, a, flat, tg, s);
       if (e != hipSuccess) return e;
       // ---- heads too large for one closing workgroup (their entry count can reach budget + rows
       //      appended since): the same grid finishes them in parts
       bool big = false;
       for (int i = 0; i < nl; ++i) big = big || int64_t(mc[i]) * kChunk > a.big_rows;
       if (big) {
-        e = launch_decode_split(c, a, mc, nl, og, s);
+        e = launch_decode_split(c, a, mc, nl, tg.out, s);
         if (e != hipSuccess) return e;
       }
     }

@@ -33,7 +33,7 @@ constexpr int kSub = 64;                // rows one wavefront handles at a time 
 
 struct DecodeArgs {
   int32_t* ccount;
-  int32_t* ctotal;    // [L][B][Hkv] entries of this step (count + 1): written by decode_prepare, never by decode_attend
+  int32_t* ctotal;    // [L][B][Hkv] entries (count + 1) of a head that decode_attend leaves to the split kernels, else 0
   double* ctau;
   const int32_t* meta;
   void* cK;
@@ -50,8 +50,6 @@ struct DecodeArgs {
                       // query heads, [G..2G) exp-sums relative to them, [2G..2G+kCand) the candidates' best
                       // cosine, [2G+kCand..2G+2kCand) its slot (-1 none); written with one store
   float* pacc;        // [chunk][B][Hkv][G][d] partial outputs, relative to the chunk's softmax maximum
-  double* vecs;       // [L][B][Hkv][(G + kCand) * d] queries and candidate keys as fp64, in the order of operand_index
-  double* cnorm;      // [L][B][Hkv][kCand] |k| of the candidates
   int32_t* ev_evicted;
   int32_t* ev_target;
   double* ev_ustar;
@@ -146,7 +144,7 @@ __device__ __forceinline__ int64_t elog_index(const DecodeArgs& a, int64_t bh, i
   return (((int64_t(chunk0) + (j >> 8)) * (a.B * a.Hkv) + bh) * G + g) * kChunk + (j & (kChunk - 1));
 }
 
-// Place of element c of operand vector v (queries, then candidate keys) in a head's table: the order in
+// Place of element c of operand vector v (queries, then candidate keys) in the LDS table: the order in
 // which the lanes of the K pass's matrix instructions fetch it.  A row piece of 64 bytes is four
 // parts of 16 (k = 0..3); two consecutive elements of every part and vector form a step.
 template <typename T, int NV>
@@ -193,19 +191,20 @@ __device__ __forceinline__ float4 ld_agent4(const float* p) {  // 16 bytes as tw
 }
 
 // Which entry of the call's layer list a flat chunk index belongs to (block-uniform), that entry's
-// layer and first index.  The list is sorted by size, so the workgroups dispatched last belong to the
-// smallest caches.  Unused entries of lay_off hold INT_MAX.  Every lane looks at one entry: two vector
+// layer, first index and number of chunks.  The list is sorted by size, so the workgroups dispatched last belong to the
+// smallest caches.  Unused entries of lay_off hold INT_MAX.  Every lane looks at one entry: three vector
 // loads of the kernel arguments and a count of the lanes whose entry starts at or before x.  (As
 // 63 scalar compares this was 186 vector and 300 scalar instructions per wavefront, a twelfth of
 // the vector instructions of a chunk of the fp8 cache, whose launch is bound by their issue.)
 struct LayerEntry {
-  int first, layer;
+  int first, layer, chunks;
 };
 __device__ __forceinline__ LayerEntry find_entry(const DecodeArgs& a, int x) {
   static_assert(kMaxLayersPerCall == 64, "an entry per lane");
-  const int lane = threadIdx.x & 63, off = a.lay_off[lane], id = a.lay_id[lane];
+  const int lane = threadIdx.x & 63, off = a.lay_off[lane], next = a.lay_off[lane + 1], id = a.lay_id[lane];
   const int e = __popcll(__ballot(x >= off)) - 1;  // (lay_off[0] is 0)
-  return LayerEntry{__builtin_amdgcn_readlane(off, e), __builtin_amdgcn_readlane(id, e)};
+  const int first = __builtin_amdgcn_readlane(off, e);
+  return LayerEntry{first, __builtin_amdgcn_readlane(id, e), __builtin_amdgcn_readlane(next, e) - first};
 }
 
 // (u larger, then position smaller) wins; slot < 0 means "no entry".
@@ -244,7 +243,8 @@ __device__ __forceinline__ Best fast_wave_first_evicted(const Best& b) {
   return Best{smin, pmax, __builtin_amdgcn_readlane(b.slot, src)};
 }
 // This thread's elements of the two rows a step merges, the evicted one (ke, ve) and its match (kt, vt),
-// as they were before the step; fp8 cache: with the rows' powers of two.
+// as they were before the step; fp8 cache: with the rows' powers of two.  (Agent-scope loads: either may be
+// the new token's row, written by another workgroup of the launch.)
 template <typename T>
 struct MergeRows {
   T ke, ve, kt, vt;
@@ -257,16 +257,16 @@ __device__ __forceinline__ MergeRows<T> load_merge_rows(const DecodeArgs& a, int
   if (threadIdx.x < D) {
     const T* Kc = static_cast<const T*>(a.cK) + slot0 * D + threadIdx.x;
     const T* Vc = static_cast<const T*>(a.cV) + slot0 * D + threadIdx.x;
-    r.ke = Kc[int64_t(e) * D];
-    r.ve = Vc[int64_t(e) * D];
-    r.kt = Kc[int64_t(t) * D];
-    r.vt = Vc[int64_t(t) * D];
+    r.ke = ld_agent(Kc + int64_t(e) * D);
+    r.ve = ld_agent(Vc + int64_t(e) * D);
+    r.kt = ld_agent(Kc + int64_t(t) * D);
+    r.vt = ld_agent(Vc + int64_t(t) * D);
   }
   if constexpr (sizeof(T) == 1) {
-    r.xke = a.cKe[slot0 + e];
-    r.xve = a.cVe[slot0 + e];
-    r.xkt = a.cKe[slot0 + t];
-    r.xvt = a.cVe[slot0 + t];
+    r.xke = ld_agent(a.cKe + slot0 + e);
+    r.xve = ld_agent(a.cVe + slot0 + e);
+    r.xkt = ld_agent(a.cKe + slot0 + t);
+    r.xvt = ld_agent(a.cVe + slot0 + t);
   }
   return r;
 }
@@ -306,7 +306,7 @@ __device__ __forceinline__ void finish_head(const DecodeArgs& a, int64_t lbh, in
     // its largest magnitude: a reduction over the workgroup (`red`: one double per wavefront).
     int8_t* Ke = a.cKe + slot0;
     int8_t* Ve = a.cVe + slot0;
-    int ekl = Ke[last], evl = Ve[last];  // the last row's powers of two travel with its codes
+    int ekl = ld_agent(Ke + last), evl = ld_agent(Ve + last);  // the last row's powers of two travel with its codes
     if (do_merge) {
       double km = 0.0, vm = 0.0;
       if (tid < D) {
@@ -563,6 +563,8 @@ __device__ __forceinline__ void close_head(const DecodeArgs& a, int64_t lbh, int
     // Not foreseen (the first step after a cache import, or a candidate overtaken by a token
     // outside the list): a second pass over the head's keys.
     if (tid == 0) a.cmiss[lbh] += 1u;
+    // (the new token's row and position were written by another workgroup of the launch: they are read after this)
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     m = scan_matches<T, D>(a, slot0, es, total, dred, sred);
     m = fast_wave_best_match(m.u, m.pos, m.slot);
     lds_barrier();
