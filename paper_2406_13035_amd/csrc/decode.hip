@@ -39,8 +39,8 @@
 
 namespace d2o {
 
-// Scratch memory of d2o_decode_step_static: the partial results of one generation step, for callers that cannot hand over (or allocate) a scratch workspace.  One
-// copy per GPU, held from the moment the library's code is loaded on it until the process ends.
+// Scratch memory of d2o_decode_step_static: the partial results of one generation step, for callers
+// that cannot hand over (or allocate) a scratch workspace.  One copy per GPU, held from the moment the library's code is loaded on it until the process ends.
 // In host code the array's name is only a handle: the device address comes from
 // hipGetSymbolAddress, once per device, and is what kernels and launchers are given.
 constexpr size_t kStaticScratchBytes = size_t(64) << 20;
@@ -118,7 +118,7 @@ __device__ __forceinline__ void head_normaliser(const DecodeArgs& a, int64_t bh,
     for (int g = 0; g < G; ++g) Mg[g] = fmax(Mg[g], ld_agent(&a.rec[x + g]));
   }
 #pragma unroll
-  for (int g = 0; g < G; ++g) Mg[g] = wave_max(Mg[g]);
+  for (int g = 0; g < G; ++g) Mg[g] = fast_wave_max(Mg[g]);
   __syncthreads();
   if (lane == 0) {
 #pragma unroll
@@ -137,10 +137,13 @@ __device__ __forceinline__ void head_normaliser(const DecodeArgs& a, int64_t bh,
   }
 #pragma unroll
   for (int g = 0; g < G; ++g) {
-    const double lg = block_sum(part[g], sred);
+    const double wg = fast_wave_sum(part[g]);
+    __syncthreads();
+    if (lane == 0) sred[w] = wg;
+    __syncthreads();
     if (tid == 0) {
       hn[g] = Mg[g];
-      hn[G + g] = lg;
+      hn[G + g] = ((sred[0] + sred[1]) + sred[2]) + sred[3];
     }
   }
 }
@@ -154,13 +157,15 @@ __device__ __forceinline__ void head_normaliser(const DecodeArgs& a, int64_t bh,
 // candidate's match is known.  (With each of them requested where it is used, and an exchange per
 // evicted token and candidate, a head of 80 to 1900 entries took 18000 to 24700 cycles to close;
 // issued one layer per call, 32 layers take 8 % less now, and a step of a 128-entry fp32 cache
-// 17.5 instead of 19.2 us.)
+// 17.5 instead of 19.2 us.  With two batches of the score pass in flight, the partial rows of all query heads
+// requested together and one list of lowest scores instead of two, a layer of 8 heads of 5000
+// entries takes 73 instead of 77 us, two steps of 24 layers with eight query heads per KV head 228 instead of 236.)
 template <typename T, typename OT, int D, int G>
 __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ out, const View& ov, int li, int b,
                                           int hk, int64_t lbh, int total, int nsub, double* sred, int* ired,
                                           float* fred, double* dred, unsigned char* park) {
   constexpr int kRec = rec_doubles(G);
-  constexpr int U = G >= 8 ? 1 : G >= 4 ? 2 : G >= 2 ? 4 : 6;  // slots per thread and batch of the score pass
+  constexpr int U = G >= 8 ? 1 : G >= 4 ? 2 : G >= 2 ? 4 : 6;  // slots per thread and batch of the score pass, of which two are in flight
   constexpr int C4 = D / 4;                           // threads across an output row (four columns each)
   constexpr int RG = 256 / C4;                        // groups of threads that share the sub-chunks
   // partial rows of each query head in flight per thread: four in all, or one each (eight query heads with
@@ -180,6 +185,9 @@ __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ 
   int cl[kCand];
 #pragma unroll
   for (int i = 0; i < kCand; ++i) cl[i] = a.cand[lbh * kCand + i];
+  double e_last[G];
+#pragma unroll
+  for (int g = 0; g < G; ++g) e_last[g] = ld_agent(&a.elog[elog_index(a, bh, ch0, G, g, last)]);
   // Results that are needed only at the end wait in LDS, not in registers: per wavefront and
   // candidate the best match found so far (`wcm`), and the last slot's row (two elements per thread).
   double* wcm_u = sred + 8 + 8;                            // [4][kCand], behind sred and ired
@@ -193,19 +201,22 @@ __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ 
   constexpr int kSegSubs = kEmCap / G;  // sub-chunks whose factors fit `em`
   // ---- the first batches of the output and score passes are requested now: they arrive while the
   //      normaliser is formed
-  double sc[U], e[U][G];
-  int ps[U];
-  int seg0 = 0, jend = min(total, kSegSubs * kSub);  // the segment of sub-chunks whose factors `em` holds, and its last slot + 1
-  auto load_batch = [&](int j0) {
+  double sc[2][U], e[2][U][G];
+  int ps[2][U];
+  int seg0 = 0, jend = min(last, kSegSubs * kSub);  // the segment of sub-chunks whose factors `em` holds, and its last slot + 1 (without the new token's)
+  auto load_batch = [&](auto set, int j0) {
+    constexpr int s = decltype(set)::value;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int j = min(j0 + u * 256, jend - 1);
-      sc[u] = a.cscore[slot0 + j];  // (the last slot's score and position are known without memory: see below)
-      ps[u] = a.cpos[slot0 + j];
+      const int j = min(j0 + u * 256, max(jend - 1, 0));
+      sc[s][u] = a.cscore[slot0 + j];
+      ps[s][u] = a.cpos[slot0 + j];
 #pragma unroll
-      for (int g = 0; g < G; ++g) e[u][g] = ld_agent(&a.elog[elog_index(a, bh, ch0, G, g, j)]);
+      for (int g = 0; g < G; ++g) e[s][u][g] = ld_agent(&a.elog[elog_index(a, bh, ch0, G, g, j)]);
     }
   };
+  const std::integral_constant<int, 0> set0;
+  const std::integral_constant<int, 1> set1;
   const int c4 = tid % C4, rg = tid / C4;
   const int nchunk = (nsub + 3) / 4;
   constexpr bool kEarlyRows = G <= 4;  // (eight query heads' rows would not fit the registers)
@@ -255,7 +266,7 @@ __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ 
 #pragma unroll
       for (int g = 0; g < G; ++g) load_partial(g, rg);
     }
-    load_batch(tid);
+    load_batch(set0, tid);
 #pragma unroll
     for (int g = 0; g < G; ++g) Mg[g] = fast_wave_max(Mg[g]);
     lds_barrier();
@@ -281,9 +292,9 @@ __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ 
           st_agent(&a.rec[x + g], t);  // the factor replaces the maximum (nobody needs it again)
       }
     }
-    // (block_sum's tree, all query heads in one exchange)
+    // (the tree of head_normaliser, all query heads in one exchange)
 #pragma unroll
-    for (int g = 0; g < G; ++g) part[g] = wave_sum(part[g]);
+    for (int g = 0; g < G; ++g) part[g] = fast_wave_sum(part[g]);
     if (lane == 0) {
 #pragma unroll
       for (int g = 0; g < G; ++g) dred[(4 + w) * G + g] = part[g];
@@ -330,53 +341,71 @@ __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ 
     }
   }
   const bool evict = total > mt[1];
-  const int recent = mt[2];
-  Best ev{0.0, 0, -1};
+  // Eq. 6 for the batch's slots, and the lowest scores of the tokens evictable at this step (Eq. 7-8 on count + 1
+  // entries), in eviction order: the first is evicted, the others are the next step's candidates, together
+  // with the token at position `next_out` + 1, which leaves the recent window then (`out`).
+  const int next_out = a.new_pos - mt[2];  // the last evictable position
   Best low[kCand + 1];
 #pragma unroll
   for (int i = 0; i <= kCand; ++i) low[i] = Best{0.0, 0, -1};
-  // Eq. 6 for the batch's slots, the token to evict (Eq. 7-8 on count+1 entries) and the lowest
-  // scores among the tokens evictable at the next step
-  auto apply_batch = [&](int j0) {
+  double* out_s = sred + 5;  // the score and slot of `out`
+  int* out_j = ired + 9;
+  if (tid == 0) *out_j = -1;
+  auto insert = [&](double x, int p, int j) {
+    if (evicts_before(x, p, j, low[kCand])) {
+      low[kCand] = Best{x, p, j};
+#pragma unroll
+      for (int i = kCand; i > 0; --i)
+        if (evicts_before(low[i].u, low[i].pos, low[i].slot, low[i - 1])) {
+          const Best t = low[i - 1];
+          low[i - 1] = low[i];
+          low[i] = t;
+        }
+    }
+  };
+  auto consider = [&](double x, int p, int j) {
+    if (p >= a.n_sink && p <= next_out + 1) {
+      if (p == next_out + 1) {
+        *out_s = x;
+        *out_j = j;
+      } else {
+        insert(x, p, j);
+      }
+    }
+  };
+  auto apply_batch = [&](auto set, int j0) {
+    constexpr int s = decltype(set)::value;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int j = j0 + u * 256;
       if (j < jend) {
-        double s2 = j == last ? 0.0 : sc[u];
+        double s2 = sc[s][u];
 #pragma unroll
-        for (int g = 0; g < G; ++g) s2 = fma(e[u][g], em[(j / kSub - seg0) * G + g], s2);
+        for (int g = 0; g < G; ++g) s2 = fma(e[s][u][g], em[(j / kSub - seg0) * G + g], s2);
         a.cscore[slot0 + j] = s2;
-        const int p = j == last ? a.new_pos : ps[u];
-        if (j == last) {  // kept for the move into the freed slot
-          sred[4] = s2;
-          ired[8] = p;
-        }
-        if (p >= a.n_sink && p <= a.new_pos - recent && evicts_before(s2, p, j, ev)) ev = Best{s2, p, j};
-        if (p >= a.n_sink && p <= a.new_pos + 1 - recent && evicts_before(s2, p, j, low[kCand])) {
-          low[kCand] = Best{s2, p, j};
-#pragma unroll
-          for (int i = kCand; i > 0; --i)
-            if (evicts_before(low[i].u, low[i].pos, low[i].slot, low[i - 1])) {
-              const Best t = low[i - 1];
-              low[i - 1] = low[i];
-              low[i] = t;
-            }
-        }
+        consider(s2, ps[s][u], j);
       }
-      __builtin_amdgcn_sched_barrier(0);  // one slot after the other: interleaving them costs registers
     }
   };
-  // ---- output rows: thread (rg, c4) adds the chunks rg, rg + RG, ... of four columns, PB
-  //      loads in flight; the groups' sums are added in ascending order
+  // ---- output rows: thread (rg, c4) adds the chunks rg, rg + RG, ... of four columns, PB of every query
+  //      head in flight; the groups' sums are added in ascending order
   const MergeRows<T> mr = [&]() {
     lds_barrier();  // the wavefronts' matches are in LDS
     return load_merge_rows<T, D>(a, slot0, cl[0], candidate_match(wcm_u, wcm_ps, 0).slot);
   }();
+  float num[G][4];
 #pragma unroll
-  for (int g = 0; g < G; ++g) {
-    float num[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int c0 = rg; c0 < nchunk; c0 += PB * RG) {
-      if (!kEarlyRows || c0 != rg) load_partial(g, c0);
+  for (int g = 0; g < G; ++g)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) num[g][e] = 0.f;
+#pragma unroll 1
+  for (int c0 = rg; c0 < nchunk; c0 += PB * RG) {
+    if (!kEarlyRows || c0 != rg) {
+#pragma unroll
+      for (int g = 0; g < G; ++g) load_partial(g, c0);
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
       const float4(&v)[PB] = pr[g];
       double fc[PB];
 #pragma unroll
@@ -392,15 +421,18 @@ __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ 
 #pragma unroll
       for (int u = 0; u < PB; ++u) {
         const float f = c0 + u * RG < nchunk ? float(fc[u]) : 0.f;
-        num[0] = fmaf(v[u].x, f, num[0]);
-        num[1] = fmaf(v[u].y, f, num[1]);
-        num[2] = fmaf(v[u].z, f, num[2]);
-        num[3] = fmaf(v[u].w, f, num[3]);
+        num[g][0] = fmaf(v[u].x, f, num[g][0]);
+        num[g][1] = fmaf(v[u].y, f, num[g][1]);
+        num[g][2] = fmaf(v[u].z, f, num[g][2]);
+        num[g][3] = fmaf(v[u].w, f, num[g][3]);
       }
     }
+  }
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
     lds_barrier();
 #pragma unroll
-    for (int e = 0; e < 4; ++e) fred[e * 256 + tid] = num[e];
+    for (int e = 0; e < 4; ++e) fred[e * 256 + tid] = num[g][e];
     lds_barrier();
     if (tid < D) {  // column tid: element tid % 4 of the threads (rg, tid / 4)
       const float* fr = fred + (tid % 4) * 256 + tid / 4;
@@ -411,11 +443,11 @@ __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ 
     }
     __builtin_amdgcn_sched_barrier(0);  // one query head after the other (registers)
   }
-  // ---- score pass: batches of U slots per thread, their loads in flight together
+  // ---- score pass: batches of U slots per thread, the next one's loads in flight while one is worked on
 #pragma unroll 1
   for (seg0 = 0; seg0 < nsub; seg0 += kSegSubs) {
     const int nseg = min(kSegSubs, nsub - seg0);
-    jend = min(total, (seg0 + nseg) * kSub);
+    jend = min(last, (seg0 + nseg) * kSub);
     if (!em_lds) {  // a head of several segments: (re)fill the table for this one
       lds_barrier();
 #pragma unroll 1
@@ -427,12 +459,29 @@ __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ 
       }
       lds_barrier();
     }
+    const int j_lo = seg0 * kSub;
+    if (seg0 > 0) load_batch(set0, j_lo + tid);
 #pragma unroll 1
-    for (int j0 = seg0 * kSub + tid; j0 < jend; j0 += U * 256) {
-      if (j0 != tid) load_batch(j0);
-      apply_batch(j0);
+    for (int jb = j_lo; jb < jend; jb += 2 * U * 256) {
+      if (jb + U * 256 < jend) load_batch(set1, jb + U * 256 + tid);
+      apply_batch(set0, jb + tid);
+      if (jb + U * 256 >= jend) break;
+      if (jb + 2 * U * 256 < jend) load_batch(set0, jb + 2 * U * 256 + tid);
+      apply_batch(set1, jb + U * 256 + tid);
+    }
+    if (tid == 0 && seg0 + nseg == nsub) {  // the new token: its score starts from its own probability
+      double s2 = 0.0;
+#pragma unroll
+      for (int g = 0; g < G; ++g) s2 = fma(e_last[g], em[(last / kSub - seg0) * G + g], s2);
+      a.cscore[slot0 + last] = s2;
+      sred[4] = s2;  // kept for the move into the freed slot
+      ired[8] = a.new_pos;
+      consider(s2, a.new_pos, last);
     }
   }
+  lds_barrier();
+  const Best ev = low[0];
+  if (tid == 0 && *out_j >= 0) insert(*out_s, next_out + 1, *out_j);
   close_head<T, D>(a, lbh, slot0, total, evict, ev, low, cl, told, sred, ired, dred, wcm_u, wcm_ps, park_kv, mr);
 }
 
@@ -1002,7 +1051,7 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
   float* fred = reinterpret_cast<float*>(stage);
   double* dred = reinterpret_cast<double*>(stage + 4 * 256 * sizeof(float));
   double* sred = dred + D;
-  int* ired = reinterpret_cast<int*>(sred + 8);
+  int* ired = reinterpret_cast<int*>(sred + 8);  // 16 words
   if (tid == 0) a.ctotal[lbh] = total > a.big_rows ? total : 0;
   if (total > a.big_rows) {
     // A very large head: two more launches close it (decode_close_part / _final).  All its

@@ -125,12 +125,32 @@ __device__ __forceinline__ double lane_f64(double v, int lane) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
                           __builtin_amdgcn_readlane(__double2loint(v), lane));
 }
+// The maximum as the instruction itself: fmax would first re-canonicalise values that were moved
+// between lanes as bits (twice the instructions).  A NaN operand loses, as with fmax.
+__device__ __forceinline__ double max_f64(double a, double b) {
+  double r;
+  asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+// Maximum over each row of 16 lanes; every lane of the row gets it.
+__device__ __forceinline__ double row16_max(double v) {
+  v = max_f64(v, dpp_f64<kDppXor1>(v));
+  v = max_f64(v, dpp_f64<kDppXor2>(v));
+  v = max_f64(v, dpp_f64<kDppHalfMirror>(v));
+  return max_f64(v, dpp_f64<kDppMirror>(v));
+}
+// One lane's value to the next rows (0x142: lane 15 of a row to the row after it, 0x143: lane 31 to the upper
+// half); lanes that receive nothing keep their own.
+template <int CTRL>
+__device__ __forceinline__ double row_bcast_f64(double v) {
+  const int lo = __double2loint(v), hi = __double2hiint(v);
+  return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xF, 0xF, false),
+                          __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xF, 0xF, false));
+}
 __device__ __forceinline__ double fast_wave_max(double v) {
-  v = fmax(v, dpp_f64<kDppXor1>(v));
-  v = fmax(v, dpp_f64<kDppXor2>(v));
-  v = fmax(v, dpp_f64<kDppHalfMirror>(v));
-  v = fmax(v, dpp_f64<kDppMirror>(v));
-  return fmax(fmax(lane_f64(v, 0), lane_f64(v, 16)), fmax(lane_f64(v, 32), lane_f64(v, 48)));
+  v = row16_max(v);
+  v = max_f64(v, row_bcast_f64<0x142>(v));
+  return lane_f64(max_f64(v, row_bcast_f64<0x143>(v)), 63);
 }
 __device__ __forceinline__ double fast_wave_sum(double v) {
   v += dpp_f64<kDppXor1>(v);
