@@ -105,6 +105,7 @@ void layout(d2o_ctx* x, char* persistent, char* scratch, size_t* pbytes, size_t*
   s.take(x->amb_cnt, bh);
   s.take(x->m_ncand, bh * np);
   s.take(x->m_clist, bh * np * 8);
+  x->colpart = reinterpret_cast<float*>(x->m_clist);  // (G <= 8)
   s.take(x->m_ustar, bh * np);
   s.take(x->m_tgt, bh * np);
   s.take(x->m_pass, bh * np);

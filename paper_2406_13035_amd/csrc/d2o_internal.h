@@ -15,8 +15,7 @@ constexpr int kPartRecDoubles = 32;  // doubles of a part record of the split cl
 constexpr int kMaxQuerySlices = 16;  // block append: workgroups that share the queries of a (head, chunk)
 constexpr int kMinAutoSplitRows = 6144, kMaxAutoSplitRows = 16384;  // bounds of the automatic split_rows (below the lower one the two extra launches cost more than a single closing workgroup)
 constexpr int kChunk = 256;        // cache slots handled by one workgroup in the decode kernels
-constexpr int kColBN = 256;        // keys per workgroup, column-sum pass (bf16)
-constexpr int kF32BN = 32;         // the same, fp32
+constexpr int kF32BN = 32;         // keys per workgroup, column-sum pass (fp32)
 constexpr int kVmaxShares = 64;    // workgroups per head that look for the largest value of V (bf16)
 
 // A strided [b][head][token][d] (or [layer][b][head][d]) tensor, strides in elements.
@@ -108,6 +107,7 @@ struct d2o_ctx {
   int32_t* amb_cnt = nullptr;    // [B][Hkv]
   int32_t* m_ncand = nullptr;    // candidates collected for a flagged row
   int32_t* m_clist = nullptr;    // [..][npad][8] their retained ranks
+  float* colpart = nullptr;      // [B][Hq][npad] column sums per query head (bf16, G > 1): the memory of m_clist, which no attention call needs
   double* m_ustar = nullptr;     // exact best similarity per evicted row
   int32_t* m_tgt = nullptr;      // exact match (retained rank)
   uint8_t* m_pass = nullptr;     // threshold test

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace d2o {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
@@ -175,6 +177,15 @@ __device__ __forceinline__ double row16_sum(double v) {
   v += dpp_f64<kDppXor2>(v);
   v += dpp_f64<kDppHalfMirror>(v);
   v += dpp_f64<kDppMirror>(v);
+  return v;
+}
+
+__device__ __forceinline__ float row16_sum(float v) {
+  auto moved = [](auto ctrl, float x) { return __int_as_float(dpp_i32<decltype(ctrl)::value>(__float_as_int(x))); };
+  v += moved(std::integral_constant<int, kDppXor1>{}, v);
+  v += moved(std::integral_constant<int, kDppXor2>{}, v);
+  v += moved(std::integral_constant<int, kDppHalfMirror>{}, v);
+  v += moved(std::integral_constant<int, kDppMirror>{}, v);
   return v;
 }
 

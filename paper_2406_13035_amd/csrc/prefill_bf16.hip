@@ -438,64 +438,62 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
   }
 }
 
-// 256 keys per workgroup (8 wavefronts x 32 keys, the stationary A operand).  Query tiles of
-// 64 rows are double-buffered in LDS and visited from the END of the prompt downwards: every
+// A workgroup owns BN = 32 KW keys (KW wavefronts x 32 keys, the stationary A operand) of one query head and streams query tiles of TQ rows through LDS, double-buffered; QW groups of such wavefronts share
+// a tile's 32-row sub-tiles.  Tiles are visited from the END of the prompt downwards: every
 // workgroup of a head then reads the same query tiles at about the same time (all start at
 // the last tile), so the tiles are served from L2 instead of HBM.  The tiles pass through registers
 // on their way to LDS: loaded straight into it, which gains the attention kernel 3 %, this one
-// takes 4 % (32768 tokens) to 13 % longer.
-constexpr int kColNW = 8;
-__global__ __launch_bounds__(64 * kColNW) __attribute__((amdgpu_waves_per_eu(4, 4))) void colsum_bf16(const uint16_t* __restrict__ Q, View qv,
+// takes 4 % (32768 tokens) to 13 % longer.  (64 keys per wavefront, every LDS operand feeding two products, with two
+// wavefronts per SIMD: 4.85 instead of 4.61 ms at 32768 tokens.)  Query heads that share a KV head are
+// workgroups of their own: one after the other in one workgroup, 8 KV heads of 2048 tokens
+// with four query heads each were 32 workgroups and 209 us instead of 43.
+template <int KW, int QW, int TQ>
+__global__ __launch_bounds__(64 * KW * QW) __attribute__((amdgpu_waves_per_eu(4, 4))) void colsum_bf16(const uint16_t* __restrict__ Q, View qv,
                                                            const uint16_t* __restrict__ K, View kv,
-                                                           const float* __restrict__ lse2, float* __restrict__ score,
+                                                           const float* __restrict__ lse2, float* __restrict__ colsum,
                                                            double* __restrict__ varpart, int n, int npad, int G,
-                                                           int Hq, int nblk) {
-  __shared__ __attribute__((aligned(16))) uint16_t Qs[2][64 * kLdQ];
-  __shared__ float ls[2][64];
-  __shared__ float cs[kColBN];
-  __shared__ double red[kColNW];
-  constexpr int NT = 64 * kColNW;
-  constexpr int NCH = 1024 / NT;
-  const int Hkv = gridDim.y;
-  int bx = blockIdx.x, hz = blockIdx.y + Hkv * blockIdx.z;
-  xcd_remap(gridDim.x, Hkv * gridDim.z, bx, hz);
-  const int hk = hz % Hkv, b = hz / Hkv;
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, m = lane & 31, h = lane >> 5;
+                                                           int nblk) {
+  constexpr int NW = KW * QW, NT = 64 * NW, BN = 32 * KW, NCH = TQ * 16 / NT;
+  static_assert(BN <= NT && BN % 128 == 0 && TQ % (32 * QW) == 0 && BN % TQ == 0, "a thread per key, whole sub-tiles per wavefront");
+  __shared__ __attribute__((aligned(16))) uint16_t Qs[2][TQ * kLdQ];
+  __shared__ float ls[2][TQ];
+  __shared__ float cs[QW][BN];
+  __shared__ double red[NW][2];
+  const int Hq = gridDim.y;
+  int bx = blockIdx.x, hz = blockIdx.y + Hq * blockIdx.z;
+  xcd_remap(gridDim.x, Hq * gridDim.z, bx, hz);
+  const int hq = hz % Hq, b = hz / Hq, hk = hq / G;
+  const int tid = threadIdx.x, w = tid >> 6, kw = w % KW, qw = w / KW, lane = tid & 63, m = lane & 31, h = lane >> 5;
   const float scale2 = kLog2e / sqrtf(float(kD));
+  const uint16_t* qb = Q + b * qv.sb + hq * qv.sh;
+  const float* lrow = lse2 + (int64_t(b) * Hq + hq) * npad;
   // The work of a key block grows with the number of queries behind it (causal), from one
   // query tile for the last block to all of them for the first.  A workgroup takes block x and
   // then block nblk - 1 - x: every workgroup then has the same amount of work and the launch
   // fills the chip in whole rounds (with one block per workgroup the CUs held 1.3 of 2 possible
   // workgroups on average, and the longest workgroup alone was a fifth of the kernel time).
   for (int pass = 0; pass < 2; ++pass) {
-  const int tile = pass == 0 ? bx : nblk - 1 - bx;
-  if (pass == 1 && tile <= bx) break;
-  const int kb0 = tile * kColBN, kw0 = kb0 + w * 32;  // first key of the workgroup / wavefront
-
-  const uint16_t* kp = K + b * kv.sb + hk * kv.sh + int64_t(min(kw0 + m, n - 1)) * kv.sn;
-  bf16x8 ak[8];
+    const int tile = pass == 0 ? bx : nblk - 1 - bx;
+    if (pass == 1 && tile <= bx) break;
+    const int kb0 = tile * BN, kw0 = kb0 + kw * 32;  // first key of the workgroup / wavefront
+    const uint16_t* kp = K + b * kv.sb + hk * kv.sh + int64_t(min(kw0 + m, n - 1)) * kv.sn;
+    bf16x8 ak[8];
 #pragma unroll
-  for (int ks = 0; ks < 8; ++ks) ak[ks] = *reinterpret_cast<const bf16x8*>(kp + ks * 16 + h * 8);
-
-  const int nqt = (n - kb0 + 63) / 64;  // query tiles [kb0 + 64 j, kb0 + 64 j + 64), visited j descending
-  float total = 0.f;                    // thread t < 256 owns key kb0 + t
-  for (int g = 0; g < G; ++g) {
-    const int hq = hk * G + g;
-    const uint16_t* qb = Q + b * qv.sb + hq * qv.sh;
-    const float* lrow = lse2 + (int64_t(b) * Hq + hq) * npad;
+    for (int ks = 0; ks < 8; ++ks) ak[ks] = *reinterpret_cast<const bf16x8*>(kp + ks * 16 + h * 8);
+    const int nqt = (n - kb0 + TQ - 1) / TQ;  // query tiles [kb0 + TQ j, kb0 + TQ j + TQ), visited j descending
     float acc[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.f;
     u32x4 qr[NCH];
     float lr = 0.f;
     auto issue = [&](int j) {
-      const int q0 = kb0 + 64 * j;
+      const int q0 = kb0 + TQ * j;
 #pragma unroll
       for (int i = 0; i < NCH; ++i) {
         const int c = tid + NT * i, row = c >> 4, col = (c & 15) * 8;
         qr[i] = *reinterpret_cast<const u32x4*>(qb + int64_t(min(q0 + row, n - 1)) * qv.sn + col);
       }
-      if (tid < 64) lr = (q0 + tid < n) ? lrow[q0 + tid] : INFINITY;  // +inf => p = 0
+      if (tid < TQ) lr = (q0 + tid < n) ? lrow[q0 + tid] : INFINITY;  // +inf => p = 0
     };
     auto stage = [&](int buf) {
 #pragma unroll
@@ -503,22 +501,21 @@ __global__ __launch_bounds__(64 * kColNW) __attribute__((amdgpu_waves_per_eu(4, 
         const int c = tid + NT * i, row = c >> 4, col = (c & 15) * 8;
         *reinterpret_cast<u32x4*>(&Qs[buf][row * kLdQ + col]) = qr[i];
       }
-      if (tid < 64) ls[buf][tid] = lr;
+      if (tid < TQ) ls[buf][tid] = lr;
     };
-    __syncthreads();  // previous head's readers are done with both buffers
+    __syncthreads();  // the previous block's readers are done with both buffers
     issue(nqt - 1);
     stage(0);
     __syncthreads();
     for (int it = 0; it < nqt; ++it) {
-      const int j = nqt - 1 - it, buf = it & 1, q0 = kb0 + 64 * j;
-      if (j > 0) issue(j - 1);
+      const int jt = nqt - 1 - it, buf = it & 1, q0 = kb0 + TQ * jt;
+      if (jt > 0) issue(jt - 1);
 #pragma unroll
-      for (int qt = 0; qt < 2; ++qt) {
-        const int qbase = q0 + qt * 32;
+      for (int qi = 0; qi < TQ / 32 / QW; ++qi) {
+        const int qt = qi * QW + qw, qbase = q0 + qt * 32;
         if (qbase + 31 < kw0) continue;  // every query precedes every key of this wavefront
-        f32x16 sacc;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sacc[r] = 0.f;
+        const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        f32x16 sacc = zero;
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) {
           const bf16x8 bqv = *reinterpret_cast<const bf16x8*>(&Qs[buf][(qt * 32 + m) * kLdQ + ks * 16 + h * 8]);
@@ -539,45 +536,49 @@ __global__ __launch_bounds__(64 * kColNW) __attribute__((amdgpu_waves_per_eu(4, 
           for (int r = 0; r < 16; ++r) acc[r] += __builtin_amdgcn_exp2f(fmaf(sacc[r], scale2, -lq));
         }
       }
-      if (j > 0) stage(buf ^ 1);
+      if (jt > 0) stage(buf ^ 1);
       __syncthreads();
     }
-    // add the 32 query columns held by the lanes of each half
+    // add the 32 query columns held by the lanes of each half, then the groups that shared the tiles
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      float v = acc[r];
-#pragma unroll
-      for (int o = 16; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-      acc[r] = v;
-    }
-    if (m == 0) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) cs[w * 32 + (r >> 2) * 8 + h * 4 + (r & 3)] = acc[r];
+      float v = row16_sum(acc[r]);
+      v += __shfl_xor(v, 16, 64);
+      if (m == 0) cs[qw][kw * 32 + (r >> 2) * 8 + h * 4 + (r & 3)] = v;
     }
     __syncthreads();
     double c1 = 0.0, c2 = 0.0;
-    if (tid < kColBN && kb0 + tid < n) {
-      const float c = cs[tid];
-      total += c;
+    if (tid < BN && kb0 + tid < n) {
+      float c = cs[0][tid];
+#pragma unroll
+      for (int i = 1; i < QW; ++i) c += cs[i][tid];
+      colsum[(int64_t(b) * Hq + hq) * npad + kb0 + tid] = c;
       c1 = double(c);
       c2 = double(c) * double(c);
     }
-    // partial sums per 128-key block (the unit the density reduction adds up)
-    const bool lo = tid < 128;
-    const double s1a = block_sum(lo ? c1 : 0.0, red), s2a = block_sum(lo ? c2 : 0.0, red);
-    const double s1b = block_sum(lo ? 0.0 : c1, red), s2b = block_sum(lo ? 0.0 : c2, red);
-    if (tid == 0) {
-      double* vp = varpart + ((int64_t(b) * Hq + hq) * (npad / 128) + tile * 2) * 2;
-      vp[0] = s1a;
-      vp[1] = s2a;
-      if (kb0 + 128 < npad) {
-        vp[2] = s1b;
-        vp[3] = s2b;
-      }
+    // partial sums per 128-key block (the unit the density reduction adds up): two wavefronts' keys each
+    c1 = fast_wave_sum(c1);
+    c2 = fast_wave_sum(c2);
+    if (lane == 0) {
+      red[w][0] = c1;
+      red[w][1] = c2;
+    }
+    __syncthreads();
+    if (tid < BN / 128 && kb0 + 128 * tid < npad) {
+      double* vp = varpart + ((int64_t(b) * Hq + hq) * (npad / 128) + tile * (BN / 128) + tid) * 2;
+      vp[0] = red[2 * tid][0] + red[2 * tid + 1][0];
+      vp[1] = red[2 * tid][1] + red[2 * tid + 1][1];
     }
   }
-  if (tid < kColBN && kb0 + tid < n) score[(int64_t(b) * Hkv + hk) * npad + kb0 + tid] = total;
-  }
+}
+
+template <int KW, int QW, int TQ>
+void run_colsum(d2o_ctx* c, View Q, View K, float* colsum, int n, hipStream_t s) {
+  const d2o_config& cf = c->cfg;
+  const int nblk = (n + 32 * KW - 1) / (32 * KW);
+  colsum_bf16<KW, QW, TQ><<<dim3((nblk + 1) / 2, cf.n_q_heads, cf.batch), 64 * KW * QW, 0, s>>>(
+      (const uint16_t*)Q.ptr, Q, (const uint16_t*)K.ptr, K, c->lse, colsum, c->varpart, n, c->npad, cf.n_q_heads / cf.n_kv_heads,
+      nblk);
 }
 
 }  // namespace
@@ -587,7 +588,6 @@ hipError_t launch_prefill_bf16(d2o_ctx* c, int layer, View Q, View K, View V, Vi
   const int G = cf.n_q_heads / cf.n_kv_heads;
   float* score = c->score_pre + size_t(layer) * cf.batch * cf.n_kv_heads * c->npad;
   const int nblk = (n + kAttnBM - 1) / kAttnBM;
-  const int nblk_col = (n + kColBN - 1) / kColBN;
   {  // the attribute is per device; setting it is a cheap host-side call, so it is not cached
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_fwd_bf16<kAttnRW, kAttnNW>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, kAttnSmemBytes);
@@ -604,9 +604,16 @@ hipError_t launch_prefill_bf16(d2o_ctx* c, int layer, View Q, View K, View V, Vi
       c->npad, G, cf.out_f32, nblk);
   }
   KernelTimer kt(c, D2O_K_COLSUM, s);
-  colsum_bf16<<<dim3((nblk_col + 1) / 2, cf.n_kv_heads, cf.batch), 64 * kColNW, 0, s>>>(
-      (const uint16_t*)Q.ptr, Q, (const uint16_t*)K.ptr, K, c->lse, score, c->varpart, n, c->npad, G, cf.n_q_heads,
-      nblk_col);
+  // with several query heads per KV head the column sums of each go to c->colpart; launch_density adds them up
+  float* colsum = G == 1 ? score : c->colpart;
+  // 256 keys per workgroup, eight wavefronts, where such workgroups fill the chip (two fit a CU); below, half as
+  // many keys, the eight wavefronts sharing them and the tile's queries.  (32 heads: 1000 tokens 29 instead
+  // of 41 us, 2048 tokens 43 / 61, 16384 tokens and 8 heads 377 / 386, 4096 tokens 118 both, 8192
+  // tokens 374 / 325.)
+  if (int64_t((n + 511) / 512) * cf.n_q_heads * cf.batch < 512)
+    run_colsum<4, 2, 64>(c, Q, K, colsum, n, s);
+  else
+    run_colsum<8, 1, 64>(c, Q, K, colsum, n, s);
   return hipGetLastError();
 }
 

@@ -13,6 +13,8 @@
 // against keys 4q .. 4q+3.  The contraction runs over d in an order of its own (part q of a row
 // is its q-th quarter, taken element by element), so that every lane reads contiguous memory,
 // and operands come straight from memory: the matrices of these sizes live in L2.
+#include <algorithm>
+
 #include "d2o_internal.h"
 #include "device_utils.h"
 
@@ -278,10 +280,29 @@ __global__ __launch_bounds__(64 * kColWaves) void colsum_f32(const float* __rest
 // partial sums of its blocks of bn keys, and their mean over heads.  One wavefront per head, the
 // blocks over its lanes: as one thread per head adding them up one by one this took 5 to 130 us
 // (4096 to 131072 tokens) of nothing but memory latency.
+// The workgroups behind the first one of a sequence (y > 0; bf16 with G > 1 query heads per KV head) add the query
+// heads' column sums up to the KV heads' scores, in ascending head order.
 __global__ __launch_bounds__(1024) void density_kernel(const double* __restrict__ varpart, double* __restrict__ head_var,
-                               double* __restrict__ layer_F, int n, int npad, int Hq, int bn) {
+                               double* __restrict__ layer_F, const float* __restrict__ colpart, float* __restrict__ score,
+                               int n, int npad, int Hq, int G, int bn) {
   __shared__ double hv[256];
   const int b = blockIdx.x, lane = threadIdx.x & 63;
+  if (blockIdx.y > 0) {
+    const int Hkv = Hq / G;
+    const int64_t nv = int64_t(Hkv) * (npad / 4), step = int64_t(gridDim.y - 1) * 1024;  // npad is a multiple of 128
+    for (int64_t x = int64_t(blockIdx.y - 1) * 1024 + threadIdx.x; x < nv; x += step) {
+      const int hk = int(x / (npad / 4)), k = int(x % (npad / 4)) * 4;
+      if (k >= n) continue;
+      const float* cp = colpart + (int64_t(b) * Hq + hk * G) * npad + k;
+      f32x4 t = {0.f, 0.f, 0.f, 0.f};
+      for (int g = 0; g < G; ++g) t += *reinterpret_cast<const f32x4*>(cp + int64_t(g) * npad);
+      float* out = score + (int64_t(b) * Hkv + hk) * npad + k;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (k + i < n) out[i] = t[i];
+    }
+    return;
+  }
   const int nblk = (n + bn - 1) / bn;
   for (int hq = threadIdx.x >> 6; hq < Hq; hq += 16) {
     const double* vp = varpart + (int64_t(b) * Hq + hq) * (npad / bn) * 2;
@@ -334,9 +355,13 @@ hipError_t launch_prefill_f32(d2o_ctx* c, int layer, View Q, View K, View V, Vie
 
 hipError_t launch_density(d2o_ctx* c, int layer, int n, hipStream_t s) {
   const d2o_config& cf = c->cfg;
-  density_kernel<<<cf.batch, 1024, 0, s>>>(c->varpart, c->head_var + size_t(layer) * cf.batch * cf.n_q_heads,
-                                          c->layer_F + size_t(layer) * cf.batch, n, c->npad, cf.n_q_heads,
-                                          cf.dtype == D2O_F32 ? kF32BN : 128);
+  const int G = cf.n_q_heads / cf.n_kv_heads;
+  const bool add = cf.dtype == D2O_BF16 && G > 1;
+  const int adders = add ? int(std::min<int64_t>(64, (int64_t(cf.n_kv_heads) * (c->npad / 4) + 1023) / 1024)) : 0;
+  density_kernel<<<dim3(cf.batch, 1 + adders), 1024, 0, s>>>(
+      c->varpart, c->head_var + size_t(layer) * cf.batch * cf.n_q_heads, c->layer_F + size_t(layer) * cf.batch, c->colpart,
+      c->score_pre + size_t(layer) * cf.batch * cf.n_kv_heads * c->npad, n, c->npad, cf.n_q_heads, G,
+      cf.dtype == D2O_F32 ? kF32BN : 128);
   return hipGetLastError();
 }
 
