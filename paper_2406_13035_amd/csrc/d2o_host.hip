@@ -217,13 +217,6 @@ __global__ void fill_many(Fills f) {
   for (size_t i = size_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += size_t(gridDim.x) * blockDim.x) p[i] = v;
 }
 
-// The per-sequence geometry of one layer travels to the device as kernel arguments (up to
-// kMetaPerLaunch heads per launch): no host buffer has to outlive the call, so the caller's
-// stream is neither synchronised nor fed from pageable memory.
-constexpr int kMetaPerLaunch = 64;
-struct MetaPack {
-  int32_t v[kMetaPerLaunch * 4];
-};
 // `stage`, when given, is the copy for the staging rows of an fp8 cache: a head's start at row 0.
 __global__ void write_meta_kernel(int32_t* dst, int32_t* stage, MetaPack m, int n_words) {
   const int i = threadIdx.x;
@@ -234,19 +227,23 @@ __global__ void write_meta_kernel(int32_t* dst, int32_t* stage, MetaPack m, int 
 
 }  // namespace
 
+MetaPack pack_meta(const d2o_ctx* x, int layer, int b0, int nb) {
+  MetaPack m{};
+  for (int i = 0; i < nb; ++i) {
+    const LayerMeta& t = x->layers[layer].meta[b0 + i];
+    m.v[4 * i + 0] = t.base;
+    m.v[4 * i + 1] = t.budget;
+    m.v[4 * i + 2] = t.recent;
+    m.v[4 * i + 3] = t.chunk_base;
+  }
+  return m;
+}
+
 hipError_t launch_write_meta(d2o_ctx* x, int layer, hipStream_t s) {
-  const LayerState& st = x->layers[layer];
   const int B = x->cfg.batch * x->cfg.n_kv_heads;  // one entry per (sequence, KV head)
   for (int b0 = 0; b0 < B; b0 += kMetaPerLaunch) {
     const int nb = std::min(kMetaPerLaunch, B - b0);
-    MetaPack m;
-    for (int i = 0; i < nb; ++i) {
-      const LayerMeta& t = st.meta[b0 + i];
-      m.v[4 * i + 0] = t.base;
-      m.v[4 * i + 1] = t.budget;
-      m.v[4 * i + 2] = t.recent;
-      m.v[4 * i + 3] = t.chunk_base;
-    }
+    const MetaPack m = pack_meta(x, layer, b0, nb);
     const size_t off = (size_t(layer) * B + b0) * 4;
     write_meta_kernel<<<1, kMetaPerLaunch * 4, 0, s>>>(x->meta + off, x->cfg.cache_fp8 ? x->meta_stage + off : nullptr, m, nb * 4);
     const hipError_t e = hipGetLastError();
@@ -555,14 +552,13 @@ static int compress_layer_impl(d2o_ctx* x, int32_t layer, d2o_view K, d2o_view V
   if (rc) return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e;
-  if ((e = launch_write_meta(x, layer, s)) != hipSuccess) return fail(x, D2O_ERR_HIP, std::string("meta: ") + hipGetErrorString(e));
+  if (c.batch * c.n_kv_heads > kMetaPerLaunch && (e = launch_write_meta(x, layer, s)) != hipSuccess) return fail(x, D2O_ERR_HIP, std::string("meta: ") + hipGetErrorString(e));
   if ((e = launch_select(x, layer, n, s)) != hipSuccess) return fail(x, D2O_ERR_HIP, std::string("select: ") + hipGetErrorString(e));
   if ((e = launch_gather(x, layer, to_view(K), to_view(V), n, s)) != hipSuccess) return fail(x, D2O_ERR_HIP, std::string("gather: ") + hipGetErrorString(e));
   if ((e = launch_match(x, layer, to_view(K), n, s)) != hipSuccess) return fail(x, D2O_ERR_HIP, std::string("match: ") + hipGetErrorString(e));
-  if ((e = launch_threshold_group(x, layer, n, s)) != hipSuccess) return fail(x, D2O_ERR_HIP, std::string("threshold: ") + hipGetErrorString(e));
+  if ((e = launch_threshold_group(x, layer, n, st.next_pos, s)) != hipSuccess) return fail(x, D2O_ERR_HIP, std::string("threshold: ") + hipGetErrorString(e));
   if ((e = launch_merge(x, layer, to_view(K), to_view(V), n, s)) != hipSuccess) return fail(x, D2O_ERR_HIP, std::string("merge: ") + hipGetErrorString(e));
   if (c.cache_fp8 && (e = launch_encode_layer(x, layer, s)) != hipSuccess) return fail(x, D2O_ERR_HIP, std::string("encode: ") + hipGetErrorString(e));
-  if ((e = launch_init_candidates(x, layer, st.next_pos, s)) != hipSuccess) return fail(x, D2O_ERR_HIP, std::string("candidates: ") + hipGetErrorString(e));
   // (a failed launch leaves the layer's slots reserved but the layer not ready: d2o_reset recovers)
   st.phase = kReady;
   x->last_compress_layer = layer;
@@ -676,10 +672,9 @@ int d2o_append_chunk(d2o_ctx* x, int32_t layer, d2o_view Q, d2o_view K, d2o_view
   if ((e = launch_select(x, layer, n_eff, s, true)) != hipSuccess) return fail(x, D2O_ERR_HIP, std::string("append, select: ") + hipGetErrorString(e));
   if ((e = launch_gather(x, layer, aK, aV, n_eff, s, true)) != hipSuccess) return fail(x, D2O_ERR_HIP, std::string("append, gather: ") + hipGetErrorString(e));
   if ((e = launch_match(x, layer, aK, n_eff, s)) != hipSuccess) return fail(x, D2O_ERR_HIP, std::string("append, match: ") + hipGetErrorString(e));
-  if ((e = launch_threshold_group(x, layer, n_eff, s, true)) != hipSuccess) return fail(x, D2O_ERR_HIP, std::string("append, threshold: ") + hipGetErrorString(e));
+  if ((e = launch_threshold_group(x, layer, n_eff, st.next_pos, s, true)) != hipSuccess) return fail(x, D2O_ERR_HIP, std::string("append, threshold: ") + hipGetErrorString(e));
   if ((e = launch_merge(x, layer, aK, aV, n_eff, s)) != hipSuccess) return fail(x, D2O_ERR_HIP, std::string("append, merge: ") + hipGetErrorString(e));
   if (c.cache_fp8 && (e = launch_encode_layer(x, layer, s)) != hipSuccess) return fail(x, D2O_ERR_HIP, std::string("append, encode: ") + hipGetErrorString(e));
-  if ((e = launch_init_candidates(x, layer, st.next_pos, s)) != hipSuccess) return fail(x, D2O_ERR_HIP, std::string("append, candidates: ") + hipGetErrorString(e));
   x->last_append_layer = layer;
   x->last_compress_layer = -1;  // the prompt-phase events shared the scratch lists and are gone
   return D2O_OK;

@@ -34,6 +34,13 @@ struct LayerMeta {
   int32_t chunk_base;  // first chunk index of this layer in the decode partial buffers
 };
 
+// The geometry of up to kMetaPerLaunch heads of a layer as kernel arguments, [head][4] as in LayerMeta: no host
+// buffer has to outlive the call, so the caller's stream is neither synchronised nor fed from pageable memory.
+constexpr int kMetaPerLaunch = 64;
+struct MetaPack {
+  int32_t v[kMetaPerLaunch * 4];
+};
+
 enum LayerPhase { kEmpty = 0, kAttended = 1, kReady = 2 };
 
 struct LayerState {
@@ -182,10 +189,12 @@ hipError_t launch_prefill_bf16(d2o_ctx* c, int layer, View Q, View K, View V, Vi
 hipError_t launch_density(d2o_ctx* c, int layer, int n, hipStream_t s);
 // append = true: the stages run on the position-ordered copy of the cache (app_*): fp64 scores,
 // per-head entry counts, positions through app_pos, EMA form of the threshold
+// (a prompt layer of up to kMetaPerLaunch heads: launch_select also writes the layer's host meta to the device)
 hipError_t launch_select(d2o_ctx* c, int layer, int n, hipStream_t s, bool append = false);
 hipError_t launch_gather(d2o_ctx* c, int layer, View K, View V, int n, hipStream_t s, bool append = false);
 hipError_t launch_match(d2o_ctx* c, int layer, View K, int n, hipStream_t s);
-hipError_t launch_threshold_group(d2o_ctx* c, int layer, int n, hipStream_t s, bool append = false);
+// also chooses the eviction candidates of the layer's next generation step, the token at new_pos
+hipError_t launch_threshold_group(d2o_ctx* c, int layer, int n, int new_pos, hipStream_t s, bool append = false);
 hipError_t launch_cache_sort(d2o_ctx* c, int layer, hipStream_t s);  // cache -> app_* in ascending position
 // A block of m tokens: rows appended, attention and Eq. 6 for every token of the block, nothing evicted.
 hipError_t launch_block_attend(d2o_ctx* c, int layer, View q, View k, View v, View out, int m, int first_pos,
@@ -212,7 +221,7 @@ hipError_t static_scratch_address(unsigned char** out);  // per device; first ca
 size_t decode_static_scratch_need(const d2o_ctx* c);     // bytes of it a decode step of this context uses
 size_t decode_static_scratch_capacity();
 int decode_candidates();  // eviction candidates tracked per (layer, sequence, KV head)
-hipError_t launch_init_candidates(d2o_ctx* c, int layer, int new_pos, hipStream_t s);
+MetaPack pack_meta(const d2o_ctx* c, int layer, int b0, int nb);  // heads b0 .. b0 + nb - 1 of the layer's host meta
 hipError_t launch_write_meta(d2o_ctx* c, int layer, hipStream_t s);  // the layer's host meta -> device, by a kernel
 
 }  // namespace d2o

@@ -1099,80 +1099,6 @@ hipError_t run_decode_g(d2o_ctx* c, const DecodeArgs& a, int fc, const StepViews
 
 int decode_candidates() { return kCand; }
 
-
-// The eviction candidates of the first generation step of one layer, chosen after prompt
-// compression: the kCand lowest scores among the cached tokens that are evictable when token
-// `new_pos` arrives (Eq. 7-8 on count + 1 entries: neither sink nor inside the recent window).
-// A prediction like the one every step makes for the next: a miss costs that step's closing
-// workgroup a second pass over the keys and nothing else.
-__global__ __launch_bounds__(256) void init_candidates(const int32_t* __restrict__ ccount,
-                                                       const int32_t* __restrict__ meta,  // the layer's [B][Hkv][4]
-                                                       const double* __restrict__ cscore,
-                                                       const int32_t* __restrict__ cpos, int32_t* __restrict__ cand,
-                                                       int layer, int B, int Hkv, int64_t slots, int new_pos,
-                                                       int n_sink) {
-  __shared__ double sred[4];
-  __shared__ int ired[8];
-  const int hk = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int64_t lbh = (int64_t(layer) * B + b) * Hkv + hk;
-  const int total = ccount[lbh], recent = meta[(b * Hkv + hk) * 4 + 2];
-  const int64_t slot0 = (int64_t(b) * Hkv + hk) * slots + meta[(b * Hkv + hk) * 4 + 0];
-  Best low[kCand + 1];
-#pragma unroll
-  for (int i = 0; i <= kCand; ++i) low[i] = Best{0.0, 0, -1};
-  for (int j0 = tid; j0 < total; j0 += 8 * 256) {  // eight entries in flight per thread
-    double sc[8];
-    int ps[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      sc[u] = cscore[slot0 + min(j0 + u * 256, total - 1)];
-      ps[u] = cpos[slot0 + min(j0 + u * 256, total - 1)];
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int j = j0 + u * 256, p = ps[u];
-      if (j < total && p >= n_sink && p <= new_pos - recent && evicts_before(sc[u], p, j, low[kCand - 1])) {
-        low[kCand - 1] = Best{sc[u], p, j};
-#pragma unroll
-        for (int i = kCand - 1; i > 0; --i)
-          if (evicts_before(low[i].u, low[i].pos, low[i].slot, low[i - 1])) {
-            const Best t = low[i - 1];
-            low[i - 1] = low[i];
-            low[i] = t;
-          }
-      }
-    }
-  }
-#pragma unroll
-  for (int r = 0; r < kCand; ++r) {  // repeated block-wide extraction of the first in eviction order
-    Best h = fast_wave_first_evicted(low[0]);
-    __syncthreads();
-    if (lane == 0) {
-      sred[w] = h.u;
-      ired[w] = h.pos;
-      ired[4 + w] = h.slot;
-    }
-    __syncthreads();
-    h = Best{sred[0], ired[0], ired[4]};
-#pragma unroll
-    for (int i = 1; i < 4; ++i)
-      if (evicts_before(sred[i], ired[i], ired[4 + i], h)) h = Best{sred[i], ired[i], ired[4 + i]};
-    if (tid == 0) cand[lbh * kCand + r] = h.slot;
-    if (h.slot >= 0 && low[0].slot == h.slot) {  // the owner pops its head
-#pragma unroll
-      for (int i = 0; i < kCand; ++i) low[i] = low[i + 1];
-    }
-  }
-}
-
-hipError_t launch_init_candidates(d2o_ctx* c, int layer, int new_pos, hipStream_t s) {
-  const d2o_config& cf = c->cfg;
-  init_candidates<<<dim3(cf.n_kv_heads, cf.batch), 256, 0, s>>>(c->ccount, c->meta + size_t(layer) * cf.batch * cf.n_kv_heads * 4,
-                                                                c->cscore, c->cpos, c->ccand, layer, cf.batch,
-                                                                cf.n_kv_heads, cf.slots_per_seq, new_pos, cf.n_sink);
-  return hipGetLastError();
-}
-
 // Sizes (in bytes, each rounded up to 256) of the four scratch arrays of a decode step, in the
 // order elog, rec, pacc, part.
 static void decode_scratch_sizes(const d2o_ctx* c, size_t (&sz)[4]) {

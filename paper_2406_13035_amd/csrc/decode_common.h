@@ -242,6 +242,61 @@ __device__ __forceinline__ Best fast_wave_first_evicted(const Best& b) {
   const int src = __ffsll((long long)who) - 1;
   return Best{smin, pmax, __builtin_amdgcn_readlane(b.slot, src)};
 }
+// The eviction candidates of the first generation step of one head, chosen after prompt
+// compression by a workgroup of NT threads: the kCand lowest scores among the cached tokens that are evictable when token
+// `new_pos` arrives (Eq. 7-8 on count + 1 entries: neither sink nor inside the recent window).
+// A prediction like the one every step makes for the next: a miss costs that step's closing
+// workgroup a second pass over the keys and nothing else.
+template <int NT>
+__device__ __forceinline__ void first_candidates(const double* __restrict__ cscore, const int32_t* __restrict__ cpos,
+                                                 int total, int recent, int new_pos, int n_sink, int32_t* __restrict__ cand) {
+  constexpr int NW = NT / 64;
+  __shared__ Best ex[NW];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  Best low[kCand + 1];
+#pragma unroll
+  for (int i = 0; i <= kCand; ++i) low[i] = Best{0.0, 0, -1};
+  for (int j0 = tid; j0 < total; j0 += 4 * NT) {  // four entries in flight per thread
+    double sc[4];
+    int ps[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      sc[u] = cscore[min(j0 + u * NT, total - 1)];
+      ps[u] = cpos[min(j0 + u * NT, total - 1)];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int j = j0 + u * NT, p = ps[u];
+      if (j < total && p >= n_sink && p <= new_pos - recent && evicts_before(sc[u], p, j, low[kCand - 1])) {
+        low[kCand - 1] = Best{sc[u], p, j};
+#pragma unroll
+        for (int i = kCand - 1; i > 0; --i)
+          if (evicts_before(low[i].u, low[i].pos, low[i].slot, low[i - 1])) {
+            const Best t = low[i - 1];
+            low[i - 1] = low[i];
+            low[i] = t;
+          }
+      }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < kCand; ++r) {  // repeated block-wide extraction of the first in eviction order
+    Best h = fast_wave_first_evicted(low[0]);
+    __syncthreads();
+    if (lane == 0) ex[w] = h;
+    __syncthreads();
+    h = ex[0];
+#pragma unroll
+    for (int i = 1; i < NW; ++i)
+      if (evicts_before(ex[i].u, ex[i].pos, ex[i].slot, h)) h = ex[i];
+    if (tid == 0) cand[r] = h.slot;
+    if (h.slot >= 0 && low[0].slot == h.slot) {  // the owner pops its head
+#pragma unroll
+      for (int i = 0; i < kCand; ++i) low[i] = low[i + 1];
+    }
+  }
+}
+
 // This thread's elements of the two rows a step merges, the evicted one (ke, ve) and its match (kt, vt),
 // as they were before the step; fp8 cache: with the rows' powers of two.  (Agent-scope loads: either may be
 // the new token's row, written by another workgroup of the launch.)

@@ -7,6 +7,7 @@
 // outputs do not depend on reduction shapes; the bf16 matrix-core product in match_filter_bf16
 // only pre-selects candidates and flags rows whose two best candidates are too close for fp32.
 #include "d2o_internal.h"
+#include "decode_common.h"
 #include "device_utils.h"
 
 namespace d2o {
@@ -52,8 +53,11 @@ __device__ __forceinline__ void block_scan_int(int v, int& ex, int& tot, int* wa
 
 // S: score type (fp32 column sums after prompt encoding; fp64 cumulative scores of a cache that a
 // block of tokens was appended to).  nvec, when given, holds the number of entries per head.
-template <typename S>
-__global__ __launch_bounds__(1024) void select_kernel(const S* __restrict__ score, const int32_t* __restrict__ meta,
+// PACKED: the layer's geometry comes with the launch; it goes to `meta` (and, fp8 cache, with row 0 as every head's
+// start to `stage`) here, where a launch of its own cost 3 us.
+template <typename S, bool PACKED>
+__global__ __launch_bounds__(1024) void select_kernel(const S* __restrict__ score, MetaPack pack, int32_t* __restrict__ meta,
+                                                      int32_t* __restrict__ stage, int32_t* __restrict__ amb_cnt,
                                                       int32_t* __restrict__ ret, int32_t* __restrict__ evi,
                                                       int32_t* __restrict__ cnt, int n_all, const int32_t* __restrict__ nvec,
                                                       int npad, int n_sink) {
@@ -69,8 +73,13 @@ __global__ __launch_bounds__(1024) void select_kernel(const S* __restrict__ scor
   const S* sc = score + bh * npad;
   int32_t* r = ret + bh * npad;
   int32_t* e = evi + bh * npad;
-  const int budget = meta[bh * 4 + 1], recent = meta[bh * 4 + 2];
   const int tid = threadIdx.x;
+  if (PACKED && tid < 4) {
+    meta[bh * 4 + tid] = pack.v[bh * 4 + tid];
+    if (stage) stage[bh * 4 + tid] = tid == 0 ? 0 : pack.v[bh * 4 + tid];
+  }
+  if (tid == 0) amb_cnt[bh] = 0;  // (counted up by match_filter_bf16)
+  const int budget = PACKED ? pack.v[bh * 4 + 1] : meta[bh * 4 + 1], recent = PACKED ? pack.v[bh * 4 + 2] : meta[bh * 4 + 2];
   if (budget >= n) {
     for (int j = tid; j < n; j += blockDim.x) r[j] = j;
     if (tid == 0) {
@@ -191,10 +200,29 @@ __global__ __launch_bounds__(1024) void select_kernel(const S* __restrict__ scor
   }
 }
 
+// 1/|k_j| in fp32 for sixteen prompt keys from row0 on (used by the bf16 candidate filter only).
+__device__ __forceinline__ void inverse_norms(const uint16_t* __restrict__ kb, int64_t sn, float* __restrict__ invn, int row0, int n) {
+  const int row = row0 + threadIdx.x / 16, c = (threadIdx.x % 16) * 8;
+  float s = 0.f;
+  if (row < n) {
+    const u32x4 v = *reinterpret_cast<const u32x4*>(kb + int64_t(row) * sn + c);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float lo = __uint_as_float(v[i] << 16), hi = __uint_as_float(v[i] & 0xFFFF0000u);
+      s = fmaf(lo, lo, s);
+      s = fmaf(hi, hi, s);
+    }
+  }
+#pragma unroll
+  for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+  if (row < n && (threadIdx.x % 16) == 0) invn[row] = s > 0.f ? 1.0f / sqrtf(s) : 0.f;
+}
+
 // ------------------------------------------------------------------------------------------
 // Compaction: retained rows of K, V into the layer's cache region; scores widen to fp64.
 // APPEND: the source is the position-ordered copy of a cache: fp64 scores (sc64) and token
-// positions (apos) indexed like its rows.
+// positions (apos) indexed like its rows.  The workgroups behind the first `row_blocks` form the inverse norms of
+// all n keys (bf16; the two are independent, and as two launches each was mostly its start and end).
 template <typename T, bool APPEND>
 __global__ __launch_bounds__(256) void gather_kernel(const T* __restrict__ K, View kv, const T* __restrict__ V, View vv,
                                                      const float* __restrict__ score, const double* __restrict__ sc64,
@@ -203,9 +231,15 @@ __global__ __launch_bounds__(256) void gather_kernel(const T* __restrict__ K, Vi
                                                      T* __restrict__ cK, T* __restrict__ cV, double* __restrict__ cscore,
                                                      int32_t* __restrict__ cpos, int32_t* __restrict__ ccount,
                                                      int npad, int d, int64_t slots, const int32_t* __restrict__ row_meta,
-                                                     int64_t row_slots) {
+                                                     int64_t row_slots, int row_blocks, float* __restrict__ invn, int n) {
   const int hk = blockIdx.y, b = blockIdx.z, Hkv = gridDim.y;
   const int64_t bh = int64_t(b) * Hkv + hk;
+  if constexpr (sizeof(T) == 2) {
+    if (int(blockIdx.x) >= row_blocks) {
+      inverse_norms(K + b * kv.sb + hk * kv.sh, kv.sn, invn + bh * npad, (int(blockIdx.x) - row_blocks) * 16, n);
+      return;
+    }
+  }
   const int nret = cnt[bh * 2];
   constexpr int kVec = 16 / sizeof(T);
   const int tpr = d / kVec;                 // threads per row
@@ -231,27 +265,6 @@ __global__ __launch_bounds__(256) void gather_kernel(const T* __restrict__ K, Vi
 // ------------------------------------------------------------------------------------------
 // Matching.
 
-// 1/|k_j| in fp32 for every prompt key (used by the bf16 candidate filter only).
-__global__ __launch_bounds__(256) void invnorm_bf16(const uint16_t* __restrict__ K, View kv, float* __restrict__ invn,
-                                                    int n, int npad) {
-  const int hk = blockIdx.y, b = blockIdx.z, Hkv = gridDim.y;
-  const int row = blockIdx.x * 16 + threadIdx.x / 16, c = (threadIdx.x % 16) * 8;
-  float s = 0.f;
-  if (row < n) {
-    const u32x4 v = *reinterpret_cast<const u32x4*>(K + b * kv.sb + hk * kv.sh + int64_t(row) * kv.sn + c);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float lo = __uint_as_float(v[i] << 16), hi = __uint_as_float(v[i] & 0xFFFF0000u);
-      s = fmaf(lo, lo, s);
-      s = fmaf(hi, hi, s);
-    }
-  }
-#pragma unroll
-  for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-  if (row < n && (threadIdx.x % 16) == 0)
-    invn[(int64_t(b) * Hkv + hk) * npad + row] = s > 0.f ? 1.0f / sqrtf(s) : 0.f;
-}
-
 // Candidate filter on the matrix cores.  A workgroup owns 128 evicted rows (4 wavefronts x 32,
 // the stationary B operand) and streams the retained keys, read contiguously from the cache
 // region they were compacted into, in double-buffered tiles of 64 through LDS (the A operand),
@@ -259,7 +272,8 @@ __global__ __launch_bounds__(256) void invnorm_bf16(const uint16_t* __restrict__
 //   COLLECT = false: per row, track the best and second-best fp32 cosine and the best's
 //     retained rank.  A row whose two best values differ by less than kAmbiguous is flagged and
 //     its acceptance threshold (best - kAmbiguous, in the un-normalised domain) is stored.
-//   COLLECT = true: second sweep over the flagged rows only (compacted list): every retained
+//   COLLECT = true: second sweep over the flagged rows only (a list in no particular order; the rows are
+//     independent of each other): every retained
 //     key whose fp32 cosine reaches the row's threshold is appended to the row's candidate
 //     list (up to kMaxCand; more than that falls back to the exhaustive search).  The sweep
 //     repeats the first one's arithmetic exactly, so the best value is found again.  Few rows are
@@ -280,8 +294,8 @@ __global__ __launch_bounds__(256) void match_filter_bf16(const uint16_t* __restr
                                                          const int32_t* __restrict__ ret,
                                                          const int32_t* __restrict__ evi,
                                                          const int32_t* __restrict__ cnt, int32_t* __restrict__ cand,
-                                                         float* __restrict__ thr, const int32_t* __restrict__ amb_list,
-                                                         const int32_t* __restrict__ amb_cnt,
+                                                         float* __restrict__ thr, int32_t* __restrict__ amb_list,
+                                                         int32_t* __restrict__ amb_cnt,
                                                          int32_t* __restrict__ ncand, int32_t* __restrict__ clist,
                                                          int npad, int ksplit) {
   constexpr int kTile = 64;     // retained keys per LDS tile
@@ -430,38 +444,11 @@ __global__ __launch_bounds__(256) void match_filter_bf16(const uint16_t* __restr
     const bool amb = !(best - second >= margin);                // also true for NaN / equal / zero norm
     cand[bh * npad + erank] = bi | (amb ? int(0x80000000u) : 0);
     thr[bh * npad + erank] = best - margin;
-  }
-}
-
-// Ordered list of the flagged rows of one (sequence, KV head), and cleared candidate counters.
-__global__ __launch_bounds__(1024) void amb_compact_kernel(const int32_t* __restrict__ cand, const int32_t* __restrict__ cnt,
-                                                           int32_t* __restrict__ amb_list, int32_t* __restrict__ amb_cnt,
-                                                           int32_t* __restrict__ ncand, int npad) {
-  __shared__ int wa[16];
-  const int hk = blockIdx.x, b = blockIdx.y, Hkv = gridDim.x;
-  const int64_t bh = int64_t(b) * Hkv + hk;
-  const int nevi = cnt[bh * 2 + 1];
-  constexpr int PT = 4;  // consecutive rows per thread and block-wide scan
-  int base = 0;
-  for (int i0 = 0; i0 < nevi; i0 += PT * 1024) {
-    const int it = i0 + PT * int(threadIdx.x);
-    bool amb[PT];
-    int n = 0;
-#pragma unroll
-    for (int u = 0; u < PT; ++u) {
-      amb[u] = it + u < nevi && cand[bh * npad + it + u] < 0;
-      if (it + u < nevi) ncand[bh * npad + it + u] = 0;
-      n += amb[u] ? 1 : 0;
+    if (amb) {
+      amb_list[bh * npad + atomicAdd(&amb_cnt[bh], 1)] = erank;
+      ncand[bh * npad + erank] = 0;
     }
-    int ex, tot;
-    block_scan_int(n, ex, tot, wa);
-    int at = base + ex;
-#pragma unroll
-    for (int u = 0; u < PT; ++u)
-      if (amb[u]) amb_list[bh * npad + at++] = it + u;
-    base += tot;
   }
-  if (threadIdx.x == 0) amb_cnt[bh] = base;
 }
 
 // Exact similarity in fp64, operation order of Eq. 9 as written: dot / (|k_i| * |k_j|), 0 when
@@ -637,19 +624,34 @@ __global__ __launch_bounds__(256) void match_refine(const T* __restrict__ K, Vie
 // counters live in LDS up to kGroupSlots retained tokens (as words in memory beyond), and a thread has
 // four tokens in flight.  (One token at a time and counters in memory: 16.9 us at 32 heads x 4096
 // tokens, 112 us at 32768; now 8.5 and 41 us.)
+// The workgroups with z = 1 choose the eviction candidates of the next generation step meanwhile (they need
+// the compacted scores only).
 constexpr int kGroupSlots = 15360;  // 60 KB
+struct FirstCandidates {  // the layer's arrays, [B][Hkv]
+  const double* cscore;
+  const int32_t *cpos, *ccount, *meta;
+  int32_t* cand;
+  int64_t slots;
+  int new_pos, n_sink;
+};
 __global__ __launch_bounds__(1024) void threshold_group_kernel(const double* __restrict__ ustar,
                                                                const int32_t* __restrict__ tgt,
                                                                const int32_t* __restrict__ cnt, uint8_t* __restrict__ pass,
                                                                int32_t* __restrict__ gcnt, int32_t* __restrict__ goff,
                                                                int32_t* __restrict__ gcur, int32_t* __restrict__ gsrc,
                                                                double* __restrict__ tau_out, int npad, double tau_force,
-                                                               int ema, double beta) {
+                                                               int ema, double beta, FirstCandidates fc) {
   __shared__ double red[16];
   __shared__ int wa[16];
   __shared__ int slot_lds[kGroupSlots];  // counts of the slots' sources, then the places of their next ones
   const int hk = blockIdx.x, b = blockIdx.y, Hkv = gridDim.x;
   const int64_t bh = int64_t(b) * Hkv + hk;
+  if (blockIdx.z == 1) {
+    const int64_t slot0 = bh * fc.slots + fc.meta[bh * 4 + 0];
+    dec::first_candidates<1024>(fc.cscore + slot0, fc.cpos + slot0, fc.ccount[bh], fc.meta[bh * 4 + 2], fc.new_pos, fc.n_sink,
+                                fc.cand + bh * dec::kCand);
+    return;
+  }
   const int nret = cnt[bh * 2], nevi = cnt[bh * 2 + 1];
   const int tid = threadIdx.x;
   const bool in_lds = nret < kGroupSlots;
@@ -914,35 +916,48 @@ __global__ __launch_bounds__(256) void merge_kernel(const T* __restrict__ K, Vie
 hipError_t launch_select(d2o_ctx* c, int layer, int n, hipStream_t s, bool append) {
   const d2o_config& cf = c->cfg;
   const float* score = c->score_pre + size_t(layer) * cf.batch * cf.n_kv_heads * c->npad;
-  const int32_t* meta = c->meta + size_t(layer) * cf.batch * cf.n_kv_heads * 4;
+  const int bh = cf.batch * cf.n_kv_heads;
+  int32_t* meta = c->meta + size_t(layer) * bh * 4;
+  const dim3 grid(cf.n_kv_heads, cf.batch);
   KernelTimer kt(c, D2O_K_SELECT, s);
   if (append)
-    select_kernel<double><<<dim3(cf.n_kv_heads, cf.batch), 1024, 0, s>>>(c->app_score, meta, c->sel_ret, c->sel_evi,
-                                                                         c->sel_cnt, n, c->app_n, c->npad, cf.n_sink);
+    select_kernel<double, false><<<grid, 1024, 0, s>>>(c->app_score, MetaPack{}, meta, nullptr, c->amb_cnt, c->sel_ret, c->sel_evi,
+                                                       c->sel_cnt, n, c->app_n, c->npad, cf.n_sink);
+  else if (bh <= kMetaPerLaunch)
+    select_kernel<float, true><<<grid, 1024, 0, s>>>(score, pack_meta(c, layer, 0, bh), meta,
+                                                     cf.cache_fp8 ? c->meta_stage + size_t(layer) * bh * 4 : nullptr, c->amb_cnt,
+                                                     c->sel_ret, c->sel_evi, c->sel_cnt, n, nullptr, c->npad, cf.n_sink);
   else
-    select_kernel<float><<<dim3(cf.n_kv_heads, cf.batch), 1024, 0, s>>>(score, meta, c->sel_ret, c->sel_evi, c->sel_cnt,
-                                                                        n, nullptr, c->npad, cf.n_sink);
+    select_kernel<float, false><<<grid, 1024, 0, s>>>(score, MetaPack{}, meta, nullptr, c->amb_cnt, c->sel_ret, c->sel_evi,
+                                                      c->sel_cnt, n, nullptr, c->npad, cf.n_sink);
   return hipGetLastError();
 }
 
 template <typename T>
-static void run_gather(d2o_ctx* c, int layer, View K, View V, int max_budget, bool append, hipStream_t s) {
+static void run_gather(d2o_ctx* c, int layer, View K, View V, int max_budget, int n_norms, bool append, hipStream_t s) {
   const d2o_config& cf = c->cfg;
   const float* score = c->score_pre + size_t(layer) * cf.batch * cf.n_kv_heads * c->npad;
   const int32_t* meta = c->meta + size_t(layer) * cf.batch * cf.n_kv_heads * 4;
   int32_t* ccount = c->ccount + size_t(layer) * cf.batch * cf.n_kv_heads;
   const int rows = 256 / (cf.head_dim * int(sizeof(T)) / 16);
-  const dim3 grid((max_budget + rows - 1) / rows, cf.n_kv_heads, cf.batch);
+  const int row_blocks = (max_budget + rows - 1) / rows;
+  const dim3 grid(row_blocks + (n_norms + 15) / 16, cf.n_kv_heads, cf.batch);
   if (append)
     gather_kernel<T, true><<<grid, 256, 0, s>>>((const T*)K.ptr, K, (const T*)V.ptr, V, score, c->app_score, c->app_pos,
                                                 c->sel_ret, c->sel_cnt, meta, (T*)prompt_rows_K(c), (T*)prompt_rows_V(c), c->cscore,
                                                 c->cpos, ccount, c->npad, cf.head_dim, cf.slots_per_seq,
-                                                prompt_rows_meta(c, layer), prompt_rows_stride(c));
+                                                prompt_rows_meta(c, layer), prompt_rows_stride(c), row_blocks, c->invnorm, n_norms);
   else
     gather_kernel<T, false><<<grid, 256, 0, s>>>((const T*)K.ptr, K, (const T*)V.ptr, V, score, nullptr, nullptr,
                                                  c->sel_ret, c->sel_cnt, meta, (T*)prompt_rows_K(c), (T*)prompt_rows_V(c), c->cscore,
                                                  c->cpos, ccount, c->npad, cf.head_dim, cf.slots_per_seq,
-                                                 prompt_rows_meta(c, layer), prompt_rows_stride(c));
+                                                 prompt_rows_meta(c, layer), prompt_rows_stride(c), row_blocks, c->invnorm, n_norms);
+}
+
+static int max_evicted(const d2o_ctx* c, int layer, int n) {
+  int m = 0;
+  for (const auto& mt : c->layers[layer].meta) m = std::max(m, n - std::min(mt.budget, n));
+  return m;
 }
 
 hipError_t launch_gather(d2o_ctx* c, int layer, View K, View V, int n, hipStream_t s, bool append) {
@@ -950,16 +965,10 @@ hipError_t launch_gather(d2o_ctx* c, int layer, View K, View V, int n, hipStream
   int max_budget = 0;
   for (const auto& mt : c->layers[layer].meta) max_budget = std::max(max_budget, std::min(mt.budget, n));
   if (cf.dtype == D2O_BF16)
-    run_gather<uint16_t>(c, layer, K, V, max_budget, append, s);
+    run_gather<uint16_t>(c, layer, K, V, max_budget, max_evicted(c, layer, n) > 0 ? n : 0, append, s);
   else
-    run_gather<float>(c, layer, K, V, max_budget, append, s);
+    run_gather<float>(c, layer, K, V, max_budget, 0, append, s);
   return hipGetLastError();
-}
-
-static int max_evicted(const d2o_ctx* c, int layer, int n) {
-  int m = 0;
-  for (const auto& mt : c->layers[layer].meta) m = std::max(m, n - std::min(mt.budget, n));
-  return m;
 }
 
 hipError_t launch_match(d2o_ctx* c, int layer, View K, int n, hipStream_t s) {
@@ -971,8 +980,6 @@ hipError_t launch_match(d2o_ctx* c, int layer, View K, int n, hipStream_t s) {
   const dim3 gr((me + refine_rows - 1) / refine_rows, cf.n_kv_heads, cf.batch);
   if (cf.dtype == D2O_BF16) {
     const dim3 gf((me + 127) / 128, cf.n_kv_heads, cf.batch);
-    invnorm_bf16<<<dim3((n + 15) / 16, cf.n_kv_heads, cf.batch), 256, 0, s>>>((const uint16_t*)K.ptr, K, c->invnorm, n,
-                                                                             c->npad);
     {
       KernelTimer kt(c, D2O_K_MATCH_FILTER, s);
       match_filter_bf16<false><<<gf, 256, 0, s>>>((const uint16_t*)K.ptr, K, (const uint16_t*)prompt_rows_K(c),
@@ -980,8 +987,6 @@ hipError_t launch_match(d2o_ctx* c, int layer, View K, int n, hipStream_t s) {
                                                   c->invnorm, c->sel_ret, c->sel_evi,
                                                   c->sel_cnt, c->m_cand, c->m_thr, c->amb_list, c->amb_cnt,
                                                   c->m_ncand, c->m_clist, c->npad, 1);
-      amb_compact_kernel<<<dim3(cf.n_kv_heads, cf.batch), 1024, 0, s>>>(c->m_cand, c->sel_cnt, c->amb_list,
-                                                                        c->amb_cnt, c->m_ncand, c->npad);
       constexpr int kSplit = 8;
       match_filter_bf16<true><<<dim3(gf.x * kSplit, gf.y, gf.z), 256, 0, s>>>((const uint16_t*)K.ptr, K, (const uint16_t*)prompt_rows_K(c),
                                                  prompt_rows_meta(c, layer), prompt_rows_stride(c),
@@ -1004,12 +1009,15 @@ hipError_t launch_match(d2o_ctx* c, int layer, View K, int n, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_threshold_group(d2o_ctx* c, int layer, int n, hipStream_t s, bool append) {
+hipError_t launch_threshold_group(d2o_ctx* c, int layer, int n, int new_pos, hipStream_t s, bool append) {
   const d2o_config& cf = c->cfg;
-  double* tau = c->ctau + size_t(layer) * cf.batch * cf.n_kv_heads;
-  threshold_group_kernel<<<dim3(cf.n_kv_heads, cf.batch), 1024, 0, s>>>(c->m_ustar, c->m_tgt, c->sel_cnt, c->m_pass,
+  const size_t lo = size_t(layer) * cf.batch * cf.n_kv_heads;
+  double* tau = c->ctau + lo;
+  const FirstCandidates fc{c->cscore, c->cpos, c->ccount + lo, c->meta + lo * 4, c->ccand + lo * decode_candidates(),
+                           cf.slots_per_seq, new_pos, cf.n_sink};
+  threshold_group_kernel<<<dim3(cf.n_kv_heads, cf.batch, 2), 1024, 0, s>>>(c->m_ustar, c->m_tgt, c->sel_cnt, c->m_pass,
                                                                         c->g_cnt, c->g_off, c->g_cur, c->g_src, tau,
-                                                                        c->npad, cf.tau_force, append ? 1 : 0, cf.beta);
+                                                                        c->npad, cf.tau_force, append ? 1 : 0, cf.beta, fc);
   return hipGetLastError();
 }
 
