@@ -352,11 +352,16 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
       }
     }
   };
+  // The wavefront in its matrix phase issues first: its instructions are few and keep the matrix core busy, the
+  // other wavefront's softmax fills the slots between them (32768 tokens, 32 heads: 8.39 -> 8.08 ms; with the
+  // softmax first 8.19).
   auto pv_qk = [&](int t, bool with_qk) {
+    __builtin_amdgcn_s_setprio(1);
     if (with_qk)
       mma_phase(t, std::true_type{});
     else
       mma_phase(t, std::false_type{});
+    __builtin_amdgcn_s_setprio(0);
   };
 
   // ---- ping-pong schedule.  The two wavefronts that share a SIMD (w and w + NW/2) run half a
