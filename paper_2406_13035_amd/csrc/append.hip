@@ -5,7 +5,7 @@
 // cache's slots are physically unordered, so this file lays every cache of the layer out in
 // position order first:
 //
-//   rank_by_position   per (sequence, KV head): rank of every slot's position among the head's
+//   rank_by_bits, rank_by_position   per (sequence, KV head): rank of every slot's position among the head's
 //                      positions (positions are distinct), the ordered positions and fp64 scores,
 //                      and the number of entries;
 //   permute_rows       K and V rows of every slot to their rank in the ordered copy.
@@ -65,6 +65,88 @@ __global__ __launch_bounds__(256) void rank_by_position(const int32_t* __restric
         opos[bh * npad + cnt[u]] = mine[u];
         oscore[bh * npad + cnt[u]] = cscore[slot0 + j];
       }
+    }
+  }
+}
+
+// The same for caches whose positions are all below 32 kBitWords: a set of the positions as bits in LDS, and the
+// number of bits below a position is its rank.  One workgroup per head; comparing every slot with every other took 25 us
+// for 32 heads of 2304 entries, this takes 6.
+constexpr int kBitWords = 16384;  // 64 KB: positions up to 524287
+__global__ __launch_bounds__(1024) void rank_by_bits(const int32_t* __restrict__ ccount, const int32_t* __restrict__ meta,
+                                                     const double* __restrict__ cscore, const int32_t* __restrict__ cpos,
+                                                     int32_t* __restrict__ rank, int32_t* __restrict__ opos,
+                                                     double* __restrict__ oscore, int32_t* __restrict__ on, int npad,
+                                                     int64_t slots, int nwords) {
+  extern __shared__ uint32_t bits[];          // [nwords], a multiple of 1024
+  int* below = reinterpret_cast<int*>(bits + nwords);  // [1024] bits in the words before thread t's
+  __shared__ int wsum[16];
+  const int hk = blockIdx.x, b = blockIdx.y, Hkv = gridDim.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int64_t bh = int64_t(b) * Hkv + hk;
+  const int n = ccount[bh];
+  const int64_t slot0 = bh * slots + meta[bh * 4 + 0];
+  if (tid == 0) on[bh] = n;
+  constexpr int U = 4;  // slots in flight per thread
+  int outside = 0;
+  for (int i = tid; i < nwords; i += 1024) bits[i] = 0;
+  __syncthreads();
+  for (int j0 = tid; j0 < n; j0 += U * 1024) {
+    int p[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) p[u] = cpos[slot0 + min(j0 + u * 1024, n - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool in = uint32_t(p[u]) < uint32_t(nwords) * 32u;
+      if (!in) outside = 1;
+      if (in && j0 + u * 1024 < n) atomicOr(&bits[p[u] >> 5], 1u << (p[u] & 31));
+    }
+  }
+  if (__syncthreads_or(outside)) {  // (an imported cache may hold any positions: every slot against every other)
+    for (int j = tid; j < n; j += 1024) {
+      const int p = cpos[slot0 + j];
+      int r = 0;
+      for (int i = 0; i < n; ++i) r += cpos[slot0 + i] < p;
+      rank[bh * npad + j] = r;
+      opos[bh * npad + r] = p;
+      oscore[bh * npad + r] = cscore[slot0 + j];
+    }
+    return;
+  }
+  // thread t counts the words [t per, t per + per); a scan over the threads counts those before
+  const int per = nwords / 1024;
+  int mine = 0;
+  for (int i = 0; i < per; ++i) mine += __popc(bits[tid * per + i]);
+  int inc = mine;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int t = __shfl_up(inc, o, 64);
+    if (lane >= o) inc += t;
+  }
+  if (lane == 63) wsum[w] = inc;
+  __syncthreads();
+  int off = 0;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) off += i < w ? wsum[i] : 0;
+  below[tid] = off + inc - mine;
+  __syncthreads();
+  for (int j0 = tid; j0 < n; j0 += U * 1024) {
+    int p[U];
+    double sc[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      p[u] = cpos[slot0 + min(j0 + u * 1024, n - 1)];
+      sc[u] = cscore[slot0 + min(j0 + u * 1024, n - 1)];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int j = j0 + u * 1024;
+      if (j >= n) continue;
+      const int word = p[u] >> 5, t = word / per;
+      int r = below[t] + __popc(bits[word] & ((1u << (p[u] & 31)) - 1u));
+      for (int i = t * per; i < word; ++i) r += __popc(bits[i]);
+      rank[bh * npad + j] = r;
+      opos[bh * npad + r] = p[u];
+      oscore[bh * npad + r] = sc[u];
     }
   }
 }
@@ -231,19 +313,29 @@ struct BlockRows {
 #pragma unroll
         for (int t = 0; t < 4; ++t) S[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(elem(raw[t], e), bq[s + e], S[t], 0, 0, 0);
     }
-    // (times the rounded reciprocal of sqrt(d), exact for d = 64: a block's logits are compared
-    // within the float tolerance, and a division per element would cost a tenth of the pass)
-    const double inv_root_d = 1.0 / sqrt(double(D));
 #pragma unroll
     for (int t = 0; t < 4; ++t)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         double v = S[t][r];
         if constexpr (sizeof(T) == 1) v *= reinterpret_cast<const double*>(smem + kRowsBytes)[g * 64 + t * 16 + 4 * r + kq];
-        S[t][r] = v * inv_root_d;
+        S[t][r] = div_root<D>(v);
       }
   }
 };
+
+// The logits of rows this lane's query does not see (behind the last row, or later block tokens) to minus
+// infinity, whose exponential is zero: the exponentials of a tile are then one straight run of
+// instructions (each behind a branch of its own, they ran one after the other).  `last`: the last row it
+// sees; tile_last: the last row that all queries of the tile see; j0: the row of S[0][0].
+__device__ __forceinline__ void mask_logits(f64x4 (&S)[4], int j0, int last, int group_last, int tile_last) {
+  if (group_last <= tile_last) return;  // (the same for the wavefront)
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (j0 + t * 16 + 4 * r > last) S[t][r] = -INFINITY;
+}
 
 // sum / maximum over the four lanes that hold the same query column (kq = 0..3)
 __device__ __forceinline__ double kq_max(double v) {
@@ -303,34 +395,32 @@ __global__ __launch_bounds__(256) void block_stats(const int32_t* __restrict__ c
     const int q0 = qt * kQT, query = q0 + c;
     double bq[BR::KS];
     BR::load_queries(aq + int64_t(bh) * maxq * D, q0, lane, bq);
-    const int seen = nc + query / G;  // the last row this query attends to
+    const int seen = min(nc + query / G, N - 1);  // the last row this query attends to
+    const int tile_last = min(nc + q0 / G, N - 1);
     double M = -INFINITY, L = 0.0;
 #pragma unroll 1
     for (int g = 0; g < ngroup; ++g) {
       f64x4 S[4];
       BR::logits(smem, g, lane, bq, S);
       const int j0 = chunk * kChunk + g * 64 + kq;
-      double mg = -INFINITY;
+      mask_logits(S, j0, seen, chunk * kChunk + g * 64 + 63, tile_last);
+      double mg = S[0][0];
 #pragma unroll
       for (int t = 0; t < 4; ++t)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int j = j0 + t * 16 + 4 * r;
-          if (j < N && j <= seen) mg = fmax(mg, S[t][r]);
-        }
+        for (int r = 0; r < 4; ++r) mg = max_f64(mg, S[t][r]);
       mg = kq_max(mg);
-      if (mg == -INFINITY) continue;  // (the same for the four lanes of a query)
-      double lg = 0.0;
+      // (a query that sees no row of the group: its exponentials are zero relative to any finite value)
+      const double ref = mg == -INFINITY ? 0.0 : mg;
+      double lt[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int t = 0; t < 4; ++t)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int j = j0 + t * 16 + 4 * r;
-          if (j < N && j <= seen) lg += exp(S[t][r] - mg);
-        }
-      lg = kq_sum(lg);
+        for (int r = 0; r < 4; ++r) lt[r] += exp(S[t][r] - ref);
+      const double lg = kq_sum((lt[0] + lt[1]) + (lt[2] + lt[3]));
       const double Mn = fmax(M, mg);
-      L = (M == -INFINITY ? 0.0 : L * exp(M - Mn)) + lg * exp(mg - Mn);
+      if (Mn == -INFINITY) continue;
+      L = (M == -INFINITY ? 0.0 : L * exp(M - Mn)) + (mg == -INFINITY ? 0.0 : lg * exp(mg - Mn));
       M = Mn;
     }
     if (kq == 0 && query < nq) {
@@ -392,8 +482,10 @@ __global__ __launch_bounds__(256, 2) void block_apply(const int32_t* __restrict_
     const int q0 = qt * kQT, query = q0 + c;
     double bq[BR::KS];
     BR::load_queries(aq + int64_t(bh) * maxq * D, q0, lane, bq);
-    const int seen = query < nq ? nc + query / G : -1;  // a padding query sees nothing
-    const double M = norm[(int64_t(bh) * maxq + query) * 2], Linv = 1.0 / norm[(int64_t(bh) * maxq + query) * 2 + 1];
+    const int seen = query < nq ? min(nc + query / G, N - 1) : -1;  // a padding query sees nothing
+    const int tile_last = q0 + kQT <= nq ? min(nc + q0 / G, N - 1) : -1;
+    const double M = query < nq ? norm[(int64_t(bh) * maxq + query) * 2] : 0.0;
+    const double Linv = query < nq ? 1.0 / norm[(int64_t(bh) * maxq + query) * 2 + 1] : 0.0;
     f32x4 O[CT];
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) O[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -412,19 +504,26 @@ __global__ __launch_bounds__(256, 2) void block_apply(const int32_t* __restrict_
       };
       load_v(0);
       BR::logits(smem, g, lane, bq, S);
+      mask_logits(S, j0, seen, chunk * kChunk + g * 64 + 63, tile_last);
       double pr[16];  // the probabilities, value 4 t + r
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         __builtin_amdgcn_sched_barrier(0);
         if (t < 3) load_v(t + 1);
         __builtin_amdgcn_sched_barrier(0);
+        // (the division by the normaliser is a multiplication by its reciprocal here: the
+        // probabilities are compared within the float tolerance, never bit for bit)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) pr[4 * t + r] = exp(S[t][r] - M) * Linv;
+        if (chunk * kChunk + g * 64 + 63 > tile_last) {  // (a normaliser that is not finite stays with the rows the query sees)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (j0 + t * 16 + 4 * r > seen) pr[4 * t + r] = 0.0;
+        }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int row = g * 64 + t * 16 + 4 * r + kq, j = j0 + t * 16 + 4 * r;
-          // (the division by the normaliser is a multiplication by its reciprocal here: the
-          // probabilities are compared within the float tolerance, never bit for bit)
-          const double p = (j < N && j <= seen) ? exp(S[t][r] - M) * Linv : 0.0;
-          pr[4 * t + r] = p;
+          const int row = g * 64 + t * 16 + 4 * r + kq;
+          const double p = pr[4 * t + r];
           // P V: this (t, r) is one contraction step over the rows 16 t + 4 r + kq
           float pa = float(p);
           if constexpr (sizeof(T) == 1) pa *= reinterpret_cast<const float*>(smem + BR::kRowsBytes + 256 * 8)[row];
@@ -597,7 +696,15 @@ hipError_t launch_cache_sort(d2o_ctx* c, int layer, hipStream_t s) {
   const int32_t* ccount = c->ccount + size_t(layer) * cf.batch * cf.n_kv_heads;
   int max_rows = 0;
   for (const auto& mt : c->layers[layer].meta) max_rows = std::max(max_rows, mt.budget + c->grow);
-  if (max_rows <= 8192)
+  const int64_t words = (int64_t(c->layers[layer].next_pos) + 32 * 1024 - 1) / (32 * 1024) * 1024;  // every position is below the next one
+  if (words <= kBitWords) {
+    const int lds = int(words + 1024) * int(sizeof(uint32_t));
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(rank_by_bits), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (kBitWords + 1024) * int(sizeof(uint32_t)));
+    if (e != hipSuccess) return e;
+    rank_by_bits<<<dim3(cf.n_kv_heads, cf.batch), 1024, lds, s>>>(ccount, meta, c->cscore, c->cpos, c->app_rank, c->app_pos,
+                                                                  c->app_score, c->app_n, c->npad, cf.slots_per_seq, int(words));
+  } else if (max_rows <= 8192)
     rank_by_position<1><<<dim3(cf.n_kv_heads, cf.batch, (max_rows + 255) / 256), 256, 0, s>>>(
         ccount, meta, c->cscore, c->cpos, c->app_rank, c->app_pos, c->app_score, c->app_n, c->npad, cf.slots_per_seq);
   else

@@ -555,7 +555,6 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
   unsigned char* mine = stage + w * kWaveStage;
   double* mine_opnd = opnd[kOwnOpnd ? w : 0];
   const int ln = lane;
-  const double root_d = sqrt(double(D));
   // K loads of a sub-chunk.  The K pass takes a row's bytes in pieces of 64 (one LDS staging round
   // each); the loads fetch two pieces at a time as whole 128-byte lines: 8 lanes per row, 8 rows
   // per load, 8 loads.  They are non-temporal like the V loads below: every K and V byte is
@@ -851,7 +850,7 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-      const double sg = dot[g] / root_d;
+      const double sg = div_root<D>(dot[g]);
       const double mx = fast_wave_max(valid ? sg : -INFINITY);
       const double e = valid ? exp(sg - mx) : 0.0;
       if constexpr (kMmaV) {
