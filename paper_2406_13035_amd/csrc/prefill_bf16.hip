@@ -145,16 +145,30 @@ __device__ __forceinline__ void xcd_remap(int nx, int nhz, int& bx, int& hz) {
   bx = s % nx;
 }
 
+// The same for a launch of single blocks of very different lengths, the longest (bx = 0) first in every XCD over
+// all of its heads: what joins a busy CU at the end is short.
+__device__ __forceinline__ void xcd_remap_longest_first(int nx, int nhz, int& bx, int& hz) {
+  constexpr int kXcd = 8;
+  const int lin = bx + nx * hz, per = nhz / kXcd;
+  if (nhz % kXcd) {
+    hz = lin % nhz;
+    bx = lin / nhz;
+  } else {
+    const int s = lin / kXcd;
+    hz = lin % kXcd * per + s % per;
+    bx = s / per;
+  }
+}
+
 constexpr int kKsElems = 16 * kGroupLd;  // one K tile in LDS
 constexpr int kVsElems = 16 * kGroupLd;  // one V^T tile in LDS
 constexpr int kAttnSmemBytes = 2 * (kKsElems + kVsElems) * 2;
 constexpr int kAttnRW = 1;                     // 32-row blocks per wavefront
-constexpr int kAttnNW = 8;                     // wavefronts per workgroup
-constexpr int kAttnBM = 32 * kAttnRW * kAttnNW;
 
 // NW wavefronts per workgroup, each owning RW 32-row MFMA column blocks (blocks of one
 // wavefront share every K / V^T operand read from LDS).  Built as 8 x 1: 256 query rows per
-// workgroup, two wavefronts per SIMD, which measured faster than 4 x 2.  K and V^T tiles of 64
+// workgroup, two wavefronts per SIMD, which measured faster than 4 x 2; and as 4 x 1 for launches that
+// do not fill the chip with those (see the launch).  K and V^T tiles of 64
 // keys are double-buffered in LDS.  A tile costs a wavefront about as many vector-ALU cycles
 // (32 exponentials per lane at a quarter of the ALU rate) as matrix-core cycles (32 MFMAs), so
 // the two wavefronts of a SIMD alternate between the two units (see the schedule below).
@@ -163,13 +177,16 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
                                                      const uint16_t* __restrict__ K, View kv,
                                                      const uint16_t* __restrict__ VT, const float* __restrict__ unscale,
                                                      void* __restrict__ O, View ov, float* __restrict__ lse2, int n,
-                                                     int npad, int G, int out_f32, int nblk) {
+                                                     int npad, int G, int out_f32, int nblk, int paired) {
   extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
   uint16_t* Ks = smem;                 // [2][kKsElems]
   uint16_t* Vs = smem + 2 * kKsElems;  // [2][kVsElems]
   const int Hq = gridDim.y, Hkv = Hq / G;
   int bx = blockIdx.x, hz = blockIdx.y + Hq * blockIdx.z;
-  xcd_remap(gridDim.x, Hq * gridDim.z, bx, hz);
+  if (paired)
+    xcd_remap(gridDim.x, Hq * gridDim.z, bx, hz);
+  else
+    xcd_remap_longest_first(gridDim.x, Hq * gridDim.z, bx, hz);
   const int hq = hz % Hq, b = hz / Hq, hk = hq / G;
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, m = lane & 31, h = lane >> 5;
   constexpr int kWR = 32 * RW;   // rows per wavefront
@@ -180,7 +197,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
   // nblk - 1 - x (the longer one first) and then row block x: every workgroup has the same
   // amount of work and the launch fills the chip in whole rounds (with one row block per
   // workgroup the longest ones ran on a nearly empty chip at the end: 80 % packing).
-  for (int pass = 0; pass < 2; ++pass) {
+  for (int pass = 0; pass < 1 + paired; ++pass) {
   const int blk = pass == 0 ? nblk - 1 - bx : bx;
   if (pass == 1 && blk >= nblk - 1 - bx) break;
   const int rb = blk * BM;
@@ -457,7 +474,7 @@ __global__ __launch_bounds__(64 * KW * QW) __attribute__((amdgpu_waves_per_eu(4,
                                                            const uint16_t* __restrict__ K, View kv,
                                                            const float* __restrict__ lse2, float* __restrict__ colsum,
                                                            double* __restrict__ varpart, int n, int npad, int G,
-                                                           int nblk) {
+                                                           int nblk, int paired) {
   constexpr int NW = KW * QW, NT = 64 * NW, BN = 32 * KW, NCH = TQ * 16 / NT;
   static_assert(BN <= NT && BN % 128 == 0 && TQ % (32 * QW) == 0 && BN % TQ == 0, "a thread per key, whole sub-tiles per wavefront");
   __shared__ __attribute__((aligned(16))) uint16_t Qs[2][TQ * kLdQ];
@@ -466,7 +483,10 @@ __global__ __launch_bounds__(64 * KW * QW) __attribute__((amdgpu_waves_per_eu(4,
   __shared__ double red[NW][2];
   const int Hq = gridDim.y;
   int bx = blockIdx.x, hz = blockIdx.y + Hq * blockIdx.z;
-  xcd_remap(gridDim.x, Hq * gridDim.z, bx, hz);
+  if (paired)
+    xcd_remap(gridDim.x, Hq * gridDim.z, bx, hz);
+  else
+    xcd_remap_longest_first(gridDim.x, Hq * gridDim.z, bx, hz);
   const int hq = hz % Hq, b = hz / Hq, hk = hq / G;
   const int tid = threadIdx.x, w = tid >> 6, kw = w % KW, qw = w / KW, lane = tid & 63, m = lane & 31, h = lane >> 5;
   const float scale2 = kLog2e / sqrtf(float(kD));
@@ -477,7 +497,7 @@ __global__ __launch_bounds__(64 * KW * QW) __attribute__((amdgpu_waves_per_eu(4,
   // then block nblk - 1 - x: every workgroup then has the same amount of work and the launch
   // fills the chip in whole rounds (with one block per workgroup the CUs held 1.3 of 2 possible
   // workgroups on average, and the longest workgroup alone was a fifth of the kernel time).
-  for (int pass = 0; pass < 2; ++pass) {
+  for (int pass = 0; pass < 1 + paired; ++pass) {
     const int tile = pass == 0 ? bx : nblk - 1 - bx;
     if (pass == 1 && tile <= bx) break;
     const int kb0 = tile * BN, kw0 = kb0 + kw * 32;  // first key of the workgroup / wavefront
@@ -578,12 +598,27 @@ __global__ __launch_bounds__(64 * KW * QW) __attribute__((amdgpu_waves_per_eu(4,
 }
 
 template <int KW, int QW, int TQ>
-void run_colsum(d2o_ctx* c, View Q, View K, float* colsum, int n, hipStream_t s) {
+void run_colsum(d2o_ctx* c, View Q, View K, float* colsum, int n, bool paired, hipStream_t s) {
   const d2o_config& cf = c->cfg;
   const int nblk = (n + 32 * KW - 1) / (32 * KW);
-  colsum_bf16<KW, QW, TQ><<<dim3((nblk + 1) / 2, cf.n_q_heads, cf.batch), 64 * KW * QW, 0, s>>>(
+  colsum_bf16<KW, QW, TQ><<<dim3(paired ? (nblk + 1) / 2 : nblk, cf.n_q_heads, cf.batch), 64 * KW * QW, 0, s>>>(
       (const uint16_t*)Q.ptr, Q, (const uint16_t*)K.ptr, K, c->lse, colsum, c->varpart, n, c->npad, cf.n_q_heads / cf.n_kv_heads,
-      nblk);
+      nblk, paired ? 1 : 0);
+}
+
+template <int NW>
+hipError_t run_attn(d2o_ctx* c, View Q, View K, View O, int n, bool paired, hipStream_t s) {
+  const d2o_config& cf = c->cfg;
+  constexpr int BM = 32 * kAttnRW * NW;
+  const int nblk = (n + BM - 1) / BM;
+  // the attribute is per device; setting it is a cheap host-side call, so it is not cached
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_fwd_bf16<kAttnRW, NW>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, kAttnSmemBytes);
+  if (e != hipSuccess) return e;
+  attn_fwd_bf16<kAttnRW, NW><<<dim3(paired ? (nblk + 1) / 2 : nblk, cf.n_q_heads, cf.batch), 64 * NW, kAttnSmemBytes, s>>>(
+      (const uint16_t*)Q.ptr, Q, (const uint16_t*)K.ptr, K, (const uint16_t*)c->vt, c->vt_unscale, O.ptr, O, c->lse, n,
+      c->npad, cf.n_q_heads / cf.n_kv_heads, cf.out_f32, nblk, paired ? 1 : 0);
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -592,33 +627,31 @@ hipError_t launch_prefill_bf16(d2o_ctx* c, int layer, View Q, View K, View V, Vi
   const d2o_config& cf = c->cfg;
   const int G = cf.n_q_heads / cf.n_kv_heads;
   float* score = c->score_pre + size_t(layer) * cf.batch * cf.n_kv_heads * c->npad;
-  const int nblk = (n + kAttnBM - 1) / kAttnBM;
-  {  // the attribute is per device; setting it is a cheap host-side call, so it is not cached
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_fwd_bf16<kAttnRW, kAttnNW>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, kAttnSmemBytes);
-    if (e != hipSuccess) return e;
-  }
   const int shares = std::min(kVmaxShares, (n * 16 + 255) / 256);
   vabsmax_kernel<<<dim3(shares, cf.n_kv_heads, cf.batch), 256, 0, s>>>((const uint16_t*)V.ptr, V, c->vmax_bits, n);
   transpose_v<<<dim3(c->npad / 64, cf.n_kv_heads, cf.batch), 256, 0, s>>>((const uint16_t*)V.ptr, V, (uint16_t*)c->vt,
                                                                          c->vmax_bits, c->vt_unscale, n, c->npad, shares);
   {
-  KernelTimer kt(c, D2O_K_ATTN_FWD, s);
-  attn_fwd_bf16<kAttnRW, kAttnNW><<<dim3((nblk + 1) / 2, cf.n_q_heads, cf.batch), 64 * kAttnNW, kAttnSmemBytes, s>>>(
-      (const uint16_t*)Q.ptr, Q, (const uint16_t*)K.ptr, K, (const uint16_t*)c->vt, c->vt_unscale, O.ptr, O, c->lse, n,
-      c->npad, G, cf.out_f32, nblk);
+    KernelTimer kt(c, D2O_K_ATTN_FWD, s);
+    // Row blocks of 256, two per workgroup (a long and a short one); where there are so few rows that the chip holds
+    // all blocks of 128, a workgroup each and two per CU, those: the longest block then takes half as long.
+    // (32 heads: 1000 tokens 51 -> 35 us, 2048 tokens 79 -> 68; 8 heads, 500 tokens 36 -> 21; 16 heads, 2900 tokens
+    // 100 -> 83; 2 heads, 24000 tokens 638 -> 623, 30000 tokens 771 -> 786.)
+    const bool few = int64_t((n + 127) / 128) * cf.n_q_heads * cf.batch <= 512;
+    const hipError_t e = few ? run_attn<4>(c, Q, K, O, n, false, s) : run_attn<8>(c, Q, K, O, n, true, s);
+    if (e != hipSuccess) return e;
   }
   KernelTimer kt(c, D2O_K_COLSUM, s);
   // with several query heads per KV head the column sums of each go to c->colpart; launch_density adds them up
   float* colsum = G == 1 ? score : c->colpart;
   // 256 keys per workgroup, eight wavefronts, where such workgroups fill the chip (two fit a CU); below, half as
-  // many keys, the eight wavefronts sharing them and the tile's queries.  (32 heads: 1000 tokens 29 instead
-  // of 41 us, 2048 tokens 43 / 61, 16384 tokens and 8 heads 377 / 386, 4096 tokens 118 both, 8192
-  // tokens 374 / 325.)
+  // many keys, the eight wavefronts sharing them and the tile's queries, and a block per workgroup instead
+  // of two where there is a CU for each.  (32 heads: 1000 tokens 41, 25 and 21 us; 2048 tokens 61, 38 and 37; 4096 tokens
+  // 118, 118; 8192 tokens 325, 374; 8 heads of 16384 tokens 386, 377; 4 heads of 14000 tokens 173 in pairs, 183 singly.)
   if (int64_t((n + 511) / 512) * cf.n_q_heads * cf.batch < 512)
-    run_colsum<4, 2, 64>(c, Q, K, colsum, n, s);
+    run_colsum<4, 2, 64>(c, Q, K, colsum, n, int64_t((n + 127) / 128) * cf.n_q_heads * cf.batch > 256, s);
   else
-    run_colsum<8, 1, 64>(c, Q, K, colsum, n, s);
+    run_colsum<8, 1, 64>(c, Q, K, colsum, n, true, s);
   return hipGetLastError();
 }
 
