@@ -271,3 +271,143 @@ def test_a_head_whose_scores_are_nan_stays_inside_its_cache(cache_fp8, split_row
         assert all(np.array_equal(x, y, equal_nan=True) for x, y in zip(c0[lh], c1[lh]))
     K, V, s, p, _ = c1[(1, 0)]
     assert np.isnan(s).all() and np.array_equal(np.sort(p), np.arange(budget)) and np.isfinite(K).all() and np.isfinite(V).all()
+
+
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+@pytest.mark.parametrize("fp8", [False, True])
+def test_generation_step_outputs_to_fp32_accuracy(fp8, G):
+    """P V multiplies on the matrix core with every fp32 probability as three bf16 terms.  The products are
+    exact; an output passes through the sums of 64 rows, 3 terms, 4 wavefronts and the chunks, about 75
+    roundings of 2^-24 of a value of at most max |v|, and the probability and the chunk's factor are rounded
+    once each: 5e-6 max |v|.  Entry counts around the wavefront (64 rows) and the chunk (256), values at both
+    ends of the range (the terms of a small probability times a small row must not be lost)."""
+    storage, Hkv, d = ("fp8" if fp8 else "bf16"), 2, 128
+    for total, vscale in ((1, 1.0), (2, 1.0), (63, 1.0), (64, 1.0), (65, 1.0), (257, 1.0), (700, 1.0), (130, 1e-30), (130, 1e30)):
+        g = np.random.default_rng(100 * G + total)
+        ctx = binding.D2O(1, 1, G * Hkv, Hkv, d, 1024, 1100, dtype="bf16", out_f32=True, cache_fp8=fp8)
+        ctx.d2o_layer_reserve(0, 1000, 1000, 0)  # (nothing is evicted)
+        caches = []
+        for h in range(Hkv):
+            K = ref.round_storage(g.standard_normal((total - 1, d)), "bf16")
+            V = ref.round_storage(vscale * g.standard_normal((total - 1, d)), "bf16")
+            pos, score = np.arange(total - 1, dtype=np.int32), np.ones(total - 1)
+            ctx.d2o_cache_import(0, 0, h, K, V, score, pos, 0.1, 1000)
+            caches.append(ref.HeadCache(ref.round_storage(K, storage), ref.round_storage(V, storage), score.copy(),
+                                        pos.astype(np.int64), 0.1, storage))
+        x = [ref.round_storage(s * g.standard_normal((1, 1, h, d)), "bf16") for h, s in ((G * Hkv, 2.0), (Hkv, 1.0), (Hkv, vscale))]
+        out = torch.empty(1, 1, G * Hkv, d, device="cuda:0")
+        ctx.d2o_decode_step(0, 1, *(torch.from_numpy(a).to(torch.bfloat16).cuda() for a in x), out)
+        got = out[0, 0].double().cpu().numpy()
+        for h, cache in enumerate(caches):
+            want, _ = ref.decode_step_head(cache, x[0][0, 0, h * G:(h + 1) * G], x[1][0, 0, h], x[2][0, 0, h], 1000, 1000, 0, 0, 0.7)
+            err = np.abs(got[h * G:(h + 1) * G] - want).max() / np.abs(cache.V).max()
+            assert err <= 5e-6, f"total {total} scale {vscale} head {h}: {err}"
+        ctx.close()
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,n", [
+    (1, 2, 1, 1), (1, 2, 2, 127), (2, 2, 1, 128), (1, 4, 1, 129), (1, 8, 8, 255), (1, 8, 2, 257), (1, 3, 3, 700),
+    (1, 16, 4, 2049),     # 128-row blocks up to the last that the chip holds at once (272), key blocks in pairs
+    (2, 64, 16, 700),     # 256-row blocks in pairs with a partial last one
+    (2, 128, 16, 513),    # ... and 256-key blocks
+])
+def test_bf16_prompt_attention_block_edges(B, Hq, Hkv, n):
+    """Row blocks of 128 and 256, key blocks of 128 and 256, singly and in pairs, heads in multiples of the
+    XCDs and not, against the oracle on up to three KV heads; all scores must add up to the number of rows."""
+    d, G = 128, Hq // Hkv
+    g = torch.Generator().manual_seed(n + Hq)
+    Q, K, V = (torch.randn(B, h, n, d, generator=g).to(torch.bfloat16) for h in (Hq, Hkv, Hkv))
+    ctx = binding.D2O(B, 1, Hq, Hkv, d, n, n + 2, dtype="bf16", out_f32=True)
+    O = torch.empty(B, Hq, n, d, device="cuda:0")
+    ctx.d2o_prefill_attend(0, Q.cuda(), K.cuda(), V.cuda(), O)
+    score, (_, var) = ctx.d2o_scores_export(0, n), ctx.d2o_get_density(heads=True)
+    Qd, Kd, Vd, got = (binding.tensor_to_f64(t) for t in (Q, K, V, O))
+    assert np.abs(score.sum(-1) / (G * n) - 1.0).max() < 1e-5
+    for b, h in {(0, 0), (B - 1, Hkv - 1), (0, Hkv // 2)}:
+        o, s, v = ref.prefill_kv_head(Qd[b, h * G:(h + 1) * G], Kd[b, h], Vd[b, h])
+        assert H.rownorm_err(got[b, h * G:(h + 1) * G], o) <= H.FLOAT_TOL
+        assert np.abs(score[b, h] - s).max() <= H.FLOAT_TOL * s.max()
+        assert np.abs(var[b, 0, h * G:(h + 1) * G] - v).max() <= H.FLOAT_TOL * max(np.max(v), 1e-3)
+    ctx.close()
+
+
+@pytest.mark.parametrize("dtype,d,fp8", [("bf16", 128, False), ("bf16", 128, True), ("f32", 64, False), ("f32", 128, False)])
+@pytest.mark.parametrize("m,G", [(2, 1), (16, 1), (17, 1), (32, 1), (33, 1), (4, 4), (9, 4), (2, 8), (5, 8), (9, 8)])
+def test_block_append_of_few_query_tiles(dtype, d, fp8, m, G):
+    """One, two, three and more tiles of 16 queries per head, which four, two or one of a workgroup's wavefronts
+    share, on caches that end inside the chunk's 64-row groups and at its end."""
+    storage = "fp8" if fp8 else dtype
+    for budget in (7, 64 - m, 200, 256 - m, 330):
+        if budget < 5:
+            continue
+        _append_against_oracle(dtype, storage, d, G, m, budget, np.arange(400), 400)
+
+
+@pytest.mark.parametrize("positions,next_pos", [
+    (np.arange(0, 32768, 7), 32768),           # one word of the set per thread
+    (np.arange(0, 200000, 41), 200003),        # seven
+    (np.arange(0, 700000, 101), 700001),       # more positions than the set holds: slots compared with each other
+])
+def test_block_append_ranks_any_positions(positions, next_pos):
+    """The position order of a cache, and so the retained, evicted and matched tokens, for small and large
+    positions; three generation steps, which move the last slot into a freed one, run first."""
+    _append_against_oracle("bf16", "bf16", 128, 1, 20, 150, positions, next_pos, steps=3)
+
+
+def test_block_append_keeps_rows_whose_positions_lie_behind_the_next_one():
+    """An imported cache may hold any positions; ones outside the set are ranked by comparison.  Nothing is
+    evicted, so every row must come out of the reordering with its position and score."""
+    g, n, m, d = np.random.default_rng(0), 90, 6, 128
+    pos = np.sort(np.r_[g.choice(3000, 60, replace=False), 40000 + g.choice(10 ** 6, 30, replace=False)]).astype(np.int32)
+    K, V = (ref.round_storage(g.standard_normal((n, d)), "bf16") for _ in range(2))
+    ctx = binding.D2O(1, 1, 1, 1, d, 512, 200, dtype="bf16", out_f32=True, max_append=m)
+    ctx.d2o_layer_reserve(0, 400, 120, 0)
+    ctx.d2o_cache_import(0, 0, 0, K, V, 1.0 + np.arange(n), pos, 0.1, 3000)
+    x = [torch.randn(1, 1, m, d).to(torch.bfloat16).cuda() for _ in range(3)]
+    ctx.d2o_append_chunk(0, *x, torch.empty(1, 1, m, d, device="cuda:0"))
+    gK, gV, gs, gp, _ = ctx.d2o_cache_export(0, 0, 0, 120)
+    order = np.argsort(np.r_[pos, 3000 + np.arange(m)], kind="stable")
+    assert np.array_equal(gp, np.r_[pos, 3000 + np.arange(m)][order])
+    assert np.array_equal(gK, np.r_[K, binding.tensor_to_f64(x[1])[0, 0]][order])
+    assert np.array_equal(gV, np.r_[V, binding.tensor_to_f64(x[2])[0, 0]][order])
+    old = order < n  # every score has grown by at most the block's probabilities
+    grown = gs[old] - (1.0 + order[old])
+    assert grown.min() >= 0 and grown.max() <= m and abs(grown.sum() + gs[~old].sum() - m) < 1e-9
+    ctx.close()
+
+
+def _append_against_oracle(dtype, storage, d, G, m, budget, positions, next_pos, steps=0):
+    Hkv, beta, g = 2, 0.7, np.random.default_rng(m + budget)
+    ctx = binding.D2O(1, 1, G * Hkv, Hkv, d, 512, budget + m + 8, dtype=dtype, beta=beta, out_f32=True, max_append=m,
+                      cache_fp8=storage == "fp8")
+    ctx.d2o_layer_reserve(0, 400, budget, budget // 4)
+    caches, tdt = [], torch.float32 if dtype == "f32" else torch.bfloat16
+    for h in range(Hkv):
+        K, V = (ref.round_storage(g.standard_normal((budget, d)), dtype) for _ in range(2))
+        score, pos = 1.0 + g.random(budget), np.sort(g.choice(positions, budget, replace=False)).astype(np.int32)
+        if positions.max() < next_pos:  # (the recent window holds the last positions)
+            pos[budget - budget // 4:] = np.arange(next_pos - budget // 4, next_pos)
+            pos[:budget - budget // 4] = np.sort(g.choice(positions[positions < next_pos - budget // 4], budget - budget // 4, replace=False))
+        ctx.d2o_cache_import(0, 0, h, K, V, score, pos, 0.1, next_pos)
+        caches.append(ref.HeadCache(ref.round_storage(K, storage), ref.round_storage(V, storage), score.copy(),
+                                    pos.astype(np.int64), 0.1, storage))
+    for t in range(steps):
+        x = [ref.round_storage(g.standard_normal((1, 1, h, d)), dtype) for h in (G * Hkv, Hkv, Hkv)]
+        out = torch.empty(1, 1, G * Hkv, d, device="cuda:0")
+        ctx.d2o_decode_step(0, 1, *(torch.from_numpy(a).to(tdt).cuda() for a in x), out)
+        for h, cache in enumerate(caches):
+            ref.decode_step_head(cache, x[0][0, 0, h * G:(h + 1) * G], x[1][0, 0, h], x[2][0, 0, h], next_pos + t, budget, budget // 4, 0, beta)
+    x = [ref.round_storage(g.standard_normal((1, h, m, d)), dtype) for h in (G * Hkv, Hkv, Hkv)]
+    out = torch.empty(1, G * Hkv, m, d, device="cuda:0")
+    ctx.d2o_append_chunk(0, *(torch.from_numpy(a).to(tdt).cuda() for a in x), out)
+    got = out[0].double().cpu().numpy()
+    for h, cache in enumerate(caches):
+        want, ev = ref.append_chunk_head(cache, x[0][0, h * G:(h + 1) * G], x[1][0, h], x[2][0, h], next_pos + steps, budget,
+                                         budget // 4, 0, beta)
+        assert H.rownorm_err(got[h * G:(h + 1) * G], want) <= H.FLOAT_TOL, f"budget {budget} head {h}"
+        evi, tgt, us, ps = ctx.d2o_append_events(0, 0, h, budget + m)
+        assert np.array_equal(evi, ev.evicted) and np.array_equal(tgt, ev.target) and np.array_equal(ps, ev.passed), f"budget {budget} head {h}"
+        gK, gV, gs, gp, gtau = ctx.d2o_cache_export(0, 0, h, budget + m)
+        assert np.array_equal(gp, cache.pos) and np.array_equal(gK, cache.K) and np.array_equal(gV, cache.V)
+        np.testing.assert_allclose(gs, cache.score, rtol=1e-12)
+    ctx.close()
