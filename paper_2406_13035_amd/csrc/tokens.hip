@@ -279,6 +279,10 @@ __global__ __launch_bounds__(256) void gather_kernel(const T* __restrict__ K, Vi
 //     repeats the first one's arithmetic exactly, so the best value is found again.  Few rows are
 //     flagged (a workgroup or two per head), so the retained keys are split over `ksplit`
 //     workgroups per row block: the lists are appended with atomics and read order-free.
+// The filter is bound by the vector ALU (68 instructions per 32 x 32 sub-tile and wavefront beside 8 products), as
+// long as no wavefront waits for LDS: with the operands and inverse norms requested half a sub-tile ahead and the
+// padding confined to the last tile, at four wavefronts per SIMD, 940 -> 867 us (32768 tokens, 32 heads, a tenth
+// kept), 37 -> 34 (4096, a fifth), 54 -> 41 (256 of 2304 rows leave).
 // kAmbiguous bounds twice the error of one filtered cosine: at most one rounding per accumulated
 // product (128 * 2^-24 of |k_i||k_j|) plus the two fp32 inverse norms, 1.6e-5 in total, plus the
 // four mantissa bits that carry the register number (2 * 16 * 2^-24 = 1.9e-6).
@@ -287,7 +291,7 @@ constexpr int kMaxCand = 8;
 constexpr int kLdM = 128 + 8;
 
 template <bool COLLECT>
-__global__ __launch_bounds__(256) void match_filter_bf16(const uint16_t* __restrict__ K, View kv,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(COLLECT ? 3 : 4, 4))) void match_filter_bf16(const uint16_t* __restrict__ K, View kv,
                                                          const uint16_t* __restrict__ cK,
                                                          const int32_t* __restrict__ meta, int64_t slots,
                                                          const float* __restrict__ invn,
@@ -337,6 +341,7 @@ __global__ __launch_bounds__(256) void match_filter_bf16(const uint16_t* __restr
   const int tper = (ntile + ksplit - 1) / ksplit;
   const int tbeg = part * tper, tend = min(ntile, tbeg + tper);  // this workgroup's tiles
   if (tbeg >= tend) return;
+  const int tfull = min(tend, nret / kTile);  // the first tile that is not full
   auto issue = [&](int t) {
     const int r0 = t * kTile;
 #pragma unroll
@@ -357,33 +362,44 @@ __global__ __launch_bounds__(256) void match_filter_bf16(const uint16_t* __restr
       rbias[buf][tid] = rv < 0.f ? -3.0e38f : 0.f;
     }
   };
-  auto one_tile = [&](int t) {
+  auto one_tile = [&](int t, auto last) {  // `last`: the tile that may hold rows past the end
+    constexpr bool padded = decltype(last)::value;
     const int buf = t & 1, r0 = t * kTile;
     if (t + 1 < tend) issue(t + 1);
-    const int nsub = min(kTile / 32, (nret - r0 + 31) / 32);
-    const bool padded = r0 + kTile > nret;  // only the last tile can hold rows past the end
+    auto operand = [&](int st, int ks) {
+      return *reinterpret_cast<const bf16x8*>(&Rs[buf][(st * 32 + m) * kLdM + ks * 16 + h * 8]);
+    };
+    bf16x8 a[4];
+    f32x4 ri[4];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) a[ks] = operand(0, ks);
+    // The operands of the second four products arrive during the first four, those of the next sub-tile's first
+    // four and the inverse norms during the second four.
     auto mma = [&](int st) -> f32x16 {
-      bf16x8 a[8];
-#pragma unroll
-      for (int ks = 0; ks < 8; ++ks)
-        a[ks] = *reinterpret_cast<const bf16x8*>(&Rs[buf][(st * 32 + m) * kLdM + ks * 16 + h * 8]);
       const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      f32x16 s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], be[0], zero, 0, 0, 0);
+      f32x16 s = zero;
 #pragma unroll
-      for (int ks = 1; ks < 8; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks], be[ks], s, 0, 0, 0);
+      for (int ks = 0; ks < 8; ++ks) {
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks & 3], be[ks], s, 0, 0, 0);
+        if (ks < 4)
+          a[ks] = operand(st, ks + 4);
+        else if (st == 0)
+          a[ks & 3] = operand(1, ks & 3);
+        if (ks >= 4) ri[ks & 3] = *reinterpret_cast<const f32x4*>(&rin[buf][st * 32 + (ks & 3) * 8 + h * 4]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
       return s;
     };
     auto post = [&](const f32x16& s, int st) {
       // register r: retained row st*32 + (r/4)*8 + 4h + r%4 of this tile, evicted row = lane's;
-      // the four rows of a register group are neighbours, so their 1/|k| come in one LDS read
+      // the four rows of a register group are neighbours, so their 1/|k| came in one LDS read
       float tv[16];
 #pragma unroll
       for (int g4 = 0; g4 < 4; ++g4) {
         const int rb = st * 32 + g4 * 8 + h * 4;
-        const f32x4 ri = *reinterpret_cast<const f32x4*>(&rin[buf][rb]);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) tv[g4 * 4 + i] = s[g4 * 4 + i] * ri[i];
-        if (padded) {  // block-uniform
+        for (int i = 0; i < 4; ++i) tv[g4 * 4 + i] = s[g4 * 4 + i] * ri[g4][i];
+        if (padded) {
           const f32x4 bi = *reinterpret_cast<const f32x4*>(&rbias[buf][rb]);
 #pragma unroll
           for (int i = 0; i < 4; ++i) tv[g4 * 4 + i] += bi[i];
@@ -407,19 +423,26 @@ __global__ __launch_bounds__(256) void match_filter_bf16(const uint16_t* __restr
         // decided by the exact refinement.
         const float before = m1;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const float key = __uint_as_float((__float_as_uint(tv[r]) & ~15u) | uint32_t(r));
-          m2 = __builtin_amdgcn_fmed3f(m1, m2, key);
-          // (the maximum as the instruction itself: fmaxf would first re-canonicalise a value
-          // that was put together from bits)
-          asm("v_max_f32 %0, %1, %2" : "=v"(m1) : "v"(m1), "v"(key));
+        for (int r = 0; r < 16; r += 4) {
+          float key[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) key[i] = __uint_as_float((__float_as_uint(tv[r + i]) & ~15u) | uint32_t(r + i));
+          // (the maximum as the instruction itself: fmaxf would first re-canonicalise a value that was put
+          // together from bits; and in pairs: apart, the compiler runs all maxima first and keeps them)
+          asm("v_med3_f32 %1, %0, %1, %2\n\tv_max_f32 %0, %0, %2\n\t"
+              "v_med3_f32 %1, %0, %1, %3\n\tv_max_f32 %0, %0, %3\n\t"
+              "v_med3_f32 %1, %0, %1, %4\n\tv_max_f32 %0, %0, %4\n\t"
+              "v_med3_f32 %1, %0, %1, %5\n\tv_max_f32 %0, %0, %5"
+              : "+&v"(m1), "+&v"(m2)
+              : "v"(key[0]), "v"(key[1]), "v"(key[2]), "v"(key[3]));
         }
         isub = (m1 != before) ? (r0 + st * 32) : isub;
       }
     };
     // (two sub-tiles as two independent accumulation chains need 160 registers and cost a
     // wavefront per SIMD: slower)
-    for (int st = 0; st < nsub; ++st) post(mma(st), st);
+    post(mma(0), 0);
+    if (!padded || nret - r0 > 32) post(mma(1), 1);
     if (t + 1 < tend) stage(buf ^ 1);
     __syncthreads();
   };
@@ -427,7 +450,8 @@ __global__ __launch_bounds__(256) void match_filter_bf16(const uint16_t* __restr
   stage(tbeg & 1);
   __syncthreads();
 #pragma unroll 1
-  for (int t = tbeg; t < tend; ++t) one_tile(t);
+  for (int t = tbeg; t < tfull; ++t) one_tile(t, std::false_type{});
+  if (tfull < tend) one_tile(tfull, std::true_type{});
   if (COLLECT) return;
   // the best's retained rank: its sub-tile, and the register number carried in its low bits
   const int rbest = int(__float_as_uint(m1) & 15u);
