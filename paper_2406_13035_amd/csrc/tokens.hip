@@ -290,6 +290,60 @@ constexpr float kAmbiguous = 2.4e-5f;
 constexpr int kMaxCand = 8;
 constexpr int kLdM = 128 + 8;
 
+// Best and second-best value of a lane's evicted row, two operations per value: the low four
+// mantissa bits of a value are replaced by its register number (a change of at most 16
+// units in the last place, which kAmbiguous covers), so that the maximum carries the
+// position inside the sub-tile with it; which sub-tile it came from is noted once per
+// sub-tile.  Values that are equal up to those bits end up flagged as ambiguous and are
+// decided by the exact refinement.
+struct BestTwo {
+  float m1 = -INFINITY, m2 = -INFINITY;
+  int isub = 0;  // first retained rank of the sub-tile the best came from
+  __device__ __forceinline__ void take(const float (&tv)[16], int first) {
+    const float before = m1;
+#pragma unroll
+    for (int r = 0; r < 16; r += 4) {
+      float key[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) key[i] = __uint_as_float((__float_as_uint(tv[r + i]) & ~15u) | uint32_t(r + i));
+      // (the maximum as the instruction itself: fmaxf would first re-canonicalise a value that was put
+      // together from bits; and in pairs: apart, the compiler runs all maxima first and keeps them)
+      asm("v_med3_f32 %1, %0, %1, %2\n\tv_max_f32 %0, %0, %2\n\t"
+          "v_med3_f32 %1, %0, %1, %3\n\tv_max_f32 %0, %0, %3\n\t"
+          "v_med3_f32 %1, %0, %1, %4\n\tv_max_f32 %0, %0, %4\n\t"
+          "v_med3_f32 %1, %0, %1, %5\n\tv_max_f32 %0, %0, %5"
+          : "+&v"(m1), "+&v"(m2)
+          : "v"(key[0]), "v"(key[1]), "v"(key[2]), "v"(key[3]));
+    }
+    isub = (m1 != before) ? first : isub;
+  }
+  // the best's retained rank: its sub-tile, and the register number carried in its low bits (h: the lane's half)
+  __device__ __forceinline__ int rank(int h) const {
+    const int r = int(__float_as_uint(m1) & 15u);
+    return isub + (r >> 2) * 8 + h * 4 + (r & 3);
+  }
+};
+
+// Adds another candidate for best, of retained rank oi, and its second to (best, second, bi).
+__device__ __forceinline__ void join_best(float& best, float& second, int& bi, float om1, float om2, int oi) {
+  second = fmaxf(fminf(best, om1), fmaxf(second, om2));
+  bi = (om1 > best) ? oi : bi;
+  best = fmaxf(best, om1);
+}
+
+// A row's candidate, its threshold for the second sweep, and the list of ambiguous rows.  ie: the row's inverse norm.
+__device__ __forceinline__ void note_row(float best, float second, int bi, float ie, int erank, int64_t base, int64_t bh,
+                                         int32_t* cand, float* thr, int32_t* amb_list, int32_t* amb_cnt, int32_t* ncand) {
+  const float margin = ie > 0.f ? kAmbiguous / ie : INFINITY;  // threshold in the un-normalised domain
+  const bool amb = !(best - second >= margin);                // also true for NaN / equal / zero norm
+  cand[base + erank] = bi | (amb ? int(0x80000000u) : 0);
+  thr[base + erank] = best - margin;
+  if (amb) {
+    amb_list[base + atomicAdd(&amb_cnt[bh], 1)] = erank;
+    ncand[base + erank] = 0;
+  }
+}
+
 template <bool COLLECT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(COLLECT ? 3 : 4, 4))) void match_filter_bf16(const uint16_t* __restrict__ K, View kv,
                                                          const uint16_t* __restrict__ cK,
@@ -330,8 +384,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(COLLECT ? 3
 #pragma unroll
   for (int ks = 0; ks < 8; ++ks)
     be[ks] = *reinterpret_cast<const bf16x8*>(kb + int64_t(epos) * kv.sn + ks * 16 + h * 8);
-  float m1 = -INFINITY, m2 = -INFINITY;
-  int isub = 0;  // first retained rank of the sub-tile the running best came from
+  BestTwo two;
   const float mythr = COLLECT ? thr[bh * npad + erank] : 0.f;
   // Tiles travel global -> registers -> LDS: the next tile is requested when work on a tile
   // starts and written to the other LDS buffer when it ends.
@@ -415,28 +468,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(COLLECT ? 3
           }
         }
       } else {
-        // Running best and second best of the lane's row, two operations per value: the low four
-        // mantissa bits of a value are replaced by its register number (a change of at most 16
-        // units in the last place, which kAmbiguous covers), so that the maximum carries the
-        // position inside the sub-tile with it; which sub-tile it came from is noted once per
-        // sub-tile.  Values that are equal up to those bits end up flagged as ambiguous and are
-        // decided by the exact refinement.
-        const float before = m1;
-#pragma unroll
-        for (int r = 0; r < 16; r += 4) {
-          float key[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) key[i] = __uint_as_float((__float_as_uint(tv[r + i]) & ~15u) | uint32_t(r + i));
-          // (the maximum as the instruction itself: fmaxf would first re-canonicalise a value that was put
-          // together from bits; and in pairs: apart, the compiler runs all maxima first and keeps them)
-          asm("v_med3_f32 %1, %0, %1, %2\n\tv_max_f32 %0, %0, %2\n\t"
-              "v_med3_f32 %1, %0, %1, %3\n\tv_max_f32 %0, %0, %3\n\t"
-              "v_med3_f32 %1, %0, %1, %4\n\tv_max_f32 %0, %0, %4\n\t"
-              "v_med3_f32 %1, %0, %1, %5\n\tv_max_f32 %0, %0, %5"
-              : "+&v"(m1), "+&v"(m2)
-              : "v"(key[0]), "v"(key[1]), "v"(key[2]), "v"(key[3]));
-        }
-        isub = (m1 != before) ? (r0 + st * 32) : isub;
+        two.take(tv, r0 + st * 32);
       }
     };
     // (two sub-tiles as two independent accumulation chains need 160 registers and cost a
@@ -453,25 +485,109 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(COLLECT ? 3
   for (int t = tbeg; t < tfull; ++t) one_tile(t, std::false_type{});
   if (tfull < tend) one_tile(tfull, std::true_type{});
   if (COLLECT) return;
-  // the best's retained rank: its sub-tile, and the register number carried in its low bits
-  const int rbest = int(__float_as_uint(m1) & 15u);
-  const int i1 = isub + (rbest >> 2) * 8 + h * 4 + (rbest & 3);
   // combine the two lane halves that share an evicted row
-  const float om1 = __shfl_xor(m1, 32, 64), om2 = __shfl_xor(m2, 32, 64);
-  const int oi1 = __shfl_xor(i1, 32, 64);
-  const float best = fmaxf(m1, om1);
-  const float second = fmaxf(fminf(m1, om1), fmaxf(m2, om2));
-  const int bi = (om1 > m1) ? oi1 : i1;
-  if (h == 0 && live) {
-    const float ie = inl[epos];
-    const float margin = ie > 0.f ? kAmbiguous / ie : INFINITY;  // threshold in the un-normalised domain
-    const bool amb = !(best - second >= margin);                // also true for NaN / equal / zero norm
-    cand[bh * npad + erank] = bi | (amb ? int(0x80000000u) : 0);
-    thr[bh * npad + erank] = best - margin;
-    if (amb) {
-      amb_list[bh * npad + atomicAdd(&amb_cnt[bh], 1)] = erank;
-      ncand[bh * npad + erank] = 0;
+  float best = two.m1, second = two.m2;
+  int bi = two.rank(h);
+  join_best(best, second, bi, __shfl_xor(best, 32, 64), __shfl_xor(second, 32, 64), __shfl_xor(bi, 32, 64));
+  if (h == 0 && live) note_row(best, second, bi, inl[epos], erank, bh * npad, bh, cand, thr, amb_list, amb_cnt, ncand);
+}
+
+// The first sweep for launches of few rows: 32 evicted rows per workgroup, whose wavefronts take the 32-key sub-tiles
+// in turn, operands and inverse norms straight from memory one sub-tile ahead (no wavefront shares
+// them, so LDS would only add a barrier per tile), and join their best two at the end.  Same values, in
+// the same order of products.  Bound by the operands' way from the L2, which every 32 rows take (eight
+// wavefronts instead of four: level).  A launch of few rows leaves most of the chip idle in blocks of 128: both
+// sweeps of 32 heads, 256 rows against 2048 keys, 53 -> 37 us, 200 against 800 keys 29 -> 22; from two workgroups per
+// CU on the blocks of 128, which read the keys a quarter as often, are the faster ones (512 rows against 128 keys 18.4
+// where this takes 20.4, 800 against 200 18.5 where it takes 31).
+constexpr int kFewWaves = 4;
+__global__ __launch_bounds__(64 * kFewWaves) void match_filter_few(const uint16_t* __restrict__ K, View kv,
+                                                                   const uint16_t* __restrict__ cK,
+                                                                   const int32_t* __restrict__ meta, int64_t slots,
+                                                                   const float* __restrict__ invn,
+                                                                   const int32_t* __restrict__ ret,
+                                                                   const int32_t* __restrict__ evi,
+                                                                   const int32_t* __restrict__ cnt,
+                                                                   int32_t* __restrict__ cand, float* __restrict__ thr,
+                                                                   int32_t* __restrict__ amb_list,
+                                                                   int32_t* __restrict__ amb_cnt,
+                                                                   int32_t* __restrict__ ncand, int npad) {
+  __shared__ __attribute__((aligned(16))) float rin[kFewWaves][32];  // of the wavefront's sub-tile
+  __shared__ float best_s[kFewWaves][32], second_s[kFewWaves][32];
+  __shared__ int rank_s[kFewWaves][32];
+  const int hk = blockIdx.y, b = blockIdx.z, Hkv = gridDim.y;
+  const int64_t bh = int64_t(b) * Hkv + hk;
+  const int nret = cnt[bh * 2], nevi = cnt[bh * 2 + 1];
+  const int e0 = int(blockIdx.x) * 32;
+  if (e0 >= nevi || nret == 0) return;
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, m = lane & 31, h = lane >> 5;
+  const uint16_t* rk = cK + (bh * slots + meta[bh * 4 + 0]) * 128;
+  const int32_t* rl = ret + bh * npad;
+  const float* inl = invn + bh * npad;
+  const int erank = min(e0 + m, nevi - 1);
+  const int epos = evi[bh * npad + erank];
+  const uint16_t* erow = K + b * kv.sb + hk * kv.sh + int64_t(epos) * kv.sn;
+  bf16x8 be[8];
+#pragma unroll
+  for (int ks = 0; ks < 8; ++ks) be[ks] = *reinterpret_cast<const bf16x8*>(erow + ks * 16 + h * 8);
+  const int nsub = (nret + 31) / 32;
+  auto rank_of = [&](int j) { return min(j * 32 + m, nret - 1); };
+  auto load = [&](bf16x8 (&a)[8], int j) {
+    const uint16_t* row = rk + int64_t(rank_of(j)) * 128 + h * 8;
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) a[ks] = *reinterpret_cast<const bf16x8*>(row + ks * 16);
+  };
+  BestTwo two;
+  // a, norm: sub-tile j; a_next, norm_next: the wavefront's next one; pos: the position of the row behind that
+  auto one = [&](int j, const bf16x8 (&a)[8], float norm, bf16x8 (&a_next)[8], float& norm_next, int& pos) {
+    if (h == 0) rin[w][m] = norm;
+    __builtin_amdgcn_wave_barrier();
+    load(a_next, j + kFewWaves);
+    norm_next = inl[pos];
+    pos = rl[rank_of(j + 2 * kFewWaves)];
+    f32x16 s = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks], be[ks], s, 0, 0, 0);
+    float tv[16];
+#pragma unroll
+    for (int g4 = 0; g4 < 4; ++g4) {
+      const f32x4 ri = *reinterpret_cast<const f32x4*>(&rin[w][g4 * 8 + h * 4]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) tv[g4 * 4 + i] = s[g4 * 4 + i] * ri[i];
     }
+    if (j * 32 + 32 > nret) {  // copies of the last row past the end: the lowest value, or NaN as the row itself
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (j * 32 + (r >> 2) * 8 + h * 4 + (r & 3) >= nret) tv[r] = s[r] * 0.f - 3.0e38f;
+    }
+    two.take(tv, j * 32);
+    __builtin_amdgcn_wave_barrier();
+  };
+  bf16x8 a0[8], a1[8];
+  float n0 = 0.f, n1 = 0.f;
+  if (w < nsub) {
+    load(a0, w);
+    int pos = rl[rank_of(w + kFewWaves)];
+    n0 = inl[rl[rank_of(w)]];
+#pragma unroll 1
+    for (int j = w; j < nsub; j += 2 * kFewWaves) {
+      one(j, a0, n0, a1, n1, pos);
+      if (j + kFewWaves < nsub) one(j + kFewWaves, a1, n1, a0, n0, pos);
+    }
+  }
+  float best = two.m1, second = two.m2;
+  int bi = two.rank(h);
+  join_best(best, second, bi, __shfl_xor(best, 32, 64), __shfl_xor(second, 32, 64), __shfl_xor(bi, 32, 64));
+  if (h == 0) {
+    best_s[w][m] = best;
+    second_s[w][m] = second;
+    rank_s[w][m] = bi;
+  }
+  __syncthreads();
+  if (tid < 32 && e0 + tid < nevi) {
+#pragma unroll
+    for (int u = 1; u < kFewWaves; ++u) join_best(best, second, bi, best_s[u][tid], second_s[u][tid], rank_s[u][tid]);
+    note_row(best, second, bi, inl[epos], erank, bh * npad, bh, cand, thr, amb_list, amb_cnt, ncand);
   }
 }
 
@@ -1006,11 +1122,18 @@ hipError_t launch_match(d2o_ctx* c, int layer, View K, int n, hipStream_t s) {
     const dim3 gf((me + 127) / 128, cf.n_kv_heads, cf.batch);
     {
       KernelTimer kt(c, D2O_K_MATCH_FILTER, s);
-      match_filter_bf16<false><<<gf, 256, 0, s>>>((const uint16_t*)K.ptr, K, (const uint16_t*)prompt_rows_K(c),
-                                                  prompt_rows_meta(c, layer), prompt_rows_stride(c),
-                                                  c->invnorm, c->sel_ret, c->sel_evi,
-                                                  c->sel_cnt, c->m_cand, c->m_thr, c->amb_list, c->amb_cnt,
-                                                  c->m_ncand, c->m_clist, c->npad, 1);
+      // Up to a workgroup of 32 rows per CU: blocks of 128 rows would leave three CUs of four idle.
+      const dim3 few((me + 31) / 32, cf.n_kv_heads, cf.batch);
+      if (int64_t(few.x) * few.y * few.z <= 256)
+        match_filter_few<<<few, 64 * kFewWaves, 0, s>>>(
+            (const uint16_t*)K.ptr, K, (const uint16_t*)prompt_rows_K(c), prompt_rows_meta(c, layer), prompt_rows_stride(c),
+            c->invnorm, c->sel_ret, c->sel_evi, c->sel_cnt, c->m_cand, c->m_thr, c->amb_list, c->amb_cnt, c->m_ncand, c->npad);
+      else
+        match_filter_bf16<false><<<gf, 256, 0, s>>>((const uint16_t*)K.ptr, K, (const uint16_t*)prompt_rows_K(c),
+                                                    prompt_rows_meta(c, layer), prompt_rows_stride(c),
+                                                    c->invnorm, c->sel_ret, c->sel_evi,
+                                                    c->sel_cnt, c->m_cand, c->m_thr, c->amb_list, c->amb_cnt,
+                                                    c->m_ncand, c->m_clist, c->npad, 1);
       constexpr int kSplit = 8;
       match_filter_bf16<true><<<dim3(gf.x * kSplit, gf.y, gf.z), 256, 0, s>>>((const uint16_t*)K.ptr, K, (const uint16_t*)prompt_rows_K(c),
                                                  prompt_rows_meta(c, layer), prompt_rows_stride(c),

@@ -411,3 +411,33 @@ def _append_against_oracle(dtype, storage, d, G, m, budget, positions, next_pos,
         assert np.array_equal(gp, cache.pos) and np.array_equal(gK, cache.K) and np.array_equal(gV, cache.V)
         np.testing.assert_allclose(gs, cache.score, rtol=1e-12)
     ctx.close()
+
+
+# Matching with the rows spread over workgroups of 32 (up to 256 of them) and of 128 (beyond): one row, remainders of
+# both tiles, fewer retained keys than wavefronts have sub-tiles for, the last launch of the one kind and the
+# first of the other (8 heads x 32 blocks), a padded last tile; with twin retained keys, whose first one wins.
+@pytest.mark.parametrize("B,Hkv,n,budget", [
+    (1, 1, 33, 32), (1, 2, 40, 7), (1, 1, 65, 32), (1, 2, 97, 33), (2, 3, 700, 191), (1, 1, 3000, 2433), (1, 2, 4000, 64),
+    (2, 4, 1124, 100), (2, 4, 1125, 100), (2, 4, 1200, 127), (2, 4, 1200, 128), (2, 4, 1200, 129), (2, 4, 1300, 161)])
+def test_matching_of_few_and_of_many_rows(B, Hkv, n, budget):
+    g = np.random.default_rng(n + budget)
+    K, V = (ref.round_storage(g.standard_normal((B, Hkv, n, 128)), "bf16") for _ in range(2))
+    score = g.random((B, Hkv, n)).astype(np.float32)
+    top = np.argsort(-score[..., :n - 1], axis=-1)[..., :4]  # (the last position is retained as the recent one)
+    if budget > 8:
+        for b in range(B):
+            for h in range(Hkv):
+                K[b, h, top[b, h, 1]] = K[b, h, top[b, h, 0]]
+                K[b, h, top[b, h, 3]] = K[b, h, top[b, h, 0]]
+    ctx = binding.D2O(B, 1, Hkv, Hkv, 128, n, budget + 8, dtype="bf16")
+    ctx.d2o_scores_import(0, score)
+    ctx.d2o_compress_layer(0, *(torch.from_numpy(x).to(torch.bfloat16).cuda() for x in (K, V)), budget, 1)
+    for b in range(B):
+        for h in range(Hkv):
+            ret, evi, tgt, _, _ = ctx.d2o_prefill_events(0, b, h, n)
+            assert len(ret) == budget and len(evi) == n - budget
+            x = K[b, h].astype(np.float64)
+            norm = np.sqrt((x * x).sum(-1))
+            cos = (x[evi] @ x[ret].T) / (norm[evi][:, None] * norm[ret][None, :])
+            assert np.array_equal(tgt, ret[cos.argmax(-1)]), f"sequence {b} head {h}"
+    ctx.close()
