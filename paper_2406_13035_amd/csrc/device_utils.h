@@ -124,6 +124,8 @@ constexpr int kDppXor1 = 0xB1;         // quad_perm [1,0,3,2]
 constexpr int kDppXor2 = 0x4E;         // quad_perm [2,3,0,1]
 constexpr int kDppHalfMirror = 0x141;  // lane i <-> 7 - i within 8
 constexpr int kDppMirror = 0x140;      // lane i <-> 15 - i within 16
+constexpr int kDppRor4 = 0x124;        // lane i <- (i - 4) mod 16 within 16
+constexpr int kDppRor8 = 0x128;        // lane i <-> i ^ 8 within 16
 template <int CTRL>
 __device__ __forceinline__ int dpp_i32(int v) {
   return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, true);
@@ -190,12 +192,15 @@ __device__ __forceinline__ double row16_sum(double v) {
   return v;
 }
 
-__device__ __forceinline__ float row16_sum(float v) {
+// Sum over each half of the wavefront (32 lanes) by halves: lanes 16 apart first, then 8, 4, 2 and 1 apart
+// (once lanes eight apart agree, a rotation by four reaches the lane four apart); every lane gets its half's sum.
+__device__ __forceinline__ float half_wave_sum(float v) {
   auto moved = [](auto ctrl, float x) { return __int_as_float(dpp_i32<decltype(ctrl)::value>(__float_as_int(x))); };
-  v += moved(std::integral_constant<int, kDppXor1>{}, v);
+  v += __shfl_xor(v, 16, 64);
+  v += moved(std::integral_constant<int, kDppRor8>{}, v);
+  v += moved(std::integral_constant<int, kDppRor4>{}, v);
   v += moved(std::integral_constant<int, kDppXor2>{}, v);
-  v += moved(std::integral_constant<int, kDppHalfMirror>{}, v);
-  v += moved(std::integral_constant<int, kDppMirror>{}, v);
+  v += moved(std::integral_constant<int, kDppXor1>{}, v);
   return v;
 }
 

@@ -564,11 +564,11 @@ __global__ __launch_bounds__(64 * KW * QW) __attribute__((amdgpu_waves_per_eu(4,
       if (jt > 0) stage(buf ^ 1);
       __syncthreads();
     }
-    // add the 32 query columns held by the lanes of each half, then the groups that shared the tiles
+    // add the 32 query columns held by the lanes of each half (by halves: the selection of a long prompt decides
+    // near-ties on a score's last bits, so the order stays as it is), then the groups that shared the tiles
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      float v = row16_sum(acc[r]);
-      v += __shfl_xor(v, 16, 64);
+      const float v = half_wave_sum(acc[r]);
       if (m == 0) cs[qw][kw * 32 + (r >> 2) * 8 + h * 4 + (r & 3)] = v;
     }
     __syncthreads();

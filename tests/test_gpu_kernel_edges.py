@@ -331,6 +331,27 @@ def test_bf16_prompt_attention_block_edges(B, Hq, Hkv, n):
     ctx.close()
 
 
+@pytest.mark.parametrize("n", [17, 20, 27, 32])
+def test_column_sums_add_a_tile_of_queries_by_halves(n):
+    """The order of a score's fp32 additions decides near-tied selections, so it is held exactly: the 32 queries of a
+    tile are added by halves (16 apart, 8, 4, 2, 1).  Keys of zeros make every logit zero: the probability of a query is one
+    number for all its keys, and the last key's score is the last query's probability alone."""
+    ctx = binding.D2O(1, 1, 1, 1, 128, 32, 34, dtype="bf16", out_f32=True)
+    x, zero = torch.ones(1, 1, 32, 128, dtype=torch.bfloat16, device="cuda:0"), torch.zeros(1, 1, 32, 128, dtype=torch.bfloat16, device="cuda:0")
+    prob = np.zeros(32, dtype=np.float32)
+    for i in range(n):
+        ctx.d2o_reset()
+        ctx.d2o_prefill_attend(0, x[:, :, :i + 1], zero[:, :, :i + 1], x[:, :, :i + 1])
+        score = ctx.d2o_scores_export(0, i + 1)[0, 0]
+        prob[i] = score[i]
+    for key in range(n):
+        v = np.where(np.arange(32) >= key, prob, np.float32(0))
+        for step in (16, 8, 4, 2, 1):
+            v = v[:step] + v[step:2 * step]
+        assert score[key] == v[0], f"key {key}: {score[key]} {v[0]}"
+    ctx.close()
+
+
 @pytest.mark.parametrize("dtype,d,fp8", [("bf16", 128, False), ("bf16", 128, True), ("f32", 64, False), ("f32", 128, False)])
 @pytest.mark.parametrize("m,G", [(2, 1), (16, 1), (17, 1), (32, 1), (33, 1), (4, 4), (9, 4), (2, 8), (5, 8), (9, 8)])
 def test_block_append_of_few_query_tiles(dtype, d, fp8, m, G):
