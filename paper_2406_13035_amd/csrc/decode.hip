@@ -569,8 +569,8 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
   // cost six, 190 of a bf16 chunk's 2300 vector instructions per wavefront).
   const int sub = __builtin_amdgcn_readfirstlane(grp * (kChunk / kSub) + w);
   const int rows = min(kSub, total - sub * kSub);  // <= 0: nothing for this wavefront
-  // The new token's row: its wavefront (at most one of the head) writes it to the cache, and takes its
-  // products and its term of P V from registers; the streams end before it.
+  // The new token's row: its wavefront (at most one of the head) writes it to the cache, puts its K among the staged
+  // rows and takes its term of P V from registers; the streams end before it.
   const int jnew = count - sub * kSub;
   const bool owner = jnew >= 0 && jnew < kSub;
   const uint32_t cached = uint32_t(max(min(kSub, jnew), 0) * RB);
@@ -623,28 +623,30 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
     cn[c] = sqrt(fast_wave_sum(part));
   }
   if (!kOwnOpnd) lds_barrier();  // the operands are in LDS; the K rows may still be on their way
-  // the new row's K and V as they enter the cache
-  double knew[E];
+  // the new row's K and V as they enter the cache: K as stored, with an fp8 row's power of two, and V's values
+  typename RowShare::Bits knew = 0;
+  int kexp = 0;
   float vnew[E];
   if (owner) {
-    double x[E], y[E];
-    Share::widen(kraw, x);
+    double y[E];
     Share::widen(vraw, y);
     T* Kc = static_cast<T*>(a.cK) + (slot0 + count) * D;
     T* Vc = static_cast<T*>(a.cV) + (slot0 + count) * D;
-    typename RowShare::Bits kst, vst;
+    typename RowShare::Bits vst;
     if constexpr (sizeof(T) == 1) {
       // fp8 cache: encoded; the row's largest magnitude decides its power of two
       static_assert(E == 2, "two elements per lane");
+      double x[E];
+      Share::widen(kraw, x);
       const int ek = fp8_row_exponent(fast_wave_max(fmax(fabs(x[0]), fabs(x[1]))));
       const int ev = fp8_row_exponent(fast_wave_max(fmax(fabs(y[0]), fabs(y[1]))));
-      kst = vst = 0;
+      kexp = ek;
+      vst = 0;
 #pragma unroll
       for (int e = 0; e < E; ++e) {
         const uint8_t ck = fp8_encode(ldexp(x[e], -ek)), cv = fp8_encode(ldexp(y[e], -ev));
-        kst |= typename RowShare::Bits(ck) << (8 * e);
+        knew |= typename RowShare::Bits(ck) << (8 * e);
         vst |= typename RowShare::Bits(cv) << (8 * e);
-        knew[e] = Elem<T>::to_f64(ck) * pow2_f64(ek);
         vnew[e] = Elem<T>::to_f32(cv) * pow2_f32(ev);
       }
       if (lane == 0) {
@@ -652,16 +654,13 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
         st_agent(a.cVe + slot0 + count, int8_t(ev));
       }
     } else {
-      kst = kraw;
+      knew = kraw;
       vst = vraw;
 #pragma unroll
-      for (int e = 0; e < E; ++e) {
-        knew[e] = x[e];
-        vnew[e] = float(y[e]);
-      }
+      for (int e = 0; e < E; ++e) vnew[e] = float(y[e]);
     }
     // (write-through: the head's closing workgroup may read the row in this launch, and stores the score again)
-    st_agent(reinterpret_cast<typename RowShare::Bits*>(Kc) + lane, kst);
+    st_agent(reinterpret_cast<typename RowShare::Bits*>(Kc) + lane, knew);
     st_agent(reinterpret_cast<typename RowShare::Bits*>(Vc) + lane, vst);
     if (lane == 0) {
       st_agent(a.cscore + slot0 + count, 0.0);
@@ -716,9 +715,10 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
     // fp8 cache: the powers of two of this lane's K and V row
     int rek = 0, rev = 0;
     if constexpr (sizeof(T) == 1) {
-      rek = valid && !fresh ? a.cKe[slot0 + j] : 0;
+      rek = fresh ? kexp : valid ? a.cKe[slot0 + j] : 0;
       rev = valid && !fresh ? a.cVe[slot0 + j] : -120;
     }
+    constexpr int kShareLanes = kPiece / int(sizeof(knew));  // lanes that hold a piece of the new row
     auto stage_piece = [&](int p) {
       // The staging area is private to the wavefront and LDS serves a wavefront's requests in
       // order, so the piece hand-over needs compiler ordering only.
@@ -728,6 +728,16 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
 #pragma unroll
         for (int i = 0; i < 8; ++i)
           *reinterpret_cast<u32x4*>(srow + (((2 * i) & 3) * 4 + (i >> 1)) * kPitch) = kreg[i];
+      }
+      // The new row, over the zeros that were loaded in its place: its sums then have the order of every other
+      // row's, so that twin keys tie (fp32 rows: an order of its own made the newer of two twins the
+      // better match in a third of all cases).
+      if (owner) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (ln / kShareLanes == p)
+          *reinterpret_cast<typename RowShare::Bits*>(mine + (jnew & 3) * kSetBytes + (((jnew >> 2) & 3) * 4 + (jnew >> 4)) * kPitch +
+                                                      ln % kShareLanes * int(sizeof(knew))) = knew;
       }
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
@@ -815,21 +825,6 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
 #pragma unroll
       for (int v = 0; v < NV; ++v) dot[v] *= sk;
       nr *= sk * sk;
-    }
-    if (owner) {  // the new row's products: E of its elements per lane, summed over the wavefront
-      double nn = 0.0;
-#pragma unroll
-      for (int e = 0; e < E; ++e) nn = fma(knew[e], knew[e], nn);
-      nn = fast_wave_sum(nn);
-      nr = fresh ? nn : nr;
-#pragma unroll
-      for (int v = 0; v < NV; ++v) {
-        double dv = 0.0;
-#pragma unroll
-        for (int e = 0; e < E; ++e) dv = fma(knew[e], mine_opnd[operand_index<T, NV>(v, E * lane + e)], dv);
-        dv = fast_wave_sum(dv);
-        dot[v] = fresh ? dv : dot[v];
-      }
     }
     // ---- softmax statistics of the sub-chunk; the lane owns cache row sub*kSub + lane
     const int64_t pidx = sub_index(a, bh, mt3, sub) * G;

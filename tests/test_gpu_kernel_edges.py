@@ -305,6 +305,32 @@ def test_generation_step_outputs_to_fp32_accuracy(fp8, G):
         ctx.close()
 
 
+@pytest.mark.parametrize("n", [60, 200])  # the twins in one 64-row sub-chunk and in two
+@pytest.mark.parametrize("dtype,d,G", [("f32", 64, 1), ("f32", 64, 4), ("f32", 128, 1), ("f32", 128, 4), ("bf16", 128, 1)])
+def test_the_new_token_ties_with_the_twin_of_its_key(dtype, d, G, n):
+    """Eq. 9 takes the first maximum in ascending position: where the new token's key equals a cached one and the evicted
+    key lies next to both, the older of the two is its match.  32 heads (the sums of the two rows in different orders
+    make the new row's cosine the larger one in a third of them)."""
+    B, Hkv, twin, leaves = 2, 16, 20, 50
+    g = torch.Generator().manual_seed(n + d + G)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    K, V, k, v = (torch.randn(B, Hkv, t, d, generator=g) for t in (n, n, 1, 1))
+    K[:, :, leaves] = K[:, :, twin] + 0.05 * torch.randn(B, Hkv, d, generator=g)
+    k[:, :, 0] = K[:, :, twin]
+    q = torch.randn(1, B, Hkv * G, d, generator=g)
+    score = 100.0 + np.random.default_rng(n).random((B, Hkv, n)).astype(np.float32)
+    score[:, :, leaves] = 0.0
+    ctx = binding.D2O(B, 1, Hkv * G, Hkv, d, n, n + 8, dtype=dtype, tau_force=float("-inf"), out_f32=True)
+    ctx.d2o_scores_import(0, score)
+    ctx.d2o_compress_layer(0, K.to(dt).cuda(), V.to(dt).cuda(), n, 4)
+    out = torch.empty(1, B, Hkv * G, d, device="cuda:0")
+    ctx.d2o_decode_step(0, 1, q.to(dt).cuda(), k[:, :, 0].to(dt).cuda()[None], v[:, :, 0].to(dt).cuda()[None], out)
+    evicted, target, _ = ctx.d2o_last_events(0)
+    assert np.all(evicted == leaves) and np.all(target == twin), (evicted, target)
+    assert ctx.d2o_candidate_misses() == 0
+    ctx.close()
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,n", [
     (1, 2, 1, 1), (1, 2, 2, 127), (2, 2, 1, 128), (1, 4, 1, 129), (1, 8, 8, 255), (1, 8, 2, 257), (1, 3, 3, 700),
     (1, 16, 4, 2049),     # 128-row blocks up to the last that the chip holds at once (272), key blocks in pairs
