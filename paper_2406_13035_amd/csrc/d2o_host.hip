@@ -88,8 +88,11 @@ void layout(d2o_ctx* x, char* persistent, char* scratch, size_t* pbytes, size_t*
   p.take(x->cmiss, L * B * Hkv);
   *pbytes = (p.off + 255) & ~size_t(255);
 
+  // (No array serves both an attention call and a compression or block append: a caller may run the attention of one
+  // layer beside the compression of another, on streams of their own.)
   Carver s{scratch};
   s.take(x->lse, B * Hq * np);
+  s.take(x->colpart, c.dtype == D2O_BF16 && G > 1 ? B * Hq * np : 0);
   s.take_raw(x->vt, c.dtype == D2O_BF16 ? B * Hkv * d * np * es : 0);
   s.take(x->vmax_bits, B * Hkv * kVmaxShares);
   s.take(x->vt_unscale, B * Hkv);
@@ -105,7 +108,6 @@ void layout(d2o_ctx* x, char* persistent, char* scratch, size_t* pbytes, size_t*
   s.take(x->amb_cnt, bh);
   s.take(x->m_ncand, bh * np);
   s.take(x->m_clist, bh * np * 8);
-  x->colpart = reinterpret_cast<float*>(x->m_clist);  // (G <= 8)
   s.take(x->m_ustar, bh * np);
   s.take(x->m_tgt, bh * np);
   s.take(x->m_pass, bh * np);

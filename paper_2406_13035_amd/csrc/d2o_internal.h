@@ -99,6 +99,7 @@ struct d2o_ctx {
   // ---- scratch workspace (device) ----
   // prefill attention
   float* lse = nullptr;          // [B][Hq][npad]   row log-sum-exp (natural log, scaled logits)
+  float* colpart = nullptr;      // [B][Hq][npad] column sums per query head (bf16, G > 1)
   void* vt = nullptr;            // [B][Hkv][npad/64][d][64] transposed values, tile by tile, as scaled fp16 (bf16 path)
   uint32_t* vmax_bits = nullptr; // [B][Hkv][kVmaxShares] bit pattern of max |v| of the workgroups' shares
   float* vt_unscale = nullptr;   // [B][Hkv] power of two that undoes the fp16 scaling
@@ -114,7 +115,6 @@ struct d2o_ctx {
   int32_t* amb_cnt = nullptr;    // [B][Hkv]
   int32_t* m_ncand = nullptr;    // candidates collected for a flagged row
   int32_t* m_clist = nullptr;    // [..][npad][8] their retained ranks
-  float* colpart = nullptr;      // [B][Hq][npad] column sums per query head (bf16, G > 1): the memory of m_clist, which no attention call needs
   double* m_ustar = nullptr;     // exact best similarity per evicted row
   int32_t* m_tgt = nullptr;      // exact match (retained rank)
   uint8_t* m_pass = nullptr;     // threshold test

@@ -65,6 +65,21 @@ def test_workspace_query_and_config_validation(lib):
     assert bf16_bytes - p.value > 0.9 * 32 * 30000 * 128 * 2
 
 
+@pytest.mark.parametrize("dtype,per_row", [(binding.D2O_F32, 4 + 16 / 32), (binding.D2O_BF16, 4 + 4 + 16 / 128)])
+def test_scratch_of_attention_is_its_own(lib, dtype, per_row):
+    """What grows with query heads times prompt length is the attention's alone: a row's log-sum-exp, the shares of the
+    density sums, and with grouped bf16 queries a column sum per query head.  None of it may lie in
+    the lists of a compression, which may run beside the attention of another layer."""
+    def scratch(q_heads, n):
+        cfg = binding.d2o_config(2, 2, q_heads, 4, 128, n, 3000, dtype, 0, 0.7, float("nan"), 0)
+        p, s = C.c_size_t(), C.c_size_t()
+        assert lib.d2o_workspace_bytes(C.byref(cfg), C.byref(p), C.byref(s)) == 0
+        return s.value
+    heads, rows = 16, 4096
+    grown = (scratch(32, 2 * rows) - scratch(16, 2 * rows)) - (scratch(32, rows) - scratch(16, rows))
+    assert grown == 2 * heads * rows * per_row
+
+
 def test_allocate_budgets_matches_oracle_bit_for_bit(lib):
     g = np.random.default_rng(2024)
     for trial in range(300):

@@ -488,3 +488,44 @@ def test_matching_of_few_and_of_many_rows(B, Hkv, n, budget):
             cos = (x[evi] @ x[ret].T) / (norm[evi][:, None] * norm[ret][None, :])
             assert np.array_equal(tgt, ret[cos.argmax(-1)]), f"sequence {b} head {h}"
     ctx.close()
+
+
+@pytest.mark.parametrize("fp8", [False, True])
+def test_attention_beside_the_compression_of_another_layer(fp8):
+    """Attention and compression keep no scratch memory in common: layer 1's attention (grouped queries) on one stream,
+    layer 0's compression on another, with keys in pairs of twins so that the matching's lists are in use, give the
+    bits of the same calls one after the other."""
+    Hq, Hkv, n, budget = 32, 8, 2048, 500
+    g = torch.Generator().manual_seed(11)
+    x = [[torch.randn(1, h, n, 128, generator=g).to(torch.bfloat16) for h in (Hq, Hkv, Hkv)] for _ in range(2)]
+    for _, K, _ in x:
+        K[:, :, n // 2:] = K[:, :, :n // 2]
+    x = [[t.cuda() for t in layer] for layer in x]
+    ctx = binding.D2O(1, 2, Hq, Hkv, 128, n, 2 * budget + 8, dtype="bf16", cache_fp8=fp8)
+    streams = [torch.cuda.Stream() for _ in range(2)]
+
+    def results():
+        torch.cuda.synchronize()
+        out = [ctx.d2o_scores_export(l, n) for l in range(2)]
+        out += [a for h in range(Hkv) for a in ctx.d2o_prefill_events(0, 0, h, n)]
+        ctx.d2o_compress_layer(1, x[1][1], x[1][2], budget, 100)
+        for l in range(2):
+            for h in range(Hkv):
+                out += [np.asarray(a) for a in ctx.d2o_cache_export(l, 0, h, budget + 1)]
+        return out
+
+    ctx.d2o_prefill_attend(0, *x[0])
+    ctx.d2o_prefill_attend(1, *x[1])
+    ctx.d2o_compress_layer(0, x[0][1], x[0][2], budget, 100)
+    want = results()
+    for _ in range(3):
+        ctx.d2o_reset()
+        ctx.d2o_prefill_attend(0, *x[0])
+        torch.cuda.synchronize()
+        with torch.cuda.stream(streams[0]):
+            ctx.d2o_prefill_attend(1, *x[1])
+        with torch.cuda.stream(streams[1]):
+            ctx.d2o_compress_layer(0, x[0][1], x[0][2], budget, 100)
+        for got, first in zip(results(), want):
+            assert np.array_equal(got, first, equal_nan=True)
+    ctx.close()
