@@ -935,14 +935,45 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
         }
       }
       const float back = sizeof(T) == 1 ? pow2_f32(rev_max) : 1.f;
+      float all = 0.f;  // not finite if a sum is not
 #pragma unroll
-      for (int gb = 0; gb < GB; ++gb) {
-        const int g = gb * 4 + tr;
-        if (g < G) {
+      for (int gb = 0; gb < GB; ++gb)
 #pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            const f32x4 d = o[gb][j];
-            xch[g * D + tc * 8 + j] = ((d[2] + d[1]) + d[0]) * back;
+        for (int j = 0; j < 8; ++j) {
+          const f32x4 d = o[gb][j];
+          o[gb][j][0] = (d[2] + d[1]) + d[0];
+          all += o[gb][j][0];
+        }
+      if (sizeof(T) == 2 && __ballot(!(fabsf(all) < INFINITY))) {
+        // An infinite element of V meets terms that are zero, which makes NaN of what is infinite: the
+        // rows once more, two columns per lane, with each probability in one piece.
+        float pv[G][2];
+#pragma unroll
+        for (int g = 0; g < G; ++g) pv[g][0] = pv[g][1] = 0.f;
+#pragma unroll 1
+        for (int r = 0; r < int(cached / RB); ++r) {
+          const uint32_t x = __builtin_amdgcn_raw_buffer_load_b32(Vb, r * RB + ln * 4, 0, 0);
+          const uint16_t* tp = reinterpret_cast<const uint16_t*>(mine) + (r & 3) * 16 + (r >> 2);
+#pragma unroll
+          for (int g = 0; g < G; ++g) {
+            float p = 0.f;
+#pragma unroll
+            for (int t = 2; t >= 0; --t) p += __uint_as_float(uint32_t(tp[(3 * g + t) * (kTermPitch / 2)]) << 16);
+            pv[g][0] = fmaf(p, __uint_as_float(x << 16), pv[g][0]);
+            pv[g][1] = fmaf(p, __uint_as_float(x & 0xFFFF0000u), pv[g][1]);
+          }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int g = 0; g < G; ++g) *reinterpret_cast<float2*>(xch + g * D + ln * 2) = make_float2(pv[g][0], pv[g][1]);
+      } else {
+#pragma unroll
+        for (int gb = 0; gb < GB; ++gb) {
+          const int g = gb * 4 + tr;
+          if (g < G) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) xch[g * D + tc * 8 + j] = o[gb][j][0] * back;
           }
         }
       }

@@ -305,6 +305,37 @@ def test_generation_step_outputs_to_fp32_accuracy(fp8, G):
         ctx.close()
 
 
+@pytest.mark.parametrize("G", [4, 8])
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64), ("f32", 128)])
+@pytest.mark.parametrize("value", [float("inf"), float("-inf")])
+def test_generation_step_with_an_infinite_value(dtype, d, G, value):
+    """One infinite element of V makes its column infinite, with its sign, and leaves the others alone: in the row with the
+    largest logit and in others, first and last of the cache, in the middle of it, and the new token's."""
+    Hkv, n = 4, 300
+    g = torch.Generator().manual_seed(d + G)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    q, K, V = (torch.randn(1, h, t, d, generator=g).to(dt) for h, t in ((Hkv * G, 1), (Hkv, n + 1), (Hkv, n + 1)))
+    rows = [0, 77, n - 1, n]
+    for h, r in enumerate(rows):
+        K[0, h, r] = 0.5 * q[0, h * G, 0]  # the largest logit of the head's first query
+        V[0, h, r, r % d] = value
+    ctx = binding.D2O(1, 1, Hkv * G, Hkv, d, n, n + 16, dtype=dtype, out_f32=True)
+    ctx.d2o_scores_import(0, np.ones((1, Hkv, n), dtype=np.float32))
+    ctx.d2o_compress_layer(0, K[:, :, :n].cuda(), V[:, :, :n].cuda(), n + 8, 4)
+    out = torch.empty(1, 1, Hkv * G, d, device="cuda:0")
+    ctx.d2o_decode_step(0, 1, q[:, :, 0].cuda()[None], K[:, :, n].cuda()[None], V[:, :, n].cuda()[None], out)
+    got = out[0, 0].double().cpu().numpy()
+    qd, Kd, Vd = (binding.tensor_to_f64(t) for t in (q, K, V))
+    for h, r in enumerate(rows):
+        logit = qd[0, h * G:(h + 1) * G, 0] @ Kd[0, h].T / np.sqrt(d)
+        p = np.exp(logit - logit.max(-1, keepdims=True))
+        want = (p / p.sum(-1, keepdims=True)) @ Vd[0, h]
+        o, others = got[h * G:(h + 1) * G], np.arange(d) != r % d
+        assert np.all(o[:, r % d] == value), f"row {r}: {o[:, r % d]}"
+        assert np.abs(o[:, others] - want[:, others]).max() <= H.FLOAT_TOL * np.abs(want[:, others]).max()
+    ctx.close()
+
+
 @pytest.mark.parametrize("n", [60, 200])  # the twins in one 64-row sub-chunk and in two
 @pytest.mark.parametrize("dtype,d,G", [("f32", 64, 1), ("f32", 64, 4), ("f32", 128, 1), ("f32", 128, 4), ("bf16", 128, 1)])
 def test_the_new_token_ties_with_the_twin_of_its_key(dtype, d, G, n):
