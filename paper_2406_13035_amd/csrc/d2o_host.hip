@@ -767,6 +767,10 @@ int d2o_cache_import(d2o_ctx* x, int32_t layer, int32_t b, int32_t h, const void
   // the imported rows have no known eviction candidates yet
   D2O_HIP_CHECK(x, fill32(x->ccand + lbh * decode_candidates(), 0xFFFFFFFFu, sizeof(int32_t) * decode_candidates(), s));
   D2O_HIP_CHECK(x, hipStreamSynchronize(s));
+  auto cover = [&](int32_t p) { st.pos_end = std::max(st.pos_end, int64_t(uint32_t(p)) + 1); };
+  for (int i = 0; i < count; ++i) cover(pos[i]);
+  if (st.next_pos > 0) cover(st.next_pos - 1);  // the other heads' rows
+  if (next_pos < 0) cover(next_pos);
   st.next_pos = next_pos;
   return D2O_OK;
 }

@@ -47,6 +47,7 @@ struct LayerState {
   int phase = kEmpty;
   int32_t n = 0;          // prompt length seen by the prefill calls
   int32_t next_pos = 0;   // position of the next generated token
+  int64_t pos_end = 0;    // every position that an import brought, or left behind the next one, is below this (a negative one counts as 2^32 more)
   std::vector<LayerMeta> meta;  // [B][Hkv]
 };
 
