@@ -419,7 +419,7 @@ __global__ __launch_bounds__(256) void block_stats(const int32_t* __restrict__ c
       BR::logits(smem, g, lane, bq, S);
       const int j0 = chunk * kChunk + g * 64 + kq;
       mask_logits(S, j0, seen, chunk * kChunk + g * 64 + 63, tile_last);
-      double mg = S[0][0];
+      double mg = -INFINITY;  // (stays so where every logit is NaN: rows with NaN keys leave the others' probabilities alone)
 #pragma unroll
       for (int t = 0; t < 4; ++t)
 #pragma unroll

@@ -512,6 +512,35 @@ def test_captured_block_append_replayed_on_another_cache():
     ctx.close()
 
 
+@pytest.mark.parametrize("m", [4, 24, 48])  # four, two and one of a workgroup's wavefronts per tile of queries
+def test_block_append_with_a_group_of_rows_whose_keys_are_nan(m):
+    """64 neighbouring cache rows whose keys are all NaN: outputs are NaN, and so are those rows' scores, but the other
+    rows keep the scores that the softmax over them gives."""
+    n, d, bad = 200, 128, slice(64, 128)
+    g = torch.Generator().manual_seed(m)
+    K, V = (torch.randn(n, d, generator=g).to(torch.bfloat16).double().numpy() for _ in range(2))
+    K[bad] = np.nan
+    x = [torch.randn(1, 1, m, d, generator=g).to(torch.bfloat16) for _ in range(3)]
+    ctx = binding.D2O(1, 1, 1, 1, d, 512, 300, dtype="bf16", out_f32=True, max_append=m)
+    ctx.d2o_layer_reserve(0, 400, n + m, 0)
+    ctx.d2o_cache_import(0, 0, 0, K, V, np.zeros(n), np.arange(n, dtype=np.int32), 0.1, n)
+    out = torch.empty(1, 1, m, d, device="cuda:0")
+    ctx.d2o_append_chunk(0, *(t.cuda() for t in x), out)
+    score = ctx.d2o_cache_export(0, 0, 0, n + m)[2]
+    keys = np.r_[K, x[1][0, 0].double().numpy()]
+    want = np.zeros(n + m)
+    good = np.arange(n + m)
+    good = good[(good < bad.start) | (good >= bad.stop)]
+    for i in range(m):
+        seen = good[good <= n + i]
+        logit = keys[seen] @ x[0][0, 0, i].double().numpy() / np.sqrt(d)
+        p = np.exp(logit - logit.max())
+        want[seen] += p / p.sum()
+    assert torch.isnan(out).all() and np.isnan(score[bad]).all()
+    np.testing.assert_allclose(score[good], want[good], rtol=1e-12)
+    ctx.close()
+
+
 def _append_against_oracle(dtype, storage, d, G, m, budget, positions, next_pos, steps=0):
     Hkv, beta, g = 2, 0.7, np.random.default_rng(m + budget)
     ctx = binding.D2O(1, 1, G * Hkv, Hkv, d, 512, budget + m + 8, dtype=dtype, beta=beta, out_f32=True, max_append=m,
