@@ -831,14 +831,18 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
     double recv = 0.0;  // this lane's element of the sub-chunk record
     // The probabilities go to the staging area (the K pass is done with it) for the V pass: as fp32, or, for
     // its matrix products, each as three bf16 terms that add up to it exactly (an fp32 value has three times
-    // eight significant bits), in the order of their A operand: term t of query head g is row 3 g + t of
+    // eight significant bits) but for a power of two, in the order of their A operand: term t of query head g is row 3 g + t of
     // kTermPitch bytes, cache row r its element 16 (r % 4) + r / 4.
     constexpr int kTermPitch = 128 + 16;
     static_assert(!kMmaV || (RPI == 4 && 3 * G * kTermPitch <= kWaveStage), "the terms fit the staging area");
     float* psf = reinterpret_cast<float*>(mine);  // [G][kSub]
     unsigned char* const term = mine + ((ln & 3) * 16 + (ln >> 2)) * 2;
+    // bf16 ends at 2^-133, an fp32 probability at 2^-149: the terms are those of the probability times 2^kTermScale, which
+    // the sums are rid of again (unscaled, a probability of 2e-38 lost 9 of its bits, which a V element of 1e38 shows).
     // fp8 cache: the V pass works on the codes, so a row's power of two rides on its probability, taken
-    // relative to the largest of the sub-chunk (which multiplies the sums: the terms keep their range)
+    // relative to the largest of the sub-chunk (which multiplies the sums: the terms keep their range).  These powers lie
+    // up to 240 apart, and codes end at 448, 64 of which times 2^112 are finite.
+    constexpr int kTermScale = sizeof(T) == 1 ? 112 : 24;
     const int rev_max = sizeof(T) == 1 ? -fast_wave_min(-rev) : 0;  // (-120, the smallest there is, in lanes without a cached row)
     float pnew[G];  // the new row's probabilities
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -849,7 +853,7 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
       const double mx = fast_wave_max(valid ? sg : -INFINITY);
       const double e = valid ? exp(sg - mx) : 0.0;
       if constexpr (kMmaV) {
-        const float p1 = sizeof(T) == 1 ? ldexpf(float(e), rev - rev_max) : float(e);
+        const float p1 = sizeof(T) == 1 ? ldexpf(float(e), rev - rev_max + kTermScale) : float(e) * pow2_f32(kTermScale);
         const float p2 = p1 - __uint_as_float(__float_as_uint(p1) & 0xFFFF0000u);
         const float p3 = p2 - __uint_as_float(__float_as_uint(p2) & 0xFFFF0000u);
         *reinterpret_cast<uint16_t*>(term + (3 * g) * kTermPitch) = uint16_t(__float_as_uint(p1) >> 16);
@@ -934,7 +938,7 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
           }
         }
       }
-      const float back = sizeof(T) == 1 ? pow2_f32(rev_max) : 1.f;
+      auto back = [&](float x) { return sizeof(T) == 1 ? ldexpf(x, rev_max - kTermScale) : x * pow2_f32(-kTermScale); };
       float all = 0.f;  // not finite if a sum is not
 #pragma unroll
       for (int gb = 0; gb < GB; ++gb)
@@ -945,8 +949,8 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
           all += o[gb][j][0];
         }
       if (sizeof(T) == 2 && __ballot(!(fabsf(all) < INFINITY))) {
-        // An infinite element of V meets terms that are zero, which makes NaN of what is infinite: the
-        // rows once more, two columns per lane, with each probability in one piece.
+        // An infinite element of V meets terms that are zero, which makes NaN of what is infinite, and scaled sums may
+        // overflow (from 2^104 on): the rows once more, two columns per lane, with each probability in one piece.
         float pv[G][2];
 #pragma unroll
         for (int g = 0; g < G; ++g) pv[g][0] = pv[g][1] = 0.f;
@@ -959,6 +963,7 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
             float p = 0.f;
 #pragma unroll
             for (int t = 2; t >= 0; --t) p += __uint_as_float(uint32_t(tp[(3 * g + t) * (kTermPitch / 2)]) << 16);
+            p = back(p);
             pv[g][0] = fmaf(p, __uint_as_float(x << 16), pv[g][0]);
             pv[g][1] = fmaf(p, __uint_as_float(x & 0xFFFF0000u), pv[g][1]);
           }
@@ -973,7 +978,7 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
           const int g = gb * 4 + tr;
           if (g < G) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) xch[g * D + tc * 8 + j] = o[gb][j][0] * back;
+            for (int j = 0; j < 8; ++j) xch[g * D + tc * 8 + j] = back(o[gb][j][0]);
           }
         }
       }

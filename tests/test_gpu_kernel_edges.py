@@ -3,6 +3,8 @@ which a kernel's loop, remainder or variant changes.  (What the calls do as a wh
 test_gpu_parity.py.)"""
 from __future__ import annotations
 
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -333,6 +335,41 @@ def test_generation_step_with_an_infinite_value(dtype, d, G, value):
         o, others = got[h * G:(h + 1) * G], np.arange(d) != r % d
         assert np.all(o[:, r % d] == value), f"row {r}: {o[:, r % d]}"
         assert np.abs(o[:, others] - want[:, others]).max() <= H.FLOAT_TOL * np.abs(want[:, others]).max()
+    ctx.close()
+
+
+@pytest.mark.parametrize("G", [1, 4, 8])
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("gap", [30.0, 87.0, 88.4, 90.5, 200.0])
+def test_generation_step_of_large_values_with_small_probabilities(fp8, G, gap):
+    """One V row near the end of the number range, its logit `gap` below the others': what it adds to the output, down to
+    fp32 probabilities without their full 24 bits, and what it leaves of the other rows' values, which are small beside it.  A
+    probability is rounded to fp32 (2^-150 off at most, which the large value multiplies), sums of 41 terms are fp32."""
+    d, n, far, large = 128, 40, 11, 2.0 ** 127
+    g = torch.Generator().manual_seed(G)
+    q, K, V = (torch.randn(1, h, t, d, generator=g) for h, t in ((G, 1), (1, n + 1), (1, n + 1)))
+    q[..., 0], K[..., 0] = 64.0, 0.0
+    K[0, 0, far] = 0.0
+    K[0, 0, far, 0] = -gap * math.sqrt(d) / 64
+    V[0, 0, far] = large * torch.linspace(0.5, 1.0, d)
+    if gap > 100:
+        V[0, 0, :far] *= 1e-6
+        V[0, 0, far + 1:] *= 1e-6
+    q, K, V = (t.to(torch.bfloat16) for t in (q, K, V))
+    ctx = binding.D2O(1, 1, G, 1, d, n, n + 16, dtype="bf16", out_f32=True, cache_fp8=fp8)
+    ctx.d2o_scores_import(0, np.ones((1, 1, n), dtype=np.float32))
+    ctx.d2o_compress_layer(0, K[:, :, :n].cuda(), V[:, :, :n].cuda(), n + 8, 4)
+    out = torch.empty(1, 1, G, d, device="cuda:0")
+    ctx.d2o_decode_step(0, 1, q[:, :, 0].cuda()[None], K[:, :, n].cuda()[None], V[:, :, n].cuda()[None], out)
+    qd, Kd, Vd = (binding.tensor_to_f64(t)[0] for t in (q, K, V))
+    if fp8:
+        Kd, Vd = (ref.round_storage(x[0], "fp8")[None] for x in (Kd, Vd))
+    logit = qd[:, 0] @ Kd[0].T / np.sqrt(d)
+    p = np.exp(logit - logit.max(-1, keepdims=True))
+    p /= p.sum(-1, keepdims=True)
+    want, got = p @ Vd[0], out[0, 0].double().cpu().numpy()
+    bound = 41 * 2.0 ** -24 * (p @ np.abs(Vd[0])) + (2.0 ** -149 * large if gap < 100 else 0.0)
+    assert np.all(np.abs(got - want) <= bound), (np.abs(got - want) / bound).max()
     ctx.close()
 
 
