@@ -101,6 +101,27 @@ struct LaneShare {
   }
 };
 
+// Sum of the squares of a key's elements, E neighbours per lane.  Squares of bf16 elements and fp8 codes add up exactly in any
+// order; those of fp32 elements do not, and where a candidate is the twin of its match a last bit of its norm can
+// decide the threshold test (both 1 but for rounding), so their order is held (BY_HALVES): elements 32, 16, 8, 4, 2
+// and 1 apart in every 64 of them.
+template <bool BY_HALVES, int E>
+__device__ __forceinline__ double square_sum(const double (&x)[E]) {
+  if constexpr (!BY_HALVES) {
+    double s = 0.0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) s = fma(x[e], x[e], s);
+    return fast_wave_sum(s);
+  } else if constexpr (E == 1) {
+    const double s = x[0] * x[0];
+    return half_wave_sum(s + __shfl_xor(s, 32, 64));
+  } else {
+    static_assert(E == 2, "one or two elements per lane");
+    const double s = half_wave_sum(x[0] * x[0]) + half_wave_sum(x[1] * x[1]);
+    return lane_f64(s, 0) + lane_f64(s, 32);
+  }
+}
+
 // Softmax maximum and exact normaliser sum_j exp(s_j - max) of each query head of one head, from
 // its sub-chunk records (fixed summation tree), by one workgroup of 256 threads of the launch
 // that wrote the records; result: hn[g] = maximum, hn[G + g] = normaliser.
@@ -612,15 +633,12 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
   double cn[kCand];
 #pragma unroll
   for (int c = 0; c < kCand; ++c) {
-    double x[E], part = 0.0;
+    double x[E];
     RowShare::widen(craw[c], x);
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-      x[e] = cs[c] < 0 ? 0.0 : sizeof(T) == 1 ? x[e] * pow2_f64(cexp[c]) : x[e];
-      part = fma(x[e], x[e], part);
-    }
+    for (int e = 0; e < E; ++e) x[e] = cs[c] < 0 ? 0.0 : sizeof(T) == 1 ? x[e] * pow2_f64(cexp[c]) : x[e];
     if (kOwnOpnd || w == c % 4) lay_out(G + c, x);
-    cn[c] = sqrt(fast_wave_sum(part));
+    cn[c] = sqrt(square_sum<sizeof(T) == 4, E>(x));
   }
   if (!kOwnOpnd) lds_barrier();  // the operands are in LDS; the K rows may still be on their way
   // the new row's K and V as they enter the cache: K as stored, with an fp8 row's power of two, and V's values

@@ -194,8 +194,14 @@ __device__ __forceinline__ double row16_sum(double v) {
 
 // Sum over each half of the wavefront (32 lanes) by halves: lanes 16 apart first, then 8, 4, 2 and 1 apart
 // (once lanes eight apart agree, a rotation by four reaches the lane four apart); every lane gets its half's sum.
-__device__ __forceinline__ float half_wave_sum(float v) {
-  auto moved = [](auto ctrl, float x) { return __int_as_float(dpp_i32<decltype(ctrl)::value>(__float_as_int(x))); };
+template <typename F>
+__device__ __forceinline__ F half_wave_sum(F v) {
+  auto moved = [](auto ctrl, F x) {
+    if constexpr (sizeof(F) == 8)
+      return dpp_f64<decltype(ctrl)::value>(x);
+    else
+      return __int_as_float(dpp_i32<decltype(ctrl)::value>(__float_as_int(x)));
+  };
   v += __shfl_xor(v, 16, 64);
   v += moved(std::integral_constant<int, kDppRor8>{}, v);
   v += moved(std::integral_constant<int, kDppRor4>{}, v);

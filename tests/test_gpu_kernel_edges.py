@@ -399,6 +399,38 @@ def test_the_new_token_ties_with_the_twin_of_its_key(dtype, d, G, n):
     ctx.close()
 
 
+@pytest.mark.parametrize("G", [1, 4])
+@pytest.mark.parametrize("d", [64, 128])
+def test_the_evicted_keys_norm_has_one_order_of_additions(d, G):
+    """With fp32 keys a last bit of the evicted key's norm can decide the threshold test of twins, so its squares are added
+    by halves of every 64 elements (32, 16, 8, 4, 2 and 1 apart).  The match points along the first axis: its products with
+    the evicted key and its own norm are exact, and the similarity is the first element over the evicted key's norm."""
+    B, Hkv, n, leaves = 2, 16, 60, 50
+    g = torch.Generator().manual_seed(d)
+    K, V, v = (torch.randn(B, Hkv, t, d, generator=g) for t in (n, n, 1))
+    e = torch.randn(B, Hkv, d, generator=g)
+    e[..., 0] = e[..., 0].abs()
+    K[:], K[..., 0] = 0.0, -1.0
+    K[:, :, 20, 0] = 1.0
+    K[:, :, leaves] = e
+    q = torch.randn(1, B, Hkv * G, d, generator=g)
+    score = 100.0 + np.random.default_rng(n).random((B, Hkv, n)).astype(np.float32)
+    score[:, :, leaves] = 0.0
+    ctx = binding.D2O(B, 1, Hkv * G, Hkv, d, n, n + 8, dtype="f32", out_f32=True)
+    ctx.d2o_scores_import(0, score)
+    ctx.d2o_compress_layer(0, K.cuda(), V.cuda(), n, 4)
+    out = torch.empty(1, B, Hkv * G, d, device="cuda:0")
+    ctx.d2o_decode_step(0, 1, q.cuda(), K[:, :, 0].cuda()[None], v[:, :, 0].cuda()[None], out)
+    evicted, _, u = ctx.d2o_last_events(0)
+    assert np.all(evicted == leaves) and ctx.d2o_candidate_misses() == 0
+    s = e.double().numpy().reshape(B, Hkv, d // 64, 64) ** 2
+    for step in (32, 16, 8, 4, 2, 1):
+        s = s[..., :step] + s[..., step:2 * step]
+    norm = np.sqrt(s.sum((-1, -2)))  # (one or two sums of 64)
+    assert np.array_equal(u, e[..., 0].double().numpy() / norm)
+    ctx.close()
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,n", [
     (1, 2, 1, 1), (1, 2, 2, 127), (2, 2, 1, 128), (1, 4, 1, 129), (1, 8, 8, 255), (1, 8, 2, 257), (1, 3, 3, 700),
     (1, 16, 4, 2049),     # 128-row blocks up to the last that the chip holds at once (272), key blocks in pairs
