@@ -319,11 +319,11 @@ int d2o_prefill_events(d2o_ctx* ctx, int32_t layer, int32_t b, int32_t kv_head,
 
 /* Kernel timing aid for benchmarks (not part of the method).  While enabled (on >= 1), launches
  * of the kernels below are bracketed by two HIP events recorded on the launch stream: every
- * launch of the prompt-phase kernels, and every on-th launch of the two decode kernels (the
- * on-th, 2 on-th, ... after enabling; the events of a decode step cost it about 3 % at the
- * largest configuration; on = 1 times every step).  d2o_timing_read synchronises `stream`, returns the summed duration in milliseconds and
- * the number of timed launches of one kernel since the last read of that kernel, and forgets
- * them. */
+ * launch of the prompt-phase kernels and of the split closing kernels, and every on-th launch of
+ * D2O_K_DECODE_ATTEND (the on-th, 2 on-th, ... after enabling; the events of a decode step cost
+ * it about 3 % at the largest configuration; on = 1 times every step).  d2o_timing_read
+ * synchronises `stream`, returns the summed duration in milliseconds and the number of timed
+ * launches of one kernel since the last read of that kernel, and forgets them. */
 typedef enum {
   D2O_K_ATTN_FWD = 0,      /* prefill attention, pass 1 (O and row log-sum-exp)            */
   D2O_K_COLSUM = 1,        /* prefill attention, pass 2 (per-key column sums)              */
@@ -331,8 +331,9 @@ typedef enum {
   D2O_K_MATCH_FILTER = 3,  /* matrix-core cosine candidate filter                          */
   D2O_K_MATCH_REFINE = 4,  /* exact fp64 cosine / arg-max                                  */
   D2O_K_MERGE = 5,
-  D2O_K_DECODE_ATTEND = 6,  /* attention over the cache + score update + evict/merge         */
-  D2O_K_DECODE_PREPARE = 7, /* append of the new token, operand set-up: part of the launch of D2O_K_DECODE_ATTEND, whose time it repeats */
+  D2O_K_DECODE_ATTEND = 6,  /* append, attention over the cache, score update, evict/merge   */
+  D2O_K_DECODE_PREPARE = 7, /* reserved, never launched (reads as 0 ms, 0 launches): the      */
+                            /* append of the new token is part of D2O_K_DECODE_ATTEND         */
   D2O_K_DECODE_CLOSE = 8,   /* closing work of very large heads, split over workgroups        */
   D2O_K_COUNT = 9
 } d2o_kernel_id;

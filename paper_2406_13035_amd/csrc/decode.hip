@@ -1120,7 +1120,7 @@ struct StepViews {
 template <typename T, typename OT, int D, int G>
 hipError_t run_attend(d2o_ctx* c, const DecodeArgs& a, int flat_chunks, const StepViews& t, hipStream_t s) {
   typedef typename TensorType<T>::type IT;
-  KernelTimer kt(c, D2O_K_DECODE_ATTEND, s), kp(c, D2O_K_DECODE_PREPARE, s);
+  KernelTimer kt(c, D2O_K_DECODE_ATTEND, s);
   decode_attend<T, OT, D, G><<<dim3(a.B * a.Hkv, flat_chunks), 256, 0, s>>>(a, (const IT*)t.q.ptr, t.q, (const IT*)t.k.ptr, t.k,
                                                                            (const IT*)t.v.ptr, t.v, (OT*)t.out.ptr, t.out);
   return hipGetLastError();
