@@ -541,6 +541,8 @@ __global__ __launch_bounds__(64 * kFewWaves) void match_filter_few(const uint16_
   // a, norm: sub-tile j; a_next, norm_next: the wavefront's next one; pos: the position of the row behind that
   auto one = [&](int j, const bf16x8 (&a)[8], float norm, bf16x8 (&a_next)[8], float& norm_next, int& pos) {
     if (h == 0) rin[w][m] = norm;
+    // (within the wavefront; LDS serves its requests in order, so the hand-over needs compiler ordering only)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     load(a_next, j + kFewWaves);
     norm_next = inl[pos];
@@ -561,6 +563,7 @@ __global__ __launch_bounds__(64 * kFewWaves) void match_filter_few(const uint16_
         if (j * 32 + (r >> 2) * 8 + h * 4 + (r & 3) >= nret) tv[r] = s[r] * 0.f - 3.0e38f;
     }
     two.take(tv, j * 32);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
   };
   bf16x8 a0[8], a1[8];
