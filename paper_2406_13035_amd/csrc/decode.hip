@@ -1012,13 +1012,12 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
 #pragma unroll
         for (int i = 0; i < VQ; ++i) {
           const int r = (q * VQ + i) * RPI + tr;
-          float x[kVec];
-          cvt16f<T>(vbuf[(q & 1) * VQ + i], x);
+          const VRaw& x = vbuf[(q & 1) * VQ + i];
 #pragma unroll
           for (int g = 0; g < G; ++g) {
             const float p = psf[g * kSub + r];  // 0 for rows beyond the end
 #pragma unroll
-            for (int e = 0; e < kVec; ++e) pv[g][e] = fmaf(p, x[e], pv[g][e]);
+            for (int e = 0; e < kVec; ++e) pv[g][e] = fmaf(p, __uint_as_float(x[e]), pv[g][e]);
           }
         }
         if (q + 2 < 4) {

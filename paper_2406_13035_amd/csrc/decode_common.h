@@ -89,31 +89,6 @@ __device__ __forceinline__ void cvt16<uint8_t>(const u32x4& v, double* out) {  /
     out[4 * i + 3] = double(__builtin_amdgcn_cvt_f32_fp8(int(v[i]), 3));
   }
 }
-template <typename T>
-__device__ __forceinline__ void cvt16f(const u32x4& v, float* out);
-template <>
-__device__ __forceinline__ void cvt16f<uint16_t>(const u32x4& v, float* out) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    out[2 * i] = __uint_as_float(v[i] << 16);
-    out[2 * i + 1] = __uint_as_float(v[i] & 0xFFFF0000u);
-  }
-}
-template <>
-__device__ __forceinline__ void cvt16f<float>(const u32x4& v, float* out) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) out[i] = __uint_as_float(v[i]);
-}
-template <>
-__device__ __forceinline__ void cvt16f<uint8_t>(const u32x4& v, float* out) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    out[4 * i] = __builtin_amdgcn_cvt_f32_fp8(int(v[i]), 0);
-    out[4 * i + 1] = __builtin_amdgcn_cvt_f32_fp8(int(v[i]), 1);
-    out[4 * i + 2] = __builtin_amdgcn_cvt_f32_fp8(int(v[i]), 2);
-    out[4 * i + 3] = __builtin_amdgcn_cvt_f32_fp8(int(v[i]), 3);
-  }
-}
 
 // 8 or 16 bytes of consecutive elements held as raw bits.
 template <int BYTES> struct RawBits;
