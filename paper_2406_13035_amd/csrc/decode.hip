@@ -567,515 +567,516 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
   asm volatile("" : "+s"(count) : "s"(mt0), "s"(mt3));  // all of them are on their way before the first wait; count is read once
   const int total = count + 1;  // with the new token
   if (grp * kChunk < total) {
-  const int64_t bh = int64_t(b) * a.Hkv + hk;
-  const int64_t slot0 = bh * a.slots + mt0;
-  const unsigned char* Kh = static_cast<const unsigned char*>(a.cK) + slot0 * RB;
-  const unsigned char* Vh = static_cast<const unsigned char*>(a.cV) + slot0 * RB;
-  // A workgroup owns a chunk of 256 slots; each wavefront works alone on 64 rows ("sub-chunk") of it:
-  // while it computes on its keys, its V rows are in flight.
-  unsigned char* mine = stage + w * kWaveStage;
-  double* mine_opnd = opnd[kOwnOpnd ? w : 0];
-  const int ln = lane;
-  // K loads of a sub-chunk.  The K pass takes a row's bytes in pieces of 64 (one LDS staging round
-  // each); the loads fetch two pieces at a time as whole 128-byte lines: 8 lanes per row, 8 rows
-  // per load, 8 loads.  They are non-temporal like the V loads below: every K and V byte is
-  // needed once per step, and a stream that does not settle in the caches leaves them to the
-  // step's small read-write arrays (measured on a streaming probe with this access pattern:
-  // 6.25 -> 6.7 TB/s; in 64-byte half lines the hint costs bandwidth instead, the second half
-  // of a line then comes from memory again).  The next pair is requested as soon as this one
-  // sits in LDS.
-  static_assert(NP % 2 == 0, "pieces are loaded in pairs");
-  // Both streams go through buffer descriptors that end with the wavefront's last row: rows past it
-  // read as zero, and a load costs at most one address instruction (64-bit addresses of clamped rows
-  // cost six, 190 of a bf16 chunk's 2300 vector instructions per wavefront).
-  const int sub = __builtin_amdgcn_readfirstlane(grp * (kChunk / kSub) + w);
-  const int rows = min(kSub, total - sub * kSub);  // <= 0: nothing for this wavefront
-  // The new token's row: its wavefront (at most one of the head) writes it to the cache, puts its K among the staged
-  // rows and takes its term of P V from registers; the streams end before it.
-  const int jnew = count - sub * kSub;
-  const bool owner = jnew >= 0 && jnew < kSub;
-  const uint32_t cached = uint32_t(max(min(kSub, jnew), 0) * RB);
-  const __amdgpu_buffer_rsrc_t Kb = buffer_of(Kh + int64_t(sub) * kSub * RB, cached);
-  const __amdgpu_buffer_rsrc_t Vb = buffer_of(Vh + int64_t(sub) * kSub * RB, cached);
-  u32x4 kreg[8];
-  const uint32_t koff = (ln >> 3) * RB + (ln & 7) * 16;
-  auto load_pair = [&](int p0) {
+    const int64_t bh = int64_t(b) * a.Hkv + hk;
+    const int64_t slot0 = bh * a.slots + mt0;
+    const unsigned char* Kh = static_cast<const unsigned char*>(a.cK) + slot0 * RB;
+    const unsigned char* Vh = static_cast<const unsigned char*>(a.cV) + slot0 * RB;
+    // A workgroup owns a chunk of 256 slots; each wavefront works alone on 64 rows ("sub-chunk") of it:
+    // while it computes on its keys, its V rows are in flight.
+    unsigned char* mine = stage + w * kWaveStage;
+    double* mine_opnd = opnd[kOwnOpnd ? w : 0];
+    const int ln = lane;
+    // K loads of a sub-chunk.  The K pass takes a row's bytes in pieces of 64 (one LDS staging round
+    // each); the loads fetch two pieces at a time as whole 128-byte lines: 8 lanes per row, 8 rows
+    // per load, 8 loads.  They are non-temporal like the V loads below: every K and V byte is
+    // needed once per step, and a stream that does not settle in the caches leaves them to the
+    // step's small read-write arrays (measured on a streaming probe with this access pattern:
+    // 6.25 -> 6.7 TB/s; in 64-byte half lines the hint costs bandwidth instead, the second half
+    // of a line then comes from memory again).  The next pair is requested as soon as this one
+    // sits in LDS.
+    static_assert(NP % 2 == 0, "pieces are loaded in pairs");
+    // Both streams go through buffer descriptors that end with the wavefront's last row: rows past it
+    // read as zero, and a load costs at most one address instruction (64-bit addresses of clamped rows
+    // cost six, 190 of a bf16 chunk's 2300 vector instructions per wavefront).
+    const int sub = __builtin_amdgcn_readfirstlane(grp * (kChunk / kSub) + w);
+    const int rows = min(kSub, total - sub * kSub);  // <= 0: nothing for this wavefront
+    // The new token's row: its wavefront (at most one of the head) writes it to the cache, puts its K among the staged
+    // rows and takes its term of P V from registers; the streams end before it.
+    const int jnew = count - sub * kSub;
+    const bool owner = jnew >= 0 && jnew < kSub;
+    const uint32_t cached = uint32_t(max(min(kSub, jnew), 0) * RB);
+    const __amdgpu_buffer_rsrc_t Kb = buffer_of(Kh + int64_t(sub) * kSub * RB, cached);
+    const __amdgpu_buffer_rsrc_t Vb = buffer_of(Vh + int64_t(sub) * kSub * RB, cached);
+    u32x4 kreg[8];
+    const uint32_t koff = (ln >> 3) * RB + (ln & 7) * 16;
+    auto load_pair = [&](int p0) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) kreg[i] = stream16(Kb, koff + p0 * kPiece + i * 8 * RB);
-  };
-  // (the candidate's row is needed first, and loads arrive in order)
-  typename RowShare::Bits craw[kCand];
-  int cexp[kCand];
-#pragma unroll
-  for (int c = 0; c < kCand; ++c) {
-    craw[c] = RowShare::load(static_cast<const T*>(a.cK) + (slot0 + max(cs[c], 0)) * D, lane);
-    cexp[c] = sizeof(T) == 1 ? int(a.cKe[slot0 + max(cs[c], 0)]) : 0;
-  }
-  typename Share::Bits kraw = 0, vraw = 0;
-  if (owner) {
-    kraw = Share::load(kn + li * kv.sn + b * kv.sb + hk * kv.sh, lane);
-    vraw = Share::load(vn + li * vv.sn + b * vv.sb + hk * vv.sh, lane);
-  }
-  if (rows > 0) load_pair(0);
-  // ---- operands to LDS: queries, and the keys of the eviction candidates with their norms
-  auto lay_out = [&](int v, const double (&x)[E]) {
-    if constexpr (E == 2)
-      *reinterpret_cast<double2*>(mine_opnd + operand_index<T, NV>(v, 2 * lane)) = make_double2(x[0], x[1]);
-    else
-      mine_opnd[operand_index<T, NV>(v, lane)] = x[0];
-  };
-#pragma unroll
-  for (int i = 0; i < NQ; ++i) {
-    double x[E];
-    Share::widen(qraw[i], x);
-    if (head_of(i) < G) lay_out(head_of(i), x);
-  }
-  double cn[kCand];
-#pragma unroll
-  for (int c = 0; c < kCand; ++c) {
-    double x[E];
-    RowShare::widen(craw[c], x);
-#pragma unroll
-    for (int e = 0; e < E; ++e) x[e] = cs[c] < 0 ? 0.0 : sizeof(T) == 1 ? x[e] * pow2_f64(cexp[c]) : x[e];
-    if (kOwnOpnd || w == c % 4) lay_out(G + c, x);
-    cn[c] = sqrt(square_sum<sizeof(T) == 4, E>(x));
-  }
-  if (!kOwnOpnd) lds_barrier();  // the operands are in LDS; the K rows may still be on their way
-  // the new row's K and V as they enter the cache: K as stored, with an fp8 row's power of two, and V's values
-  typename RowShare::Bits knew = 0;
-  int kexp = 0;
-  float vnew[E];
-  if (owner) {
-    double y[E];
-    Share::widen(vraw, y);
-    T* Kc = static_cast<T*>(a.cK) + (slot0 + count) * D;
-    T* Vc = static_cast<T*>(a.cV) + (slot0 + count) * D;
-    typename RowShare::Bits vst;
-    if constexpr (sizeof(T) == 1) {
-      // fp8 cache: encoded; the row's largest magnitude decides its power of two
-      static_assert(E == 2, "two elements per lane");
-      double x[E];
-      Share::widen(kraw, x);
-      const int ek = fp8_row_exponent(fast_wave_max(fmax(fabs(x[0]), fabs(x[1]))));
-      const int ev = fp8_row_exponent(fast_wave_max(fmax(fabs(y[0]), fabs(y[1]))));
-      kexp = ek;
-      vst = 0;
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
-        const uint8_t ck = fp8_encode(ldexp(x[e], -ek)), cv = fp8_encode(ldexp(y[e], -ev));
-        knew |= typename RowShare::Bits(ck) << (8 * e);
-        vst |= typename RowShare::Bits(cv) << (8 * e);
-        vnew[e] = Elem<T>::to_f32(cv) * pow2_f32(ev);
-      }
-      if (lane == 0) {
-        st_agent(a.cKe + slot0 + count, int8_t(ek));
-        st_agent(a.cVe + slot0 + count, int8_t(ev));
-      }
-    } else {
-      knew = kraw;
-      vst = vraw;
-#pragma unroll
-      for (int e = 0; e < E; ++e) vnew[e] = float(y[e]);
-    }
-    // (write-through: the head's closing workgroup may read the row in this launch, and stores the score again)
-    st_agent(reinterpret_cast<typename RowShare::Bits*>(Kc) + lane, knew);
-    st_agent(reinterpret_cast<typename RowShare::Bits*>(Vc) + lane, vst);
-    if (lane == 0) {
-      st_agent(a.cscore + slot0 + count, 0.0);
-      st_agent(a.cpos + slot0 + count, a.new_pos);
-    }
-  }
-  if (rows <= 0) {  // this wavefront only takes part in the combination
-    if (ln < G) wmax[w][ln] = -INFINITY;
-  } else {
-    const int tr = ln / TPR, tc = ln % TPR;
-    // ---- K pass in the layout of v_mfma_f64_4x4x4_4b: D[i][j] += A[i][k] B[k][j] in four blocks b,
-    // where lane i + 4 b + 16 k holds A, lane j + 4 b + 16 k holds B and lane j + 4 b + 16 i holds D.
-    // i is one of four cache rows, j one of four operand vectors (queries, candidate keys), and k one
-    // of the four 16-byte parts of a row piece: a lane takes its part's elements one after the other,
-    // for four rows (set s of the staged rows holds rows s + 4 b + 16 i), so that an operand read
-    // from LDS serves four products.  Four vectors go through the matrix instruction, which adds the parts
-    // up; it does 16 products per cycle, like the vector ALU, so one or two
-    // vectors, which would leave its columns empty, are multiplied there (with the squared norm) and
-    // only added up by it, as products with ones.
-    // Either way the lane's own row (its lane number) is one transposition inside a quad of lanes away.
-    // With one row per lane and the operands as scalar loads, fetched a step ahead, a wavefront of a
-    // small launch spent 12900 cycles here, most of them waiting for one cache line of operands after
-    // the other (2 KB per head at G = 1); it now spends 5300.  Where the stream of K and V is the bound
-    // both forms take the same time; issued one layer per call, 32 layers take 4.8 % less.
-    double acc[4][CG > 0 ? CG : 1], part[4][NR + 1];
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-#pragma unroll
-      for (int c = 0; c < CG; ++c) acc[s][c] = 0.0;
-#pragma unroll
-      for (int c = 0; c <= NR; ++c) part[s][c] = 0.0;
-    }
-    const unsigned char* arow = mine + (((ln >> 2) & 3) * 4 + (ln & 3)) * kPitch + (ln >> 4) * 16;
-    const double* bcol = mine_opnd + (min(ln & 3, NV - 1) * 4 + (ln >> 4)) * 2;  // vector ln % 4 of a group (three: the last one twice)
-    const double* ball = mine_opnd + (CG * 16 + (ln >> 4)) * 2;       // first of the left-over vectors
-    // the staging lanes' rows: i * 8 + t
-    const int t = ln >> 3;
-    unsigned char* srow = mine + (t & 3) * kSetBytes + (t >> 2) * 4 * kPitch + (ln & 3) * 16;
-    // V rows (load i: rows i * RPI + tr): a bf16 or fp8 sub-chunk is requested whole, as far as the
-    // registers allow during the last piece of the K pass (fp8 all of it, bf16 half) and the rest right after;
-    // fp32 rows travel in quarters through two register sets.
-    constexpr int VE = kMmaV ? (sizeof(T) == 1 ? NVL : NVL / 2) : NVL / 2;  // loads requested during the K pass
-    constexpr int VQ = NVL / 4;
-    VRaw vbuf[kMmaV ? NVL : NVL / 2];
-    const uint32_t voff = tr * RB + tc * VB;
-    auto load_v = [&](int i, int slot) { vbuf[slot] = stream_raw<VB>(Vb, voff + i * RPI * RB); };
-    // this lane's score-side loads ride along
-    const bool valid = ln < rows;
-    const int j = sub * kSub + ln;
-    const bool fresh = ln == jnew;  // (only in the new row's wavefront)
-    const int pos = fresh ? a.new_pos : valid ? a.cpos[slot0 + j] : 0;
-    // fp8 cache: the powers of two of this lane's K and V row
-    int rek = 0, rev = 0;
-    if constexpr (sizeof(T) == 1) {
-      rek = fresh ? kexp : valid ? a.cKe[slot0 + j] : 0;
-      rev = valid && !fresh ? a.cVe[slot0 + j] : -120;
-    }
-    constexpr int kShareLanes = kPiece / int(sizeof(knew));  // lanes that hold a piece of the new row
-    auto stage_piece = [&](int p) {
-      // The staging area is private to the wavefront and LDS serves a wavefront's requests in
-      // order, so the piece hand-over needs compiler ordering only.
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      if (((ln >> 2) & 1) == (p & 1)) {  // the lanes that hold this piece's half of the lines
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-          *reinterpret_cast<u32x4*>(srow + (((2 * i) & 3) * 4 + (i >> 1)) * kPitch) = kreg[i];
-      }
-      // The new row, over the zeros that were loaded in its place: its sums then have the order of every other
-      // row's, so that twin keys tie (fp32 rows: an order of its own made the newer of two twins the
-      // better match in a third of all cases).
-      if (owner) {
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        if (ln / kShareLanes == p)
-          *reinterpret_cast<typename RowShare::Bits*>(mine + (jnew & 3) * kSetBytes + (((jnew >> 2) & 3) * 4 + (jnew >> 4)) * kPitch +
-                                                      ln % kShareLanes * int(sizeof(knew))) = knew;
-      }
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
+      for (int i = 0; i < 8; ++i) kreg[i] = stream16(Kb, koff + p0 * kPiece + i * 8 * RB);
     };
-    auto multiply_piece = [&](int p) {
-      u32x4 ar[4];
-#pragma unroll
-      for (int s = 0; s < 4; ++s) ar[s] = *reinterpret_cast<const u32x4*>(arow + s * kSetBytes);
-#pragma unroll
-      for (int e = 0; e < EL / 2; ++e) {
-        double2 bg[CG > 0 ? CG : 1], br[NR > 0 ? NR : 1];
-#pragma unroll
-        for (int c = 0; c < CG; ++c) bg[c] = *reinterpret_cast<const double2*>(bcol + (p * (EL / 2) + e) * NV * 8 + c * 32);
-#pragma unroll
-        for (int c = 0; c < NR; ++c) br[c] = *reinterpret_cast<const double2*>(ball + (p * (EL / 2) + e) * NV * 8 + c * 8);
-#pragma unroll
-        for (int s0 = 0; s0 < 4; s0 += 2) {  // two sets at a time: independent products, few registers
-          double x0[2], x1[2];
-#pragma unroll
-          for (int i = 0; i < 2; ++i) {
-            pair_f64<T>(ar[s0 + i], e, x0[i], x1[i]);
-#pragma unroll
-            for (int c = 0; c < CG; ++c)
-              acc[s0 + i][c] = __builtin_amdgcn_mfma_f64_4x4x4f64(x0[i], bg[c].x, acc[s0 + i][c], 0, 0, 0);
-          }
-#pragma unroll
-          for (int i = 0; i < 2; ++i) {
-            double(&ps)[NR + 1] = part[s0 + i];
-#pragma unroll
-            for (int c = 0; c < CG; ++c)
-              acc[s0 + i][c] = __builtin_amdgcn_mfma_f64_4x4x4f64(x1[i], bg[c].y, acc[s0 + i][c], 0, 0, 0);
-#pragma unroll
-            for (int c = 0; c < NR; ++c) ps[c] = fma(x1[i], br[c].y, fma(x0[i], br[c].x, ps[c]));
-            ps[NR] = fma(x1[i], x1[i], fma(x0[i], x0[i], ps[NR]));
-          }
-          __builtin_amdgcn_sched_barrier(0);  // interleaving more of them costs registers
-        }
-      }
-    };
-#pragma unroll 1
-    for (int p = 0; p < NP - 1; ++p) {
-      stage_piece(p);
-      if (p & 1) load_pair(p + 1);
-      multiply_piece(p);
-    }
-    stage_piece(NP - 1);
-#pragma unroll
-    for (int i = 0; i < VE; ++i) load_v(i, i);
-    multiply_piece(NP - 1);
-    if constexpr (kMmaV) {
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int i = VE; i < NVL; ++i) load_v(i, i);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    // every lane takes its own row's products
-    auto own = [&](double v0, double v1, double v2, double v3) {
-      const double lo = (ln & 1) ? v1 : v0, hi = (ln & 1) ? v3 : v2;
-      return (ln & 2) ? hi : lo;
-    };
-    double dot[NV], nr;
-#pragma unroll
-    for (int c = 0; c <= NR; ++c) {
-      double t4[4];
-#pragma unroll
-      for (int s = 0; s < 4; ++s) t4[s] = __builtin_amdgcn_mfma_f64_4x4x4f64(part[s][c], 1.0, 0.0, 0, 0, 0);
-      (c == NR ? nr : dot[CG * 4 + c]) = own(t4[0], t4[1], t4[2], t4[3]);
-    }
-#pragma unroll
-    for (int c = 0; c < CG; ++c) {
-      auto column = [&](auto jc) {  // operand vector 4 c + jc: lane jc of every quad holds its results
-        constexpr int j = decltype(jc)::value, bcast = j * 0x55;
-        if (4 * c + j < NV) dot[4 * c + j] = own(dpp_f64<bcast>(acc[0][c]), dpp_f64<bcast>(acc[1][c]),
-                                                 dpp_f64<bcast>(acc[2][c]), dpp_f64<bcast>(acc[3][c]));
-      };
-      column(std::integral_constant<int, 0>{});
-      column(std::integral_constant<int, 1>{});
-      column(std::integral_constant<int, 2>{});
-      column(std::integral_constant<int, 3>{});
-    }
-    if constexpr (sizeof(T) == 1) {
-      // the K pass worked on the codes: the row's power of two scales its dot products and its
-      // squared norm (exactly: the sums are exact, see the precision notes of the file header)
-      const double sk = pow2_f64(rek);
-#pragma unroll
-      for (int v = 0; v < NV; ++v) dot[v] *= sk;
-      nr *= sk * sk;
-    }
-    // ---- softmax statistics of the sub-chunk; the lane owns cache row sub*kSub + lane
-    const int64_t pidx = sub_index(a, bh, mt3, sub) * G;
-    double recv = 0.0;  // this lane's element of the sub-chunk record
-    // The probabilities go to the staging area (the K pass is done with it) for the V pass: as fp32, or, for
-    // its matrix products, each as three bf16 terms that add up to it exactly (an fp32 value has three times
-    // eight significant bits) but for a power of two, in the order of their A operand: term t of query head g is row 3 g + t of
-    // kTermPitch bytes, cache row r its element 16 (r % 4) + r / 4.
-    constexpr int kTermPitch = 128 + 16;
-    static_assert(!kMmaV || (RPI == 4 && 3 * G * kTermPitch <= kWaveStage), "the terms fit the staging area");
-    float* psf = reinterpret_cast<float*>(mine);  // [G][kSub]
-    unsigned char* const term = mine + ((ln & 3) * 16 + (ln >> 2)) * 2;
-    // bf16 ends at 2^-133, an fp32 probability at 2^-149: the terms are those of the probability times 2^kTermScale, which
-    // the sums are rid of again (unscaled, a probability of 2e-38 lost 9 of its bits, which a V element of 1e38 shows).
-    // fp8 cache: the V pass works on the codes, so a row's power of two rides on its probability, taken
-    // relative to the largest of the sub-chunk (which multiplies the sums: the terms keep their range).  These powers lie
-    // up to 240 apart, and codes end at 448, 64 of which times 2^112 are finite.
-    constexpr int kTermScale = sizeof(T) == 1 ? 112 : 24;
-    const int rev_max = sizeof(T) == 1 ? -fast_wave_min(-rev) : 0;  // (-120, the smallest there is, in lanes without a cached row)
-    float pnew[G];  // the new row's probabilities
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      const double sg = div_root<D>(dot[g]);
-      const double mx = fast_wave_max(valid ? sg : -INFINITY);
-      const double e = valid ? exp(sg - mx) : 0.0;
-      if constexpr (kMmaV) {
-        const float p1 = sizeof(T) == 1 ? ldexpf(float(e), rev - rev_max + kTermScale) : float(e) * pow2_f32(kTermScale);
-        const float p2 = p1 - __uint_as_float(__float_as_uint(p1) & 0xFFFF0000u);
-        const float p3 = p2 - __uint_as_float(__float_as_uint(p2) & 0xFFFF0000u);
-        *reinterpret_cast<uint16_t*>(term + (3 * g) * kTermPitch) = uint16_t(__float_as_uint(p1) >> 16);
-        *reinterpret_cast<uint16_t*>(term + (3 * g + 1) * kTermPitch) = uint16_t(__float_as_uint(p2) >> 16);
-        *reinterpret_cast<uint16_t*>(term + (3 * g + 2) * kTermPitch) = uint16_t(__float_as_uint(p3) >> 16);
-      } else {
-        psf[g * kSub + ln] = float(e);
-      }
-      if (owner) pnew[g] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(float(e)), jnew));
-      if (valid) st_agent(&a.elog[elog_index(a, bh, mt3, G, g, j)], e);
-      const double sm = fast_wave_sum(e);
-      if (ln == g) {
-        recv = mx;
-        wmax[w][g] = mx;
-      }
-      if (ln == G + g) recv = sm;
-    }
-    // candidates: cosine of this row against each candidate key (Eq. 9), sub-chunk arg-max
-    const double nrow = sqrt(nr);
+    // (the candidate's row is needed first, and loads arrive in order)
+    typename RowShare::Bits craw[kCand];
+    int cexp[kCand];
 #pragma unroll
     for (int c = 0; c < kCand; ++c) {
-      const double den = cn[c] * nrow;
-      const double u = den > 0.0 ? dot[G + c] / den : 0.0;
-      const Best m = fast_wave_best_match(u, pos, (valid && cs[c] >= 0 && j != cs[c]) ? j : -1);
-      if (ln == 2 * G + c) recv = m.u;
-      if (ln == 2 * G + kCand + c) recv = double(m.slot);
+      craw[c] = RowShare::load(static_cast<const T*>(a.cK) + (slot0 + max(cs[c], 0)) * D, lane);
+      cexp[c] = sizeof(T) == 1 ? int(a.cKe[slot0 + max(cs[c], 0)]) : 0;
     }
-    if (ln < kRec) st_agent(&a.rec[(pidx / G) * kRec + ln], recv);  // the record in one store
-    // ---- partial P V.  The wavefront's partial rows (one per query head) go to its staging area for the
-    // combination over the workgroup.
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    float* xch = reinterpret_cast<float*>(mine);
-    if constexpr (kMmaV) {
-      // On the matrix core, in fp32: v_mfma_f32_16x16x32_bf16 (lane l: A[l % 16][8 (l / 16) ..], B[8 (l / 16) ..][l % 16],
-      // D[4 (l / 16) + r][l % 16]) multiplies the probabilities' terms, query head g's as its rows
-      // 4 g .. 4 g + 2, with 32 V rows.  A lane holds eight columns of every fourth row, so instruction
-      // j takes column j of every lane, and two rows' elements are one permutation away from a word
-      // of its B operand.  The products are exact, the sums over the rows need no exchange between lanes.
-      // (One multiply-add per element, query head and lane, and the sums over the row groups through
-      // LDS: 780 vector instructions per wavefront with four query heads, 328 with an fp8 cache; now 100 and 120.)
-      constexpr int GB = (G + 3) / 4;  // blocks of four query heads
-      bf16x8 pa[GB][2];
+    typename Share::Bits kraw = 0, vraw = 0;
+    if (owner) {
+      kraw = Share::load(kn + li * kv.sn + b * kv.sb + hk * kv.sh, lane);
+      vraw = Share::load(vn + li * vv.sn + b * vv.sb + hk * vv.sh, lane);
+    }
+    if (rows > 0) load_pair(0);
+    // ---- operands to LDS: queries, and the keys of the eviction candidates with their norms
+    auto lay_out = [&](int v, const double (&x)[E]) {
+      if constexpr (E == 2)
+        *reinterpret_cast<double2*>(mine_opnd + operand_index<T, NV>(v, 2 * lane)) = make_double2(x[0], x[1]);
+      else
+        mine_opnd[operand_index<T, NV>(v, lane)] = x[0];
+    };
 #pragma unroll
-      for (int gb = 0; gb < GB; ++gb)
+    for (int i = 0; i < NQ; ++i) {
+      double x[E];
+      Share::widen(qraw[i], x);
+      if (head_of(i) < G) lay_out(head_of(i), x);
+    }
+    double cn[kCand];
 #pragma unroll
-        for (int hf = 0; hf < 2; ++hf) {
-          const int g = min(gb * 4 + (tc >> 2), G - 1), t = min(tc & 3, 2);  // (rows without a term repeat another; their sums are not used)
-          pa[gb][hf] = *reinterpret_cast<const bf16x8*>(mine + (3 * g + t) * kTermPitch + tr * 32 + hf * 16);
+    for (int c = 0; c < kCand; ++c) {
+      double x[E];
+      RowShare::widen(craw[c], x);
+#pragma unroll
+      for (int e = 0; e < E; ++e) x[e] = cs[c] < 0 ? 0.0 : sizeof(T) == 1 ? x[e] * pow2_f64(cexp[c]) : x[e];
+      if (kOwnOpnd || w == c % 4) lay_out(G + c, x);
+      cn[c] = sqrt(square_sum<sizeof(T) == 4, E>(x));
+    }
+    if (!kOwnOpnd) lds_barrier();  // the operands are in LDS; the K rows may still be on their way
+    // the new row's K and V as they enter the cache: K as stored, with an fp8 row's power of two, and V's values
+    typename RowShare::Bits knew = 0;
+    int kexp = 0;
+    float vnew[E];
+    if (owner) {
+      double y[E];
+      Share::widen(vraw, y);
+      T* Kc = static_cast<T*>(a.cK) + (slot0 + count) * D;
+      T* Vc = static_cast<T*>(a.cV) + (slot0 + count) * D;
+      typename RowShare::Bits vst;
+      if constexpr (sizeof(T) == 1) {
+        // fp8 cache: encoded; the row's largest magnitude decides its power of two
+        static_assert(E == 2, "two elements per lane");
+        double x[E];
+        Share::widen(kraw, x);
+        const int ek = fp8_row_exponent(fast_wave_max(fmax(fabs(x[0]), fabs(x[1]))));
+        const int ev = fp8_row_exponent(fast_wave_max(fmax(fabs(y[0]), fabs(y[1]))));
+        kexp = ek;
+        vst = 0;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          const uint8_t ck = fp8_encode(ldexp(x[e], -ek)), cv = fp8_encode(ldexp(y[e], -ev));
+          knew |= typename RowShare::Bits(ck) << (8 * e);
+          vst |= typename RowShare::Bits(cv) << (8 * e);
+          vnew[e] = Elem<T>::to_f32(cv) * pow2_f32(ev);
         }
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      f32x4 o[GB][8];
-#pragma unroll
-      for (int j2 = 0; j2 < 4; ++j2) {  // columns 2 j2 and 2 j2 + 1 of the lane's eight
-#pragma unroll
-        for (int hf = 0; hf < 2; ++hf) {
-          u32x4 b0, b1;
-#pragma unroll
-          for (int x = 0; x < 4; ++x) {  // rows 2 x and 2 x + 1 of the lane's eight
-            const VRaw &r0 = vbuf[hf * 8 + 2 * x], &r1 = vbuf[hf * 8 + 2 * x + 1];
-            uint32_t lo, hi;  // the two rows' columns, as bf16 pairs
-            if constexpr (sizeof(T) == 1) {
-              // (codes have four significant bits: exact in bf16)
-              const uint32_t pair = __builtin_amdgcn_perm(r1[j2 / 2], r0[j2 / 2], j2 & 1 ? 0x07030602u : 0x05010400u);
-              lo = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(pair, 1.0f, false));
-              hi = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(pair, 1.0f, true));
-            } else {
-              lo = __builtin_amdgcn_perm(r1[j2], r0[j2], 0x05040100u);
-              hi = __builtin_amdgcn_perm(r1[j2], r0[j2], 0x07060302u);
-            }
-            b0[x] = lo;
-            b1[x] = hi;
-          }
-#pragma unroll
-          for (int gb = 0; gb < GB; ++gb) {
-            const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-            o[gb][2 * j2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa[gb][hf], __builtin_bit_cast(bf16x8, b0),
-                                                                    hf ? o[gb][2 * j2] : zero, 0, 0, 0);
-            o[gb][2 * j2 + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa[gb][hf], __builtin_bit_cast(bf16x8, b1),
-                                                                        hf ? o[gb][2 * j2 + 1] : zero, 0, 0, 0);
-          }
+        if (lane == 0) {
+          st_agent(a.cKe + slot0 + count, int8_t(ek));
+          st_agent(a.cVe + slot0 + count, int8_t(ev));
         }
+      } else {
+        knew = kraw;
+        vst = vraw;
+#pragma unroll
+        for (int e = 0; e < E; ++e) vnew[e] = float(y[e]);
       }
-      auto back = [&](float x) { return sizeof(T) == 1 ? ldexpf(x, rev_max - kTermScale) : x * pow2_f32(-kTermScale); };
-      float all = 0.f;  // not finite if a sum is not
+      // (write-through: the head's closing workgroup may read the row in this launch, and stores the score again)
+      st_agent(reinterpret_cast<typename RowShare::Bits*>(Kc) + lane, knew);
+      st_agent(reinterpret_cast<typename RowShare::Bits*>(Vc) + lane, vst);
+      if (lane == 0) {
+        st_agent(a.cscore + slot0 + count, 0.0);
+        st_agent(a.cpos + slot0 + count, a.new_pos);
+      }
+    }
+    if (rows <= 0) {  // this wavefront only takes part in the combination
+      if (ln < G) wmax[w][ln] = -INFINITY;
+    } else {
+      const int tr = ln / TPR, tc = ln % TPR;
+      // ---- K pass in the layout of v_mfma_f64_4x4x4_4b: D[i][j] += A[i][k] B[k][j] in four blocks b,
+      // where lane i + 4 b + 16 k holds A, lane j + 4 b + 16 k holds B and lane j + 4 b + 16 i holds D.
+      // i is one of four cache rows, j one of four operand vectors (queries, candidate keys), and k one
+      // of the four 16-byte parts of a row piece: a lane takes its part's elements one after the other,
+      // for four rows (set s of the staged rows holds rows s + 4 b + 16 i), so that an operand read
+      // from LDS serves four products.  Four vectors go through the matrix instruction, which adds the parts
+      // up; it does 16 products per cycle, like the vector ALU, so one or two
+      // vectors, which would leave its columns empty, are multiplied there (with the squared norm) and
+      // only added up by it, as products with ones.
+      // Either way the lane's own row (its lane number) is one transposition inside a quad of lanes away.
+      // With one row per lane and the operands as scalar loads, fetched a step ahead, a wavefront of a
+      // small launch spent 12900 cycles here, most of them waiting for one cache line of operands after
+      // the other (2 KB per head at G = 1); it now spends 5300.  Where the stream of K and V is the bound
+      // both forms take the same time; issued one layer per call, 32 layers take 4.8 % less.
+      double acc[4][CG > 0 ? CG : 1], part[4][NR + 1];
 #pragma unroll
-      for (int gb = 0; gb < GB; ++gb)
+      for (int s = 0; s < 4; ++s) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const f32x4 d = o[gb][j];
-          o[gb][j][0] = (d[2] + d[1]) + d[0];
-          all += o[gb][j][0];
+        for (int c = 0; c < CG; ++c) acc[s][c] = 0.0;
+#pragma unroll
+        for (int c = 0; c <= NR; ++c) part[s][c] = 0.0;
+      }
+      const unsigned char* arow = mine + (((ln >> 2) & 3) * 4 + (ln & 3)) * kPitch + (ln >> 4) * 16;
+      const double* bcol = mine_opnd + (min(ln & 3, NV - 1) * 4 + (ln >> 4)) * 2;  // vector ln % 4 of a group (three: the last one twice)
+      const double* ball = mine_opnd + (CG * 16 + (ln >> 4)) * 2;       // first of the left-over vectors
+      // the staging lanes' rows: i * 8 + t
+      const int t = ln >> 3;
+      unsigned char* srow = mine + (t & 3) * kSetBytes + (t >> 2) * 4 * kPitch + (ln & 3) * 16;
+      // V rows (load i: rows i * RPI + tr): a bf16 or fp8 sub-chunk is requested whole, as far as the
+      // registers allow during the last piece of the K pass (fp8 all of it, bf16 half) and the rest right after;
+      // fp32 rows travel in quarters through two register sets.
+      constexpr int VE = kMmaV ? (sizeof(T) == 1 ? NVL : NVL / 2) : NVL / 2;  // loads requested during the K pass
+      constexpr int VQ = NVL / 4;
+      VRaw vbuf[kMmaV ? NVL : NVL / 2];
+      const uint32_t voff = tr * RB + tc * VB;
+      auto load_v = [&](int i, int slot) { vbuf[slot] = stream_raw<VB>(Vb, voff + i * RPI * RB); };
+      // this lane's score-side loads ride along
+      const bool valid = ln < rows;
+      const int j = sub * kSub + ln;
+      const bool fresh = ln == jnew;  // (only in the new row's wavefront)
+      const int pos = fresh ? a.new_pos : valid ? a.cpos[slot0 + j] : 0;
+      // fp8 cache: the powers of two of this lane's K and V row
+      int rek = 0, rev = 0;
+      if constexpr (sizeof(T) == 1) {
+        rek = fresh ? kexp : valid ? a.cKe[slot0 + j] : 0;
+        rev = valid && !fresh ? a.cVe[slot0 + j] : -120;
+      }
+      constexpr int kShareLanes = kPiece / int(sizeof(knew));  // lanes that hold a piece of the new row
+      auto stage_piece = [&](int p) {
+        // The staging area is private to the wavefront and LDS serves a wavefront's requests in
+        // order, so the piece hand-over needs compiler ordering only.
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (((ln >> 2) & 1) == (p & 1)) {  // the lanes that hold this piece's half of the lines
+#pragma unroll
+          for (int i = 0; i < 8; ++i)
+            *reinterpret_cast<u32x4*>(srow + (((2 * i) & 3) * 4 + (i >> 1)) * kPitch) = kreg[i];
         }
-      if (sizeof(T) == 2 && __ballot(!(fabsf(all) < INFINITY))) {
-        // An infinite element of V meets terms that are zero, which makes NaN of what is infinite, and scaled sums may
-        // overflow (from 2^104 on): the rows once more, two columns per lane, with each probability in one piece.
-        float pv[G][2];
-#pragma unroll
-        for (int g = 0; g < G; ++g) pv[g][0] = pv[g][1] = 0.f;
-#pragma unroll 1
-        for (int r = 0; r < int(cached / RB); ++r) {
-          const uint32_t x = __builtin_amdgcn_raw_buffer_load_b32(Vb, r * RB + ln * 4, 0, 0);
-          const uint16_t* tp = reinterpret_cast<const uint16_t*>(mine) + (r & 3) * 16 + (r >> 2);
-#pragma unroll
-          for (int g = 0; g < G; ++g) {
-            float p = 0.f;
-#pragma unroll
-            for (int t = 2; t >= 0; --t) p += __uint_as_float(uint32_t(tp[(3 * g + t) * (kTermPitch / 2)]) << 16);
-            p = back(p);
-            pv[g][0] = fmaf(p, __uint_as_float(x << 16), pv[g][0]);
-            pv[g][1] = fmaf(p, __uint_as_float(x & 0xFFFF0000u), pv[g][1]);
-          }
+        // The new row, over the zeros that were loaded in its place: its sums then have the order of every other
+        // row's, so that twin keys tie (fp32 rows: an order of its own made the newer of two twins the
+        // better match in a third of all cases).
+        if (owner) {
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+          __builtin_amdgcn_wave_barrier();
+          if (ln / kShareLanes == p)
+            *reinterpret_cast<typename RowShare::Bits*>(mine + (jnew & 3) * kSetBytes + (((jnew >> 2) & 3) * 4 + (jnew >> 4)) * kPitch +
+                                                        ln % kShareLanes * int(sizeof(knew))) = knew;
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
+      };
+      auto multiply_piece = [&](int p) {
+        u32x4 ar[4];
 #pragma unroll
-        for (int g = 0; g < G; ++g) *reinterpret_cast<float2*>(xch + g * D + ln * 2) = make_float2(pv[g][0], pv[g][1]);
-      } else {
+        for (int s = 0; s < 4; ++s) ar[s] = *reinterpret_cast<const u32x4*>(arow + s * kSetBytes);
 #pragma unroll
-        for (int gb = 0; gb < GB; ++gb) {
-          const int g = gb * 4 + tr;
-          if (g < G) {
+        for (int e = 0; e < EL / 2; ++e) {
+          double2 bg[CG > 0 ? CG : 1], br[NR > 0 ? NR : 1];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) xch[g * D + tc * 8 + j] = back(o[gb][j][0]);
+          for (int c = 0; c < CG; ++c) bg[c] = *reinterpret_cast<const double2*>(bcol + (p * (EL / 2) + e) * NV * 8 + c * 32);
+#pragma unroll
+          for (int c = 0; c < NR; ++c) br[c] = *reinterpret_cast<const double2*>(ball + (p * (EL / 2) + e) * NV * 8 + c * 8);
+#pragma unroll
+          for (int s0 = 0; s0 < 4; s0 += 2) {  // two sets at a time: independent products, few registers
+            double x0[2], x1[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+              pair_f64<T>(ar[s0 + i], e, x0[i], x1[i]);
+#pragma unroll
+              for (int c = 0; c < CG; ++c)
+                acc[s0 + i][c] = __builtin_amdgcn_mfma_f64_4x4x4f64(x0[i], bg[c].x, acc[s0 + i][c], 0, 0, 0);
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+              double(&ps)[NR + 1] = part[s0 + i];
+#pragma unroll
+              for (int c = 0; c < CG; ++c)
+                acc[s0 + i][c] = __builtin_amdgcn_mfma_f64_4x4x4f64(x1[i], bg[c].y, acc[s0 + i][c], 0, 0, 0);
+#pragma unroll
+              for (int c = 0; c < NR; ++c) ps[c] = fma(x1[i], br[c].y, fma(x0[i], br[c].x, ps[c]));
+              ps[NR] = fma(x1[i], x1[i], fma(x0[i], x0[i], ps[NR]));
+            }
+            __builtin_amdgcn_sched_barrier(0);  // interleaving more of them costs registers
           }
         }
+      };
+#pragma unroll 1
+      for (int p = 0; p < NP - 1; ++p) {
+        stage_piece(p);
+        if (p & 1) load_pair(p + 1);
+        multiply_piece(p);
       }
-    } else {
-      // fp32 rows: TPR lanes per row, RPI rows per load, then a sum over the row groups
-      float pv[G][kVec];
+      stage_piece(NP - 1);
 #pragma unroll
-      for (int g = 0; g < G; ++g)
+      for (int i = 0; i < VE; ++i) load_v(i, i);
+      multiply_piece(NP - 1);
+      if constexpr (kMmaV) {
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int e = 0; e < kVec; ++e) pv[g][e] = 0.f;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-#pragma unroll
-        for (int i = 0; i < VQ; ++i) {
-          const int r = (q * VQ + i) * RPI + tr;
-          const VRaw& x = vbuf[(q & 1) * VQ + i];
-#pragma unroll
-          for (int g = 0; g < G; ++g) {
-            const float p = psf[g * kSub + r];  // 0 for rows beyond the end
-#pragma unroll
-            for (int e = 0; e < kVec; ++e) pv[g][e] = fmaf(p, __uint_as_float(x[e]), pv[g][e]);
-          }
-        }
-        if (q + 2 < 4) {
-#pragma unroll
-          for (int i = 0; i < VQ; ++i) load_v((q + 2) * VQ + i, (q & 1) * VQ + i);
-        }
+        for (int i = VE; i < NVL; ++i) load_v(i, i);
+        __builtin_amdgcn_sched_barrier(0);
       }
+      // every lane takes its own row's products
+      auto own = [&](double v0, double v1, double v2, double v3) {
+        const double lo = (ln & 1) ? v1 : v0, hi = (ln & 1) ? v3 : v2;
+        return (ln & 2) ? hi : lo;
+      };
+      double dot[NV], nr;
+#pragma unroll
+      for (int c = 0; c <= NR; ++c) {
+        double t4[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) t4[s] = __builtin_amdgcn_mfma_f64_4x4x4f64(part[s][c], 1.0, 0.0, 0, 0, 0);
+        (c == NR ? nr : dot[CG * 4 + c]) = own(t4[0], t4[1], t4[2], t4[3]);
+      }
+#pragma unroll
+      for (int c = 0; c < CG; ++c) {
+        auto column = [&](auto jc) {  // operand vector 4 c + jc: lane jc of every quad holds its results
+          constexpr int j = decltype(jc)::value, bcast = j * 0x55;
+          if (4 * c + j < NV) dot[4 * c + j] = own(dpp_f64<bcast>(acc[0][c]), dpp_f64<bcast>(acc[1][c]),
+                                                   dpp_f64<bcast>(acc[2][c]), dpp_f64<bcast>(acc[3][c]));
+        };
+        column(std::integral_constant<int, 0>{});
+        column(std::integral_constant<int, 1>{});
+        column(std::integral_constant<int, 2>{});
+        column(std::integral_constant<int, 3>{});
+      }
+      if constexpr (sizeof(T) == 1) {
+        // the K pass worked on the codes: the row's power of two scales its dot products and its
+        // squared norm (exactly: the sums are exact, see the precision notes of the file header)
+        const double sk = pow2_f64(rek);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) dot[v] *= sk;
+        nr *= sk * sk;
+      }
+      // ---- softmax statistics of the sub-chunk; the lane owns cache row sub*kSub + lane
+      const int64_t pidx = sub_index(a, bh, mt3, sub) * G;
+      double recv = 0.0;  // this lane's element of the sub-chunk record
+      // The probabilities go to the staging area (the K pass is done with it) for the V pass: as fp32, or, for
+      // its matrix products, each as three bf16 terms that add up to it exactly (an fp32 value has three times
+      // eight significant bits) but for a power of two, in the order of their A operand: term t of query head g is row 3 g + t of
+      // kTermPitch bytes, cache row r its element 16 (r % 4) + r / 4.
+      constexpr int kTermPitch = 128 + 16;
+      static_assert(!kMmaV || (RPI == 4 && 3 * G * kTermPitch <= kWaveStage), "the terms fit the staging area");
+      float* psf = reinterpret_cast<float*>(mine);  // [G][kSub]
+      unsigned char* const term = mine + ((ln & 3) * 16 + (ln >> 2)) * 2;
+      // bf16 ends at 2^-133, an fp32 probability at 2^-149: the terms are those of the probability times 2^kTermScale, which
+      // the sums are rid of again (unscaled, a probability of 2e-38 lost 9 of its bits, which a V element of 1e38 shows).
+      // fp8 cache: the V pass works on the codes, so a row's power of two rides on its probability, taken
+      // relative to the largest of the sub-chunk (which multiplies the sums: the terms keep their range).  These powers lie
+      // up to 240 apart, and codes end at 448, 64 of which times 2^112 are finite.
+      constexpr int kTermScale = sizeof(T) == 1 ? 112 : 24;
+      const int rev_max = sizeof(T) == 1 ? -fast_wave_min(-rev) : 0;  // (-120, the smallest there is, in lanes without a cached row)
+      float pnew[G];  // the new row's probabilities
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
 #pragma unroll
       for (int g = 0; g < G; ++g) {
-#pragma unroll
-        for (int e = 0; e < kVec; ++e) {
-          float t = pv[g][e];
-#pragma unroll
-          for (int o = TPR; o < 64; o <<= 1) t += __shfl_xor(t, o, 64);
-          pv[g][e] = t;
+        const double sg = div_root<D>(dot[g]);
+        const double mx = fast_wave_max(valid ? sg : -INFINITY);
+        const double e = valid ? exp(sg - mx) : 0.0;
+        if constexpr (kMmaV) {
+          const float p1 = sizeof(T) == 1 ? ldexpf(float(e), rev - rev_max + kTermScale) : float(e) * pow2_f32(kTermScale);
+          const float p2 = p1 - __uint_as_float(__float_as_uint(p1) & 0xFFFF0000u);
+          const float p3 = p2 - __uint_as_float(__float_as_uint(p2) & 0xFFFF0000u);
+          *reinterpret_cast<uint16_t*>(term + (3 * g) * kTermPitch) = uint16_t(__float_as_uint(p1) >> 16);
+          *reinterpret_cast<uint16_t*>(term + (3 * g + 1) * kTermPitch) = uint16_t(__float_as_uint(p2) >> 16);
+          *reinterpret_cast<uint16_t*>(term + (3 * g + 2) * kTermPitch) = uint16_t(__float_as_uint(p3) >> 16);
+        } else {
+          psf[g * kSub + ln] = float(e);
         }
-        if (tr == 0) {
-#pragma unroll
-          for (int e = 0; e < kVec; ++e) xch[g * D + tc * kVec + e] = pv[g][e];
+        if (owner) pnew[g] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(float(e)), jnew));
+        if (valid) st_agent(&a.elog[elog_index(a, bh, mt3, G, g, j)], e);
+        const double sm = fast_wave_sum(e);
+        if (ln == g) {
+          recv = mx;
+          wmax[w][g] = mx;
         }
+        if (ln == G + g) recv = sm;
       }
-    }
-    if (owner) {  // the new row's term
+      // candidates: cosine of this row against each candidate key (Eq. 9), sub-chunk arg-max
+      const double nrow = sqrt(nr);
+#pragma unroll
+      for (int c = 0; c < kCand; ++c) {
+        const double den = cn[c] * nrow;
+        const double u = den > 0.0 ? dot[G + c] / den : 0.0;
+        const Best m = fast_wave_best_match(u, pos, (valid && cs[c] >= 0 && j != cs[c]) ? j : -1);
+        if (ln == 2 * G + c) recv = m.u;
+        if (ln == 2 * G + kCand + c) recv = double(m.slot);
+      }
+      if (ln < kRec) st_agent(&a.rec[(pidx / G) * kRec + ln], recv);  // the record in one store
+      // ---- partial P V.  The wavefront's partial rows (one per query head) go to its staging area for the
+      // combination over the workgroup.
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
+      float* xch = reinterpret_cast<float*>(mine);
+      if constexpr (kMmaV) {
+        // On the matrix core, in fp32: v_mfma_f32_16x16x32_bf16 (lane l: A[l % 16][8 (l / 16) ..], B[8 (l / 16) ..][l % 16],
+        // D[4 (l / 16) + r][l % 16]) multiplies the probabilities' terms, query head g's as its rows
+        // 4 g .. 4 g + 2, with 32 V rows.  A lane holds eight columns of every fourth row, so instruction
+        // j takes column j of every lane, and two rows' elements are one permutation away from a word
+        // of its B operand.  The products are exact, the sums over the rows need no exchange between lanes.
+        // (One multiply-add per element, query head and lane, and the sums over the row groups through
+        // LDS: 780 vector instructions per wavefront with four query heads, 328 with an fp8 cache; now 100 and 120.)
+        constexpr int GB = (G + 3) / 4;  // blocks of four query heads
+        bf16x8 pa[GB][2];
 #pragma unroll
-      for (int g = 0; g < G; ++g)
+        for (int gb = 0; gb < GB; ++gb)
 #pragma unroll
-        for (int e = 0; e < E; ++e) xch[g * D + E * lane + e] = fmaf(pnew[g], vnew[e], xch[g * D + E * lane + e]);
-    }
-  }
-  // ---- one partial output row per chunk and query head: the four wavefronts' rows, each
-  //      rescaled from its sub-chunk's maximum to the chunk's (fp32, like the rows themselves).
-  //      A quarter of the partial-output bytes of a row per sub-chunk: on this chip a written
-  //      byte costs the stream of K and V rows several read bytes.
-  lds_barrier();
-  for (int g = w; g < G; g += 4) {
-    double mc = wmax[0][g];
+          for (int hf = 0; hf < 2; ++hf) {
+            // (rows without a term repeat another; their sums are not used)
+            const int g = min(gb * 4 + (tc >> 2), G - 1), t = min(tc & 3, 2);
+            pa[gb][hf] = *reinterpret_cast<const bf16x8*>(mine + (3 * g + t) * kTermPitch + tr * 32 + hf * 16);
+          }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        f32x4 o[GB][8];
 #pragma unroll
-    for (int i = 1; i < 4; ++i) mc = fmax(mc, wmax[i][g]);
-    if (lane * 2 < D) {
-      float o0 = 0.f, o1 = 0.f;
+        for (int j2 = 0; j2 < 4; ++j2) {  // columns 2 j2 and 2 j2 + 1 of the lane's eight
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const double mw = wmax[i][g];
-        if (mw != -INFINITY) {
-          const float f = expf(float(mw - mc));
-          const float* xr = reinterpret_cast<const float*>(stage + i * kWaveStage) + g * D + lane * 2;
-          o0 = fmaf(f, xr[0], o0);
-          o1 = fmaf(f, xr[1], o1);
+          for (int hf = 0; hf < 2; ++hf) {
+            u32x4 b0, b1;
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {  // rows 2 x and 2 x + 1 of the lane's eight
+              const VRaw &r0 = vbuf[hf * 8 + 2 * x], &r1 = vbuf[hf * 8 + 2 * x + 1];
+              uint32_t lo, hi;  // the two rows' columns, as bf16 pairs
+              if constexpr (sizeof(T) == 1) {
+                // (codes have four significant bits: exact in bf16)
+                const uint32_t pair = __builtin_amdgcn_perm(r1[j2 / 2], r0[j2 / 2], j2 & 1 ? 0x07030602u : 0x05010400u);
+                lo = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(pair, 1.0f, false));
+                hi = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(pair, 1.0f, true));
+              } else {
+                lo = __builtin_amdgcn_perm(r1[j2], r0[j2], 0x05040100u);
+                hi = __builtin_amdgcn_perm(r1[j2], r0[j2], 0x07060302u);
+              }
+              b0[x] = lo;
+              b1[x] = hi;
+            }
+#pragma unroll
+            for (int gb = 0; gb < GB; ++gb) {
+              const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+              o[gb][2 * j2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa[gb][hf], __builtin_bit_cast(bf16x8, b0),
+                                                                      hf ? o[gb][2 * j2] : zero, 0, 0, 0);
+              o[gb][2 * j2 + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa[gb][hf], __builtin_bit_cast(bf16x8, b1),
+                                                                          hf ? o[gb][2 * j2 + 1] : zero, 0, 0, 0);
+            }
+          }
+        }
+        auto back = [&](float x) { return sizeof(T) == 1 ? ldexpf(x, rev_max - kTermScale) : x * pow2_f32(-kTermScale); };
+        float all = 0.f;  // not finite if a sum is not
+#pragma unroll
+        for (int gb = 0; gb < GB; ++gb)
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            const f32x4 d = o[gb][j];
+            o[gb][j][0] = (d[2] + d[1]) + d[0];
+            all += o[gb][j][0];
+          }
+        if (sizeof(T) == 2 && __ballot(!(fabsf(all) < INFINITY))) {
+          // An infinite element of V meets terms that are zero, which makes NaN of what is infinite, and scaled sums may
+          // overflow (from 2^104 on): the rows once more, two columns per lane, with each probability in one piece.
+          float pv[G][2];
+#pragma unroll
+          for (int g = 0; g < G; ++g) pv[g][0] = pv[g][1] = 0.f;
+#pragma unroll 1
+          for (int r = 0; r < int(cached / RB); ++r) {
+            const uint32_t x = __builtin_amdgcn_raw_buffer_load_b32(Vb, r * RB + ln * 4, 0, 0);
+            const uint16_t* tp = reinterpret_cast<const uint16_t*>(mine) + (r & 3) * 16 + (r >> 2);
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+              float p = 0.f;
+#pragma unroll
+              for (int t = 2; t >= 0; --t) p += __uint_as_float(uint32_t(tp[(3 * g + t) * (kTermPitch / 2)]) << 16);
+              p = back(p);
+              pv[g][0] = fmaf(p, __uint_as_float(x << 16), pv[g][0]);
+              pv[g][1] = fmaf(p, __uint_as_float(x & 0xFFFF0000u), pv[g][1]);
+            }
+          }
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+          __builtin_amdgcn_wave_barrier();
+#pragma unroll
+          for (int g = 0; g < G; ++g) *reinterpret_cast<float2*>(xch + g * D + ln * 2) = make_float2(pv[g][0], pv[g][1]);
+        } else {
+#pragma unroll
+          for (int gb = 0; gb < GB; ++gb) {
+            const int g = gb * 4 + tr;
+            if (g < G) {
+#pragma unroll
+              for (int j = 0; j < 8; ++j) xch[g * D + tc * 8 + j] = back(o[gb][j][0]);
+            }
+          }
+        }
+      } else {
+        // fp32 rows: TPR lanes per row, RPI rows per load, then a sum over the row groups
+        float pv[G][kVec];
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+          for (int e = 0; e < kVec; ++e) pv[g][e] = 0.f;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+#pragma unroll
+          for (int i = 0; i < VQ; ++i) {
+            const int r = (q * VQ + i) * RPI + tr;
+            const VRaw& x = vbuf[(q & 1) * VQ + i];
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+              const float p = psf[g * kSub + r];  // 0 for rows beyond the end
+#pragma unroll
+              for (int e = 0; e < kVec; ++e) pv[g][e] = fmaf(p, __uint_as_float(x[e]), pv[g][e]);
+            }
+          }
+          if (q + 2 < 4) {
+#pragma unroll
+            for (int i = 0; i < VQ; ++i) load_v((q + 2) * VQ + i, (q & 1) * VQ + i);
+          }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+#pragma unroll
+          for (int e = 0; e < kVec; ++e) {
+            float t = pv[g][e];
+#pragma unroll
+            for (int o = TPR; o < 64; o <<= 1) t += __shfl_xor(t, o, 64);
+            pv[g][e] = t;
+          }
+          if (tr == 0) {
+#pragma unroll
+            for (int e = 0; e < kVec; ++e) xch[g * D + tc * kVec + e] = pv[g][e];
+          }
         }
       }
-      const uint64_t two = uint64_t(__float_as_uint(o0)) | (uint64_t(__float_as_uint(o1)) << 32);
-      st_agent(reinterpret_cast<uint64_t*>(a.pacc + (chunk_index(a, bh, mt3, grp) * G + g) * D + lane * 2), two);
+      if (owner) {  // the new row's term
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+          for (int e = 0; e < E; ++e) xch[g * D + E * lane + e] = fmaf(pnew[g], vnew[e], xch[g * D + E * lane + e]);
+      }
     }
-  }
+    // ---- one partial output row per chunk and query head: the four wavefronts' rows, each
+    //      rescaled from its sub-chunk's maximum to the chunk's (fp32, like the rows themselves).
+    //      A quarter of the partial-output bytes of a row per sub-chunk: on this chip a written
+    //      byte costs the stream of K and V rows several read bytes.
+    lds_barrier();
+    for (int g = w; g < G; g += 4) {
+      double mc = wmax[0][g];
+#pragma unroll
+      for (int i = 1; i < 4; ++i) mc = fmax(mc, wmax[i][g]);
+      if (lane * 2 < D) {
+        float o0 = 0.f, o1 = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const double mw = wmax[i][g];
+          if (mw != -INFINITY) {
+            const float f = expf(float(mw - mc));
+            const float* xr = reinterpret_cast<const float*>(stage + i * kWaveStage) + g * D + lane * 2;
+            o0 = fmaf(f, xr[0], o0);
+            o1 = fmaf(f, xr[1], o1);
+          }
+        }
+        const uint64_t two = uint64_t(__float_as_uint(o0)) | (uint64_t(__float_as_uint(o1)) << 32);
+        st_agent(reinterpret_cast<uint64_t*>(a.pacc + (chunk_index(a, bh, mt3, grp) * G + g) * D + lane * 2), two);
+      }
+    }
   }  // (the workgroup has rows)
   // ---- ticket: the last workgroup of the head to arrive closes the head.  Every store above
   //      that it will read is a write-through store; they have completed once the memory
