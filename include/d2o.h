@@ -258,14 +258,15 @@ int d2o_append_events(d2o_ctx* ctx, int32_t layer, int32_t b, int32_t kv_head, i
 /* d2o_decode_step for callers that cannot allocate or hand over scratch memory at the time of
  * the call: code under HIP graph capture, tight serving loops, harnesses that forbid
  * allocation.  Same arguments, same results (bit for bit) and same errors as d2o_decode_step,
- * but the step's temporaries (per-slot softmax terms, per-chunk partial outputs and records,
- * the fp64 operand vectors) live in a static device array inside the library instead of the
- * context's scratch workspace, and the call makes no allocation of any kind (no device or
+ * but the step's temporaries (per-slot softmax terms, per-chunk partial outputs and records)
+ * live in a static device array inside the library instead of the context's scratch
+ * workspace, and the call makes no allocation of any kind (no device or
  * host memory, no events: kernel timing is off for these calls).  The array holds 64 MiB
  * (67108864 bytes) per GPU from the moment the library's code is loaded there until the
- * process ends; a context whose decode step needs more (about 10 G + 3 bytes per cache slot
- * of slots_per_seq, sequence and KV head, plus G + 3 KiB per layer, sequence and KV head at
- * d = 128) gets D2O_ERR_CAPACITY and nothing is launched.  All contexts on a GPU share the array, which keeps the last call's
+ * process ends; a context whose decode step needs more gets D2O_ERR_CAPACITY and nothing is
+ * launched.  It needs, per sequence and KV head and at d = 128, 10 G + 2 bytes (G = 4: + 3,
+ * G = 8: + 4) for each of slots_per_seq + 256 (n_layers + 1) slots, and 128 bytes per layer.
+ * All contexts on a GPU share the array, which keeps the last call's
  * contents: calls that overlap in time on one GPU (different streams or threads) race; calls
  * ordered on one stream do not.  Nothing is carried in it from one step to the next, so a
  * context may mix the two entry points freely. */

@@ -112,7 +112,7 @@ struct d2o_ctx {
   float* invnorm = nullptr;      // 1/|k_j| of every prompt key (fp32, filter only)
   int32_t* m_cand = nullptr;     // filter's best retained rank per evicted row; bit 31 = ambiguous
   float* m_thr = nullptr;        // filter's acceptance threshold of a flagged row
-  int32_t* amb_list = nullptr;   // flagged evicted ranks, ascending
+  int32_t* amb_list = nullptr;   // flagged evicted ranks, in no particular order
   int32_t* amb_cnt = nullptr;    // [B][Hkv]
   int32_t* m_ncand = nullptr;    // candidates collected for a flagged row
   int32_t* m_clist = nullptr;    // [..][npad][8] their retained ranks
@@ -215,7 +215,7 @@ hipError_t launch_encode_layer(d2o_ctx* c, int layer, hipStream_t s);
 hipError_t launch_encode_head(d2o_ctx* c, int layer, int b, int hk, int count, hipStream_t s);  // staging -> cache
 hipError_t launch_decode_head(d2o_ctx* c, int layer, int b, int hk, int count, hipStream_t s);  // cache -> staging
 // static_scratch: nullptr = the context's scratch workspace; otherwise the device address of the
-// library's static scratch array, which then holds the step's partial results and operands
+// library's static scratch array, which then holds the step's partial results
 hipError_t launch_decode(d2o_ctx* c, int layer0, int nl, View q, View k, View v, View out,
                          int new_pos, hipStream_t s, unsigned char* static_scratch = nullptr);
 hipError_t static_scratch_address(unsigned char** out);  // per device; first call per device looks it up
