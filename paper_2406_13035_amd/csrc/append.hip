@@ -186,10 +186,11 @@ __global__ __launch_bounds__(256) void permute_rows(const int32_t* __restrict__ 
 //                 lays the queries out as fp64 vectors, sets the entry count to N.
 //   block_stats   per (head, 256 rows, slice of the queries): the rows are staged in LDS once; a
 //                 wavefront takes tiles of 16 queries and forms their logits against the 256
-//                 rows, 64 rows at a time; per query the maximum and exp-sum over the chunk's
-//                 visible rows.
+//                 rows, 64 rows at a time; exp(logit - maximum of the 64 rows) of every one goes to
+//                 memory; per query the maximum and exp-sum over the chunk's visible rows.
 //   block_norm    per head and query: maximum and exact normaliser over the chunks.
-//   block_apply   the same tiling: logits again, p = exp(s - max) / normaliser; per row the sum
+//   block_apply   the same tiling: p = the stored exponential times exp(maximum of the 64 rows - maximum)
+//                 / normaliser; per row the sum
 //                 of the p of every query that sees it; the wavefront's 16 x d partial output
 //                 tile over the 256 rows, accumulated by the fp32 matrix instruction whose A
 //                 operand is the probability tile as the logits' instruction left it.
@@ -197,7 +198,10 @@ __global__ __launch_bounds__(256) void permute_rows(const int32_t* __restrict__ 
 //   block_finish  per head and query: the chunks' partial output rows added in ascending order.
 // A head's queries are cut into up to kMaxQuerySlices slices that run as workgroups of their own
 // (a block on a cache of a few thousand rows is too little work per head to fill the chip
-// otherwise); a row's score then grows by the slices' sums in slice order.
+// otherwise); a row's score then grows by the slices' sums in slice order.  The exponentials are kept, in fp64, because
+// the logits and they are what bounds the block (the fp64 units): with both formed again in block_apply, 256 tokens on
+// 2048-entry caches (32 heads) took 123 + 182 us in the two kernels, with 151 MB written and read 131 + 74.  They
+// have a bounded place (kBlockTermBytes): the query tiles go through the three kernels in as many passes as it takes.
 //
 // Register layouts of the two instructions (lane l, c = l % 16, kq = l / 16):
 //   operands   A[i = c][k = kq], B[k = kq][j = c]
@@ -389,11 +393,19 @@ __device__ __forceinline__ WaveWork wave_work(int w, int t_lo, int t_hi) {
   return WaveWork{share, t_lo + w / share, w % share};
 }
 
+// Place of the exponentials of row `row` of a chunk (256 rows) and query tile (counted from the pass's first):
+// [tile][chunk][head][256 rows][16 queries], so that the sixteen lanes of a row, and the four rows of an
+// instruction, are 512 bytes side by side.
+__device__ __forceinline__ int64_t term_index(int tile, int nch, int chunk, int heads, int bh, int row) {
+  return (((int64_t(tile) * nch + chunk) * heads + bh) * kChunk + row) * kQT;
+}
+
 template <typename T, int D>
 __global__ __launch_bounds__(256) void block_stats(const int32_t* __restrict__ ctotal, const int32_t* __restrict__ meta,
                                                    const T* __restrict__ cK, const int8_t* __restrict__ cKe,
-                                                   const double* __restrict__ aq, double* __restrict__ stat, int m, int G,
-                                                   int maxq, int64_t slots, int tiles_per_slice) {
+                                                   const double* __restrict__ aq, double* __restrict__ stat,
+                                                   double* __restrict__ gmax, double* __restrict__ term, int m, int G,
+                                                   int maxq, int64_t slots, int tile0, int tile1, int tiles_per_slice) {
   typedef BlockRows<T, D> BR;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int bhN = gridDim.x, bh = blockIdx.x, chunk = blockIdx.y;
@@ -401,11 +413,11 @@ __global__ __launch_bounds__(256) void block_stats(const int32_t* __restrict__ c
   if (chunk * kChunk >= N) return;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, c = lane & 15, kq = lane >> 4;
   const int64_t slot0 = int64_t(bh) * slots + meta[bh * 4 + 0];
-  const int nc = N - m, nq = m * G, ntile = (nq + kQT - 1) / kQT;
+  const int nc = N - m, nq = m * G;
   BR::stage(cK, cKe, cKe, slot0, chunk * kChunk, N - 1, smem, tid);
   const int ngroup = min(4, (N - chunk * kChunk + 63) / 64);  // 64-row groups of the chunk that hold rows
-  const int t_hi = min(ntile, (blockIdx.z + 1) * tiles_per_slice);
-  const WaveWork ww = wave_work(w, blockIdx.z * tiles_per_slice, t_hi);
+  const int t_lo = tile0 + blockIdx.z * tiles_per_slice, t_hi = min(tile1, t_lo + tiles_per_slice);
+  const WaveWork ww = wave_work(w, t_lo, t_hi);
   for (int qt = ww.tile; qt < t_hi; qt += 4) {  // this wavefront's query tiles
     const int q0 = qt * kQT, query = q0 + c;
     double bq[BR::KS];
@@ -428,10 +440,16 @@ __global__ __launch_bounds__(256) void block_stats(const int32_t* __restrict__ c
       // (a query that sees no row of the group: its exponentials are zero relative to any finite value)
       const double ref = mg == -INFINITY ? 0.0 : mg;
       double lt[4] = {0.0, 0.0, 0.0, 0.0};
+      double* const to = term + term_index(qt - tile0, gridDim.y, chunk, bhN, bh, g * 64 + kq) + c;
 #pragma unroll
       for (int t = 0; t < 4; ++t)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) lt[r] += exp(S[t][r] - ref);
+        for (int r = 0; r < 4; ++r) {
+          const double e = exp(S[t][r] - ref);
+          lt[r] += e;
+          to[(16 * t + 4 * r) * kQT] = e;
+        }
+      if (kq == 0) gmax[((int64_t(chunk) * bhN + bh) * maxq + query) * 4 + g] = mg;  // (maxq is a whole number of tiles)
       const double lg = kq_sum((lt[0] + lt[1]) + (lt[2] + lt[3]));
       const double Mn = fmax(M, mg);
       if (Mn == -INFINITY) continue;
@@ -462,12 +480,12 @@ __global__ __launch_bounds__(256) void block_stats(const int32_t* __restrict__ c
 }
 
 __global__ __launch_bounds__(256) void block_norm(const int32_t* __restrict__ ctotal, int32_t* __restrict__ ccount,
-                                                  const double* __restrict__ stat, double* __restrict__ norm, int m, int G,
+                                                  const double* __restrict__ stat, double* __restrict__ norm, int q0, int q1,
                                                   int maxq) {
   const int bhN = gridDim.x, bh = blockIdx.x;
-  const int N = ctotal[bh], nch = (N + kChunk - 1) / kChunk, nq = m * G;
+  const int N = ctotal[bh], nch = (N + kChunk - 1) / kChunk;
   if (threadIdx.x == 0) ccount[bh] = N;
-  for (int q = threadIdx.x; q < nq; q += 256) {
+  for (int q = q0 + threadIdx.x; q < q1; q += 256) {
     double M = -INFINITY;
 #pragma unroll 4
     for (int c = 0; c < nch; ++c) M = fmax(M, stat[((int64_t(c) * bhN + bh) * maxq + q) * 2]);
@@ -482,37 +500,36 @@ __global__ __launch_bounds__(256) void block_norm(const int32_t* __restrict__ ct
 }
 
 template <typename T, int D>
-__global__ __launch_bounds__(256, 2) void block_apply(const int32_t* __restrict__ ctotal, const int32_t* __restrict__ meta,
-                                                   const T* __restrict__ cK, const T* __restrict__ cV,
-                                                   const int8_t* __restrict__ cKe, const int8_t* __restrict__ cVe,
-                                                   double* __restrict__ spart, const double* __restrict__ aq,
-                                                   const double* __restrict__ norm, float* __restrict__ pout, int m,
-                                                   int G, int maxq, int64_t slots, int rows_cap, int tiles_per_slice) {
-  typedef BlockRows<T, D> BR;
-  constexpr int CT = BR::CT;
+__global__ __launch_bounds__(256, sizeof(T) == 4 && D == 128 ? 2 : 3) void block_apply(const int32_t* __restrict__ ctotal, const int32_t* __restrict__ meta,
+                                                   const T* __restrict__ cV, const int8_t* __restrict__ cVe,
+                                                   double* __restrict__ spart, const double* __restrict__ norm,
+                                                   const double* __restrict__ gmax, const double* __restrict__ term,
+                                                   float* __restrict__ pout, int m, int G, int maxq, int64_t slots,
+                                                   int rows_cap, int tile0, int tile1, int tiles_per_slice) {
+  constexpr int CT = D / 16;  // output column tiles (lane c holds columns CT c .. CT c + CT - 1)
   constexpr int VW = CT * int(sizeof(T)) / 4;
   struct alignas(VW >= 4 ? 16 : 8) VRow {  // this lane's columns of a V row, as stored
     uint32_t w[VW];
   };
+  __shared__ double rs[4 * 256];                  // per wavefront and row, the sum of its queries' probabilities
+  __shared__ float vscale[sizeof(T) == 1 ? 256 : 1];  // fp8: the rows' powers of two
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  // behind the rows (and the fp8 scales): per wavefront and row, the sum of its queries' probabilities
-  double* rs = reinterpret_cast<double*>(smem + BR::kRowsBytes + BR::kScaleBytes);
+  f32x4* ot = reinterpret_cast<f32x4*>(smem);     // [4][CT][64]: output tiles of wavefronts that share a query tile
   const int bhN = gridDim.x, bh = blockIdx.x, chunk = blockIdx.y;
   const int N = ctotal[bh];
   if (chunk * kChunk >= N) return;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, c = lane & 15, kq = lane >> 4;
   const int64_t slot0 = int64_t(bh) * slots + meta[bh * 4 + 0];
-  const int nc = N - m, nq = m * G, ntile = (nq + kQT - 1) / kQT;
+  const int nc = N - m, nq = m * G;
 #pragma unroll
   for (int i = 0; i < 4; ++i) rs[i * 256 + tid] = 0.0;
-  BR::stage(cK, cKe, cVe, slot0, chunk * kChunk, N - 1, smem, tid);
+  if constexpr (sizeof(T) == 1) vscale[tid] = pow2_f32(cVe[slot0 + min(chunk * kChunk + tid, N - 1)]);
+  __syncthreads();
   const int ngroup = min(4, (N - chunk * kChunk + 63) / 64);
-  const int t_hi = min(ntile, (blockIdx.z + 1) * tiles_per_slice);
-  const WaveWork ww = wave_work(w, blockIdx.z * tiles_per_slice, t_hi);
+  const int t_lo = tile0 + blockIdx.z * tiles_per_slice, t_hi = min(tile1, t_lo + tiles_per_slice);
+  const WaveWork ww = wave_work(w, t_lo, t_hi);
   for (int qt = ww.tile; qt < t_hi; qt += 4) {
     const int q0 = qt * kQT, query = q0 + c;
-    double bq[BR::KS];
-    BR::load_queries(aq + int64_t(bh) * maxq * D, q0, lane, bq);
     const int seen = query < nq ? min(nc + query / G, N - 1) : -1;  // a padding query sees nothing
     const int tile_last = q0 + kQT <= nq ? min(nc + q0 / G, N - 1) : -1;
     const double M = query < nq ? norm[(int64_t(bh) * maxq + query) * 2] : 0.0;
@@ -522,30 +539,30 @@ __global__ __launch_bounds__(256, 2) void block_apply(const int32_t* __restrict_
     for (int ct = 0; ct < CT; ++ct) O[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
     for (int g = ww.group; g < ngroup; g += ww.share) {
-      f64x4 S[4];
       const int j0 = chunk * kChunk + g * 64 + kq;
       // V rows come from memory four steps at a time, requested before the arithmetic that precedes them
-      // (read where they are multiplied, the compiler waited for each row in turn: 210 us for 256 tokens on 2048-entry caches, 32
-      // heads, instead of 184)
+      // (read where they are multiplied, the compiler waited for each row in turn)
       VRow vr[2][4];
       auto load_v = [&](int t) {
 #pragma unroll
         for (int r = 0; r < 4; ++r)
           vr[t & 1][r] = *reinterpret_cast<const VRow*>(cV + (slot0 + min(j0 + t * 16 + 4 * r, N - 1)) * D + c * CT);
       };
+      double pr[16];  // the exponentials, then the probabilities, value 4 t + r
+      const double* const from = term + term_index(qt - tile0, gridDim.y, chunk, bhN, bh, g * 64 + kq) + c;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) pr[i] = from[4 * i * kQT];
       load_v(0);
-      BR::logits(smem, g, lane, bq, S);
-      mask_logits(S, j0, seen, chunk * kChunk + g * 64 + 63, tile_last);
-      double pr[16];  // the probabilities, value 4 t + r
+      // (the division by the normaliser is a multiplication by its reciprocal here: the
+      // probabilities are compared within the float tolerance, never bit for bit)
+      const double f = exp(gmax[((int64_t(chunk) * bhN + bh) * maxq + query) * 4 + g] - M) * Linv;
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         __builtin_amdgcn_sched_barrier(0);
         if (t < 3) load_v(t + 1);
         __builtin_amdgcn_sched_barrier(0);
-        // (the division by the normaliser is a multiplication by its reciprocal here: the
-        // probabilities are compared within the float tolerance, never bit for bit)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) pr[4 * t + r] = exp(S[t][r] - M) * Linv;
+        for (int r = 0; r < 4; ++r) pr[4 * t + r] *= f;
         if (chunk * kChunk + g * 64 + 63 > tile_last) {  // (a normaliser that is not finite stays with the rows the query sees)
 #pragma unroll
           for (int r = 0; r < 4; ++r)
@@ -557,7 +574,7 @@ __global__ __launch_bounds__(256, 2) void block_apply(const int32_t* __restrict_
           const double p = pr[4 * t + r];
           // P V: this (t, r) is one contraction step over the rows 16 t + 4 r + kq
           float pa = float(p);
-          if constexpr (sizeof(T) == 1) pa *= reinterpret_cast<const float*>(smem + BR::kRowsBytes + 256 * 8)[row];
+          if constexpr (sizeof(T) == 1) pa *= vscale[row];
           float vb[CT];
 #pragma unroll
           for (int wd = 0; wd < VW; ++wd) {
@@ -584,9 +601,6 @@ __global__ __launch_bounds__(256, 2) void block_apply(const int32_t* __restrict_
       rs[w * 256 + g * 64 + (own >> 2) * 16 + 4 * (own & 3) + kq] += ps;
     }
     if (ww.share > 1) {  // the sharers' output tiles, added in group order
-      static_assert(4 * CT * 64 * 16 <= BR::kRowsBytes, "the output tiles fit the rows' place");
-      f32x4* ot = reinterpret_cast<f32x4*>(smem);  // [4][CT][64]: the rows are done with
-      __syncthreads();
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct) ot[(w * CT + ct) * 64 + lane] = O[ct];
       __syncthreads();
@@ -700,13 +714,6 @@ hipError_t run_block_attend(d2o_ctx* c, int layer, View q, View k, View v, View 
   for (const auto& mt : c->layers[layer].meta) max_rows = std::max(max_rows, mt.budget + m);
   const int nch = (max_rows + kChunk - 1) / kChunk;
   if (nch > c->ap_nch || m * G > maxq) return hipErrorInvalidValue;
-  // few heads and chunks give few workgroups: the query tiles of a head are cut into slices that
-  // run as workgroups of their own (whole rounds of the four wavefronts), enough of them to fill
-  // the chip a few times over
-  const int ntile = (m * G + kQT - 1) / kQT;
-  const int want = std::max(1, std::min(kMaxQuerySlices, 2048 / std::max(1, bh * nch)));
-  const int tiles_per_slice = 4 * ((ntile + 4 * want - 1) / (4 * want));
-  const int nslice = (ntile + tiles_per_slice - 1) / tiles_per_slice;
   block_begin<T, IT, D><<<dim3(cf.n_kv_heads, cf.batch, 32), 256, 0, s>>>(ccount, ctotal, meta, (T*)c->cacheK, (T*)c->cacheV, c->cscore,
                                                                          c->cpos, (const IT*)q.ptr, q, (const IT*)k.ptr, k,
                                                                          (const IT*)v.ptr, v, c->ap_q, m, G, maxq, first_pos,
@@ -716,18 +723,31 @@ hipError_t run_block_attend(d2o_ctx* c, int layer, View q, View k, View v, View 
                                                                                c->cKe, c->cVe, (const uint16_t*)k.ptr, k,
                                                                                (const uint16_t*)v.ptr, v, m, cf.slots_per_seq);
   typedef BlockRows<T, D> BR;
-  constexpr int kStatsLds = BR::kRowsBytes + BR::kScaleBytes, kApplyLds = kStatsLds + 4 * 256 * int(sizeof(double));
+  constexpr int kStatsLds = BR::kRowsBytes + BR::kScaleBytes;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(block_stats<T, D>), hipFuncAttributeMaxDynamicSharedMemorySize, kStatsLds);
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(block_apply<T, D>), hipFuncAttributeMaxDynamicSharedMemorySize, kApplyLds);
   if (e != hipSuccess) return e;
-  block_stats<T, D><<<dim3(bh, nch, nslice), 256, kStatsLds, s>>>(ctotal, meta, (const T*)c->cacheK, c->cKe, c->ap_q, c->ap_stat, m, G,
-                                                               maxq, cf.slots_per_seq, tiles_per_slice);
-  block_norm<<<dim3(bh), 256, 0, s>>>(ctotal, ccount, c->ap_stat, c->ap_norm, m, G, maxq);
   const int rows_cap = c->ap_nch * kChunk;
-  block_apply<T, D><<<dim3(bh, nch, nslice), 256, kApplyLds, s>>>(ctotal, meta, (const T*)c->cacheK, (const T*)c->cacheV, c->cKe, c->cVe,
-                                                               c->ap_spart, c->ap_q, c->ap_norm, c->ap_out, m, G, maxq,
-                                                               cf.slots_per_seq, rows_cap, tiles_per_slice);
-  block_scores<<<dim3(bh, nch), 256, 0, s>>>(ctotal, meta, c->cscore, c->ap_spart, nslice, cf.slots_per_seq, rows_cap);
+  // few heads and chunks give few workgroups: the query tiles of a head are cut into slices that
+  // run as workgroups of their own (whole rounds of the four wavefronts), enough of them to fill
+  // the chip a few times over
+  const int want = std::max(1, std::min(kMaxQuerySlices, 2048 / std::max(1, bh * nch)));
+  const int ntile = (m * G + kQT - 1) / kQT;
+  const int per_pass = int(std::min<int64_t>(ntile, int64_t(c->ap_tiles) * c->ap_nch / nch));  // query tiles whose exponentials fit
+  for (int t0 = 0; t0 < ntile; t0 += per_pass) {
+    const int t1 = std::min(ntile, t0 + per_pass);
+    const int tiles_per_slice = 4 * ((t1 - t0 + 4 * want - 1) / (4 * want));
+    const int nslice = (t1 - t0 + tiles_per_slice - 1) / tiles_per_slice;
+    const dim3 grid(bh, nch, nslice);
+    block_stats<T, D><<<grid, 256, kStatsLds, s>>>(ctotal, meta, (const T*)c->cacheK, c->cKe, c->ap_q, c->ap_stat, c->ap_gmax,
+                                                   c->ap_term, m, G, maxq, cf.slots_per_seq, t0, t1, tiles_per_slice);
+    block_norm<<<dim3(bh), 256, 0, s>>>(ctotal, ccount, c->ap_stat, c->ap_norm, t0 * kQT, std::min(m * G, t1 * kQT), maxq);
+    // (the place for shared tiles only where a slice has one or two: it would cost the others a workgroup per CU)
+    const int rest = (t1 - t0) % tiles_per_slice;
+    const int shared_tiles = rest == 1 || rest == 2 ? 4 * (D / 16) * 64 * int(sizeof(f32x4)) : 0;
+    block_apply<T, D><<<grid, 256, shared_tiles, s>>>(ctotal, meta, (const T*)c->cacheV, c->cVe, c->ap_spart, c->ap_norm, c->ap_gmax,
+                                           c->ap_term, c->ap_out, m, G, maxq, cf.slots_per_seq, rows_cap, t0, t1, tiles_per_slice);
+    block_scores<<<dim3(bh, nch), 256, 0, s>>>(ctotal, meta, c->cscore, c->ap_spart, nslice, cf.slots_per_seq, rows_cap);
+  }
   if (cf.out_f32)
     block_finish<float, D><<<dim3(bh, m * G), D, 0, s>>>(ctotal, c->ap_out, (float*)out.ptr, out, G, maxq, cf.n_kv_heads);
   else

@@ -128,6 +128,10 @@ void layout(d2o_ctx* x, char* persistent, char* scratch, size_t* pbytes, size_t*
   x->ap_nch = ap ? int(std::min<int64_t>(np, c.slots_per_seq) / kChunk + 2) : 0;
   s.take(x->ap_q, ap * bh * x->ap_maxq * d);
   s.take(x->ap_stat, ap * x->ap_nch * bh * x->ap_maxq * 2);
+  s.take(x->ap_gmax, ap * x->ap_nch * bh * x->ap_maxq * 4);
+  const size_t tile_terms = x->ap_nch * bh * kChunk * 16, tiles = x->ap_maxq / 16;
+  x->ap_tiles = ap ? int(std::min(tiles, std::max<size_t>(4, kBlockTermBytes / (tile_terms * sizeof(double))))) : 0;
+  s.take(x->ap_term, x->ap_tiles * tile_terms);
   s.take(x->ap_norm, ap * bh * x->ap_maxq * 2);
   s.take(x->ap_out, ap * x->ap_nch * bh * x->ap_maxq * d);
   s.take(x->ap_spart, ap * kMaxQuerySlices * bh * x->ap_nch * kChunk);

@@ -13,6 +13,10 @@ namespace d2o {
 
 constexpr int kPartRecDoubles = 32;  // doubles of a part record of the split closing kernels
 constexpr int kMaxQuerySlices = 16;  // block append: workgroups that share the queries of a (head, chunk)
+// Block append: bytes that the exponentials of a pass's query tiles may take (8 per row and query), but room for four
+// tiles, a workgroup's round, at least.  What one kernel writes and the next reads once then stays inside the chip's 256 MB
+// memory-side cache.
+constexpr size_t kBlockTermBytes = size_t(192) << 20;
 constexpr int kMinAutoSplitRows = 6144, kMaxAutoSplitRows = 16384;  // bounds of the automatic split_rows (below the lower one the two extra launches cost more than a single closing workgroup)
 constexpr int kChunk = 256;        // cache slots handled by one workgroup in the decode kernels
 constexpr int kF32BN = 32;         // keys per workgroup, column-sum pass (fp32)
@@ -138,6 +142,9 @@ struct d2o_ctx {
   int32_t ap_maxq = 0, ap_nch = 0;  // queries per head (max_append * G, rounded up to 16) and chunks per head the arrays hold
   double* ap_q = nullptr;        // [B][Hkv][ap_maxq][d] the block's queries as fp64
   double* ap_stat = nullptr;     // [ap_nch][B][Hkv][ap_maxq][2] per chunk: softmax maximum and exp-sum of every query
+  int ap_tiles = 0;              // query tiles of 16 whose exponentials ap_term holds for caches of ap_nch chunks
+  double* ap_gmax = nullptr;     // [ap_nch][B][Hkv][ap_maxq][4] per 64 rows: softmax maximum of every query
+  double* ap_term = nullptr;     // [ap_tiles][ap_nch][B][Hkv][256][16] exp(logit - maximum of the 64 rows)
   double* ap_norm = nullptr;     // [B][Hkv][ap_maxq][2] maximum and normaliser of every query
   float* ap_out = nullptr;       // [ap_nch][B][Hkv][ap_maxq][d] partial outputs per chunk
   double* ap_spart = nullptr;    // [kMaxQuerySlices][B][Hkv][ap_nch * 256] per row: sum of the slice's probabilities
