@@ -179,8 +179,8 @@ __global__ __launch_bounds__(256) void permute_rows(const int32_t* __restrict__ 
 // 0..i.  Logits, softmax and score accumulation in fp64 as in the generation step; P V in fp32.
 // Both products are dense contractions (rows x queries x d, queries x d x rows) and run on the
 // matrix cores: the fp64 16x16x4 instruction for the logits (its sums of products of bf16 or
-// fp8 values are exact, so they do not depend on the order of the contraction), the fp32
-// 16x16x4 instruction for P V.
+// fp8 values are exact, so they do not depend on the order of the contraction), the bf16 16x16x32
+// or, fp32 caches, fp32 16x16x4 instruction for P V.
 //
 //   block_begin   per head: appends the block's K, V rows (score 0, positions first_pos + i),
 //                 lays the queries out as fp64 vectors, sets the entry count to N.
@@ -192,7 +192,7 @@ __global__ __launch_bounds__(256) void permute_rows(const int32_t* __restrict__ 
 //   block_apply   the same tiling: p = the stored exponential times exp(maximum of the 64 rows - maximum)
 //                 / normaliser; per row the sum
 //                 of the p of every query that sees it; the wavefront's 16 x d partial output
-//                 tile over the 256 rows, accumulated by the fp32 matrix instruction whose A
+//                 tile over the 256 rows, accumulated in fp32 by the matrix instruction whose A
 //                 operand is the probability tile as the logits' instruction left it.
 //   block_scores  per row: score += the sums (Eq. 6).
 //   block_finish  per head and query: the chunks' partial output rows added in ascending order.
@@ -200,7 +200,7 @@ __global__ __launch_bounds__(256) void permute_rows(const int32_t* __restrict__ 
 // (a block on a cache of a few thousand rows is too little work per head to fill the chip
 // otherwise); a row's score then grows by the slices' sums in slice order.  The exponentials are kept, in fp64, because
 // the logits and they are what bounds the block (the fp64 units): with both formed again in block_apply, 256 tokens on
-// 2048-entry caches (32 heads) took 123 + 182 us in the two kernels, with 151 MB written and read 131 + 74.  They
+// 2048-entry caches (32 heads) took 123 + 182 us in the two kernels, with 151 MB written and read 131 + 74 (46 since).  They
 // have a bounded place (kBlockTermBytes): the query tiles go through the three kernels in as many passes as it takes.
 //
 // Register layouts of the two instructions (lane l, c = l % 16, kq = l / 16):
@@ -499,6 +499,13 @@ __global__ __launch_bounds__(256) void block_norm(const int32_t* __restrict__ ct
   }
 }
 
+// P V: what bounded this kernel was the fp32 matrix instruction (half the time of the logits' products).  The
+// elements of a bf16 or 8-bit V are bf16 numbers and an fp32 probability is the sum of three (three times eight
+// significant bits), so with these types it is three products of the bf16 instruction, exact, with fp32 sums: 74 -> 46 us
+// for 256 tokens on 2048-entry caches, 32 heads, and two thirds of the former error against 64 bits.  A probability is
+// scaled by 2^kTermScale, which keeps its last term above 2^-126, and the sums are rid of it again.
+constexpr int kTermScale = 24;
+constexpr uint32_t kHighHalves = 0x07060302u, kLowHalves = 0x05040100u;  // v_perm_b32: two words' upper, lower halves
 template <typename T, int D>
 __global__ __launch_bounds__(256, sizeof(T) == 4 && D == 128 ? 2 : 3) void block_apply(const int32_t* __restrict__ ctotal, const int32_t* __restrict__ meta,
                                                    const T* __restrict__ cV, const int8_t* __restrict__ cVe,
@@ -507,8 +514,10 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 && D == 128 ? 2 : 3) void block
                                                    float* __restrict__ pout, int m, int G, int maxq, int64_t slots,
                                                    int rows_cap, int tile0, int tile1, int tiles_per_slice) {
   constexpr int CT = D / 16;  // output column tiles (lane c holds columns CT c .. CT c + CT - 1)
+  constexpr int RB = D * int(sizeof(T));  // bytes of a cache row
   constexpr int VW = CT * int(sizeof(T)) / 4;
-  struct alignas(VW >= 4 ? 16 : 8) VRow {  // this lane's columns of a V row, as stored
+  static_assert(VW % 4 == 0 || VW == 2, "16- or 8-byte loads");
+  struct VRow {  // this lane's columns of a V row, as stored
     uint32_t w[VW];
   };
   __shared__ double rs[4 * 256];                  // per wavefront and row, the sum of its queries' probabilities
@@ -528,77 +537,199 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 && D == 128 ? 2 : 3) void block
   const int ngroup = min(4, (N - chunk * kChunk + 63) / 64);
   const int t_lo = tile0 + blockIdx.z * tiles_per_slice, t_hi = min(tile1, t_lo + tiles_per_slice);
   const WaveWork ww = wave_work(w, t_lo, t_hi);
+  const __amdgpu_buffer_rsrc_t rows = buffer_of(cV + (slot0 + chunk * kChunk) * D, uint32_t(min(kChunk, N - chunk * kChunk) * RB));
   for (int qt = ww.tile; qt < t_hi; qt += 4) {
     const int q0 = qt * kQT, query = q0 + c;
     const int seen = query < nq ? min(nc + query / G, N - 1) : -1;  // a padding query sees nothing
     const int tile_last = q0 + kQT <= nq ? min(nc + q0 / G, N - 1) : -1;
     const double M = query < nq ? norm[(int64_t(bh) * maxq + query) * 2] : 0.0;
     const double Linv = query < nq ? 1.0 / norm[(int64_t(bh) * maxq + query) * 2 + 1] : 0.0;
-    f32x4 O[CT];
+    const __amdgpu_buffer_rsrc_t terms = buffer_of(term + term_index(qt - tile0, gridDim.y, chunk, bhN, bh, 0), kChunk * kQT * 8);
+    // the probabilities of a group's rows 16 t + 4 r + kq, value 4 t + r
+    auto load_probs = [&](int g, float (&pf)[16], bool add) {
+      double pr[16];
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct) O[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-    for (int g = ww.group; g < ngroup; g += ww.share) {
-      const int j0 = chunk * kChunk + g * 64 + kq;
-      // V rows come from memory four steps at a time, requested before the arithmetic that precedes them
-      // (read where they are multiplied, the compiler waited for each row in turn)
-      VRow vr[2][4];
-      auto load_v = [&](int t) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          vr[t & 1][r] = *reinterpret_cast<const VRow*>(cV + (slot0 + min(j0 + t * 16 + 4 * r, N - 1)) * D + c * CT);
-      };
-      double pr[16];  // the exponentials, then the probabilities, value 4 t + r
-      const double* const from = term + term_index(qt - tile0, gridDim.y, chunk, bhN, bh, g * 64 + kq) + c;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) pr[i] = from[4 * i * kQT];
-      load_v(0);
+      for (int i = 0; i < 16; ++i)
+        pr[i] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(
+                                               terms, ((g * 64 + kq) * kQT + c) * 8 + i * (4 * kQT * 8), 0, 0));
       // (the division by the normaliser is a multiplication by its reciprocal here: the
       // probabilities are compared within the float tolerance, never bit for bit)
       const double f = exp(gmax[((int64_t(chunk) * bhN + bh) * maxq + query) * 4 + g] - M) * Linv;
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        __builtin_amdgcn_sched_barrier(0);
-        if (t < 3) load_v(t + 1);
-        __builtin_amdgcn_sched_barrier(0);
+      for (int i = 0; i < 16; ++i) pr[i] *= f;
+      const int j0 = chunk * kChunk + g * 64 + kq;
+      if (chunk * kChunk + g * 64 + 63 > tile_last) {  // (a normaliser that is not finite stays with the rows the query sees)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) pr[4 * t + r] *= f;
-        if (chunk * kChunk + g * 64 + 63 > tile_last) {  // (a normaliser that is not finite stays with the rows the query sees)
+        for (int i = 0; i < 16; ++i)
+          if (j0 + 4 * i > seen) pr[i] = 0.0;
+      }
+      if (add) {  // Eq. 6: the rows' sums over the tile's queries, one row per lane, then over the wavefront's tiles
+        const double ps = row16_sums(pr, c);
+        const int own = row16_sums_owner(c);
+        rs[w * 256 + g * 64 + (own >> 2) * 16 + 4 * (own & 3) + kq] += ps;
+      }
 #pragma unroll
-          for (int r = 0; r < 4; ++r)
-            if (j0 + t * 16 + 4 * r > seen) pr[4 * t + r] = 0.0;
+      for (int i = 0; i < 16; ++i) pf[i] = float(pr[i]);
+    };
+    auto v_row = [&](int g, int i) {  // of probability i (zero past the last row)
+      const int off = (g * 64 + kq) * RB + c * (CT * int(sizeof(T))) + i * 4 * RB;
+      VRow v;
+      if constexpr (VW >= 4) {
+#pragma unroll
+        for (int x = 0; x < VW; x += 4) {
+          const u32x4 q = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rows, off + x * 4, 0, 0));
+#pragma unroll
+          for (int y = 0; y < 4; ++y) v.w[x + y] = q[y];
+        }
+      } else {
+        const u32x2 q = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rows, off, 0, 0));
+        v.w[0] = q[0];
+        v.w[1] = q[1];
+      }
+      return v;
+    };
+    f32x4 O[CT];
+    auto clear = [&]() {
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) O[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    // P V on the fp32 matrix instruction, a contraction step per probability (rows 4 i + kq), for V rows that came four at a time
+    auto multiply_f32 = [&](int g, const float (&pf)[16], const VRow (&vr)[4], int i0) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        float pa = pf[i0 + r];
+        if constexpr (sizeof(T) == 1) pa *= vscale[g * 64 + 4 * (i0 + r) + kq];
+        float vb[CT];
+#pragma unroll
+        for (int wd = 0; wd < VW; ++wd) {
+          const uint32_t raw = vr[r].w[wd];
+          if constexpr (sizeof(T) == 1) {
+            vb[4 * wd] = __builtin_amdgcn_cvt_f32_fp8(int(raw), 0);
+            vb[4 * wd + 1] = __builtin_amdgcn_cvt_f32_fp8(int(raw), 1);
+            vb[4 * wd + 2] = __builtin_amdgcn_cvt_f32_fp8(int(raw), 2);
+            vb[4 * wd + 3] = __builtin_amdgcn_cvt_f32_fp8(int(raw), 3);
+          } else if constexpr (sizeof(T) == 2) {
+            vb[2 * wd] = __uint_as_float(raw << 16);
+            vb[2 * wd + 1] = __uint_as_float(raw & 0xFFFF0000u);
+          } else {
+            vb[wd] = __uint_as_float(raw);
+          }
         }
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int row = g * 64 + t * 16 + 4 * r + kq;
-          const double p = pr[4 * t + r];
-          // P V: this (t, r) is one contraction step over the rows 16 t + 4 r + kq
-          float pa = float(p);
-          if constexpr (sizeof(T) == 1) pa *= vscale[row];
-          float vb[CT];
+        for (int ct = 0; ct < CT; ++ct) O[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(pa, vb[ct], O[ct], 0, 0, 0);
+      }
+    };
+    clear();
+#pragma unroll 1
+    for (int g = ww.group; g < ngroup; g += ww.share) {
+      float pf[16];
+      if constexpr (sizeof(T) == 4) {
+        // V rows come from memory four steps at a time, requested before the arithmetic that precedes them
+        // (read where they are multiplied, the compiler waited for each row in turn)
+        VRow vr[2][4];
+        auto load_v = [&](int t) {
 #pragma unroll
-          for (int wd = 0; wd < VW; ++wd) {
-            const uint32_t raw = vr[t & 1][r].w[wd];
-            if constexpr (sizeof(T) == 1) {
-              vb[4 * wd] = __builtin_amdgcn_cvt_f32_fp8(int(raw), 0);
-              vb[4 * wd + 1] = __builtin_amdgcn_cvt_f32_fp8(int(raw), 1);
-              vb[4 * wd + 2] = __builtin_amdgcn_cvt_f32_fp8(int(raw), 2);
-              vb[4 * wd + 3] = __builtin_amdgcn_cvt_f32_fp8(int(raw), 3);
-            } else if constexpr (sizeof(T) == 2) {
-              vb[2 * wd] = __uint_as_float(raw << 16);
-              vb[2 * wd + 1] = __uint_as_float(raw & 0xFFFF0000u);
-            } else {
-              vb[wd] = __uint_as_float(raw);
+          for (int r = 0; r < 4; ++r) vr[t & 1][r] = v_row(g, 4 * t + r);
+        };
+        load_v(0);
+        load_probs(g, pf, true);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          __builtin_amdgcn_sched_barrier(0);
+          if (t < 3) load_v(t + 1);
+          __builtin_amdgcn_sched_barrier(0);
+          multiply_f32(g, pf, vr[t & 1], 4 * t);
+        }
+      } else {
+        VRow vr[8];
+        auto load_v = [&](int h) {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) vr[j] = v_row(g, 8 * h + j);
+        };
+        load_v(0);
+        load_probs(g, pf, true);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          if (h == 1) load_v(1);
+          __builtin_amdgcn_sched_barrier(0);
+          // v_mfma_f32_16x16x32_bf16: lane l holds A[l % 16][8 (l / 16) ..] and B[8 (l / 16) ..][l % 16]; contraction index
+          // 8 kq + j is row 4 (8 h + j) + kq.
+          bf16x8 a[3];
+          {
+            u32x4 t1, t2, t3;
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+              uint32_t b1[2], b2[2], b3[2];
+#pragma unroll
+              for (int y = 0; y < 2; ++y) {
+                const int i = 8 * h + 2 * x + y;
+                float p1 = pf[i] * pow2_f32(kTermScale);
+                if constexpr (sizeof(T) == 1) p1 *= vscale[g * 64 + 4 * i + kq];
+                const float p2 = p1 - __uint_as_float(__float_as_uint(p1) & 0xFFFF0000u);
+                const float p3 = p2 - __uint_as_float(__float_as_uint(p2) & 0xFFFF0000u);
+                b1[y] = __float_as_uint(p1);
+                b2[y] = __float_as_uint(p2);
+                b3[y] = __float_as_uint(p3);
+              }
+              t1[x] = __builtin_amdgcn_perm(b1[1], b1[0], kHighHalves);
+              t2[x] = __builtin_amdgcn_perm(b2[1], b2[0], kHighHalves);
+              t3[x] = __builtin_amdgcn_perm(b3[1], b3[0], kHighHalves);
             }
+            a[0] = __builtin_bit_cast(bf16x8, t1);
+            a[1] = __builtin_bit_cast(bf16x8, t2);
+            a[2] = __builtin_bit_cast(bf16x8, t3);
           }
 #pragma unroll
-          for (int ct = 0; ct < CT; ++ct) O[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(pa, vb[ct], O[ct], 0, 0, 0);
+          for (int c2 = 0; c2 < CT / 2; ++c2) {  // columns 2 c2 and 2 c2 + 1 of the lane's
+            uint32_t two[8];  // of each row, as bf16
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+              if constexpr (sizeof(T) == 1) {  // (a code has four significant bits)
+                const int wd = int(vr[j].w[c2 / 2]);
+                const auto v = c2 & 1 ? __builtin_amdgcn_cvt_pk_f32_fp8(wd, true) : __builtin_amdgcn_cvt_pk_f32_fp8(wd, false);
+                two[j] = __builtin_amdgcn_perm(__float_as_uint(v[1]), __float_as_uint(v[0]), kHighHalves);
+              } else {
+                two[j] = vr[j].w[c2];
+              }
+            }
+            u32x4 lo, hi;
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+              lo[x] = __builtin_amdgcn_perm(two[2 * x + 1], two[2 * x], kLowHalves);
+              hi[x] = __builtin_amdgcn_perm(two[2 * x + 1], two[2 * x], kHighHalves);
+            }
+            const bf16x8 b0 = __builtin_bit_cast(bf16x8, lo), b1 = __builtin_bit_cast(bf16x8, hi);
+#pragma unroll
+            for (int t = 0; t < 3; ++t) {
+              O[2 * c2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[t], b0, O[2 * c2], 0, 0, 0);
+              O[2 * c2 + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[t], b1, O[2 * c2 + 1], 0, 0, 0);
+            }
+          }
         }
       }
-      // Eq. 6: the rows' sums over the tile's queries, one row per lane, then over the wavefront's tiles
-      const double ps = row16_sums(pr, c);
-      const int own = row16_sums_owner(c);
-      rs[w * 256 + g * 64 + (own >> 2) * 16 + 4 * (own & 3) + kq] += ps;
+    }
+    if constexpr (sizeof(T) <= 2) {
+      bool finite = true;
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          finite = finite && fabsf(O[ct][r]) < INFINITY;
+          O[ct][r] *= pow2_f32(-kTermScale);
+        }
+      if (!__all(finite)) {  // a term 0 beside an infinite value, or a scaled sum out of range: whole probabilities
+        clear();
+#pragma unroll 1
+        for (int g = ww.group; g < ngroup; g += ww.share) {
+          float pf[16];
+          load_probs(g, pf, false);
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            const VRow vr[4] = {v_row(g, 4 * t), v_row(g, 4 * t + 1), v_row(g, 4 * t + 2), v_row(g, 4 * t + 3)};
+            multiply_f32(g, pf, vr, 4 * t);
+          }
+        }
+      }
     }
     if (ww.share > 1) {  // the sharers' output tiles, added in group order
 #pragma unroll

@@ -490,6 +490,44 @@ def test_block_append_of_few_query_tiles(dtype, d, fp8, m, G):
         _append_against_oracle(dtype, storage, d, G, m, budget, np.arange(400), 400)
 
 
+@pytest.mark.parametrize("dtype,d,fp8", [("bf16", 128, False), ("bf16", 128, True), ("f32", 64, False)])
+@pytest.mark.parametrize("value", [np.inf, 2.0 ** 127, 2.0 ** 110])
+@pytest.mark.parametrize("m", [3, 40])  # wavefronts that share a tile, and one per tile
+def test_block_append_with_a_value_at_the_end_of_the_range(dtype, d, fp8, value, m):
+    """One element of V infinite: its column of the outputs is infinite; near the end of the range: the outputs that 64
+    bits give, in that column and in the others, to fp32 accuracy (300 additions; an 8-bit row keeps four bits)."""
+    if fp8 and np.isinf(value):
+        return  # (an 8-bit row has no infinities)
+    n, row, col = 300, 70, 5
+    g = np.random.default_rng(m)
+    K, V = (ref.round_storage(g.standard_normal((n, d)), dtype) for _ in range(2))
+    V[row, col] = value
+    x = [ref.round_storage(g.standard_normal((1, 1, m, d)), dtype) for _ in range(3)]
+    ctx = binding.D2O(1, 1, 1, 1, d, 512, 400, dtype=dtype, out_f32=True, max_append=m, cache_fp8=fp8)
+    ctx.d2o_layer_reserve(0, 400, n, 0)
+    ctx.d2o_cache_import(0, 0, 0, K, V, np.ones(n), np.arange(n, dtype=np.int32), 0.1, n)
+    K, V = ctx.d2o_cache_export(0, 0, 0, n)[:2]  # (as stored)
+    out = torch.empty(1, 1, m, d, device="cuda:0")
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    ctx.d2o_append_chunk(0, *(torch.from_numpy(a).to(tdt).cuda() for a in x), out)
+    got = out[0, 0].double().cpu().numpy()
+    new = (x[1][0, 0], x[2][0, 0]) if not fp8 else [ref.round_storage(a[0, 0], "fp8") for a in x[1:]]
+    keys, vals = np.r_[K, new[0]], np.r_[V, new[1]]
+    others = np.arange(d) != col
+    for i in range(m):
+        logit = keys[:n + i + 1] @ x[0][0, 0, i] / np.sqrt(d)
+        p = np.exp(logit - logit.max())
+        p /= p.sum()
+        want = p @ vals[:n + i + 1]
+        if np.isinf(value):
+            assert got[i, col] == np.inf
+        else:
+            assert abs(got[i, col] - want[col]) <= 300 * 2.0 ** -24 * want[col]
+        bound = 300 * 2.0 ** -24 * (p @ np.abs(vals[:n + i + 1]))
+        assert (np.abs(got[i] - want)[others] <= bound[others]).all()
+    ctx.close()
+
+
 def test_block_append_in_several_passes_over_the_queries():
     """128 heads and 20 tiles of queries, whose exponentials take two passes, against one of the heads alone in a single
     pass: the same outputs, and scores equal but for the order in which a row's fp64 sums over 20 tiles are added."""
