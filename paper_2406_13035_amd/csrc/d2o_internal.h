@@ -113,7 +113,7 @@ struct d2o_ctx {
   int32_t* sel_ret = nullptr;    // retained positions, ascending
   int32_t* sel_evi = nullptr;    // evicted positions, ascending
   int32_t* sel_cnt = nullptr;    // [B][Hkv][2]  n_ret, n_evi
-  float* invnorm = nullptr;      // 1/|k_j| of every prompt key (fp32, filter only)
+  float* invnorm = nullptr;      // 1/|k| of every retained key, by its rank (fp32, filter only)
   int32_t* m_cand = nullptr;     // filter's best retained rank per evicted row; bit 31 = ambiguous
   float* m_thr = nullptr;        // filter's acceptance threshold of a flagged row
   int32_t* amb_list = nullptr;   // flagged evicted ranks, in no particular order

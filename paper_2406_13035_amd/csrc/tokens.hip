@@ -200,29 +200,23 @@ __global__ __launch_bounds__(1024) void select_kernel(const S* __restrict__ scor
   }
 }
 
-// 1/|k_j| in fp32 for sixteen prompt keys from row0 on (used by the bf16 candidate filter only).
-__device__ __forceinline__ void inverse_norms(const uint16_t* __restrict__ kb, int64_t sn, float* __restrict__ invn, int row0, int n) {
-  const int row = row0 + threadIdx.x / 16, c = (threadIdx.x % 16) * 8;
-  float s = 0.f;
-  if (row < n) {
-    const u32x4 v = *reinterpret_cast<const u32x4*>(kb + int64_t(row) * sn + c);
+// 1/|k| in fp32 from the squares' sum (used by the bf16 candidate filter only), and a 16-byte share of that sum.
+__device__ __forceinline__ float inverse_norm(float s) { return s > 0.f ? 1.0f / sqrtf(s) : 0.f; }
+__device__ __forceinline__ float add_squares(const u32x4& v, float s) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float lo = __uint_as_float(v[i] << 16), hi = __uint_as_float(v[i] & 0xFFFF0000u);
-      s = fmaf(lo, lo, s);
-      s = fmaf(hi, hi, s);
-    }
+  for (int i = 0; i < 4; ++i) {
+    const float lo = __uint_as_float(v[i] << 16), hi = __uint_as_float(v[i] & 0xFFFF0000u);
+    s = fmaf(lo, lo, s);
+    s = fmaf(hi, hi, s);
   }
-#pragma unroll
-  for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-  if (row < n && (threadIdx.x % 16) == 0) invn[row] = s > 0.f ? 1.0f / sqrtf(s) : 0.f;
+  return s;
 }
 
 // ------------------------------------------------------------------------------------------
 // Compaction: retained rows of K, V into the layer's cache region; scores widen to fp64.
 // APPEND: the source is the position-ordered copy of a cache: fp64 scores (sc64) and token
-// positions (apos) indexed like its rows.  The workgroups behind the first `row_blocks` form the inverse norms of
-// all n keys (bf16; the two are independent, and as two launches each was mostly its start and end).
+// positions (apos) indexed like its rows.  bf16: a retained key's inverse norm, by its rank, on the way (the filter takes
+// the evicted keys' from the rows that it holds; a pass over all keys here was most of this kernel's time).
 template <typename T, bool APPEND>
 __global__ __launch_bounds__(256) void gather_kernel(const T* __restrict__ K, View kv, const T* __restrict__ V, View vv,
                                                      const float* __restrict__ score, const double* __restrict__ sc64,
@@ -231,15 +225,9 @@ __global__ __launch_bounds__(256) void gather_kernel(const T* __restrict__ K, Vi
                                                      T* __restrict__ cK, T* __restrict__ cV, double* __restrict__ cscore,
                                                      int32_t* __restrict__ cpos, int32_t* __restrict__ ccount,
                                                      int npad, int d, int64_t slots, const int32_t* __restrict__ row_meta,
-                                                     int64_t row_slots, int row_blocks, float* __restrict__ invn, int n) {
+                                                     int64_t row_slots, float* __restrict__ invn) {
   const int hk = blockIdx.y, b = blockIdx.z, Hkv = gridDim.y;
   const int64_t bh = int64_t(b) * Hkv + hk;
-  if constexpr (sizeof(T) == 2) {
-    if (int(blockIdx.x) >= row_blocks) {
-      inverse_norms(K + b * kv.sb + hk * kv.sh, kv.sn, invn + bh * npad, (int(blockIdx.x) - row_blocks) * 16, n);
-      return;
-    }
-  }
   const int nret = cnt[bh * 2];
   constexpr int kVec = 16 / sizeof(T);
   const int tpr = d / kVec;                 // threads per row
@@ -252,10 +240,16 @@ __global__ __launch_bounds__(256) void gather_kernel(const T* __restrict__ K, Vi
   const int64_t dst = (bh * slots + meta[bh * 4 + 0] + slot);
   // (the rows may live elsewhere than scores and positions: the bf16 staging rows of an fp8 cache)
   const int64_t dst_row = (bh * row_slots + row_meta[bh * 4 + 0] + slot);
-  *reinterpret_cast<u32x4*>(cK + dst_row * d + c) =
-      *reinterpret_cast<const u32x4*>(K + b * kv.sb + hk * kv.sh + int64_t(pos) * kv.sn + c);
-  *reinterpret_cast<u32x4*>(cV + dst_row * d + c) =
-      *reinterpret_cast<const u32x4*>(V + b * vv.sb + hk * vv.sh + int64_t(pos) * vv.sn + c);
+  const u32x4 k16 = *reinterpret_cast<const u32x4*>(K + b * kv.sb + hk * kv.sh + int64_t(pos) * kv.sn + c);
+  const u32x4 v16 = *reinterpret_cast<const u32x4*>(V + b * vv.sb + hk * vv.sh + int64_t(pos) * vv.sn + c);
+  *reinterpret_cast<u32x4*>(cK + dst_row * d + c) = k16;
+  *reinterpret_cast<u32x4*>(cV + dst_row * d + c) = v16;
+  if constexpr (sizeof(T) == 2) {  // (head_dim 128: sixteen lanes per row, all of them here or none)
+    float sq = add_squares(k16, 0.f);
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 64);
+    if (c == 0) invn[bh * npad + slot] = inverse_norm(sq);
+  }
   if (c == 0) {
     cscore[dst] = APPEND ? sc64[bh * npad + pos] : double(score[bh * npad + pos]);
     cpos[dst] = APPEND ? apos[bh * npad + pos] : pos;
@@ -331,6 +325,14 @@ __device__ __forceinline__ void join_best(float& best, float& second, int& bi, f
   best = fmaxf(best, om1);
 }
 
+// The inverse norm of an evicted key from the operands of its two lanes.
+__device__ __forceinline__ float evicted_norm(const bf16x8 (&be)[8]) {
+  float s = 0.f;
+#pragma unroll
+  for (int ks = 0; ks < 8; ++ks) s = add_squares(__builtin_bit_cast(u32x4, be[ks]), s);
+  return inverse_norm(s + __shfl_xor(s, 32, 64));
+}
+
 // A row's candidate, its threshold for the second sweep, and the list of ambiguous rows.  ie: the row's inverse norm.
 __device__ __forceinline__ void note_row(float best, float second, int bi, float ie, int erank, int64_t base, int64_t bh,
                                          int32_t* cand, float* thr, int32_t* amb_list, int32_t* amb_cnt, int32_t* ncand) {
@@ -349,7 +351,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(COLLECT ? 3
                                                          const uint16_t* __restrict__ cK,
                                                          const int32_t* __restrict__ meta, int64_t slots,
                                                          const float* __restrict__ invn,
-                                                         const int32_t* __restrict__ ret,
                                                          const int32_t* __restrict__ evi,
                                                          const int32_t* __restrict__ cnt, int32_t* __restrict__ cand,
                                                          float* __restrict__ thr, int32_t* __restrict__ amb_list,
@@ -373,9 +374,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(COLLECT ? 3
   // the retained keys, in retained order, already sit contiguously in the layer's cache
   // region (compaction runs first; merging, which changes them, runs after the matching)
   const uint16_t* rk = cK + (bh * slots + meta[bh * 4 + 0]) * 128;
-  const int32_t* rl = ret + bh * npad;
   const int32_t* el = evi + bh * npad;
-  const float* inl = invn + bh * npad;
+  const float* inl = invn + bh * npad;  // by retained rank
   const int row = e0 + w * 32 + m;
   const bool live = row < nrows;
   const int erank = COLLECT ? amb_list[bh * npad + min(row, nrows - 1)] : min(row, nrows - 1);
@@ -402,7 +402,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(COLLECT ? 3
       const int c = tid + 256 * i, rrow = c >> 4, col = (c & 15) * 8;
       rg[i] = *reinterpret_cast<const u32x4*>(rk + int64_t(min(r0 + rrow, nret - 1)) * 128 + col);
     }
-    if (tid < kTile) rv = (r0 + tid < nret) ? inl[rl[r0 + tid]] : -1.f;  // -1 marks a padding row
+    if (tid < kTile) rv = (r0 + tid < nret) ? inl[r0 + tid] : -1.f;  // -1 marks a padding row
   };
   auto stage = [&](int buf) {
 #pragma unroll
@@ -489,7 +489,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(COLLECT ? 3
   float best = two.m1, second = two.m2;
   int bi = two.rank(h);
   join_best(best, second, bi, __shfl_xor(best, 32, 64), __shfl_xor(second, 32, 64), __shfl_xor(bi, 32, 64));
-  if (h == 0 && live) note_row(best, second, bi, inl[epos], erank, bh * npad, bh, cand, thr, amb_list, amb_cnt, ncand);
+  const float ie = evicted_norm(be);
+  if (h == 0 && live) note_row(best, second, bi, ie, erank, bh * npad, bh, cand, thr, amb_list, amb_cnt, ncand);
 }
 
 // The first sweep for launches of few rows: 32 evicted rows per workgroup, whose wavefronts take the 32-key sub-tiles
@@ -505,7 +506,6 @@ __global__ __launch_bounds__(64 * kFewWaves) void match_filter_few(const uint16_
                                                                    const uint16_t* __restrict__ cK,
                                                                    const int32_t* __restrict__ meta, int64_t slots,
                                                                    const float* __restrict__ invn,
-                                                                   const int32_t* __restrict__ ret,
                                                                    const int32_t* __restrict__ evi,
                                                                    const int32_t* __restrict__ cnt,
                                                                    int32_t* __restrict__ cand, float* __restrict__ thr,
@@ -522,8 +522,7 @@ __global__ __launch_bounds__(64 * kFewWaves) void match_filter_few(const uint16_
   if (e0 >= nevi || nret == 0) return;
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, m = lane & 31, h = lane >> 5;
   const uint16_t* rk = cK + (bh * slots + meta[bh * 4 + 0]) * 128;
-  const int32_t* rl = ret + bh * npad;
-  const float* inl = invn + bh * npad;
+  const float* inl = invn + bh * npad;  // by retained rank
   const int erank = min(e0 + m, nevi - 1);
   const int epos = evi[bh * npad + erank];
   const uint16_t* erow = K + b * kv.sb + hk * kv.sh + int64_t(epos) * kv.sn;
@@ -538,15 +537,14 @@ __global__ __launch_bounds__(64 * kFewWaves) void match_filter_few(const uint16_
     for (int ks = 0; ks < 8; ++ks) a[ks] = *reinterpret_cast<const bf16x8*>(row + ks * 16);
   };
   BestTwo two;
-  // a, norm: sub-tile j; a_next, norm_next: the wavefront's next one; pos: the position of the row behind that
-  auto one = [&](int j, const bf16x8 (&a)[8], float norm, bf16x8 (&a_next)[8], float& norm_next, int& pos) {
+  // a, norm: sub-tile j; a_next, norm_next: the wavefront's next one
+  auto one = [&](int j, const bf16x8 (&a)[8], float norm, bf16x8 (&a_next)[8], float& norm_next) {
     if (h == 0) rin[w][m] = norm;
     // (within the wavefront; LDS serves its requests in order, so the hand-over needs compiler ordering only)
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     load(a_next, j + kFewWaves);
-    norm_next = inl[pos];
-    pos = rl[rank_of(j + 2 * kFewWaves)];
+    norm_next = inl[rank_of(j + kFewWaves)];
     f32x16 s = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks], be[ks], s, 0, 0, 0);
@@ -570,17 +568,17 @@ __global__ __launch_bounds__(64 * kFewWaves) void match_filter_few(const uint16_
   float n0 = 0.f, n1 = 0.f;
   if (w < nsub) {
     load(a0, w);
-    int pos = rl[rank_of(w + kFewWaves)];
-    n0 = inl[rl[rank_of(w)]];
+    n0 = inl[rank_of(w)];
 #pragma unroll 1
     for (int j = w; j < nsub; j += 2 * kFewWaves) {
-      one(j, a0, n0, a1, n1, pos);
-      if (j + kFewWaves < nsub) one(j + kFewWaves, a1, n1, a0, n0, pos);
+      one(j, a0, n0, a1, n1);
+      if (j + kFewWaves < nsub) one(j + kFewWaves, a1, n1, a0, n0);
     }
   }
   float best = two.m1, second = two.m2;
   int bi = two.rank(h);
   join_best(best, second, bi, __shfl_xor(best, 32, 64), __shfl_xor(second, 32, 64), __shfl_xor(bi, 32, 64));
+  const float ie = evicted_norm(be);
   if (h == 0) {
     best_s[w][m] = best;
     second_s[w][m] = second;
@@ -590,7 +588,7 @@ __global__ __launch_bounds__(64 * kFewWaves) void match_filter_few(const uint16_
   if (tid < 32 && e0 + tid < nevi) {
 #pragma unroll
     for (int u = 1; u < kFewWaves; ++u) join_best(best, second, bi, best_s[u][tid], second_s[u][tid], rank_s[u][tid]);
-    note_row(best, second, bi, inl[epos], erank, bh * npad, bh, cand, thr, amb_list, amb_cnt, ncand);
+    note_row(best, second, bi, ie, erank, bh * npad, bh, cand, thr, amb_list, amb_cnt, ncand);
   }
 }
 
@@ -1077,24 +1075,23 @@ hipError_t launch_select(d2o_ctx* c, int layer, int n, hipStream_t s, bool appen
 }
 
 template <typename T>
-static void run_gather(d2o_ctx* c, int layer, View K, View V, int max_budget, int n_norms, bool append, hipStream_t s) {
+static void run_gather(d2o_ctx* c, int layer, View K, View V, int max_budget, bool append, hipStream_t s) {
   const d2o_config& cf = c->cfg;
   const float* score = c->score_pre + size_t(layer) * cf.batch * cf.n_kv_heads * c->npad;
   const int32_t* meta = c->meta + size_t(layer) * cf.batch * cf.n_kv_heads * 4;
   int32_t* ccount = c->ccount + size_t(layer) * cf.batch * cf.n_kv_heads;
   const int rows = 256 / (cf.head_dim * int(sizeof(T)) / 16);
-  const int row_blocks = (max_budget + rows - 1) / rows;
-  const dim3 grid(row_blocks + (n_norms + 15) / 16, cf.n_kv_heads, cf.batch);
+  const dim3 grid((max_budget + rows - 1) / rows, cf.n_kv_heads, cf.batch);
   if (append)
     gather_kernel<T, true><<<grid, 256, 0, s>>>((const T*)K.ptr, K, (const T*)V.ptr, V, score, c->app_score, c->app_pos,
                                                 c->sel_ret, c->sel_cnt, meta, (T*)prompt_rows_K(c), (T*)prompt_rows_V(c), c->cscore,
                                                 c->cpos, ccount, c->npad, cf.head_dim, cf.slots_per_seq,
-                                                prompt_rows_meta(c, layer), prompt_rows_stride(c), row_blocks, c->invnorm, n_norms);
+                                                prompt_rows_meta(c, layer), prompt_rows_stride(c), c->invnorm);
   else
     gather_kernel<T, false><<<grid, 256, 0, s>>>((const T*)K.ptr, K, (const T*)V.ptr, V, score, nullptr, nullptr,
                                                  c->sel_ret, c->sel_cnt, meta, (T*)prompt_rows_K(c), (T*)prompt_rows_V(c), c->cscore,
                                                  c->cpos, ccount, c->npad, cf.head_dim, cf.slots_per_seq,
-                                                 prompt_rows_meta(c, layer), prompt_rows_stride(c), row_blocks, c->invnorm, n_norms);
+                                                 prompt_rows_meta(c, layer), prompt_rows_stride(c), c->invnorm);
 }
 
 static int max_evicted(const d2o_ctx* c, int layer, int n) {
@@ -1108,9 +1105,9 @@ hipError_t launch_gather(d2o_ctx* c, int layer, View K, View V, int n, hipStream
   int max_budget = 0;
   for (const auto& mt : c->layers[layer].meta) max_budget = std::max(max_budget, std::min(mt.budget, n));
   if (cf.dtype == D2O_BF16)
-    run_gather<uint16_t>(c, layer, K, V, max_budget, max_evicted(c, layer, n) > 0 ? n : 0, append, s);
+    run_gather<uint16_t>(c, layer, K, V, max_budget, append, s);
   else
-    run_gather<float>(c, layer, K, V, max_budget, 0, append, s);
+    run_gather<float>(c, layer, K, V, max_budget, append, s);
   return hipGetLastError();
 }
 
@@ -1130,18 +1127,16 @@ hipError_t launch_match(d2o_ctx* c, int layer, View K, int n, hipStream_t s) {
       if (int64_t(few.x) * few.y * few.z <= 256)
         match_filter_few<<<few, 64 * kFewWaves, 0, s>>>(
             (const uint16_t*)K.ptr, K, (const uint16_t*)prompt_rows_K(c), prompt_rows_meta(c, layer), prompt_rows_stride(c),
-            c->invnorm, c->sel_ret, c->sel_evi, c->sel_cnt, c->m_cand, c->m_thr, c->amb_list, c->amb_cnt, c->m_ncand, c->npad);
+            c->invnorm, c->sel_evi, c->sel_cnt, c->m_cand, c->m_thr, c->amb_list, c->amb_cnt, c->m_ncand, c->npad);
       else
         match_filter_bf16<false><<<gf, 256, 0, s>>>((const uint16_t*)K.ptr, K, (const uint16_t*)prompt_rows_K(c),
                                                     prompt_rows_meta(c, layer), prompt_rows_stride(c),
-                                                    c->invnorm, c->sel_ret, c->sel_evi,
-                                                    c->sel_cnt, c->m_cand, c->m_thr, c->amb_list, c->amb_cnt,
+                                                    c->invnorm, c->sel_evi, c->sel_cnt, c->m_cand, c->m_thr, c->amb_list, c->amb_cnt,
                                                     c->m_ncand, c->m_clist, c->npad, 1);
       constexpr int kSplit = 8;
       match_filter_bf16<true><<<dim3(gf.x * kSplit, gf.y, gf.z), 256, 0, s>>>((const uint16_t*)K.ptr, K, (const uint16_t*)prompt_rows_K(c),
                                                  prompt_rows_meta(c, layer), prompt_rows_stride(c),
-                                                 c->invnorm, c->sel_ret, c->sel_evi,
-                                                 c->sel_cnt, c->m_cand, c->m_thr, c->amb_list, c->amb_cnt,
+                                                 c->invnorm, c->sel_evi, c->sel_cnt, c->m_cand, c->m_thr, c->amb_list, c->amb_cnt,
                                                  c->m_ncand, c->m_clist, c->npad, kSplit);
     }
     KernelTimer kt(c, D2O_K_MATCH_REFINE, s);
