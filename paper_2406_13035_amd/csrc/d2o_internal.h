@@ -45,6 +45,14 @@ struct MetaPack {
   int32_t v[kMetaPerLaunch * 4];
 };
 
+// An evicted row whose best matches the filter could not tell apart: its rank and position, and the fp32 value (cosine
+// times its norm) that its candidates reach.
+struct alignas(16) FlaggedRow {
+  int32_t erank, pos;
+  float thr;
+  int32_t unused;
+};
+
 enum LayerPhase { kEmpty = 0, kAttended = 1, kReady = 2 };
 
 struct LayerState {
@@ -114,12 +122,8 @@ struct d2o_ctx {
   int32_t* sel_evi = nullptr;    // evicted positions, ascending
   int32_t* sel_cnt = nullptr;    // [B][Hkv][2]  n_ret, n_evi
   float* invnorm = nullptr;      // 1/|k| of every retained key, by its rank (fp32, filter only)
-  int32_t* m_cand = nullptr;     // filter's best retained rank per evicted row; bit 31 = ambiguous
-  float* m_thr = nullptr;        // filter's acceptance threshold of a flagged row
-  int32_t* amb_list = nullptr;   // flagged evicted ranks, in no particular order
+  d2o::FlaggedRow* amb_list = nullptr;  // flagged evicted rows, in no particular order
   int32_t* amb_cnt = nullptr;    // [B][Hkv]
-  int32_t* m_ncand = nullptr;    // candidates collected for a flagged row
-  int32_t* m_clist = nullptr;    // [..][npad][8] their retained ranks
   double* m_ustar = nullptr;     // exact best similarity per evicted row
   int32_t* m_tgt = nullptr;      // exact match (retained rank)
   uint8_t* m_pass = nullptr;     // threshold test

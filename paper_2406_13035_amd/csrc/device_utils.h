@@ -210,6 +210,13 @@ __device__ __forceinline__ F half_wave_sum(F v) {
   return v;
 }
 
+// v + the same of the lane 32 away (a register exchange between the halves, no LDS).
+__device__ __forceinline__ double sum_halves(double v) {
+  const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+  return __hiloint2double(int(hi[0]), int(lo[0])) + __hiloint2double(int(hi[1]), int(lo[1]));
+}
+
 // Workgroup barrier for exchanges through LDS only: it waits for the wavefront's LDS traffic,
 // not for its outstanding global loads and stores (which __syncthreads would drain first).
 __device__ __forceinline__ void lds_barrier() {

@@ -259,24 +259,31 @@ __global__ __launch_bounds__(256) void gather_kernel(const T* __restrict__ K, Vi
 // ------------------------------------------------------------------------------------------
 // Matching.
 
+// The place of a workgroup in a one-dimensional launch of several workgroups per (sequence, KV head), the heads fastest:
+// with a head count that is a multiple of the XCD count all workgroups of a head, which read the same retained
+// keys, run on one XCD and share its L2.
+struct HeadGrid {
+  int Hkv, heads;  // KV heads, and KV heads of all sequences
+  __device__ __forceinline__ int index() const { return int(blockIdx.x) % heads; }
+  __device__ __forceinline__ int head() const { return index() % Hkv; }
+  __device__ __forceinline__ int sequence() const { return index() / Hkv; }
+  __device__ __forceinline__ int block() const { return int(blockIdx.x) / heads; }
+  __device__ __forceinline__ int blocks() const { return int(gridDim.x) / heads; }
+};
+
 // Candidate filter on the matrix cores.  A workgroup owns 128 evicted rows (4 wavefronts x 32,
 // the stationary B operand) and streams the retained keys, read contiguously from the cache
 // region they were compacted into, in double-buffered tiles of 64 through LDS (the A operand),
-// so each lane owns one evicted row and sees 16 retained keys per MFMA tile.
-//   COLLECT = false: per row, track the best and second-best fp32 cosine and the best's
-//     retained rank.  A row whose two best values differ by less than kAmbiguous is flagged and
-//     its acceptance threshold (best - kAmbiguous, in the un-normalised domain) is stored.
-//   COLLECT = true: second sweep over the flagged rows only (a list in no particular order; the rows are
-//     independent of each other): every retained
-//     key whose fp32 cosine reaches the row's threshold is appended to the row's candidate
-//     list (up to kMaxCand; more than that falls back to the exhaustive search).  The sweep
-//     repeats the first one's arithmetic exactly, so the best value is found again.  Few rows are
-//     flagged (a workgroup or two per head), so the retained keys are split over `ksplit`
-//     workgroups per row block: the lists are appended with atomics and read order-free.
+// so each lane owns one evicted row and sees 16 retained keys per MFMA tile.  Per row, the best and
+// second-best fp32 cosine and the best's retained rank.  A row whose two best values differ by less than
+// kAmbiguous is flagged and its acceptance threshold (best - kAmbiguous, in the un-normalised domain) is stored, for
+// match_flagged; the others have one candidate, whose exact similarity the two lanes that hold the row form
+// at once.  (As a launch of its own, which read the evicted rows again, that took 19 us at 32 heads x 4096 tokens, a
+// fifth kept, and 153 at 32768, a tenth kept.)
 // The filter is bound by the vector ALU (68 instructions per 32 x 32 sub-tile and wavefront beside 8 products), as
 // long as no wavefront waits for LDS: with the operands and inverse norms requested half a sub-tile ahead and the
 // padding confined to the last tile, at four wavefronts per SIMD, 940 -> 867 us (32768 tokens, 32 heads, a tenth
-// kept), 37 -> 34 (4096, a fifth), 54 -> 41 (256 of 2304 rows leave).
+// kept), 37 -> 34 (4096, a fifth), 54 -> 41 (256 of 2304 rows leave); with the exact similarities 864 and 40.
 // kAmbiguous bounds twice the error of one filtered cosine: at most one rounding per accumulated
 // product (128 * 2^-24 of |k_i||k_j|) plus the two fp32 inverse norms, 1.6e-5 in total, plus the
 // four mantissa bits that carry the register number (2 * 16 * 2^-24 = 1.9e-6).
@@ -333,42 +340,82 @@ __device__ __forceinline__ float evicted_norm(const bf16x8 (&be)[8]) {
   return inverse_norm(s + __shfl_xor(s, 32, 64));
 }
 
-// A row's candidate, its threshold for the second sweep, and the list of ambiguous rows.  ie: the row's inverse norm.
-__device__ __forceinline__ void note_row(float best, float second, int bi, float ie, int erank, int64_t base, int64_t bh,
-                                         int32_t* cand, float* thr, int32_t* amb_list, int32_t* amb_cnt, int32_t* ncand) {
-  const float margin = ie > 0.f ? kAmbiguous / ie : INFINITY;  // threshold in the un-normalised domain
-  const bool amb = !(best - second >= margin);                // also true for NaN / equal / zero norm
-  cand[base + erank] = bi | (amb ? int(0x80000000u) : 0);
-  thr[base + erank] = best - margin;
-  if (amb) {
-    amb_list[base + atomicAdd(&amb_cnt[bh], 1)] = erank;
-    ncand[base + erank] = 0;
-  }
+// The margin of a row's best two, in the un-normalised domain (ie: the row's inverse norm), and whether they are too close;
+// also true for NaN / equal / zero norm.
+__device__ __forceinline__ float margin_of(float ie) { return ie > 0.f ? kAmbiguous / ie : INFINITY; }
+__device__ __forceinline__ bool is_ambiguous(float best, float second, float ie) { return !(best - second >= margin_of(ie)); }
+__device__ __forceinline__ void flag_row(float best, float ie, int erank, int epos, int64_t base, int64_t bh,
+                                         FlaggedRow* amb_list, int32_t* amb_cnt) {
+  amb_list[base + atomicAdd(&amb_cnt[bh], 1)] = FlaggedRow{erank, epos, best - margin_of(ie), 0};
 }
 
-template <bool COLLECT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(COLLECT ? 3 : 4, 4))) void match_filter_bf16(const uint16_t* __restrict__ K, View kv,
+// Exact similarity in fp64, operation order of Eq. 9 as written: dot / (|k_i| * |k_j|), 0 when
+// a norm is 0.  Products of bf16 values are exact in fp64 and their sums stay
+// exact at these magnitudes; the order of additions is the same everywhere all the same: eight neighbouring
+// elements one after the other, then neighbouring sums in pairs.
+struct DotNorms {
+  double dot, ne, nr;  // evicted key . retained key, and their squared norms
+};
+__device__ __forceinline__ DotNorms operator+(const DotNorms& a, const DotNorms& b) {
+  return DotNorms{a.dot + b.dot, a.ne + b.ne, a.nr + b.nr};
+}
+__device__ __forceinline__ DotNorms dot_of_eight(const u32x4& x, const u32x4& y) {
+  DotNorms s{0.0, 0.0, 0.0};
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const double a = double(__uint_as_float(e & 1 ? x[e / 2] & 0xFFFF0000u : x[e / 2] << 16));
+    const double b = double(__uint_as_float(e & 1 ? y[e / 2] & 0xFFFF0000u : y[e / 2] << 16));
+    s.dot = fma(a, b, s.dot);
+    s.ne = fma(a, a, s.ne);
+    s.nr = fma(b, b, s.nr);
+  }
+  return s;
+}
+__device__ __forceinline__ double cosine(const DotNorms& s) {
+  const double den = sqrt(s.ne) * sqrt(s.nr);
+  return den > 0.0 ? s.dot / den : 0.0;
+}
+// By sixteen neighbouring lanes, eight elements each.
+__device__ __forceinline__ double cosine_by_16(const u32x4& x, const u32x4& y) {
+  const DotNorms s = dot_of_eight(x, y);
+  return cosine(DotNorms{row16_sum(s.dot), row16_sum(s.ne), row16_sum(s.nr)});
+}
+// By lanes l and l + 32, which hold elements 16 ks + 8 (l / 32) .. of both keys, as the matrix instruction's operands.
+__device__ __forceinline__ double cosine_by_2(const bf16x8 (&be)[8], const u32x4 (&y)[8]) {
+  auto part = [&](int ks) {
+    const DotNorms s = dot_of_eight(__builtin_bit_cast(u32x4, be[ks]), y[ks]);
+    return DotNorms{sum_halves(s.dot), sum_halves(s.ne), sum_halves(s.nr)};
+  };
+  auto four = [&](int ks) { return (part(ks) + part(ks + 1)) + (part(ks + 2) + part(ks + 3)); };
+  return cosine(four(0) + four(4));
+}
+// (a non-finite key: no cosine compares above the start, and no threshold is reached)
+__device__ __forceinline__ void store_match(double u, int j, int64_t at, double* ustar, int32_t* tgt) {
+  const bool none = !(u > -2.0);
+  ustar[at] = none ? __longlong_as_double(0x7FF8000000000000ll) : u;
+  tgt[at] = none ? 0 : j;
+}
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void match_filter_bf16(const uint16_t* __restrict__ K, View kv,
                                                          const uint16_t* __restrict__ cK,
                                                          const int32_t* __restrict__ meta, int64_t slots,
                                                          const float* __restrict__ invn,
                                                          const int32_t* __restrict__ evi,
-                                                         const int32_t* __restrict__ cnt, int32_t* __restrict__ cand,
-                                                         float* __restrict__ thr, int32_t* __restrict__ amb_list,
-                                                         int32_t* __restrict__ amb_cnt,
-                                                         int32_t* __restrict__ ncand, int32_t* __restrict__ clist,
-                                                         int npad, int ksplit) {
+                                                         const int32_t* __restrict__ cnt,
+                                                         FlaggedRow* __restrict__ amb_list,
+                                                         int32_t* __restrict__ amb_cnt, double* __restrict__ ustar,
+                                                         int32_t* __restrict__ tgt, int npad, HeadGrid hg) {
   constexpr int kTile = 64;     // retained keys per LDS tile
   constexpr int NCH = kTile * 16 / 256;  // 16-byte chunks of a tile per thread
   __shared__ __attribute__((aligned(16))) uint16_t Rs[2][kTile * kLdM];
   __shared__ __attribute__((aligned(16))) float rin[2][kTile];    // 1/|k| of the staged retained keys
   __shared__ __attribute__((aligned(16))) float rbias[2][kTile];  // 0, or -3e38 for padding rows (finite: the low
                                                                   // mantissa bits of a value get overwritten below)
-  const int hk = blockIdx.y, b = blockIdx.z, Hkv = gridDim.y;
-  const int64_t bh = int64_t(b) * Hkv + hk;
+  const int hk = hg.head(), b = hg.sequence();
+  const int64_t bh = hg.index();
   const int nret = cnt[bh * 2], nevi = cnt[bh * 2 + 1];
-  const int nrows = COLLECT ? amb_cnt[bh] : nevi;
-  const int e0 = (int(blockIdx.x) / ksplit) * 128, part = int(blockIdx.x) % ksplit;
-  if (e0 >= nrows) return;
+  const int e0 = hg.block() * 128;
+  if (e0 >= nevi) return;
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, m = lane & 31, h = lane >> 5;
   const uint16_t* kb = K + b * kv.sb + hk * kv.sh;
   // the retained keys, in retained order, already sit contiguously in the layer's cache
@@ -376,25 +423,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(COLLECT ? 3
   const uint16_t* rk = cK + (bh * slots + meta[bh * 4 + 0]) * 128;
   const int32_t* el = evi + bh * npad;
   const float* inl = invn + bh * npad;  // by retained rank
-  const int row = e0 + w * 32 + m;
-  const bool live = row < nrows;
-  const int erank = COLLECT ? amb_list[bh * npad + min(row, nrows - 1)] : min(row, nrows - 1);
-  const int epos = el[erank];
+  const int epos = el[min(e0 + w * 32 + m, nevi - 1)];
   bf16x8 be[8];
 #pragma unroll
   for (int ks = 0; ks < 8; ++ks)
     be[ks] = *reinterpret_cast<const bf16x8*>(kb + int64_t(epos) * kv.sn + ks * 16 + h * 8);
   BestTwo two;
-  const float mythr = COLLECT ? thr[bh * npad + erank] : 0.f;
   // Tiles travel global -> registers -> LDS: the next tile is requested when work on a tile
   // starts and written to the other LDS buffer when it ends.
   u32x4 rg[NCH];
   float rv = 0.f;
-  const int ntile = (nret + kTile - 1) / kTile;
-  const int tper = (ntile + ksplit - 1) / ksplit;
-  const int tbeg = part * tper, tend = min(ntile, tbeg + tper);  // this workgroup's tiles
-  if (tbeg >= tend) return;
-  const int tfull = min(tend, nret / kTile);  // the first tile that is not full
+  const int tend = (nret + kTile - 1) / kTile;
+  const int tfull = nret / kTile;  // the first tile that is not full
   auto issue = [&](int t) {
     const int r0 = t * kTile;
 #pragma unroll
@@ -458,18 +498,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(COLLECT ? 3
           for (int i = 0; i < 4; ++i) tv[g4 * 4 + i] += bi[i];
         }
       }
-      if (COLLECT) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int rr = st * 32 + (r >> 2) * 8 + h * 4 + (r & 3);
-          if (live && tv[r] >= mythr) {
-            const int k = atomicAdd(&ncand[bh * npad + erank], 1);
-            if (k < kMaxCand) clist[(bh * npad + erank) * kMaxCand + k] = r0 + rr;
-          }
-        }
-      } else {
-        two.take(tv, r0 + st * 32);
-      }
+      two.take(tv, r0 + st * 32);
     };
     // (two sub-tiles as two independent accumulation chains need 160 registers and cost a
     // wavefront per SIMD: slower)
@@ -478,29 +507,82 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(COLLECT ? 3
     if (t + 1 < tend) stage(buf ^ 1);
     __syncthreads();
   };
-  issue(tbeg);
-  stage(tbeg & 1);
+  issue(0);
+  stage(0);
   __syncthreads();
 #pragma unroll 1
-  for (int t = tbeg; t < tfull; ++t) one_tile(t, std::false_type{});
+  for (int t = 0; t < tfull; ++t) one_tile(t, std::false_type{});
   if (tfull < tend) one_tile(tfull, std::true_type{});
-  if (COLLECT) return;
   // combine the two lane halves that share an evicted row
   float best = two.m1, second = two.m2;
   int bi = two.rank(h);
   join_best(best, second, bi, __shfl_xor(best, 32, 64), __shfl_xor(second, 32, 64), __shfl_xor(bi, 32, 64));
   const float ie = evicted_norm(be);
-  if (h == 0 && live) note_row(best, second, bi, ie, erank, bh * npad, bh, cand, thr, amb_list, amb_cnt, ncand);
+  const int row = e0 + w * 32 + m;
+  const bool live = row < nevi;
+  const int erank = min(row, nevi - 1);
+  const bool amb = is_ambiguous(best, second, ie);  // (both lanes agree; unless it is, they have the same candidate)
+  u32x4 y[8];
+  const uint16_t* yrow = rk + int64_t(amb ? 0 : bi) * 128 + h * 8;
+#pragma unroll
+  for (int ks = 0; ks < 8; ++ks) y[ks] = *reinterpret_cast<const u32x4*>(yrow + ks * 16);
+  const double u = cosine_by_2(be, y);
+  if (h == 0 && live) {
+    if (amb)
+      flag_row(best, ie, erank, el[erank], bh * npad, bh, amb_list, amb_cnt);
+    else
+      store_match(u, bi, bh * npad + erank, ustar, tgt);
+  }
 }
 
-// The first sweep for launches of few rows: 32 evicted rows per workgroup, whose wavefronts take the 32-key sub-tiles
-// in turn, operands and inverse norms straight from memory one sub-tile ahead (no wavefront shares
-// them, so LDS would only add a barrier per tile), and join their best two at the end.  Same values, in
-// the same order of products.  Bound by the operands' way from the L2, which every 32 rows take (eight
-// wavefronts instead of four: level).  A launch of few rows leaves most of the chip idle in blocks of 128: both
-// sweeps of 32 heads, 256 rows against 2048 keys, 53 -> 37 us, 200 against 800 keys 29 -> 22; from two workgroups per
-// CU on the blocks of 128, which read the keys a quarter as often, are the faster ones (512 rows against 128 keys 18.4
-// where this takes 20.4, 800 against 200 18.5 where it takes 31).
+// A wavefront's way through the retained keys for 32 evicted rows, whose operands it holds: the 32-key sub-tiles w, w + STEP,
+// ... come in whole lines one ahead and pass through the wavefront's own LDS (as the operands themselves, 32 bytes of every
+// row per load, a line came from the L2 four times over), with their inverse norms.  post(s, j): the sub-tile's products,
+// register r of key 32 j + (r / 4) 8 + 4 h + r % 4.  Same values as in match_filter_bf16, in the same order of products.
+template <int STEP, typename Post>
+__device__ __forceinline__ void sweep_keys(const uint16_t* rk, const float* inl, int nret, int w, int lane,
+                                           const bf16x8 (&be)[8], uint16_t* tile, float* rin, Post post) {
+  const int m = lane & 31, h = lane >> 5, nsub = (nret + 31) / 32;
+  if (w >= nsub) return;
+  u32x4 rg[8];
+  float norm;
+  // (rows and norms past the last one: zero)
+  const __amdgpu_buffer_rsrc_t norms = buffer_of(inl, uint32_t(nret) * 4);
+  auto request = [&](int j) {
+    const int js = __builtin_amdgcn_readfirstlane(j), rows = max(min(nret - js * 32, 32), 0);
+    const __amdgpu_buffer_rsrc_t keys = buffer_of(rk + int64_t(js) * 32 * 128, uint32_t(rows) * 256);
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      rg[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(keys, lane * 16 + i * 1024, 0, 0));
+    norm = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(norms, (js * 32 + m) * 4, 0, 0));
+  };
+  // (within the wavefront; LDS serves its requests in order, so the hand-overs need compiler ordering only)
+  auto hand_over = []() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  request(w);
+#pragma unroll 1
+  for (int j = w; j < nsub; j += STEP) {
+    hand_over();
+#pragma unroll
+    for (int i = 0; i < 8; ++i) *reinterpret_cast<u32x4*>(tile + (i * 4 + (lane >> 4)) * kLdM + (lane & 15) * 8) = rg[i];
+    if (h == 0) rin[m] = norm;
+    hand_over();
+    if (j + STEP < nsub) request(j + STEP);
+    f32x16 s = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks)
+      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(tile + m * kLdM + ks * 16 + h * 8), be[ks], s, 0, 0, 0);
+    post(s, j);
+  }
+}
+
+// The filter for launches of few rows: 32 evicted rows per workgroup, whose wavefronts take the sub-tiles
+// in turn and join their best two at the end.  A launch of few rows leaves most of the chip idle in blocks of 128; from
+// two workgroups per CU on those, which read the keys a quarter as often, are the faster ones (512 rows against 128 keys 18.4
+// where this takes 20.4, 800 against 200 18.5 where it takes 31).  256 rows against 2048 keys, 32 heads: 17 us with the exact
+// similarities, where the operands came straight from memory 23 without.
 constexpr int kFewWaves = 4;
 __global__ __launch_bounds__(64 * kFewWaves) void match_filter_few(const uint16_t* __restrict__ K, View kv,
                                                                    const uint16_t* __restrict__ cK,
@@ -508,46 +590,30 @@ __global__ __launch_bounds__(64 * kFewWaves) void match_filter_few(const uint16_
                                                                    const float* __restrict__ invn,
                                                                    const int32_t* __restrict__ evi,
                                                                    const int32_t* __restrict__ cnt,
-                                                                   int32_t* __restrict__ cand, float* __restrict__ thr,
-                                                                   int32_t* __restrict__ amb_list,
+                                                                   FlaggedRow* __restrict__ amb_list,
                                                                    int32_t* __restrict__ amb_cnt,
-                                                                   int32_t* __restrict__ ncand, int npad) {
+                                                                   double* __restrict__ ustar,
+                                                                   int32_t* __restrict__ tgt, int npad, HeadGrid hg) {
+  __shared__ __attribute__((aligned(16))) uint16_t tile[kFewWaves][32 * kLdM];
   __shared__ __attribute__((aligned(16))) float rin[kFewWaves][32];  // of the wavefront's sub-tile
   __shared__ float best_s[kFewWaves][32], second_s[kFewWaves][32];
   __shared__ int rank_s[kFewWaves][32];
-  const int hk = blockIdx.y, b = blockIdx.z, Hkv = gridDim.y;
-  const int64_t bh = int64_t(b) * Hkv + hk;
+  const int hk = hg.head(), b = hg.sequence();
+  const int64_t bh = hg.index();
   const int nret = cnt[bh * 2], nevi = cnt[bh * 2 + 1];
-  const int e0 = int(blockIdx.x) * 32;
-  if (e0 >= nevi || nret == 0) return;
+  const int e0 = hg.block() * 32;
+  if (e0 >= nevi) return;
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, m = lane & 31, h = lane >> 5;
   const uint16_t* rk = cK + (bh * slots + meta[bh * 4 + 0]) * 128;
-  const float* inl = invn + bh * npad;  // by retained rank
+  const uint16_t* kb = K + b * kv.sb + hk * kv.sh;
   const int erank = min(e0 + m, nevi - 1);
   const int epos = evi[bh * npad + erank];
-  const uint16_t* erow = K + b * kv.sb + hk * kv.sh + int64_t(epos) * kv.sn;
+  const uint16_t* erow = kb + int64_t(epos) * kv.sn;
   bf16x8 be[8];
 #pragma unroll
   for (int ks = 0; ks < 8; ++ks) be[ks] = *reinterpret_cast<const bf16x8*>(erow + ks * 16 + h * 8);
-  const int nsub = (nret + 31) / 32;
-  auto rank_of = [&](int j) { return min(j * 32 + m, nret - 1); };
-  auto load = [&](bf16x8 (&a)[8], int j) {
-    const uint16_t* row = rk + int64_t(rank_of(j)) * 128 + h * 8;
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) a[ks] = *reinterpret_cast<const bf16x8*>(row + ks * 16);
-  };
   BestTwo two;
-  // a, norm: sub-tile j; a_next, norm_next: the wavefront's next one
-  auto one = [&](int j, const bf16x8 (&a)[8], float norm, bf16x8 (&a_next)[8], float& norm_next) {
-    if (h == 0) rin[w][m] = norm;
-    // (within the wavefront; LDS serves its requests in order, so the hand-over needs compiler ordering only)
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    load(a_next, j + kFewWaves);
-    norm_next = inl[rank_of(j + kFewWaves)];
-    f32x16 s = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks], be[ks], s, 0, 0, 0);
+  sweep_keys<kFewWaves>(rk, invn + bh * npad, nret, w, lane, be, tile[w], rin[w], [&](const f32x16& s, int j) {
     float tv[16];
 #pragma unroll
     for (int g4 = 0; g4 < 4; ++g4) {
@@ -555,26 +621,13 @@ __global__ __launch_bounds__(64 * kFewWaves) void match_filter_few(const uint16_
 #pragma unroll
       for (int i = 0; i < 4; ++i) tv[g4 * 4 + i] = s[g4 * 4 + i] * ri[i];
     }
-    if (j * 32 + 32 > nret) {  // copies of the last row past the end: the lowest value, or NaN as the row itself
+    if (j * 32 + 32 > nret) {  // zeros past the end: the lowest value
 #pragma unroll
       for (int r = 0; r < 16; ++r)
-        if (j * 32 + (r >> 2) * 8 + h * 4 + (r & 3) >= nret) tv[r] = s[r] * 0.f - 3.0e38f;
+        if (j * 32 + (r >> 2) * 8 + h * 4 + (r & 3) >= nret) tv[r] = -3.0e38f;
     }
     two.take(tv, j * 32);
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-  };
-  bf16x8 a0[8], a1[8];
-  float n0 = 0.f, n1 = 0.f;
-  if (w < nsub) {
-    load(a0, w);
-    n0 = inl[rank_of(w)];
-#pragma unroll 1
-    for (int j = w; j < nsub; j += 2 * kFewWaves) {
-      one(j, a0, n0, a1, n1);
-      if (j + kFewWaves < nsub) one(j + kFewWaves, a1, n1, a0, n0);
-    }
-  }
+  });
   float best = two.m1, second = two.m2;
   int bi = two.rank(h);
   join_best(best, second, bi, __shfl_xor(best, 32, 64), __shfl_xor(second, 32, 64), __shfl_xor(bi, 32, 64));
@@ -585,177 +638,229 @@ __global__ __launch_bounds__(64 * kFewWaves) void match_filter_few(const uint16_
     rank_s[w][m] = bi;
   }
   __syncthreads();
-  if (tid < 32 && e0 + tid < nevi) {
+  if (tid < 32) {
 #pragma unroll
     for (int u = 1; u < kFewWaves; ++u) join_best(best, second, bi, best_s[u][tid], second_s[u][tid], rank_s[u][tid]);
-    note_row(best, second, bi, ie, erank, bh * npad, bh, cand, thr, amb_list, amb_cnt, ncand);
+    const bool live = e0 + tid < nevi, amb = is_ambiguous(best, second, ie);
+    if (live && amb) flag_row(best, ie, erank, epos, bh * npad, bh, amb_list, amb_cnt);
+    rank_s[0][tid] = live && !amb ? bi : -1;
   }
-}
-
-// Exact similarity in fp64, operation order of Eq. 9 as written: dot / (|k_i| * |k_j|), 0 when
-// a norm is 0.  A group of 16 lanes (one 16-byte slice of the key each) serves one evicted row:
-// unambiguous rows evaluate their single candidate, ambiguous rows their short candidate list;
-// rows without a usable list (and every row when no filter ran) are then searched exhaustively,
-// one at a time, with the wavefront's lanes striding over the retained keys, first maximum in
-// ascending retained order.  Products of bf16 values are exact in fp64 and their sums stay
-// exact at these magnitudes, so the result does not depend on the summation tree.
-template <typename T>
-__device__ __forceinline__ void load8(const T* p, double* out);
-template <>
-__device__ __forceinline__ void load8<uint16_t>(const uint16_t* p, double* out) {
-  const u32x4 v = *reinterpret_cast<const u32x4*>(p);
+  __syncthreads();
+  // the exact similarities, sixteen lanes per row
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    out[2 * i] = double(__uint_as_float(v[i] << 16));
-    out[2 * i + 1] = double(__uint_as_float(v[i] & 0xFFFF0000u));
+  for (int i = 0; i < 32; i += kFewWaves * 4) {
+    const int r = i + tid / 16, j = rank_s[0][r];
+    const int at = evi[bh * npad + min(e0 + r, nevi - 1)];
+    const u32x4 x = *reinterpret_cast<const u32x4*>(kb + int64_t(at) * kv.sn + tid % 16 * 8);
+    const u32x4 y = *reinterpret_cast<const u32x4*>(rk + int64_t(max(j, 0)) * 128 + tid % 16 * 8);
+    const double u = cosine_by_16(x, y);
+    if (tid % 16 == 0 && j >= 0) store_match(u, j, bh * npad + e0 + r, ustar, tgt);
   }
 }
-template <>
-__device__ __forceinline__ void load8<float>(const float* p, double* out) {  // 16 bytes: 4 elements
-  const float4 a = reinterpret_cast<const float4*>(p)[0];
-  out[0] = a.x; out[1] = a.y; out[2] = a.z; out[3] = a.w;
+
+// The flagged rows (a list in no particular order; the rows are independent of each other).  A workgroup takes 32 of
+// them at a time: its wavefronts sweep the retained keys again and list, in LDS, every key whose fp32
+// cosine reaches the row's threshold (the best value among them: the arithmetic is the first sweep's), up to kMaxCand;
+// then sixteen lanes per row decide among them exactly, first maximum in ascending retained order.  A row with more of
+// them, or none (a zero norm, a key that is not finite), is searched exhaustively by its wavefront.  Half a
+// percent of the rows is flagged, so the launch has a few workgroups per head, which stride over the list, and what bounds
+// it is the instructions of one wavefront: hits as bits instead of sixteen branches, addresses through buffer
+// descriptors, eight wavefronts (sixteen share the SIMDs and spill: 8.8 -> 16.5 us).  32 heads x 4096 tokens, a fifth kept, 8.8 us;
+// 32768, a tenth kept, 19.8; as a sweep in blocks of 128 rows by eight key ranges, most of them empty, 11 and 44.
+constexpr int kFlaggedWaves = 8;
+constexpr int kFlaggedBlocks = 16;  // workgroups per head at most
+__global__ __launch_bounds__(64 * kFlaggedWaves) void match_flagged(const uint16_t* __restrict__ K, View kv,
+                                                                    const uint16_t* __restrict__ cK,
+                                                                    const int32_t* __restrict__ meta, int64_t slots,
+                                                                    const float* __restrict__ invn,
+                                                                    const int32_t* __restrict__ cnt,
+                                                                    const FlaggedRow* __restrict__ amb_list,
+                                                                    const int32_t* __restrict__ amb_cnt,
+                                                                    double* __restrict__ ustar, int32_t* __restrict__ tgt,
+                                                                    int npad, HeadGrid hg) {
+  static_assert(kFlaggedWaves * 4 >= 32, "sixteen lanes per row");
+  constexpr int D = 128;
+  __shared__ __attribute__((aligned(16))) uint16_t tile[kFlaggedWaves][32 * kLdM];
+  __shared__ __attribute__((aligned(16))) float rin[kFlaggedWaves][32];  // of the wavefront's sub-tile
+  __shared__ int ncand[32], clist[32][kMaxCand];
+  const int hk = hg.head(), b = hg.sequence();
+  const int64_t bh = hg.index();
+  const int namb = amb_cnt[bh], nret = cnt[bh * 2];
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, m = lane & 31, h = lane >> 5;
+  const uint16_t* rk = cK + (bh * slots + meta[bh * 4 + 0]) * D;
+  const uint16_t* kb = K + b * kv.sb + hk * kv.sh;
+  const FlaggedRow* list = amb_list + bh * npad;
+#pragma unroll 1
+  for (int e0 = hg.block() * 32; e0 < namb; e0 += hg.blocks() * 32) {
+    const int rr = tid / 16, tc = tid % 16;  // the row of the exact comparison (half of the wavefronts have one)
+    const FlaggedRow fr = list[min(e0 + m, namb - 1)], own = list[min(e0 + rr, namb - 1)];
+    const float mythr = e0 + m < namb ? fr.thr : INFINITY;
+    const bool valid = rr < 32 && e0 + rr < namb;
+    const uint16_t* erow = kb + int64_t(fr.pos) * kv.sn;
+    bf16x8 be[8];
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) be[ks] = *reinterpret_cast<const bf16x8*>(erow + ks * 16 + h * 8);
+    const u32x4 x = *reinterpret_cast<const u32x4*>(kb + int64_t(own.pos) * kv.sn + tc * 8);
+    if (tid < 32) ncand[tid] = 0;
+    __syncthreads();
+    sweep_keys<kFlaggedWaves>(rk, invn + bh * npad, nret, w, lane, be, tile[w], rin[w], [&](const f32x16& s, int j) {
+      uint32_t hits = 0;
+#pragma unroll
+      for (int g4 = 0; g4 < 4; ++g4) {
+        const f32x4 ri = *reinterpret_cast<const f32x4*>(&rin[w][g4 * 8 + h * 4]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) hits |= s[g4 * 4 + i] * ri[i] >= mythr ? 1u << (g4 * 4 + i) : 0u;
+      }
+      while (hits) {
+        const int r = __ffs(hits) - 1, key = j * 32 + (r >> 2) * 8 + h * 4 + (r & 3);
+        hits &= hits - 1;
+        const int k = key < nret ? atomicAdd(&ncand[m], 1) : kMaxCand;
+        if (k < kMaxCand) clist[m][k] = key;
+      }
+    });
+    __syncthreads();
+    // ---- exactly: sixteen lanes per row, two candidates in flight
+    const int listed = valid ? ncand[rr] : 0, ncd = listed <= kMaxCand ? listed : 0;
+    double best = -2.0;
+    int bj = 0;
+    int nloop = max(ncd, __shfl_xor(ncd, 16, 64));
+    nloop = max(nloop, __shfl_xor(nloop, 32, 64));
+    for (int q = 0; q < nloop; q += 2) {
+      int j[2];
+      u32x4 y[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        j[i] = q + i < ncd ? clist[rr][q + i] : 0;
+        y[i] = *reinterpret_cast<const u32x4*>(rk + int64_t(j[i]) * D + tc * 8);
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const double u = cosine_by_16(x, y[i]);
+        if (q + i < ncd && (u > best || (u == best && j[i] < bj))) {
+          best = u;
+          bj = j[i];
+        }
+      }
+    }
+    unsigned long long todo = __ballot(valid && ncd == 0 && tc == 0);
+    while (todo) {  // one row at a time, the wavefront's lanes striding over the retained keys
+      const int src = __ffsll((long long)todo) - 1;  // first lane of the row to serve
+      todo &= todo - 1;
+      double* ke = reinterpret_cast<double*>(tile[w]);  // the row as fp64
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      double ne = 0.0;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const double v = double(__uint_as_float(e & 1 ? x[e / 2] & 0xFFFF0000u : x[e / 2] << 16));
+        if (lane / 16 == src / 16) ke[tc * 8 + e] = v;
+        ne = fma(v, v, ne);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      const double sne = sqrt(lane_f64(row16_sum(ne), src));
+      double fb = -2.0;
+      int fj = 0x7FFFFFFF;
+      for (int j = lane; j < nret; j += 64) {
+        double dot = 0.0, nr = 0.0;
+#pragma unroll 1
+        for (int c = 0; c < D; c += 8) {
+          const u32x4 y = *reinterpret_cast<const u32x4*>(rk + int64_t(j) * D + c);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const double v = double(__uint_as_float(e & 1 ? y[e / 2] & 0xFFFF0000u : y[e / 2] << 16));
+            dot = fma(ke[c + e], v, dot);
+            nr = fma(v, v, nr);
+          }
+        }
+        const double den = sne * sqrt(nr);
+        const double u = den > 0.0 ? dot / den : 0.0;
+        if (u > fb) {  // j ascends within a lane: strict > keeps the first maximum
+          fb = u;
+          fj = j;
+        }
+      }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        const double ob = __shfl_xor(fb, o, 64);
+        const int oj = __shfl_xor(fj, o, 64);
+        if (ob > fb || (ob == fb && oj < fj)) {
+          fb = ob;
+          fj = oj;
+        }
+      }
+      if (lane == src) {
+        best = fb;
+        bj = fj;
+      }
+    }
+    if (tc == 0 && valid) store_match(best, bj, bh * npad + own.erank, ustar, tgt);
+    __syncthreads();  // the lists are read before they are emptied
+  }
 }
 
-// Lanes of one row group (TPR lanes: 16, or 32 for 512-byte rows) add their partial sums.
-template <int TPR>
-__device__ __forceinline__ double group_sum(double v) {
-  v = row16_sum(v);
-  if constexpr (TPR == 32) v += __shfl_xor(v, 16, 64);
-  return v;
-}
-
-template <typename T, int D>
-__host__ __device__ constexpr int refine_rows_per_wave() {
-  return sizeof(T) == 2 ? 64 / (D * int(sizeof(T)) / 16) : 1;
-}
-template <typename T, int D>
-__global__ __launch_bounds__(256) void match_refine(const T* __restrict__ K, View kv, const int32_t* __restrict__ ret,
-                                                    const int32_t* __restrict__ evi, const int32_t* __restrict__ cnt,
-                                                    const int32_t* __restrict__ cand, const int32_t* __restrict__ ncand,
-                                                    const int32_t* __restrict__ clist, double* __restrict__ ustar,
-                                                    int32_t* __restrict__ tgt, int npad, int use_filter) {
-  constexpr int kVec = 16 / sizeof(T);  // elements per 16-byte load
-  constexpr int TPR = D / kVec;         // lanes that share one evicted row
-  // evicted rows per wavefront; fp32 rows are all searched exhaustively, by the whole wavefront one after
-  // the other, so a wavefront takes one (with four, 512 tokens and 4 heads were 96 wavefronts: 20 us, now 12 us)
-  constexpr int RW = refine_rows_per_wave<T, D>();
+// fp32: the exact search over all retained keys (no filter: 24 bits of a product are not decided by fp32 sums).  One evicted row
+// per wavefront, whose lanes stride over the retained keys, first maximum in ascending retained order; the
+// sums run over four neighbouring elements, the evicted key's norm over sixteen or 32 lanes.
+template <int D>
+__global__ __launch_bounds__(256) void match_search_f32(const float* __restrict__ K, View kv, const int32_t* __restrict__ ret,
+                                                        const int32_t* __restrict__ evi, const int32_t* __restrict__ cnt,
+                                                        double* __restrict__ ustar, int32_t* __restrict__ tgt, int npad) {
+  constexpr int TPR = D / 4;  // lanes that share the evicted row, 16 bytes each
   __shared__ double ke[4][D];
   const int hk = blockIdx.y, b = blockIdx.z, Hkv = gridDim.y;
   const int64_t bh = int64_t(b) * Hkv + hk;
   const int nret = cnt[bh * 2], nevi = cnt[bh * 2 + 1];
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, grp = lane / TPR, tc = lane % TPR;
-  if (int(blockIdx.x) * 4 * RW >= nevi) return;  // block-uniform
-  const int erank_raw = (blockIdx.x * 4 + w) * RW + grp % RW;
-  const bool valid = erank_raw < nevi && grp < RW;
-  const int erank = min(erank_raw, nevi - 1);
-  const T* kb = K + b * kv.sb + hk * kv.sh;
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, tc = lane % TPR;
+  const int erank = blockIdx.x * 4 + w;
+  if (erank >= nevi) return;
+  const float* kb = K + b * kv.sb + hk * kv.sh;
   const int32_t* rl = ret + bh * npad;
-  const int epos = evi[bh * npad + erank];
-  // this lane's slice of the evicted key
-  double x[kVec];
-  load8<T>(kb + int64_t(epos) * kv.sn + tc * kVec, x);
+  const float4 x = *reinterpret_cast<const float4*>(kb + int64_t(evi[bh * npad + erank]) * kv.sn + tc * 4);
+  const double xs[4] = {x.x, x.y, x.z, x.w};
   double ne = 0.0;
 #pragma unroll
-  for (int e = 0; e < kVec; ++e) ne = fma(x[e], x[e], ne);
-  const double sne = sqrt(group_sum<TPR>(ne));
-  // candidates: one (unambiguous), a short list (ambiguous), or every retained key (ncd < 0)
-  int ncd = -1, single = -1;
-  const int32_t* cl = clist + (bh * npad + erank) * kMaxCand;
-  if (use_filter) {
-    const int cnd = cand[bh * npad + erank];
-    if (cnd >= 0) {
-      single = cnd;
-      ncd = 1;
-    } else {
-      ncd = ncand[bh * npad + erank];
-      if (ncd > kMaxCand || ncd == 0) ncd = -1;  // overflow (or zero-norm row): exhaustive search
-    }
+  for (int e = 0; e < 4; ++e) {
+    ne = fma(xs[e], xs[e], ne);
+    if (lane < TPR) ke[w][tc * 4 + e] = xs[e];
   }
-  double best = -2.0;
-  int bj = 0x7FFFFFFF;
-  // ---- listed candidates: the row group evaluates them one after the other
-  int nloop = max(ncd, 0);
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) nloop = max(nloop, __shfl_xor(nloop, o, 64));
-  for (int q = 0; q < nloop; ++q) {
-    const bool on = q < ncd;
-    const int j = on ? (single >= 0 ? single : cl[q]) : 0;
-    double y[kVec];
-    load8<T>(kb + int64_t(rl[j]) * kv.sn + tc * kVec, y);
+  ne = row16_sum(ne);
+  if constexpr (TPR == 32) ne += __shfl_xor(ne, 16, 64);
+  const double sne = sqrt(ne);
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  double fb = -2.0;
+  int fj = 0x7FFFFFFF;
+  for (int j = lane; j < nret; j += 64) {
+    const float* rr = kb + int64_t(rl[j]) * kv.sn;
     double dot = 0.0, nr = 0.0;
+#pragma unroll 4
+    for (int c = 0; c < D; c += 4) {
+      const float4 y = *reinterpret_cast<const float4*>(rr + c);
+      const double ys[4] = {y.x, y.y, y.z, y.w};
 #pragma unroll
-    for (int e = 0; e < kVec; ++e) {
-      dot = fma(x[e], y[e], dot);
-      nr = fma(y[e], y[e], nr);
+      for (int e = 0; e < 4; ++e) {
+        dot = fma(ke[w][c + e], ys[e], dot);
+        nr = fma(ys[e], ys[e], nr);
+      }
     }
-    dot = group_sum<TPR>(dot);
-    nr = group_sum<TPR>(nr);
     const double den = sne * sqrt(nr);
     const double u = den > 0.0 ? dot / den : 0.0;
-    if (on && (u > best || (u == best && j < bj))) {
-      best = u;
-      bj = j;
+    if (u > fb) {  // j ascends within a lane: strict > keeps the first maximum
+      fb = u;
+      fj = j;
     }
   }
-  // ---- exhaustive search, one row at a time, the wavefront's lanes striding over the retained keys
-  unsigned long long todo = __ballot(valid && ncd < 0 && tc == 0);
-  while (todo) {
-    const int src = __ffsll((long long)todo) - 1;  // first lane of the row group to serve
-    todo &= todo - 1;
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    if (lane / TPR == src / TPR) {
 #pragma unroll
-      for (int e = 0; e < kVec; ++e) ke[w][tc * kVec + e] = x[e];
-    }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    const double sne_r = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(sne), src),
-                                          __builtin_amdgcn_readlane(__double2loint(sne), src));
-    double fb = -2.0;
-    int fj = 0x7FFFFFFF;
-    for (int j = lane; j < nret; j += 64) {
-      const T* rr = kb + int64_t(rl[j]) * kv.sn;
-      double dot = 0.0, nr = 0.0;
-      constexpr int kUnroll = sizeof(T) == 2 ? 1 : 4;
-      // (bf16 rows come here as exceptions: unrolled, this loop's registers would halve the wavefronts
-      // that the listed candidates above need in flight; fp32 rows always do)
-#pragma unroll kUnroll
-      for (int c = 0; c < D; c += kVec) {
-        double y[kVec];
-        load8<T>(rr + c, y);
-#pragma unroll
-        for (int i = 0; i < kVec; ++i) {
-          dot = fma(ke[w][c + i], y[i], dot);
-          nr = fma(y[i], y[i], nr);
-        }
-      }
-      const double den = sne_r * sqrt(nr);
-      const double u = den > 0.0 ? dot / den : 0.0;
-      if (u > fb) {  // j ascends within a lane: strict > keeps the first maximum
-        fb = u;
-        fj = j;
-      }
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      const double ob = __shfl_xor(fb, o, 64);
-      const int oj = __shfl_xor(fj, o, 64);
-      if (ob > fb || (ob == fb && oj < fj)) {
-        fb = ob;
-        fj = oj;
-      }
-    }
-    if (lane == src) {
-      best = fb;
-      bj = fj;
+  for (int o = 32; o > 0; o >>= 1) {
+    const double ob = __shfl_xor(fb, o, 64);
+    const int oj = __shfl_xor(fj, o, 64);
+    if (ob > fb || (ob == fb && oj < fj)) {
+      fb = ob;
+      fj = oj;
     }
   }
-  if (tc == 0 && valid) {
-    const bool none = bj == 0x7FFFFFFF;  // a non-finite key: no cosine compares above the start, and no threshold is reached
-    ustar[bh * npad + erank] = none ? __longlong_as_double(0x7FF8000000000000ll) : best;
-    tgt[bh * npad + erank] = none ? 0 : bj;
-  }
+  if (lane == 0) store_match(fb, fj, bh * npad + erank, ustar, tgt);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1115,41 +1220,33 @@ hipError_t launch_match(d2o_ctx* c, int layer, View K, int n, hipStream_t s) {
   const d2o_config& cf = c->cfg;
   const int me = max_evicted(c, layer, n);
   if (me == 0) return hipSuccess;
-  // evicted rows per workgroup of match_refine (bf16: head_dim 128)
-  const int refine_rows = 4 * (cf.dtype == D2O_BF16 ? refine_rows_per_wave<uint16_t, 128>() : refine_rows_per_wave<float, 128>());
-  const dim3 gr((me + refine_rows - 1) / refine_rows, cf.n_kv_heads, cf.batch);
   if (cf.dtype == D2O_BF16) {
-    const dim3 gf((me + 127) / 128, cf.n_kv_heads, cf.batch);
+    const int heads = cf.batch * cf.n_kv_heads;
+    const HeadGrid hg{cf.n_kv_heads, heads};
+    const uint16_t *k = (const uint16_t*)K.ptr, *rows = (const uint16_t*)prompt_rows_K(c);
+    const int32_t* meta = prompt_rows_meta(c, layer);
+    const int64_t stride = prompt_rows_stride(c);
     {
       KernelTimer kt(c, D2O_K_MATCH_FILTER, s);
       // Up to a workgroup of 32 rows per CU: blocks of 128 rows would leave three CUs of four idle.
-      const dim3 few((me + 31) / 32, cf.n_kv_heads, cf.batch);
-      if (int64_t(few.x) * few.y * few.z <= 256)
-        match_filter_few<<<few, 64 * kFewWaves, 0, s>>>(
-            (const uint16_t*)K.ptr, K, (const uint16_t*)prompt_rows_K(c), prompt_rows_meta(c, layer), prompt_rows_stride(c),
-            c->invnorm, c->sel_evi, c->sel_cnt, c->m_cand, c->m_thr, c->amb_list, c->amb_cnt, c->m_ncand, c->npad);
+      const int64_t few = int64_t((me + 31) / 32) * heads;
+      if (few <= 256)
+        match_filter_few<<<int(few), 64 * kFewWaves, 0, s>>>(k, K, rows, meta, stride, c->invnorm, c->sel_evi, c->sel_cnt,
+                                                             c->amb_list, c->amb_cnt, c->m_ustar, c->m_tgt, c->npad, hg);
       else
-        match_filter_bf16<false><<<gf, 256, 0, s>>>((const uint16_t*)K.ptr, K, (const uint16_t*)prompt_rows_K(c),
-                                                    prompt_rows_meta(c, layer), prompt_rows_stride(c),
-                                                    c->invnorm, c->sel_evi, c->sel_cnt, c->m_cand, c->m_thr, c->amb_list, c->amb_cnt,
-                                                    c->m_ncand, c->m_clist, c->npad, 1);
-      constexpr int kSplit = 8;
-      match_filter_bf16<true><<<dim3(gf.x * kSplit, gf.y, gf.z), 256, 0, s>>>((const uint16_t*)K.ptr, K, (const uint16_t*)prompt_rows_K(c),
-                                                 prompt_rows_meta(c, layer), prompt_rows_stride(c),
-                                                 c->invnorm, c->sel_evi, c->sel_cnt, c->m_cand, c->m_thr, c->amb_list, c->amb_cnt,
-                                                 c->m_ncand, c->m_clist, c->npad, kSplit);
+        match_filter_bf16<<<(me + 127) / 128 * heads, 256, 0, s>>>(k, K, rows, meta, stride, c->invnorm, c->sel_evi, c->sel_cnt,
+                                                                   c->amb_list, c->amb_cnt, c->m_ustar, c->m_tgt, c->npad, hg);
     }
     KernelTimer kt(c, D2O_K_MATCH_REFINE, s);
-    match_refine<uint16_t, 128><<<gr, 256, 0, s>>>((const uint16_t*)K.ptr, K, c->sel_ret, c->sel_evi, c->sel_cnt,
-                                                   c->m_cand, c->m_ncand, c->m_clist, c->m_ustar, c->m_tgt, c->npad, 1);
-  } else if (cf.head_dim == 64) {
-    KernelTimer kt(c, D2O_K_MATCH_REFINE, s);
-    match_refine<float, 64><<<gr, 256, 0, s>>>((const float*)K.ptr, K, c->sel_ret, c->sel_evi, c->sel_cnt, c->m_cand,
-                                               c->m_ncand, c->m_clist, c->m_ustar, c->m_tgt, c->npad, 0);
+    match_flagged<<<std::min((me + 31) / 32, kFlaggedBlocks) * heads, 64 * kFlaggedWaves, 0, s>>>(
+        k, K, rows, meta, stride, c->invnorm, c->sel_cnt, c->amb_list, c->amb_cnt, c->m_ustar, c->m_tgt, c->npad, hg);
   } else {
+    const dim3 grid((me + 3) / 4, cf.n_kv_heads, cf.batch);
     KernelTimer kt(c, D2O_K_MATCH_REFINE, s);
-    match_refine<float, 128><<<gr, 256, 0, s>>>((const float*)K.ptr, K, c->sel_ret, c->sel_evi, c->sel_cnt, c->m_cand,
-                                                c->m_ncand, c->m_clist, c->m_ustar, c->m_tgt, c->npad, 0);
+    if (cf.head_dim == 64)
+      match_search_f32<64><<<grid, 256, 0, s>>>((const float*)K.ptr, K, c->sel_ret, c->sel_evi, c->sel_cnt, c->m_ustar, c->m_tgt, c->npad);
+    else
+      match_search_f32<128><<<grid, 256, 0, s>>>((const float*)K.ptr, K, c->sel_ret, c->sel_evi, c->sel_cnt, c->m_ustar, c->m_tgt, c->npad);
   }
   return hipGetLastError();
 }

@@ -737,6 +737,29 @@ def test_matching_of_few_and_of_many_rows(B, Hkv, n, budget):
     ctx.close()
 
 
+@pytest.mark.parametrize("copies", [2, 8, 9])  # a row's list of candidates: short, full, too long (searched exhaustively)
+@pytest.mark.parametrize("Hkv,n,budget", [(1, 300, 90), (3, 300, 90), (2, 1500, 333), (9, 1300, 90)])
+def test_matching_where_every_row_has_equal_candidates(Hkv, n, budget, copies):
+    """Every retained key `copies` times over, so that every evicted row is flagged: launches of few and of many
+    rows, more flagged rows than a launch has places for at once; a key of zeros on either side."""
+    g = np.random.default_rng(n + copies)
+    K, V = (ref.round_storage(g.standard_normal((1, Hkv, n, 128)), "bf16") for _ in range(2))
+    score = g.random((1, Hkv, n)).astype(np.float32)
+    kept = np.sort(np.argsort(-score[..., :n - 1], axis=-1)[..., :budget - 1], axis=-1)
+    for h in range(Hkv):
+        K[0, h, kept[0, h]] = K[0, h, kept[0, h]][g.permutation(budget - 1) % -(-budget // copies)]
+        K[0, h, kept[0, h, 5]] = 0.0
+        K[0, h, np.setdiff1d(np.arange(n - 1), kept[0, h])[7]] = 0.0
+    ctx = binding.D2O(1, 1, Hkv, Hkv, 128, n, budget + 8, dtype="bf16")
+    ctx.d2o_scores_import(0, score)
+    ctx.d2o_compress_layer(0, *(torch.from_numpy(x).to(torch.bfloat16).cuda() for x in (K, V)), budget, 1)
+    for h in range(Hkv):
+        ret, evi, tgt, us, _ = ctx.d2o_prefill_events(0, 0, h, n)
+        want, at = ref.match(K[0, h][evi], K[0, h][ret])
+        assert np.array_equal(tgt, ret[at]) and np.allclose(us, want, rtol=0, atol=1e-14)
+    ctx.close()
+
+
 @pytest.mark.parametrize("fp8", [False, True])
 def test_attention_beside_the_compression_of_another_layer(fp8):
     """Attention and compression keep no scratch memory in common: layer 1's attention (grouped queries) on one stream,
