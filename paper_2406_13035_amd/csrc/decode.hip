@@ -181,10 +181,13 @@ __device__ __forceinline__ void head_normaliser(const DecodeArgs& a, int64_t bh,
 // 17.5 instead of 19.2 us.  With two batches of the score pass in flight, the partial rows of all query heads
 // requested together and one list of lowest scores instead of two, a layer of 8 heads of 5000
 // entries takes 73 instead of 77 us, two steps of 24 layers with eight query heads per KV head 228 instead of 236.)
+// With the normaliser, the factors and the match formed by every wavefront for itself where a head has at most 64
+// sub-chunks, the matches' positions in the records and two instead of three reductions at the end, 32 layers one per call take
+// 833 instead of 874 us, a step of a 128-entry fp32 cache 13.8 instead of 15.3.
 template <typename T, typename OT, int D, int G>
 __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ out, const View& ov, int li, int b,
-                                          int hk, int64_t lbh, int total, int nsub, double* sred, int* ired,
-                                          float* fred, double* dred, unsigned char* park) {
+                                          int hk, int64_t lbh, int64_t slot0, int ch0, int total, int nsub, double* sred,
+                                          int* ired, float* fred, double* dred, unsigned char* park) {
   constexpr int kRec = rec_doubles(G);
   constexpr int U = G >= 8 ? 1 : G >= 4 ? 2 : G >= 2 ? 4 : 6;  // slots per thread and batch of the score pass, of which two are in flight
   constexpr int C4 = D / 4;                           // threads across an output row (four columns each)
@@ -197,8 +200,6 @@ __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ 
   const int last = total - 1;
   const int32_t* mt = a.meta + lbh * 4;
   const int64_t bh = int64_t(b) * a.Hkv + hk;
-  const int64_t slot0 = bh * a.slots + mt[0];
-  const int ch0 = mt[3];  // the layer's first chunk in the partial-result arrays
   const T* Kc = static_cast<const T*>(a.cK) + slot0 * D;
   const T* Vc = static_cast<const T*>(a.cV) + slot0 * D;
   // ---- loads that depend on nothing: the threshold, this step's candidates, the last slot's row
@@ -252,114 +253,160 @@ __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ 
   //      sub-chunk and query head is kept in LDS (`em`, behind the parked values) for the output
   //      and score passes; for a head with more sub-chunks than fit, the factors overwrite the
   //      maxima in the records and the score pass brings them into LDS segment by segment.
+  //      A head of up to 64 sub-chunks, which is the usual one: every wavefront does this for itself, a record per
+  //      lane, with a table of its own, so that nothing waits for another wavefront.
   double* em = reinterpret_cast<double*>(park);  // [nsub][G]
+  constexpr bool kByWave = G <= 4;               // (four tables of eight query heads do not fit)
+  static_assert(!kByWave || 4 * 64 * G <= kEmCap, "four tables");
   const bool em_lds = nsub * G <= kEmCap;
   double Mg[G], Lg[G];
-  // The record of sub-chunk `tid` (the only one of this thread unless the head has more than 256
-  // sub-chunks) is read once, whole, and kept: the sweeps below then cost one memory round trip
-  // instead of three.
-  double own_m[G], own_l[G], own_u[kCand];
-  int own_s[kCand];
-  {
+  Best cm[kCand];  // Eq. 9: this step's candidates' matches
+  MergeRows<T> mr;
+  if (kByWave && nsub <= 64) {
+    em += w * 64 * G;
+    const int64_t x = sub_index(a, bh, ch0, min(lane, nsub - 1)) * kRec;
+    double m[G], l[G], u[kCand];
+    int s[kCand], p[kCand];
 #pragma unroll
-    for (int g = 0; g < G; ++g) Mg[g] = -INFINITY;
-    for (int c = tid; c < nsub; c += 256) {
-      const int64_t x = sub_index(a, bh, ch0, c) * kRec;
-      if (c == tid) {
+    for (int g = 0; g < G; ++g) {
+      m[g] = ld_agent(&a.rec[x + g]);
+      l[g] = ld_agent(&a.rec[x + G + g]);
+    }
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-          own_m[g] = ld_agent(&a.rec[x + g]);
-          own_l[g] = ld_agent(&a.rec[x + G + g]);
-        }
-#pragma unroll
-        for (int i = 0; i < kCand; ++i) {
-          own_u[i] = ld_agent(&a.rec[x + 2 * G + i]);
-          own_s[i] = int(ld_agent(&a.rec[x + 2 * G + kCand + i]));
-        }
-#pragma unroll
-        for (int g = 0; g < G; ++g) Mg[g] = fmax(Mg[g], own_m[g]);
-      } else {
-#pragma unroll
-        for (int g = 0; g < G; ++g) Mg[g] = fmax(Mg[g], ld_agent(&a.rec[x + g]));
-      }
+    for (int i = 0; i < kCand; ++i) {
+      u[i] = ld_agent(&a.rec[x + 2 * G + i]);
+      s[i] = int(ld_agent(&a.rec[x + 2 * G + kCand + i]));
+      p[i] = int(ld_agent(&a.rec[x + 2 * G + 2 * kCand + i]));
     }
     if constexpr (kEarlyRows) {
 #pragma unroll
       for (int g = 0; g < G; ++g) load_partial(g, rg);
     }
     load_batch(set0, tid);
+    const bool has = lane < nsub;
 #pragma unroll
-    for (int g = 0; g < G; ++g) Mg[g] = fast_wave_max(Mg[g]);
-    lds_barrier();
-    if (lane == 0) {
+    for (int i = 0; i < kCand; ++i) cm[i] = fast_wave_best_match(u[i], p[i], has ? s[i] : -1);
+    mr = load_merge_rows<T, D>(a, slot0, cl[0], cm[0].slot);
 #pragma unroll
-      for (int g = 0; g < G; ++g) dred[w * G + g] = Mg[g];
+    for (int g = 0; g < G; ++g) {
+      Mg[g] = fast_wave_max(has ? m[g] : -INFINITY);
+      const double t = has ? exp(m[g] - Mg[g]) : 0.0;
+      Lg[g] = fast_wave_sum(has ? l[g] * t : 0.0);
+      if (has) em[lane * G + g] = t / Lg[g];
     }
-    lds_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  } else {
+    // The record of sub-chunk `tid` (the only one of this thread unless the head has more than 256
+    // sub-chunks) is read once, whole, and kept: the sweeps below then cost one memory round trip
+    // instead of three.
+    double own_m[G], own_l[G], own_u[kCand];
+    int own_s[kCand], own_p[kCand];
+    {
 #pragma unroll
-    for (int g = 0; g < G; ++g) Mg[g] = fmax(fmax(dred[g], dred[G + g]), fmax(dred[2 * G + g], dred[3 * G + g]));
-    double part[G];
+      for (int g = 0; g < G; ++g) Mg[g] = -INFINITY;
+      for (int c = tid; c < nsub; c += 256) {
+        const int64_t x = sub_index(a, bh, ch0, c) * kRec;
+        if (c == tid) {
 #pragma unroll
-    for (int g = 0; g < G; ++g) part[g] = 0.0;
+          for (int g = 0; g < G; ++g) {
+            own_m[g] = ld_agent(&a.rec[x + g]);
+            own_l[g] = ld_agent(&a.rec[x + G + g]);
+          }
+#pragma unroll
+          for (int i = 0; i < kCand; ++i) {
+            own_u[i] = ld_agent(&a.rec[x + 2 * G + i]);
+            own_s[i] = int(ld_agent(&a.rec[x + 2 * G + kCand + i]));
+            own_p[i] = int(ld_agent(&a.rec[x + 2 * G + 2 * kCand + i]));
+          }
+#pragma unroll
+          for (int g = 0; g < G; ++g) Mg[g] = fmax(Mg[g], own_m[g]);
+        } else {
+#pragma unroll
+          for (int g = 0; g < G; ++g) Mg[g] = fmax(Mg[g], ld_agent(&a.rec[x + g]));
+        }
+      }
+      if constexpr (kEarlyRows) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) load_partial(g, rg);
+      }
+      load_batch(set0, tid);
+#pragma unroll
+      for (int g = 0; g < G; ++g) Mg[g] = fast_wave_max(Mg[g]);
+      lds_barrier();
+      if (lane == 0) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) dred[w * G + g] = Mg[g];
+      }
+      lds_barrier();
+#pragma unroll
+      for (int g = 0; g < G; ++g) Mg[g] = fmax(fmax(dred[g], dred[G + g]), fmax(dred[2 * G + g], dred[3 * G + g]));
+      double part[G];
+#pragma unroll
+      for (int g = 0; g < G; ++g) part[g] = 0.0;
+      for (int c = tid; c < nsub; c += 256) {
+        const int64_t x = sub_index(a, bh, ch0, c) * kRec;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          const double t = exp((c == tid ? own_m[g] : ld_agent(&a.rec[x + g])) - Mg[g]);
+          part[g] += (c == tid ? own_l[g] : ld_agent(&a.rec[x + G + g])) * t;
+          if (em_lds)
+            em[c * G + g] = t;
+          else
+            st_agent(&a.rec[x + g], t);  // the factor replaces the maximum (nobody needs it again)
+        }
+      }
+      // (the tree of head_normaliser, all query heads in one exchange)
+#pragma unroll
+      for (int g = 0; g < G; ++g) part[g] = fast_wave_sum(part[g]);
+      if (lane == 0) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) dred[(4 + w) * G + g] = part[g];
+      }
+      if (em_lds)
+        lds_barrier();
+      else
+        __syncthreads();  // the factors are in memory: the stores have been acknowledged
+#pragma unroll
+      for (int g = 0; g < G; ++g) Lg[g] = ((dred[4 * G + g] + dred[5 * G + g]) + dred[6 * G + g]) + dred[7 * G + g];
+      // the table holds the factors already divided by the normaliser: a probability is then
+      // one product, exp(s_j - m_sub) * em
+      if (em_lds) {
+        for (int c = tid; c < nsub; c += 256) {
+#pragma unroll
+          for (int g = 0; g < G; ++g) em[c * G + g] /= Lg[g];
+        }
+        lds_barrier();
+      }
+    }
+    // ---- Eq. 9 arg-max over the sub-chunks' results, for every candidate of this step (which of
+    //      them is evicted is not known yet; ties: earlier position)
+#pragma unroll
+    for (int i = 0; i < kCand; ++i) cm[i] = Best{0.0, 0, -1};
     for (int c = tid; c < nsub; c += 256) {
       const int64_t x = sub_index(a, bh, ch0, c) * kRec;
 #pragma unroll
-      for (int g = 0; g < G; ++g) {
-        const double t = exp((c == tid ? own_m[g] : ld_agent(&a.rec[x + g])) - Mg[g]);
-        part[g] += (c == tid ? own_l[g] : ld_agent(&a.rec[x + G + g])) * t;
-        if (em_lds)
-          em[c * G + g] = t;
-        else
-          st_agent(&a.rec[x + g], t);  // the factor replaces the maximum (nobody needs it again)
+      for (int i = 0; i < kCand; ++i) {
+        const int s = c == tid ? own_s[i] : int(ld_agent(&a.rec[x + 2 * G + kCand + i]));
+        if (s >= 0) {
+          const double u = c == tid ? own_u[i] : ld_agent(&a.rec[x + 2 * G + i]);
+          const int p = c == tid ? own_p[i] : int(ld_agent(&a.rec[x + 2 * G + 2 * kCand + i]));
+          if (better_match(u, p, s, cm[i])) cm[i] = Best{u, p, s};
+        }
       }
     }
-    // (the tree of head_normaliser, all query heads in one exchange)
 #pragma unroll
-    for (int g = 0; g < G; ++g) part[g] = fast_wave_sum(part[g]);
-    if (lane == 0) {
-#pragma unroll
-      for (int g = 0; g < G; ++g) dred[(4 + w) * G + g] = part[g];
-    }
-    if (em_lds)
-      lds_barrier();
-    else
-      __syncthreads();  // the factors are in memory: the stores have been acknowledged
-#pragma unroll
-    for (int g = 0; g < G; ++g) Lg[g] = ((dred[4 * G + g] + dred[5 * G + g]) + dred[6 * G + g]) + dred[7 * G + g];
-    // the table holds the factors already divided by the normaliser: a probability is then
-    // one product, exp(s_j - m_sub) * em
-    if (em_lds) {
-      for (int c = tid; c < nsub; c += 256) {
-#pragma unroll
-        for (int g = 0; g < G; ++g) em[c * G + g] /= Lg[g];
-      }
-      lds_barrier();
-    }
-  }
-  // ---- Eq. 9 arg-max over the sub-chunks' results, for every candidate of this step (which of
-  //      them is evicted is not known yet; ties: earlier position)
-  Best cm[kCand];
-#pragma unroll
-  for (int i = 0; i < kCand; ++i) cm[i] = Best{0.0, 0, -1};
-  for (int c = tid; c < nsub; c += 256) {
-    const int64_t x = sub_index(a, bh, ch0, c) * kRec;
-#pragma unroll
-    for (int i = 0; i < kCand; ++i) {
-      const int s = c == tid ? own_s[i] : int(ld_agent(&a.rec[x + 2 * G + kCand + i]));
-      if (s >= 0) {
-        const double u = c == tid ? own_u[i] : ld_agent(&a.rec[x + 2 * G + i]);
-        const int p = s == last ? a.new_pos : a.cpos[slot0 + s];
-        if (better_match(u, p, s, cm[i])) cm[i] = Best{u, p, s};
+    for (int i = 0; i < kCand; ++i) {  // (a thread's entries come from different sub-chunks: all positions differ)
+      const Best r = fast_wave_best_match(cm[i].u, cm[i].pos, cm[i].slot);
+      if (lane == 0) {
+        wcm_u[w * kCand + i] = r.u;
+        wcm_ps[w * kCand + i] = make_int2(r.pos, r.slot);
       }
     }
-  }
+    lds_barrier();  // the wavefronts' matches are in LDS
 #pragma unroll
-  for (int i = 0; i < kCand; ++i) {  // (a thread's entries come from different sub-chunks: all positions differ)
-    const Best r = fast_wave_best_match(cm[i].u, cm[i].pos, cm[i].slot);
-    if (lane == 0) {
-      wcm_u[w * kCand + i] = r.u;
-      wcm_ps[w * kCand + i] = make_int2(r.pos, r.slot);
-    }
+    for (int i = 0; i < kCand; ++i) cm[i] = candidate_match(wcm_u, wcm_ps, i);
+    mr = load_merge_rows<T, D>(a, slot0, cl[0], cm[0].slot);
   }
   const bool evict = total > mt[1];
   // Eq. 6 for the batch's slots, and the lowest scores of the tokens evictable at this step (Eq. 7-8 on count + 1
@@ -372,25 +419,13 @@ __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ 
   double* out_s = sred + 5;  // the score and slot of `out`
   int* out_j = ired + 9;
   if (tid == 0) *out_j = -1;
-  auto insert = [&](double x, int p, int j) {
-    if (evicts_before(x, p, j, low[kCand])) {
-      low[kCand] = Best{x, p, j};
-#pragma unroll
-      for (int i = kCand; i > 0; --i)
-        if (evicts_before(low[i].u, low[i].pos, low[i].slot, low[i - 1])) {
-          const Best t = low[i - 1];
-          low[i - 1] = low[i];
-          low[i] = t;
-        }
-    }
-  };
   auto consider = [&](double x, int p, int j) {
     if (p >= a.n_sink && p <= next_out + 1) {
       if (p == next_out + 1) {
         *out_s = x;
         *out_j = j;
       } else {
-        insert(x, p, j);
+        insert_entry(low, Best{x, p, j});
       }
     }
   };
@@ -410,10 +445,6 @@ __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ 
   };
   // ---- output rows: thread (rg, c4) adds the chunks rg, rg + RG, ... of four columns, PB of every query
   //      head in flight; the groups' sums are added in ascending order
-  const MergeRows<T> mr = [&]() {
-    lds_barrier();  // the wavefronts' matches are in LDS
-    return load_merge_rows<T, D>(a, slot0, cl[0], candidate_match(wcm_u, wcm_ps, 0).slot);
-  }();
   float num[G][4];
 #pragma unroll
   for (int g = 0; g < G; ++g)
@@ -500,10 +531,27 @@ __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ 
       consider(s2, a.new_pos, last);
     }
   }
+  // ---- the wavefronts' lowest entries, joined by every thread: the first one is evicted, and the next step's
+  //      candidates are the others and `out`
+  constexpr int NE = kCand + 1;
+  Best* ex = reinterpret_cast<Best*>(dred);  // [4][NE]
+  Best nx[kCand + 1];
+  wave_first_entries(low, nx);
+  if (lane == 0) {
+#pragma unroll
+    for (int r = 0; r < NE; ++r) ex[w * NE + r] = nx[r];
+  }
   lds_barrier();
-  const Best ev = low[0];
-  if (tid == 0 && *out_j >= 0) insert(*out_s, next_out + 1, *out_j);
-  close_head<T, D>(a, lbh, slot0, total, evict, ev, low, cl, told, sred, ired, dred, wcm_u, wcm_ps, park_kv, mr);
+#pragma unroll
+  for (int r = 0; r < NE; ++r) nx[r] = ex[r];
+#pragma unroll
+  for (int i = NE; i < 4 * NE; ++i) insert_entry(nx, ex[i]);
+  const Best ev = nx[0];
+  if (*out_j >= 0) {
+    if (evict && kCand == 1) nx[0] = nx[1], nx[1].slot = -1;  // (the evicted entry is no candidate)
+    insert_entry(nx, Best{*out_s, next_out + 1, *out_j});
+  }
+  close_head<T, D>(a, lbh, slot0, total, evict, ev, nx, cl, cm, told, sred, ired, dred, park_kv, mr);
 }
 
 // T: the cache's element type (uint8_t: fp8 codes).  (second launch bound: wavefronts per SIMD)
@@ -898,6 +946,7 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
         const Best m = fast_wave_best_match(u, pos, (valid && cs[c] >= 0 && j != cs[c]) ? j : -1);
         if (ln == 2 * G + c) recv = m.u;
         if (ln == 2 * G + kCand + c) recv = double(m.slot);
+        if (ln == 2 * G + 2 * kCand + c) recv = double(m.pos);
       }
       if (ln < kRec) st_agent(&a.rec[(pidx / G) * kRec + ln], recv);  // the record in one store
       // ---- partial P V.  The wavefront's partial rows (one per query head) go to its staging area for the
@@ -1109,8 +1158,8 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
     head_normaliser<G>(a, int64_t(b) * a.Hkv + hk, mt3, (total + kSub - 1) / kSub, a.hnorm + lbh * 16, dred, sred);
     return;
   }
-  head_tail<T, OT, D, G>(a, out, ov, li, b, hk, lbh, total, (total + kSub - 1) / kSub, sred, ired, fred, dred,
-                         stage + 8192);
+  head_tail<T, OT, D, G>(a, out, ov, li, b, hk, lbh, (int64_t(b) * a.Hkv + hk) * a.slots + mt0, mt3, total,
+                         (total + kSub - 1) / kSub, sred, ired, fred, dred, stage + 8192);
 }
 
 struct StepViews {

@@ -19,8 +19,8 @@ namespace dec {
 constexpr int kCand = 1;
 constexpr int kMaxLayersPerCall = 64;
 // Doubles per sub-chunk record: the G softmax maxima, the G exp-sums, then per candidate its
-// best cosine and that key's slot; rounded up to a multiple of eight (64 bytes).
-__host__ __device__ constexpr int rec_doubles(int G) { return (2 * G + 2 * kCand + 7) / 8 * 8; }
+// best cosine, that key's slot and its position; rounded up to a multiple of eight (64 bytes).
+__host__ __device__ constexpr int rec_doubles(int G) { return (2 * G + 3 * kCand + 7) / 8 * 8; }
 constexpr int kPiece = 64;              // bytes of a cache row staged per LDS round
 constexpr int kPitch = kPiece + 16;     // LDS pitch of a staged row piece (20 words: sixteen lanes that read sixteen
                                         // consecutive rows, and four lanes that write a row, meet all banks once)
@@ -48,7 +48,7 @@ struct DecodeArgs {
   double* elog;       // [chunk][B][Hkv][G][256] exp(logit - sub-chunk max)
   double* rec;        // [chunk][B][Hkv][4][rec_doubles(G)] per sub-chunk record: [0..G) softmax maxima of the
                       // query heads, [G..2G) exp-sums relative to them, [2G..2G+kCand) the candidates' best
-                      // cosine, [2G+kCand..2G+2kCand) its slot (-1 none); written with one store
+                      // cosine, [2G+kCand..2G+2kCand) its slot (-1 none), [2G+2kCand..2G+3kCand) its position; written with one store
   float* pacc;        // [chunk][B][Hkv][G][d] partial outputs, relative to the chunk's softmax maximum
   int32_t* ev_evicted;
   int32_t* ev_target;
@@ -495,51 +495,50 @@ __device__ __forceinline__ Best candidate_match(const double* wcm_u, const int2*
   return m;
 }
 
-// The end of a head's closing work, by a workgroup of 256 threads.  On entry every thread holds
-// its own first-evicted entry `ev` and its sorted list `low` of the next step's lowest evictable
-// entries (a thread's entries belong to slots no other thread holds); LDS holds, per wavefront
-// and candidate, the best match found (`wcm_u`, `wcm_ps` = (position, slot)), the last slot's
-// updated score and position (sred[4], ired[8]) and its row as it was before the step
-// (`park_kv`: K at [0, D), V at [256, 256 + D)).  `mr` holds the rows of candidate 0 and of its best
-// match (requested before the score pass, so that a step that evicts this candidate, which is the
-// normal case, waits for no memory here).  The function reduces the entries over the workgroup
-// (one exchange for the evicted token and the next candidates), writes the next step's
-// candidates, resets the head's ticket, finds the merge target (from the candidates' results,
-// else by a pass over the head's keys) and finishes the step.
-template <typename T, int D>
-__device__ __forceinline__ void close_head(const DecodeArgs& a, int64_t lbh, int64_t slot0, int total, bool evict,
-                                           Best ev, Best (&low)[kCand + 1], const int (&cl)[kCand], double told,
-                                           double* sred, int* ired, double* dred, const double* wcm_u,
-                                           const int2* wcm_ps, const T* park_kv, MergeRows<T> mr) {
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int last = total - 1;
-  // per wavefront: the first evicted, then the kCand + 1 lowest of the next step's evictable tokens
-  constexpr int NE = kCand + 2;
-  static_assert(4 * NE * 2 <= D, "the entries fit the exchange buffer");
-  Best* ex = reinterpret_cast<Best*>(dred);  // [4][NE]
-  {
-    const Best h = fast_wave_first_evicted(ev);
-    if (lane == 0) ex[w * NE] = h;
+// The kCand + 1 first of two lists in eviction order, into `a` (both sorted; no entry is in both).
+__device__ __forceinline__ void insert_entry(Best (&a)[kCand + 1], const Best& x) {
+  if (evicts_before(x.u, x.pos, x.slot, a[kCand])) {
+    a[kCand] = x;
+#pragma unroll
+    for (int i = kCand; i > 0; --i)
+      if (evicts_before(a[i].u, a[i].pos, a[i].slot, a[i - 1])) {
+        const Best t = a[i - 1];
+        a[i - 1] = a[i];
+        a[i] = t;
+      }
   }
+}
+// The kCand + 1 first of the lists of a wavefront's lanes, in eviction order; `low` is used up.
+__device__ __forceinline__ void wave_first_entries(Best (&low)[kCand + 1], Best (&out)[kCand + 1]) {
 #pragma unroll
   for (int r = 0; r <= kCand; ++r) {
-    const Best h = fast_wave_first_evicted(low[0]);
-    if (lane == 0) ex[w * NE + 1 + r] = h;
-    if (h.slot >= 0 && low[0].slot == h.slot) {  // the owner pops its head
+    out[r] = fast_wave_first_evicted(low[0]);
+    if (out[r].slot >= 0 && low[0].slot == out[r].slot) {  // the owner pops its head
 #pragma unroll
       for (int i = 0; i < kCand; ++i) low[i] = low[i + 1];
       low[kCand].slot = -1;
     }
   }
-  lds_barrier();
+}
+
+// The end of a head's closing work, by a workgroup of 256 threads, with block-uniform arguments: `ev`, the first evicted
+// entry of the head; `nx`, the lowest entries evictable at the next step, in eviction order (`ev` may be among
+// them); `cm`, this step's candidates' matches; the last slot's
+// updated score and position (sred[4], ired[8]) and its row as it was before the step
+// (`park_kv`: K at [0, D), V at [256, 256 + D)).  `mr` holds the rows of candidate 0 and of its best
+// match (requested before the score pass, so that a step that evicts this candidate, which is the
+// normal case, waits for no memory here).  The function writes the next step's
+// candidates, resets the head's ticket, finds the merge target (from the candidates' results,
+// else by a pass over the head's keys) and finishes the step.
+template <typename T, int D>
+__device__ __forceinline__ void close_head(const DecodeArgs& a, int64_t lbh, int64_t slot0, int total, bool evict,
+                                           Best ev, const Best (&nx)[kCand + 1], const int (&cl)[kCand],
+                                           const Best (&cm)[kCand], double told, double* sred, int* ired, double* dred,
+                                           const T* park_kv, MergeRows<T> mr) {
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int last = total - 1;
   const double s_last = sred[4];
   const int p_last = ired[8];
-  ev = ex[0];
-#pragma unroll
-  for (int i = 1; i < 4; ++i) {
-    const Best h = ex[i * NE];
-    if (evicts_before(h.u, h.pos, h.slot, ev)) ev = h;
-  }
   // (a candidate always exists: total > budget >= T + M; but where every score is NaN none compares below
   // another and the slot is -1: the new token leaves then)
   if (ev.slot < 0) {
@@ -547,32 +546,16 @@ __device__ __forceinline__ void close_head(const DecodeArgs& a, int64_t lbh, int
     ev.pos = p_last;
   }
   const int es = evict ? ev.slot : -1;
-  Best nx[kCand + 1];
-#pragma unroll
-  for (int i = 0; i <= kCand; ++i) nx[i] = Best{0.0, 0, -1};
-#pragma unroll
-  for (int k = 0; k < 4 * (kCand + 1); ++k) {
-    const Best h = ex[k / (kCand + 1) * NE + 1 + k % (kCand + 1)];
-    if (evicts_before(h.u, h.pos, h.slot, nx[kCand])) {
-      nx[kCand] = h;
-#pragma unroll
-      for (int i = kCand; i > 0; --i)
-        if (evicts_before(nx[i].u, nx[i].pos, nx[i].slot, nx[i - 1])) {
-          const Best t = nx[i - 1];
-          nx[i - 1] = nx[i];
-          nx[i] = t;
-        }
-    }
-  }
   int ci = -1;
 #pragma unroll
   for (int i = kCand - 1; i >= 0; --i)
     if (es >= 0 && cl[i] == es) ci = i;
   if (tid == 0) {  // the next step's candidates (every thread holds this step's list in registers)
     int k = 0;
-    for (int r = 0; r <= kCand && k < kCand; ++r) {
+#pragma unroll
+    for (int r = 0; r <= kCand; ++r) {
       int s = nx[r].slot;
-      if (s < 0 || s == es) continue;
+      if (k >= kCand || s < 0 || s == es) continue;
       if (es >= 0 && s == last) s = es;  // the last slot is about to move into the freed one
       a.cand[lbh * kCand + k++] = s;
     }
@@ -609,7 +592,9 @@ __device__ __forceinline__ void close_head(const DecodeArgs& a, int64_t lbh, int
     for (int i = 1; i < 4; ++i)
       if (better_match(sred[i], ired[i], ired[4 + i], m)) m = Best{sred[i], ired[i], ired[4 + i]};
   } else {
-    m = candidate_match(wcm_u, wcm_ps, ci);
+#pragma unroll
+    for (int i = 0; i < kCand; ++i)
+      if (i == ci) m = cm[i];
   }
   if (ci != 0) mr = load_merge_rows<T, D>(a, slot0, es, m.slot);
   T kl = T(), vl = T();

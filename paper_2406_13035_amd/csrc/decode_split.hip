@@ -111,7 +111,7 @@ __global__ __launch_bounds__(256) void decode_close_part(DecodeArgs a) {
         const int s = int(a.rec[x + 2 * G + kCand + i]);
         if (s >= 0) {
           const double u = a.rec[x + 2 * G + i];
-          const int p = a.cpos[slot0 + s];
+          const int p = int(a.rec[x + 2 * G + 2 * kCand + i]);
           if (better_match(u, p, s, cm[i])) cm[i] = Best{u, p, s};
         }
       }
@@ -346,7 +346,36 @@ __global__ __launch_bounds__(256) void decode_close_final(DecodeArgs a, OT* __re
     }
   }
   const bool evict = total > mt[1];
-  close_head<T, D>(a, lbh, slot0, total, evict, ev, low, cl, told, sred, ired, dred, wcm_u, wcm_ps, park_kv, mr);
+  // ---- per wavefront the first evicted, then the lowest of the next step's evictable tokens, joined by every thread
+  constexpr int NE = kCand + 2;
+  static_assert(4 * NE * 2 <= D, "the entries fit the exchange buffer");
+  Best* ex = reinterpret_cast<Best*>(dred);  // [4][NE]
+  {
+    const Best h = fast_wave_first_evicted(ev);
+    Best first[kCand + 1];
+    wave_first_entries(low, first);
+    if (lane == 0) {
+      ex[w * NE] = h;
+#pragma unroll
+      for (int r = 0; r <= kCand; ++r) ex[w * NE + 1 + r] = first[r];
+    }
+  }
+  lds_barrier();
+  ev = Best{0.0, 0, -1};
+  Best nx[kCand + 1];
+#pragma unroll
+  for (int i = 0; i <= kCand; ++i) nx[i] = Best{0.0, 0, -1};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const Best h = ex[i * NE];
+    if (evicts_before(h.u, h.pos, h.slot, ev)) ev = h;
+#pragma unroll
+    for (int r = 0; r <= kCand; ++r) insert_entry(nx, ex[i * NE + 1 + r]);
+  }
+  Best match[kCand];
+#pragma unroll
+  for (int i = 0; i < kCand; ++i) match[i] = candidate_match(wcm_u, wcm_ps, i);
+  close_head<T, D>(a, lbh, slot0, total, evict, ev, nx, cl, match, told, sred, ired, dred, park_kv, mr);
 }
 
 template <typename T, typename OT, int D, int G>
