@@ -183,7 +183,9 @@ __device__ __forceinline__ void head_normaliser(const DecodeArgs& a, int64_t bh,
 // entries takes 73 instead of 77 us, two steps of 24 layers with eight query heads per KV head 228 instead of 236.)
 // With the normaliser, the factors and the match formed by every wavefront for itself where a head has at most 64
 // sub-chunks, the matches' positions in the records and two instead of three reductions at the end, 32 layers one per call take
-// 833 instead of 874 us, a step of a 128-entry fp32 cache 13.8 instead of 15.3.
+// 833 instead of 874 us, a step of a 128-entry fp32 cache 13.8 instead of 15.3; with such a head's output rows by a wavefront
+// each, straight from registers, 812 and 12.4, and 16 sequences of 8 KV heads, four query heads each, 1423 -> 1375 for two
+// steps of 32 layers.
 template <typename T, typename OT, int D, int G>
 __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ out, const View& ov, int li, int b,
                                           int hk, int64_t lbh, int64_t slot0, int ch0, int total, int nsub, double* sred,
@@ -278,9 +280,12 @@ __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ 
       s[i] = int(ld_agent(&a.rec[x + 2 * G + kCand + i]));
       p[i] = int(ld_agent(&a.rec[x + 2 * G + 2 * kCand + i]));
     }
-    if constexpr (kEarlyRows) {
+    uint64_t row[16];  // the partial rows of query head w: two columns per lane of every chunk
 #pragma unroll
-      for (int g = 0; g < G; ++g) load_partial(g, rg);
+    for (int c = 0; c < 16; ++c) {
+      row[c] = 0;
+      if (c < nchunk && w < G && lane * 2 < D)
+        row[c] = ld_agent(reinterpret_cast<const uint64_t*>(a.pacc + (chunk_index(a, bh, ch0, c) * G + w) * D + lane * 2));
     }
     load_batch(set0, tid);
     const bool has = lane < nsub;
@@ -292,7 +297,34 @@ __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ 
       Mg[g] = fast_wave_max(has ? m[g] : -INFINITY);
       const double t = has ? exp(m[g] - Mg[g]) : 0.0;
       Lg[g] = fast_wave_sum(has ? l[g] * t : 0.0);
-      if (has) em[lane * G + g] = t / Lg[g];
+      const double f = t / Lg[g];
+      if (has) em[lane * G + g] = f;
+      // ---- the output row of query head w (G <= 4): the order of additions is that of the groups of threads below,
+      //      chunks r and r + RG first, then r = 0, 1, ...
+      if (g == w) {
+        double fc = has ? f : 0.0;  // exp(chunk maximum - max): the largest of its sub-chunks' factors
+        fc = max_f64(fc, dpp_f64<kDppXor1>(fc));
+        fc = max_f64(fc, dpp_f64<kDppXor2>(fc));
+        const float cf = float(fc);
+        float t0 = 0.f, t1 = 0.f;
+#pragma unroll
+        for (int r = 0; r < RG && r < 16; ++r) {
+          float n0 = 0.f, n1 = 0.f;
+#pragma unroll
+          for (int c = r; c < 16; c += RG) {
+            const float fr = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(cf), 4 * c));  // (0 past the last chunk)
+            n0 = fmaf(__uint_as_float(uint32_t(row[c])), fr, n0);
+            n1 = fmaf(__uint_as_float(uint32_t(row[c] >> 32)), fr, n1);
+          }
+          t0 = r ? t0 + n0 : n0;
+          t1 = r ? t1 + n1 : n1;
+        }
+        if (lane * 2 < D) {
+          OT* dst = out + li * ov.sn + b * ov.sb + (hk * G + g) * ov.sh + lane * 2;
+          dst[0] = Elem<OT>::from_f32(t0);
+          dst[1] = Elem<OT>::from_f32(t1);
+        }
+      }
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -407,6 +439,59 @@ __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ 
 #pragma unroll
     for (int i = 0; i < kCand; ++i) cm[i] = candidate_match(wcm_u, wcm_ps, i);
     mr = load_merge_rows<T, D>(a, slot0, cl[0], cm[0].slot);
+    // ---- output rows: thread (rg, c4) adds the chunks rg, rg + RG, ... of four columns, PB of every query
+    //      head in flight; the groups' sums are added in ascending order
+    float num[G][4];
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) num[g][e] = 0.f;
+#pragma unroll 1
+    for (int c0 = rg; c0 < nchunk; c0 += PB * RG) {
+      if (!kEarlyRows || c0 != rg) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) load_partial(g, c0);
+      }
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        const float4(&v)[PB] = pr[g];
+        double fc[PB];
+#pragma unroll
+        for (int u = 0; u < PB; ++u) {
+          const int cc = min(c0 + u * RG, nchunk - 1);
+          fc[u] = 0.0;  // exp(chunk maximum - max): the largest of its sub-chunks' factors
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (cc * 4 + i < nsub)
+              fc[u] = fmax(fc[u], em_lds ? em[(cc * 4 + i) * G + g]
+                                         : ld_agent(&a.rec[sub_index(a, bh, ch0, cc * 4 + i) * kRec + g]) / Lg[g]);
+        }
+#pragma unroll
+        for (int u = 0; u < PB; ++u) {
+          if (c0 + u * RG >= nchunk) break;
+          const float f = float(fc[u]);
+          num[g][0] = fmaf(v[u].x, f, num[g][0]);
+          num[g][1] = fmaf(v[u].y, f, num[g][1]);
+          num[g][2] = fmaf(v[u].z, f, num[g][2]);
+          num[g][3] = fmaf(v[u].w, f, num[g][3]);
+        }
+      }
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      lds_barrier();
+#pragma unroll
+      for (int e = 0; e < 4; ++e) fred[e * 256 + tid] = num[g][e];
+      lds_barrier();
+      if (tid < D) {  // column tid: element tid % 4 of the threads (rg, tid / 4)
+        const float* fr = fred + (tid % 4) * 256 + tid / 4;
+        float t = fr[0];
+#pragma unroll
+        for (int i = 1; i < RG; ++i) t += fr[i * C4];
+        out[li * ov.sn + b * ov.sb + (hk * G + g) * ov.sh + tid] = Elem<OT>::from_f32(t);
+      }
+      __builtin_amdgcn_sched_barrier(0);  // one query head after the other (registers)
+    }
   }
   const bool evict = total > mt[1];
   // Eq. 6 for the batch's slots, and the lowest scores of the tokens evictable at this step (Eq. 7-8 on count + 1
@@ -416,9 +501,8 @@ __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ 
   Best low[kCand + 1];
 #pragma unroll
   for (int i = 0; i <= kCand; ++i) low[i] = Best{0.0, 0, -1};
-  double* out_s = sred + 5;  // the score and slot of `out`
+  double* out_s = sred + 5;  // the score and slot of `out` (-1 on entry)
   int* out_j = ired + 9;
-  if (tid == 0) *out_j = -1;
   auto consider = [&](double x, int p, int j) {
     if (p >= a.n_sink && p <= next_out + 1) {
       if (p == next_out + 1) {
@@ -443,58 +527,6 @@ __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ 
       }
     }
   };
-  // ---- output rows: thread (rg, c4) adds the chunks rg, rg + RG, ... of four columns, PB of every query
-  //      head in flight; the groups' sums are added in ascending order
-  float num[G][4];
-#pragma unroll
-  for (int g = 0; g < G; ++g)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) num[g][e] = 0.f;
-#pragma unroll 1
-  for (int c0 = rg; c0 < nchunk; c0 += PB * RG) {
-    if (!kEarlyRows || c0 != rg) {
-#pragma unroll
-      for (int g = 0; g < G; ++g) load_partial(g, c0);
-    }
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      const float4(&v)[PB] = pr[g];
-      double fc[PB];
-#pragma unroll
-      for (int u = 0; u < PB; ++u) {
-        const int cc = min(c0 + u * RG, nchunk - 1);
-        fc[u] = 0.0;  // exp(chunk maximum - max): the largest of its sub-chunks' factors
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          if (cc * 4 + i < nsub)
-            fc[u] = fmax(fc[u], em_lds ? em[(cc * 4 + i) * G + g]
-                                       : ld_agent(&a.rec[sub_index(a, bh, ch0, cc * 4 + i) * kRec + g]) / Lg[g]);
-      }
-#pragma unroll
-      for (int u = 0; u < PB; ++u) {
-        const float f = c0 + u * RG < nchunk ? float(fc[u]) : 0.f;
-        num[g][0] = fmaf(v[u].x, f, num[g][0]);
-        num[g][1] = fmaf(v[u].y, f, num[g][1]);
-        num[g][2] = fmaf(v[u].z, f, num[g][2]);
-        num[g][3] = fmaf(v[u].w, f, num[g][3]);
-      }
-    }
-  }
-#pragma unroll
-  for (int g = 0; g < G; ++g) {
-    lds_barrier();
-#pragma unroll
-    for (int e = 0; e < 4; ++e) fred[e * 256 + tid] = num[g][e];
-    lds_barrier();
-    if (tid < D) {  // column tid: element tid % 4 of the threads (rg, tid / 4)
-      const float* fr = fred + (tid % 4) * 256 + tid / 4;
-      float t = fr[0];
-#pragma unroll
-      for (int i = 1; i < RG; ++i) t += fr[i * C4];
-      out[li * ov.sn + b * ov.sb + (hk * G + g) * ov.sh + tid] = Elem<OT>::from_f32(t);
-    }
-    __builtin_amdgcn_sched_barrier(0);  // one query head after the other (registers)
-  }
   // ---- score pass: batches of U slots per thread, the next one's loads in flight while one is worked on
 #pragma unroll 1
   for (seg0 = 0; seg0 < nsub; seg0 += kSegSubs) {
@@ -535,20 +567,25 @@ __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ 
   //      candidates are the others and `out`
   constexpr int NE = kCand + 1;
   Best* ex = reinterpret_cast<Best*>(dred);  // [4][NE]
-  Best nx[kCand + 1];
+  static_assert(kCand == 1, "lists of two");
+  Best nx[2];
   wave_first_entries(low, nx);
   if (lane == 0) {
-#pragma unroll
-    for (int r = 0; r < NE; ++r) ex[w * NE + r] = nx[r];
+    ex[w * NE] = nx[0];
+    ex[w * NE + 1] = nx[1];
   }
   lds_barrier();
-#pragma unroll
-  for (int r = 0; r < NE; ++r) nx[r] = ex[r];
-#pragma unroll
-  for (int i = NE; i < 4 * NE; ++i) insert_entry(nx, ex[i]);
+  {
+    Best l1[2] = {ex[2], ex[3]}, l2[2] = {ex[4], ex[5]}, l3[2] = {ex[6], ex[7]};
+    nx[0] = ex[0];
+    nx[1] = ex[1];
+    join_entries(nx, l1);
+    join_entries(l2, l3);
+    join_entries(nx, l2);
+  }
   const Best ev = nx[0];
   if (*out_j >= 0) {
-    if (evict && kCand == 1) nx[0] = nx[1], nx[1].slot = -1;  // (the evicted entry is no candidate)
+    if (evict) nx[0] = nx[1], nx[1].slot = -1;  // (the evicted entry is no candidate)
     insert_entry(nx, Best{*out_s, next_out + 1, *out_j});
   }
   close_head<T, D>(a, lbh, slot0, total, evict, ev, nx, cl, cm, told, sred, ired, dred, park_kv, mr);
@@ -1133,9 +1170,16 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  if (tid == 0)
+  // the staging area is free: it holds the closing code's exchange buffers
+  float* fred = reinterpret_cast<float*>(stage);
+  double* dred = reinterpret_cast<double*>(stage + 4 * 256 * sizeof(float));
+  double* sred = dred + D;
+  int* ired = reinterpret_cast<int*>(sred + 8);  // 16 words
+  if (tid == 0) {
     sh_last = (__hip_atomic_fetch_add(&a.ticket[lbh], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
                unsigned(entry.chunks - 1)) ? 1 : 0;
+    ired[9] = -1;  // (head_tail's `out`)
+  }
   __syncthreads();
   if (!sh_last) return;
   // Consumer side of the hand-over.  The other workgroups' results (rec, elog, pacc) are read
@@ -1144,11 +1188,6 @@ __global__ __launch_bounds__(256, G <= 4 && !(sizeof(T) == 4 && D == 128) ? 4 : 
   // above the ticket.  Plain loads in the closing code are limited to data that no other
   // workgroup of this launch writes: ctau, cand, meta of this head, and cscore and cpos of its older slots.
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-  // the staging area is free: it holds the closing code's exchange buffers
-  float* fred = reinterpret_cast<float*>(stage);
-  double* dred = reinterpret_cast<double*>(stage + 4 * 256 * sizeof(float));
-  double* sred = dred + D;
-  int* ired = reinterpret_cast<int*>(sred + 8);  // 16 words
   if (tid == 0) a.ctotal[lbh] = total > a.big_rows ? total : 0;
   if (total > a.big_rows) {
     // A very large head: two more launches close it (decode_close_part / _final).  All its

@@ -495,7 +495,7 @@ __device__ __forceinline__ Best candidate_match(const double* wcm_u, const int2*
   return m;
 }
 
-// The kCand + 1 first of two lists in eviction order, into `a` (both sorted; no entry is in both).
+// An entry more for the kCand + 1 first in eviction order.
 __device__ __forceinline__ void insert_entry(Best (&a)[kCand + 1], const Best& x) {
   if (evicts_before(x.u, x.pos, x.slot, a[kCand])) {
     a[kCand] = x;
@@ -507,6 +507,16 @@ __device__ __forceinline__ void insert_entry(Best (&a)[kCand + 1], const Best& x
         a[i] = t;
       }
   }
+}
+// The two first of two sorted lists of two (no entry is in both): half the comparisons of two insertions.
+__device__ __forceinline__ void join_entries(Best (&a)[2], const Best (&b)[2]) {
+  auto pick = [](bool first, const Best& x, const Best& y) {
+    return Best{first ? x.u : y.u, first ? x.pos : y.pos, first ? x.slot : y.slot};
+  };
+  const bool front = evicts_before(b[0].u, b[0].pos, b[0].slot, a[0]);
+  const Best x = pick(front, a[0], b[0]), y = pick(front, b[1], a[1]);
+  a[0] = pick(front, b[0], a[0]);
+  a[1] = pick(evicts_before(x.u, x.pos, x.slot, y), x, y);
 }
 // The kCand + 1 first of the lists of a wavefront's lanes, in eviction order; `low` is used up.
 __device__ __forceinline__ void wave_first_entries(Best (&low)[kCand + 1], Best (&out)[kCand + 1]) {

@@ -275,6 +275,47 @@ def test_a_head_whose_scores_are_nan_stays_inside_its_cache(cache_fp8, split_row
     assert np.isnan(s).all() and np.array_equal(np.sort(p), np.arange(budget)) and np.isfinite(K).all() and np.isfinite(V).all()
 
 
+@pytest.mark.parametrize("total", [1, 2, 63, 64, 65, 256, 257, 2049, 4095, 4096, 4097, 4353])
+@pytest.mark.parametrize("dtype,d,G", [("bf16", 128, 1), ("bf16", 128, 2), ("bf16", 128, 4), ("f32", 64, 1), ("f32", 128, 4)])
+def test_closing_work_of_heads_of_any_number_of_chunks(dtype, d, G, total):
+    """Output rows, scores and the evicted token at the edges of the forms of a head's closing work: one sub-chunk and one chunk,
+    as many chunks as there are groups of threads, one more, the last head whose wavefronts close it each
+    for itself (64 sub-chunks) and the first beyond; an infinite element of V in the last chunk."""
+    Hkv, n, bad = 3, total - 1, 3
+    g = np.random.default_rng(total + G)
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    ctx = binding.D2O(1, 1, G * Hkv, Hkv, d, 4480, total + 16, dtype=dtype, out_f32=True, beta=0.7)
+    ctx.d2o_layer_reserve(0, 4480, max(n, 1), 0)  # full: a token leaves, unless the cache is empty
+    caches = []
+    for h in range(Hkv):
+        K, V = (ref.round_storage(g.standard_normal((n, d)), dtype) for _ in range(2))
+        if h == 0 and n:
+            V[n - 1, bad] = np.inf
+        score, pos = 1.0 + g.random(n), np.arange(n)
+        if n:
+            ctx.d2o_cache_import(0, 0, h, K, V, score, pos.astype(np.int32), 0.1, n)
+        caches.append(ref.HeadCache(K, V, score.copy(), pos.astype(np.int64), 0.1 if n else float("nan"), dtype))
+    x = [ref.round_storage(g.standard_normal((1, 1, h, d)), dtype) for h in (G * Hkv, Hkv, Hkv)]
+    out = torch.empty(1, 1, G * Hkv, d, device="cuda:0")
+    next_pos = n if n else 4480
+    cache_v = [np.r_[c.V[np.isfinite(c.V)], x[2][0, 0, h]] for h, c in enumerate(caches)]
+    ctx.d2o_decode_step(0, 1, *(torch.from_numpy(a).to(tdt).cuda() for a in x), out)
+    got = out[0, 0].double().cpu().numpy()
+    for h, cache in enumerate(caches):
+        with np.errstate(invalid="ignore"):
+            want, _ = ref.decode_step_head(cache, x[0][0, 0, h * G:(h + 1) * G], x[1][0, 0, h], x[2][0, 0, h], next_pos, max(n, 1), 0, 0, 0.7)
+        cols = np.arange(d) != bad if h == 0 and n else np.arange(d) >= 0
+        assert np.isinf(got[h * G:(h + 1) * G, ~cols]).all()
+        # (64 rows, 3 terms, 4 wavefronts, up to 18 chunks, each a rounding of at most max |v|)
+        vmax = np.abs(cache_v[h]).max()
+        assert np.abs(got[h * G:(h + 1) * G, cols] - want[:, cols]).max() <= 90 * 2.0 ** -24 * vmax
+        sc, ps = ctx.d2o_cache_export(0, 0, h, total + 1)[2:4]
+        order = np.argsort(cache.pos)
+        assert np.array_equal(ps, cache.pos[order])
+        np.testing.assert_allclose(sc, cache.score[order], rtol=1e-13)
+    ctx.close()
+
+
 @pytest.mark.parametrize("G", [1, 2, 4, 8])
 @pytest.mark.parametrize("fp8", [False, True])
 def test_generation_step_outputs_to_fp32_accuracy(fp8, G):
