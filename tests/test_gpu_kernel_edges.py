@@ -498,6 +498,24 @@ def test_bf16_prompt_attention_block_edges(B, Hq, Hkv, n):
     ctx.close()
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,n", [(1, 2, 1, 1), (1, 3, 3, 700), (1, 16, 4, 2049), (2, 64, 16, 700)])
+def test_bf16_prompt_outputs_are_the_fp32_ones_rounded(B, Hq, Hkv, n):
+    """Both output types come from the same sums: bf16 rows, whose halves two lanes exchange before they are
+    stored, hold the fp32 rows rounded to nearest even, single blocks and pairs, rows up to the last alone."""
+    g = torch.Generator().manual_seed(n + Hq)
+    Q, K, V = (torch.randn(B, h, n, 128, generator=g).to(torch.bfloat16).cuda() for h in (Hq, Hkv, Hkv))
+    out = []
+    for out_f32 in (True, False):
+        ctx = binding.D2O(B, 1, Hq, Hkv, 128, n, n + 2, dtype="bf16", out_f32=out_f32)
+        O = torch.full((B, Hq, n + 1, 128), -7.0, dtype=ctx.out_dtype, device="cuda:0")
+        ctx.d2o_prefill_attend(0, Q, K, V, O[:, :, :n])
+        torch.cuda.synchronize()
+        assert (O[:, :, n] == -7.0).all()  # nothing behind the last row
+        out.append(O[:, :, :n].contiguous())
+        ctx.close()
+    assert torch.equal(out[0].to(torch.bfloat16), out[1])
+
+
 @pytest.mark.parametrize("n", [17, 20, 27, 32])
 def test_column_sums_add_a_tile_of_queries_by_halves(n):
     """The order of a score's fp32 additions decides near-tied selections, so it is held exactly: the 32 queries of a
