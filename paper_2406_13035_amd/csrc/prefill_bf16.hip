@@ -494,7 +494,10 @@ __global__ __launch_bounds__(64 * KW * QW) __attribute__((amdgpu_waves_per_eu(4,
                                                            const float* __restrict__ lse2, float* __restrict__ colsum,
                                                            double* __restrict__ varpart, int n, int npad, int G,
                                                            int nblk, int paired) {
-  constexpr int NW = KW * QW, NT = 64 * NW, BN = 32 * KW, NCH = TQ * 16 / NT;
+  constexpr int NW = KW * QW, NT = 64 * NW, BN = 32 * KW;
+  constexpr int NQI = TQ / 32 / QW;            // sub-tiles per wavefront and tile
+  constexpr int NP = TQ > 64 ? NQI : 1;        // parts in which the next tile is brought, one per sub-tile: fewer registers
+  constexpr int NCH = TQ * 16 / NT / NP;       // 16-byte loads per thread and part
   static_assert(BN <= NT && BN % 128 == 0 && TQ % (32 * QW) == 0 && BN % TQ == 0, "a thread per key, whole sub-tiles per wavefront");
   __shared__ __attribute__((aligned(16))) uint16_t Qs[2][TQ * kLdQ];
   __shared__ float ls[2][TQ];
@@ -530,57 +533,71 @@ __global__ __launch_bounds__(64 * KW * QW) __attribute__((amdgpu_waves_per_eu(4,
     for (int r = 0; r < 16; ++r) acc[r] = 0.f;
     u32x4 qr[NCH];
     float lr = 0.f;
-    auto issue = [&](int j) {
+    auto load16 = [&](int j, int i) {  // this thread's load i of tile j
+      const int c = tid + NT * i, row = c >> 4, col = (c & 15) * 8;
+      return *reinterpret_cast<const u32x4*>(qb + int64_t(min(kb0 + TQ * j + row, n - 1)) * qv.sn + col);
+    };
+    auto store16 = [&](int buf, int i, const u32x4& v) {
+      const int c = tid + NT * i, row = c >> 4, col = (c & 15) * 8;
+      *reinterpret_cast<u32x4*>(&Qs[buf][row * kLdQ + col]) = v;
+    };
+    auto issue = [&](int j, int part) {
       const int q0 = kb0 + TQ * j;
 #pragma unroll
-      for (int i = 0; i < NCH; ++i) {
-        const int c = tid + NT * i, row = c >> 4, col = (c & 15) * 8;
-        qr[i] = *reinterpret_cast<const u32x4*>(qb + int64_t(min(q0 + row, n - 1)) * qv.sn + col);
-      }
-      if (tid < TQ) lr = (q0 + tid < n) ? lrow[q0 + tid] : INFINITY;  // +inf => p = 0
+      for (int i = 0; i < NCH; ++i) qr[i] = load16(j, part * NCH + i);
+      if (part == 0 && tid < TQ) lr = (q0 + tid < n) ? lrow[q0 + tid] : INFINITY;  // +inf => p = 0
     };
-    auto stage = [&](int buf) {
+    auto stage = [&](int buf, int part) {
 #pragma unroll
-      for (int i = 0; i < NCH; ++i) {
-        const int c = tid + NT * i, row = c >> 4, col = (c & 15) * 8;
-        *reinterpret_cast<u32x4*>(&Qs[buf][row * kLdQ + col]) = qr[i];
-      }
-      if (tid < TQ) ls[buf][tid] = lr;
+      for (int i = 0; i < NCH; ++i) store16(buf, part * NCH + i, qr[i]);
+      if (part == 0 && tid < TQ) ls[buf][tid] = lr;
     };
     __syncthreads();  // the previous block's readers are done with both buffers
-    issue(nqt - 1);
-    stage(0);
+    {  // the first tile whole
+      issue(nqt - 1, 0);
+      u32x4 more[NP * NCH];
+#pragma unroll
+      for (int i = NCH; i < NP * NCH; ++i) more[i] = load16(nqt - 1, i);
+      stage(0, 0);
+#pragma unroll
+      for (int i = NCH; i < NP * NCH; ++i) store16(0, i, more[i]);
+    }
     __syncthreads();
     for (int it = 0; it < nqt; ++it) {
       const int jt = nqt - 1 - it, buf = it & 1, q0 = kb0 + TQ * jt;
-      if (jt > 0) issue(jt - 1);
+      if (NP == 1 && jt > 0) issue(jt - 1, 0);
 #pragma unroll
-      for (int qi = 0; qi < TQ / 32 / QW; ++qi) {
-        const int qt = qi * QW + qw, qbase = q0 + qt * 32;
-        if (qbase + 31 < kw0) continue;  // every query precedes every key of this wavefront
-        const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        f32x16 sacc = zero;
+      for (int qi = 0; qi < NQI; ++qi) {
+        if (NP > 1 && jt > 0) issue(jt - 1, qi);
+        // (where groups share a tile, a group's sub-tiles from the last to the first: the order of its additions does not
+        // depend on the tile's size)
+        const int qt = (QW > 1 ? NQI - 1 - qi : qi) * QW + qw, qbase = q0 + qt * 32;
+        if (qbase + 31 >= kw0) {  // (else every query precedes every key of this wavefront)
+          const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+          f32x16 sacc = zero;
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) {
-          const bf16x8 bqv = *reinterpret_cast<const bf16x8*>(&Qs[buf][(qt * 32 + m) * kLdQ + ks * 16 + h * 8]);
-          sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ak[ks], bqv, sacc, 0, 0, 0);
-        }
-        // register r: key kw0 + (r/4)*8 + 4h + r%4, query qbase + m
-        const float lq = ls[buf][qt * 32 + m];
-        const int query = qbase + m;
-        if (qbase < kw0 + 31) {  // diagonal tile: mask query < key
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int key = kw0 + (r >> 2) * 8 + h * 4 + (r & 3);
-            const float p = __builtin_amdgcn_exp2f(fmaf(sacc[r], scale2, -lq));
-            acc[r] += (query >= key) ? p : 0.f;
+          for (int ks = 0; ks < 8; ++ks) {
+            const bf16x8 bqv = *reinterpret_cast<const bf16x8*>(&Qs[buf][(qt * 32 + m) * kLdQ + ks * 16 + h * 8]);
+            sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ak[ks], bqv, sacc, 0, 0, 0);
           }
-        } else {
+          // register r: key kw0 + (r/4)*8 + 4h + r%4, query qbase + m
+          const float lq = ls[buf][qt * 32 + m];
+          const int query = qbase + m;
+          if (qbase < kw0 + 31) {  // diagonal tile: mask query < key
 #pragma unroll
-          for (int r = 0; r < 16; ++r) acc[r] += __builtin_amdgcn_exp2f(fmaf(sacc[r], scale2, -lq));
+            for (int r = 0; r < 16; ++r) {
+              const int key = kw0 + (r >> 2) * 8 + h * 4 + (r & 3);
+              const float p = __builtin_amdgcn_exp2f(fmaf(sacc[r], scale2, -lq));
+              acc[r] += (query >= key) ? p : 0.f;
+            }
+          } else {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[r] += __builtin_amdgcn_exp2f(fmaf(sacc[r], scale2, -lq));
+          }
         }
+        if (NP > 1 && jt > 0) stage(buf ^ 1, qi);
       }
-      if (jt > 0) stage(buf ^ 1);
+      if (NP == 1 && jt > 0) stage(buf ^ 1, 0);
       __syncthreads();
     }
     // add the 32 query columns held by the lanes of each half (by halves: the selection of a long prompt decides
@@ -667,10 +684,19 @@ hipError_t launch_prefill_bf16(d2o_ctx* c, int layer, View Q, View K, View V, Vi
   // many keys, the eight wavefronts sharing them and the tile's queries, and a block per workgroup instead
   // of two where there is a CU for each.  (32 heads: 1000 tokens 41, 25 and 21 us; 2048 tokens 61, 38 and 37; 4096 tokens
   // 118, 118; 8192 tokens 325, 374; 8 heads of 16384 tokens 386, 377; 4 heads of 14000 tokens 173 in pairs, 183 singly.)
-  if (int64_t((n + 511) / 512) * cf.n_q_heads * cf.batch < 512)
-    run_colsum<4, 2, 64>(c, Q, K, colsum, n, int64_t((n + 127) / 128) * cf.n_q_heads * cf.batch > 256, s);
-  else
+  if (int64_t((n + 511) / 512) * cf.n_q_heads * cf.batch < 512) {
+    const bool paired = int64_t((n + 127) / 128) * cf.n_q_heads * cf.batch > 256;
+    // Tiles of 128 queries, a barrier for twice the products, where a workgroup has its CU alone or many tiles (4 heads
+    // of 14000 tokens 174 -> 158 us, 16 of 4096 62 -> 57, 40 of 1500 29 -> 27.5, 32 of 4096 106 -> 98, 64 of 2048 59 -> 57.5);
+    // two workgroups per CU with few tiles hide each other's barriers (256 heads of 500 tokens 25 -> 29, 128 of 1024 33.5 -> 34.4).
+    const int64_t workgroups = (paired ? (n + 255) / 256 : (n + 127) / 128) * int64_t(cf.n_q_heads) * cf.batch;
+    if (workgroups <= 256 || n >= 2048)
+      run_colsum<4, 2, 128>(c, Q, K, colsum, n, paired, s);
+    else
+      run_colsum<4, 2, 64>(c, Q, K, colsum, n, paired, s);
+  } else {  // (in tiles of 128: 32 heads of 32768 tokens 4.21 -> 4.15 ms, 128 of 2048 85 -> 88 us, 256 of 700 38 -> 44)
     run_colsum<8, 1, 64>(c, Q, K, colsum, n, true, s);
+  }
   return hipGetLastError();
 }
 

@@ -475,6 +475,7 @@ def test_the_evicted_keys_norm_has_one_order_of_additions(d, G):
 @pytest.mark.parametrize("B,Hq,Hkv,n", [
     (1, 2, 1, 1), (1, 2, 2, 127), (2, 2, 1, 128), (1, 4, 1, 129), (1, 8, 8, 255), (1, 8, 2, 257), (1, 3, 3, 700),
     (1, 16, 4, 2049),     # 128-row blocks up to the last that the chip holds at once (272), key blocks in pairs
+    (1, 16, 4, 2305),     # key blocks of 128 in pairs, with tiles of 128 queries, the last of one
     (2, 64, 16, 700),     # 256-row blocks in pairs with a partial last one
     (2, 128, 16, 513),    # ... and 256-key blocks
 ])
