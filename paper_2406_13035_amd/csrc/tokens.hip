@@ -341,9 +341,12 @@ __device__ __forceinline__ float evicted_norm(const bf16x8 (&be)[8]) {
 }
 
 // The margin of a row's best two, in the un-normalised domain (ie: the row's inverse norm), and whether they are too close;
-// also true for NaN / equal / zero norm.
+// also true for NaN / equal / zero norm, and where the best is no key: padding wins where no retained key has a value (all of
+// them are NaN), and the values of the padding differ among themselves by far more than the margin.
 __device__ __forceinline__ float margin_of(float ie) { return ie > 0.f ? kAmbiguous / ie : INFINITY; }
-__device__ __forceinline__ bool is_ambiguous(float best, float second, float ie) { return !(best - second >= margin_of(ie)); }
+__device__ __forceinline__ bool is_ambiguous(float best, float second, int bi, int nret, float ie) {
+  return bi >= nret || !(best - second >= margin_of(ie));
+}
 __device__ __forceinline__ void flag_row(float best, float ie, int erank, int epos, int64_t base, int64_t bh,
                                          FlaggedRow* amb_list, int32_t* amb_cnt) {
   amb_list[base + atomicAdd(&amb_cnt[bh], 1)] = FlaggedRow{erank, epos, best - margin_of(ie), 0};
@@ -521,7 +524,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
   const int row = e0 + w * 32 + m;
   const bool live = row < nevi;
   const int erank = min(row, nevi - 1);
-  const bool amb = is_ambiguous(best, second, ie);  // (both lanes agree; unless it is, they have the same candidate)
+  const bool amb = is_ambiguous(best, second, bi, nret, ie);  // (both lanes agree; unless it is, they have the same candidate)
   u32x4 y[8];
   const uint16_t* yrow = rk + int64_t(amb ? 0 : bi) * 128 + h * 8;
 #pragma unroll
@@ -641,7 +644,7 @@ __global__ __launch_bounds__(64 * kFewWaves) void match_filter_few(const uint16_
   if (tid < 32) {
 #pragma unroll
     for (int u = 1; u < kFewWaves; ++u) join_best(best, second, bi, best_s[u][tid], second_s[u][tid], rank_s[u][tid]);
-    const bool live = e0 + tid < nevi, amb = is_ambiguous(best, second, ie);
+    const bool live = e0 + tid < nevi, amb = is_ambiguous(best, second, bi, nret, ie);
     if (live && amb) flag_row(best, ie, erank, epos, bh * npad, bh, amb_list, amb_cnt);
     rank_s[0][tid] = live && !amb ? bi : -1;
   }

@@ -820,6 +820,39 @@ def test_matching_where_every_row_has_equal_candidates(Hkv, n, budget, copies):
     ctx.close()
 
 
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+@pytest.mark.parametrize("nret", [1, 5, 8, 31, 33, 63, 64, 90])  # (the padding of the last tile wins, ties with itself, or there is none)
+@pytest.mark.parametrize("Hkv,n", [(3, 300), (9, 1300)])  # launches of few and of many rows
+def test_matching_against_retained_keys_that_are_not_finite(Hkv, n, nret, value):
+    """A head whose retained keys all hold a NaN or an infinity: its evicted tokens match the first retained key (NaN: with
+    similarity 0, infinity: with none), never a row behind the last one, and the other heads' caches are those that they are
+    beside a finite head.  In another head one evicted key is NaN."""
+    g = np.random.default_rng(nret)
+    K, V = (ref.round_storage(g.standard_normal((1, Hkv, n, 128)), "bf16") for _ in range(2))
+    score = g.random((1, Hkv, n)).astype(np.float32)
+    order = [np.argsort(-score[0, h, :n - 1]) for h in range(Hkv)]
+    K[0, 2, order[2][-1], 9] = np.nan
+    others = []
+    for bad in (False, True):
+        if bad:
+            K[0, 1, np.r_[order[1][:nret - 1], n - 1], 77] = value
+        ctx = binding.D2O(1, 1, Hkv, Hkv, 128, n, nret + 8, dtype="bf16")
+        ctx.d2o_scores_import(0, score)
+        ctx.d2o_compress_layer(0, *(torch.from_numpy(x).to(torch.bfloat16).cuda() for x in (K, V)), nret, 1)
+        for h in range(Hkv):
+            ret, evi, tgt, us, ps = ctx.d2o_prefill_events(0, 0, h, n)
+            with np.errstate(invalid="ignore"):
+                want, at = ref.match(K[0, h][evi], K[0, h][ret])
+                passed = ref.prefill_threshold(want)[1]
+            assert np.array_equal(tgt, ret[at]) and np.allclose(us, want, rtol=0, atol=1e-14, equal_nan=True), f"head {h}"
+            if h == 1 and bad:
+                assert np.array_equal(ps, passed)
+        others.append([ctx.d2o_cache_export(0, 0, h, nret) for h in range(Hkv) if h != 1])
+        ctx.close()
+    for a, b in zip(*others):
+        assert all(np.array_equal(x, y, equal_nan=True) for x, y in zip(a, b))
+
+
 @pytest.mark.parametrize("fp8", [False, True])
 def test_attention_beside_the_compression_of_another_layer(fp8):
     """Attention and compression keep no scratch memory in common: layer 1's attention (grouped queries) on one stream,
