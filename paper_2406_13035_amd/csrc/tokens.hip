@@ -661,17 +661,20 @@ __global__ __launch_bounds__(64 * kFewWaves) void match_filter_few(const uint16_
   }
 }
 
-// The flagged rows (a list in no particular order; the rows are independent of each other).  A workgroup takes 32 of
+// The flagged rows (a list in no particular order; the rows are independent of each other).  A workgroup takes 32 or 8 of
 // them at a time: its wavefronts sweep the retained keys again and list, in LDS, every key whose fp32
 // cosine reaches the row's threshold (the best value among them: the arithmetic is the first sweep's), up to kMaxCand;
 // then sixteen lanes per row decide among them exactly, first maximum in ascending retained order.  A row with more of
 // them, or none (a zero norm, a key that is not finite), is searched exhaustively by its wavefront.  Half a
-// percent of the rows is flagged, so the launch has a few workgroups per head, which stride over the list, and what bounds
+// percent of the rows is flagged, so the launch has a few workgroups per head, and what bounds
 // it is the instructions of one wavefront: hits as bits instead of sixteen branches, addresses through buffer
 // descriptors, eight wavefronts (sixteen share the SIMDs and spill: 8.8 -> 16.5 us).  32 heads x 4096 tokens, a fifth kept, 8.8 us;
 // 32768, a tenth kept, 19.8; as a sweep in blocks of 128 rows by eight key ranges, most of them empty, 11 and 44.
+// Where many rows are flagged (repeated keys, zeros), all workgroups share what lies beyond each head's first blocks; where few
+// are, a block has a row per wavefront, as the exhaustive search is a wavefront's own.  (With the head's own workgroups only and
+// blocks of 32, one head of 32768 tokens, a tenth kept: every row tied in pairs 835 us, now 72, in nines 43.5 and 3.1 ms, a tenth
+// of the evicted keys zero 4632 and 778 us; one of 4096 with a tenth zero 111 and 37.)
 constexpr int kFlaggedWaves = 8;
-constexpr int kFlaggedBlocks = 16;  // workgroups per head at most
 __global__ __launch_bounds__(64 * kFlaggedWaves) void match_flagged(const uint16_t* __restrict__ K, View kv,
                                                                     const uint16_t* __restrict__ cK,
                                                                     const int32_t* __restrict__ meta, int64_t slots,
@@ -681,124 +684,156 @@ __global__ __launch_bounds__(64 * kFlaggedWaves) void match_flagged(const uint16
                                                                     const int32_t* __restrict__ amb_cnt,
                                                                     double* __restrict__ ustar, int32_t* __restrict__ tgt,
                                                                     int npad, HeadGrid hg) {
-  static_assert(kFlaggedWaves * 4 >= 32, "sixteen lanes per row");
+  static_assert(kFlaggedWaves * 4 == 32, "sixteen lanes per row");
   constexpr int D = 128;
   __shared__ __attribute__((aligned(16))) uint16_t tile[kFlaggedWaves][32 * kLdM];
   __shared__ __attribute__((aligned(16))) float rin[kFlaggedWaves][32];  // of the wavefront's sub-tile
   __shared__ int ncand[32], clist[32][kMaxCand];
-  const int hk = hg.head(), b = hg.sequence();
-  const int64_t bh = hg.index();
-  const int namb = amb_cnt[bh], nret = cnt[bh * 2];
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, m = lane & 31, h = lane >> 5;
-  const uint16_t* rk = cK + (bh * slots + meta[bh * 4 + 0]) * D;
-  const uint16_t* kb = K + b * kv.sb + hk * kv.sh;
-  const FlaggedRow* list = amb_list + bh * npad;
+  const int rr = w + lane / 16 * kFlaggedWaves, tc = tid % 16;  // the row of the exact comparison
+  // ---- a head's own workgroups take its first blocks of rows, as many for every head; where a head has more, all
+  //      workgroups share what is left of all heads
+  int most = 0, least = 0x7FFFFFFF;  // flagged rows of a head
+  for (int x = lane; x < hg.heads; x += 64) {
+    most = max(most, amb_cnt[x]);
+    least = min(least, amb_cnt[x]);
+  }
+  const int nblk = hg.blocks();
+  const bool more = __any(most > nblk * 32);
+  int rounds = 1;  // of a head's own workgroups
+  if (more) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) least = min(least, __shfl_xor(least, o, 64));
+    rounds = max(__builtin_amdgcn_readfirstlane(least) / (nblk * 32), 1);
+  }
+  const int few = amb_cnt[hg.index()];
+  int group = few <= 8 * min(nblk, 256 / hg.heads) ? 8 : 32;  // rows of a block: one per wavefront where there is a CU for each
+  int head = hg.index(), e0 = hg.block() * group;
+  int at = 0, before = 0;  // the rest: the head in turn, and the blocks of the heads before it
 #pragma unroll 1
-  for (int e0 = hg.block() * 32; e0 < namb; e0 += hg.blocks() * 32) {
-    const int rr = tid / 16, tc = tid % 16;  // the row of the exact comparison (half of the wavefronts have one)
-    const FlaggedRow fr = list[min(e0 + m, namb - 1)], own = list[min(e0 + rr, namb - 1)];
-    const float mythr = e0 + m < namb ? fr.thr : INFINITY;
-    const bool valid = rr < 32 && e0 + rr < namb;
-    const uint16_t* erow = kb + int64_t(fr.pos) * kv.sn;
-    bf16x8 be[8];
+  for (int i = blockIdx.x, round = 1;;) {
+    const int64_t bh = head;
+    const int namb = min(amb_cnt[bh], e0 + group), nret = cnt[bh * 2];
+    if (e0 < namb) {
+      const uint16_t* rk = cK + (bh * slots + meta[bh * 4 + 0]) * D;
+      const uint16_t* kb = K + head / hg.Hkv * kv.sb + head % hg.Hkv * kv.sh;
+      const FlaggedRow* list = amb_list + bh * npad;
+      const FlaggedRow fr = list[min(e0 + m, namb - 1)], own = list[min(e0 + rr, namb - 1)];
+      const float mythr = e0 + m < namb ? fr.thr : INFINITY;
+      const bool valid = e0 + rr < namb;
+      const uint16_t* erow = kb + int64_t(fr.pos) * kv.sn;
+      bf16x8 be[8];
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) be[ks] = *reinterpret_cast<const bf16x8*>(erow + ks * 16 + h * 8);
-    const u32x4 x = *reinterpret_cast<const u32x4*>(kb + int64_t(own.pos) * kv.sn + tc * 8);
-    if (tid < 32) ncand[tid] = 0;
-    __syncthreads();
-    sweep_keys<kFlaggedWaves>(rk, invn + bh * npad, nret, w, lane, be, tile[w], rin[w], [&](const f32x16& s, int j) {
-      uint32_t hits = 0;
+      for (int ks = 0; ks < 8; ++ks) be[ks] = *reinterpret_cast<const bf16x8*>(erow + ks * 16 + h * 8);
+      const u32x4 x = *reinterpret_cast<const u32x4*>(kb + int64_t(own.pos) * kv.sn + tc * 8);
+      if (tid < 32) ncand[tid] = 0;
+      __syncthreads();
+      sweep_keys<kFlaggedWaves>(rk, invn + bh * npad, nret, w, lane, be, tile[w], rin[w], [&](const f32x16& s, int j) {
+        uint32_t hits = 0;
 #pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
-        const f32x4 ri = *reinterpret_cast<const f32x4*>(&rin[w][g4 * 8 + h * 4]);
+        for (int g4 = 0; g4 < 4; ++g4) {
+          const f32x4 ri = *reinterpret_cast<const f32x4*>(&rin[w][g4 * 8 + h * 4]);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) hits |= s[g4 * 4 + i] * ri[i] >= mythr ? 1u << (g4 * 4 + i) : 0u;
-      }
-      while (hits) {
-        const int r = __ffs(hits) - 1, key = j * 32 + (r >> 2) * 8 + h * 4 + (r & 3);
-        hits &= hits - 1;
-        const int k = key < nret ? atomicAdd(&ncand[m], 1) : kMaxCand;
-        if (k < kMaxCand) clist[m][k] = key;
-      }
-    });
-    __syncthreads();
-    // ---- exactly: sixteen lanes per row, two candidates in flight
-    const int listed = valid ? ncand[rr] : 0, ncd = listed <= kMaxCand ? listed : 0;
-    double best = -2.0;
-    int bj = 0;
-    int nloop = max(ncd, __shfl_xor(ncd, 16, 64));
-    nloop = max(nloop, __shfl_xor(nloop, 32, 64));
-    for (int q = 0; q < nloop; q += 2) {
-      int j[2];
-      u32x4 y[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        j[i] = q + i < ncd ? clist[rr][q + i] : 0;
-        y[i] = *reinterpret_cast<const u32x4*>(rk + int64_t(j[i]) * D + tc * 8);
-      }
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const double u = cosine_by_16(x, y[i]);
-        if (q + i < ncd && (u > best || (u == best && j[i] < bj))) {
-          best = u;
-          bj = j[i];
+          for (int i = 0; i < 4; ++i) hits |= s[g4 * 4 + i] * ri[i] >= mythr ? 1u << (g4 * 4 + i) : 0u;
         }
-      }
-    }
-    unsigned long long todo = __ballot(valid && ncd == 0 && tc == 0);
-    while (todo) {  // one row at a time, the wavefront's lanes striding over the retained keys
-      const int src = __ffsll((long long)todo) - 1;  // first lane of the row to serve
-      todo &= todo - 1;
-      double* ke = reinterpret_cast<double*>(tile[w]);  // the row as fp64
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      double ne = 0.0;
+        while (hits) {
+          const int r = __ffs(hits) - 1, key = j * 32 + (r >> 2) * 8 + h * 4 + (r & 3);
+          hits &= hits - 1;
+          const int k = key < nret ? atomicAdd(&ncand[m], 1) : kMaxCand;
+          if (k < kMaxCand) clist[m][k] = key;
+        }
+      });
+      __syncthreads();
+      // ---- exactly: sixteen lanes per row, two candidates in flight
+      const int listed = valid ? ncand[rr] : 0, ncd = listed <= kMaxCand ? listed : 0;
+      double best = -2.0;
+      int bj = 0;
+      int nloop = max(ncd, __shfl_xor(ncd, 16, 64));
+      nloop = max(nloop, __shfl_xor(nloop, 32, 64));
+      for (int q = 0; q < nloop; q += 2) {
+        int j[2];
+        u32x4 y[2];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const double v = double(__uint_as_float(e & 1 ? x[e / 2] & 0xFFFF0000u : x[e / 2] << 16));
-        if (lane / 16 == src / 16) ke[tc * 8 + e] = v;
-        ne = fma(v, v, ne);
-      }
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      const double sne = sqrt(lane_f64(row16_sum(ne), src));
-      double fb = -2.0;
-      int fj = 0x7FFFFFFF;
-      for (int j = lane; j < nret; j += 64) {
-        double dot = 0.0, nr = 0.0;
-#pragma unroll 1
-        for (int c = 0; c < D; c += 8) {
-          const u32x4 y = *reinterpret_cast<const u32x4*>(rk + int64_t(j) * D + c);
+        for (int i = 0; i < 2; ++i) {
+          j[i] = q + i < ncd ? clist[rr][q + i] : 0;
+          y[i] = *reinterpret_cast<const u32x4*>(rk + int64_t(j[i]) * D + tc * 8);
+        }
 #pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const double v = double(__uint_as_float(e & 1 ? y[e / 2] & 0xFFFF0000u : y[e / 2] << 16));
-            dot = fma(ke[c + e], v, dot);
-            nr = fma(v, v, nr);
+        for (int i = 0; i < 2; ++i) {
+          const double u = cosine_by_16(x, y[i]);
+          if (q + i < ncd && (u > best || (u == best && j[i] < bj))) {
+            best = u;
+            bj = j[i];
           }
         }
-        const double den = sne * sqrt(nr);
-        const double u = den > 0.0 ? dot / den : 0.0;
-        if (u > fb) {  // j ascends within a lane: strict > keeps the first maximum
-          fb = u;
-          fj = j;
-        }
       }
+      unsigned long long todo = __ballot(valid && ncd == 0 && tc == 0);
+      while (todo) {  // one row at a time, the wavefront's lanes striding over the retained keys
+        const int src = __ffsll((long long)todo) - 1;  // first lane of the row to serve
+        todo &= todo - 1;
+        double* ke = reinterpret_cast<double*>(tile[w]);  // the row as fp64
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        double ne = 0.0;
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) {
-        const double ob = __shfl_xor(fb, o, 64);
-        const int oj = __shfl_xor(fj, o, 64);
-        if (ob > fb || (ob == fb && oj < fj)) {
-          fb = ob;
-          fj = oj;
+        for (int e = 0; e < 8; ++e) {
+          const double v = double(__uint_as_float(e & 1 ? x[e / 2] & 0xFFFF0000u : x[e / 2] << 16));
+          if (lane / 16 == src / 16) ke[tc * 8 + e] = v;
+          ne = fma(v, v, ne);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const double sne = sqrt(lane_f64(row16_sum(ne), src));
+        double fb = -2.0;
+        int fj = 0x7FFFFFFF;
+        for (int j = lane; j < nret; j += 64) {
+          double dot = 0.0, nr = 0.0;
+#pragma unroll 1
+          for (int c = 0; c < D; c += 8) {
+            const u32x4 y = *reinterpret_cast<const u32x4*>(rk + int64_t(j) * D + c);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              const double v = double(__uint_as_float(e & 1 ? y[e / 2] & 0xFFFF0000u : y[e / 2] << 16));
+              dot = fma(ke[c + e], v, dot);
+              nr = fma(v, v, nr);
+            }
+          }
+          const double den = sne * sqrt(nr);
+          const double u = den > 0.0 ? dot / den : 0.0;
+          if (u > fb) {  // j ascends within a lane: strict > keeps the first maximum
+            fb = u;
+            fj = j;
+          }
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+          const double ob = __shfl_xor(fb, o, 64);
+          const int oj = __shfl_xor(fj, o, 64);
+          if (ob > fb || (ob == fb && oj < fj)) {
+            fb = ob;
+            fj = oj;
+          }
+        }
+        if (lane == src) {
+          best = fb;
+          bj = fj;
         }
       }
-      if (lane == src) {
-        best = fb;
-        bj = fj;
-      }
+      if (tc == 0 && valid) store_match(best, bj, bh * npad + own.erank, ustar, tgt);
+      __syncthreads();  // the lists are read before they are emptied
     }
-    if (tc == 0 && valid) store_match(best, bj, bh * npad + own.erank, ustar, tgt);
-    __syncthreads();  // the lists are read before they are emptied
+    if (!more) return;
+    if (round++ < rounds) {
+      e0 += nblk * 32;
+      continue;
+    }
+    auto rest = [&](int x) { return max((amb_cnt[x] + 31) / 32 - nblk * rounds, 0); };
+    while (at < hg.heads && i - before >= rest(at)) before += rest(at++);
+    if (at == hg.heads) return;
+    head = at;
+    group = 32;
+    e0 = (nblk * rounds + i - before) * 32;
+    i += gridDim.x;
   }
 }
 
@@ -1241,7 +1276,9 @@ hipError_t launch_match(d2o_ctx* c, int layer, View K, int n, hipStream_t s) {
                                                                    c->amb_list, c->amb_cnt, c->m_ustar, c->m_tgt, c->npad, hg);
     }
     KernelTimer kt(c, D2O_K_MATCH_REFINE, s);
-    match_flagged<<<std::min((me + 31) / 32, kFlaggedBlocks) * heads, 64 * kFlaggedWaves, 0, s>>>(
+    // Sixteen workgroups per head, or two for every CU where few heads leave the chip idle (one fits a CU at a time).
+    const int per_head = std::min((me + 31) / 32, std::max(16, 512 / heads));
+    match_flagged<<<per_head * heads, 64 * kFlaggedWaves, 0, s>>>(
         k, K, rows, meta, stride, c->invnorm, c->sel_cnt, c->amb_list, c->amb_cnt, c->m_ustar, c->m_tgt, c->npad, hg);
   } else {
     const dim3 grid((me + 3) / 4, cf.n_kv_heads, cf.batch);

@@ -820,6 +820,39 @@ def test_matching_where_every_row_has_equal_candidates(Hkv, n, budget, copies):
     ctx.close()
 
 
+@pytest.mark.parametrize("tied", [[0], [5]])  # the only head; one of eight
+def test_matching_of_a_head_whose_rows_all_tie_takes_the_whole_chip(tied):
+    """Every row of a head flagged, each with more candidates than a list holds: more rows than the head's own workgroups take
+    at once.  The first of equal keys wins, and the time is that of this head's work: eight such heads take longer."""
+    n, budget, copies = 8192, 1638, 9
+    g = torch.Generator().manual_seed(tied[0])
+
+    def matched(Hkv, heads):
+        K, V = (torch.randn(1, Hkv, n, 128, generator=g).to(torch.bfloat16) for _ in range(2))
+        score = torch.rand(1, Hkv, n, generator=g)
+        for h in heads:
+            kept = score[0, h, :n - 1].argsort(descending=True)[:budget - 1].sort().values
+            K[0, h, kept] = K[0, h, kept][torch.randperm(budget - 1, generator=g) % -(-budget // copies)]
+        ctx = binding.D2O(1, 3, Hkv, Hkv, 128, n, 3 * (budget + 8), dtype="bf16")
+        ctx.d2o_timing_enable(True)
+        ms = []
+        for layer in range(3):
+            ctx.d2o_scores_import(layer, score.numpy())
+            ctx.d2o_timing_read("match_refine")
+            ctx.d2o_compress_layer(layer, K.cuda(), V.cuda(), budget, 1)
+            ms.append(ctx.d2o_timing_read("match_refine")[0])
+        for h in {heads[0], Hkv - 1}:
+            ret, evi, tgt, us, _ = ctx.d2o_prefill_events(2, 0, h, n)
+            x = K[0, h].double().numpy()
+            want, at = ref.match(x[evi], x[ret])
+            assert np.array_equal(tgt, ret[at]) and np.allclose(us, want, rtol=0, atol=1e-14)
+        ctx.close()
+        return min(ms)
+
+    one, eight = matched(8 if tied[0] else 1, tied), matched(8, range(8))
+    assert one <= 0.6 * eight, f"one head {one:.3f} ms, eight {eight:.3f} ms"
+
+
 @pytest.mark.parametrize("value", [np.nan, np.inf])
 @pytest.mark.parametrize("nret", [1, 5, 8, 31, 33, 63, 64, 90])  # (the padding of the last tile wins, ties with itself, or there is none)
 @pytest.mark.parametrize("Hkv,n", [(3, 300), (9, 1300)])  # launches of few and of many rows
