@@ -102,7 +102,9 @@ typedef struct {
  * compressed cache, per-key scores and statistics for the context's life; `scratch` holds
  * per-call temporaries (contents are undefined between calls, except that the prefill
  * events of the most recent d2o_compress_layer call stay readable until the next prefill
- * call).  Errors: INVALID_ARG, UNSUPPORTED. */
+ * call).  With max_append > 1 the scratch also holds a copy of one layer's rows, up to 192 MB of
+ * softmax terms (in the copy's place as far as it goes), and per row and query of a block
+ * (d + 12) / 64 bytes for every KV head.  Errors: INVALID_ARG, UNSUPPORTED. */
 int d2o_workspace_bytes(const d2o_config* cfg, size_t* persistent, size_t* scratch);
 
 /* Creates a context over caller-owned device workspaces (256-byte aligned, at least the

@@ -114,20 +114,22 @@ void layout(d2o_ctx* x, char* persistent, char* scratch, size_t* pbytes, size_t*
   const size_t ap = c.max_append > 1 ? 1 : 0;  // the position-ordered copy exists only when blocks can be appended
   s.take_raw(x->st_K, f8 * bh * np * d * es);
   s.take_raw(x->st_V, f8 * bh * np * d * es);
-  s.take_raw(x->app_K, ap * bh * np * d * es);
-  s.take_raw(x->app_V, ap * bh * np * d * es);
+  x->ap_maxq = ap ? int((size_t(c.max_append) * G + 15) / 16 * 16) : 0;
+  x->ap_nch = ap ? int(std::min<int64_t>(np, c.slots_per_seq) / kChunk + 2) : 0;
+  const size_t tile_terms = x->ap_nch * bh * kChunk * 16 * sizeof(double), tiles = x->ap_maxq / 16;
+  x->ap_tiles = ap ? int(std::min(tiles, std::max<size_t>(4, kBlockTermBytes / tile_terms))) : 0;
+  // one place for the terms of a block's attention and, when that is done, the ordered copy
+  const size_t copy_bytes = ap * bh * np * d * es;  // of K, and of V (a multiple of 256)
+  s.take(x->ap_term, std::max(2 * copy_bytes, x->ap_tiles * tile_terms) / sizeof(double));
+  x->app_K = x->ap_term;
+  x->app_V = x->ap_term ? x->ap_term + copy_bytes / sizeof(double) : nullptr;
   s.take(x->app_score, ap * bh * np);
   s.take(x->app_pos, ap * bh * np);
   s.take(x->app_rank, ap * bh * np);
   s.take(x->app_n, ap * bh);
-  x->ap_maxq = ap ? int((size_t(c.max_append) * G + 15) / 16 * 16) : 0;
-  x->ap_nch = ap ? int(std::min<int64_t>(np, c.slots_per_seq) / kChunk + 2) : 0;
   s.take(x->ap_q, ap * bh * x->ap_maxq * d);
   s.take(x->ap_stat, ap * x->ap_nch * bh * x->ap_maxq * 2);
   s.take(x->ap_gmax, ap * x->ap_nch * bh * x->ap_maxq * 4);
-  const size_t tile_terms = x->ap_nch * bh * kChunk * 16, tiles = x->ap_maxq / 16;
-  x->ap_tiles = ap ? int(std::min(tiles, std::max<size_t>(4, kBlockTermBytes / (tile_terms * sizeof(double))))) : 0;
-  s.take(x->ap_term, x->ap_tiles * tile_terms);
   s.take(x->ap_norm, ap * bh * x->ap_maxq * 2);
   s.take(x->ap_out, ap * x->ap_nch * bh * x->ap_maxq * d);
   s.take(x->ap_spart, ap * kMaxQuerySlices * bh * x->ap_nch * kChunk);

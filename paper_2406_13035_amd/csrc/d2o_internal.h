@@ -14,8 +14,9 @@ namespace d2o {
 constexpr int kPartRecDoubles = 32;  // doubles of a part record of the split closing kernels
 constexpr int kMaxQuerySlices = 16;  // block append: workgroups that share the queries of a (head, chunk)
 // Block append: bytes that the exponentials of a pass's query tiles may take (8 per row and query), but room for four
-// tiles, a workgroup's round, at least.  What one kernel writes and the next reads once then stays inside the chip's 256 MB
-// memory-side cache.
+// tiles, a workgroup's round, at least.  Up to this bound what one kernel writes and the next reads once stays inside the chip's
+// 256 MB memory-side cache.  They lie where the position-ordered copy of K and V is made afterwards, which is as large as the
+// four tiles of bf16 rows (but for a part of a chunk per head), so that a context needs no more than these bytes beside it.
 constexpr size_t kBlockTermBytes = size_t(192) << 20;
 constexpr int kMinAutoSplitRows = 6144, kMaxAutoSplitRows = 16384;  // bounds of the automatic split_rows (below the lower one the two extra launches cost more than a single closing workgroup)
 constexpr int kChunk = 256;        // cache slots handled by one workgroup in the decode kernels
@@ -137,7 +138,7 @@ struct d2o_ctx {
   void* st_V = nullptr;          // [B][Hkv][npad][d]
   // multi-token append: the cache in ascending token position (block-level Eq. 7-12 run on it)
   void* app_K = nullptr;         // [B][Hkv][npad][d]
-  void* app_V = nullptr;         // [B][Hkv][npad][d]
+  void* app_V = nullptr;         // [B][Hkv][npad][d]  (both in the place of ap_term)
   double* app_score = nullptr;   // [B][Hkv][npad] cumulative scores, fp64
   int32_t* app_pos = nullptr;    // [B][Hkv][npad] token positions, ascending
   int32_t* app_rank = nullptr;   // [B][Hkv][npad] rank of every cache slot's position

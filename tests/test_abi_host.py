@@ -80,6 +80,27 @@ def test_scratch_of_attention_is_its_own(lib, dtype, per_row):
     assert grown == 2 * heads * rows * per_row
 
 
+@pytest.mark.parametrize("heads,slots", [(32, 131072), (8, 131072), (128, 8192), (1, 4096)])
+def test_scratch_of_block_appends_is_bounded(lib, heads, slots):
+    """Scratch grows with the block's size by what a query takes in the arrays that hold all of them; the softmax terms of a pass,
+    eight bytes per slot and query, lie in the place of the position-ordered copy and take no more than 192 MB beside it, or what
+    four tiles of queries need for the last, partial chunks of the heads."""
+    def scratch(max_append):
+        cfg = binding.d2o_config(1, 2, heads, heads, 128, slots, slots, binding.D2O_BF16, 0, 0.7, float("nan"), 0)
+        cfg.max_append = max_append
+        p, s = C.c_size_t(), C.c_size_t()
+        assert lib.d2o_workspace_bytes(C.byref(cfg), C.byref(p), C.byref(s)) == 0
+        return s.value
+    chunks = slots // 256 + 2
+    per_query = heads * (chunks * (16 + 32 + 4 * 128) + 8 * 128 + 16)  # statistics, maxima and partial outputs; the query, its norm
+    place = [scratch(m) - m * per_query for m in (16, 64, 512, 2048)]
+    copy = heads * slots * 2 * 128 * 2
+    other = scratch(1) + copy + heads * slots * (8 + 4 + 4) + 16 * heads * chunks * 256 * 8 + 4 * heads  # scores, positions, slices' sums
+    beside = max((192 << 20) - copy, heads * 512 * 64 * 8, 0)
+    for p in place:
+        assert 0 <= p - other <= beside + 16 * 256, (p - other) / 2 ** 20
+
+
 def test_allocate_budgets_matches_oracle_bit_for_bit(lib):
     g = np.random.default_rng(2024)
     for trial in range(300):

@@ -588,26 +588,33 @@ def test_block_append_with_a_value_at_the_end_of_the_range(dtype, d, fp8, value,
     ctx.close()
 
 
-def test_block_append_in_several_passes_over_the_queries():
-    """128 heads and 20 tiles of queries, whose exponentials take two passes, against one of the heads alone in a single
-    pass: the same outputs, and scores equal but for the order in which a row's fp64 sums over 20 tiles are added."""
-    m, d, budget, Hkv, B = 320, 128, 512, 32, 4
+@pytest.mark.parametrize("budget,m,slots", [
+    (512, 320, 1024),   # ten tiles of queries at a time
+    (7200, 80, 7296),   # four, the fewest
+])
+def test_block_append_in_several_passes_over_the_queries(budget, m, slots):
+    """128 heads whose exponentials take several passes over the query tiles, against one of the heads alone in a single
+    pass: the same outputs, and scores equal but for the order in which a row's fp64 sums over the tiles are added."""
+    d, Hkv, B = 128, 32, 4
     g = np.random.default_rng(3)
     K, V = (ref.round_storage(g.standard_normal((budget, d)), "bf16") for _ in range(2))
     score = 1.0 + g.random(budget)
     x = [torch.from_numpy(g.standard_normal((1, 1, m, d))).to(torch.bfloat16).cuda() for _ in range(3)]
     got = []
     for b, h in ((1, 1), (B, Hkv)):
-        ctx = binding.D2O(b, 1, h, h, d, 1024, 1024, dtype="bf16", out_f32=True, max_append=m)
-        ctx.d2o_layer_reserve(0, 700, budget, 100)
-        ctx.d2o_cache_import(0, b - 1, h - 1, K, V, score, np.arange(budget, dtype=np.int32), 0.1, budget)
+        ctx = binding.D2O(b, 1, h, h, d, slots, slots, dtype="bf16", out_f32=True, max_append=m)
+        ctx.d2o_layer_reserve(0, budget, budget, 100)
+        full = sorted({(0, 0), (b // 2, h // 2), (b - 1, h - 1)})
+        for i, j in full:
+            ctx.d2o_cache_import(0, i, j, K, V, score, np.arange(budget, dtype=np.int32), 0.1, budget)
         out = torch.empty(b, h, m, d, device="cuda:0")
         ctx.d2o_append_chunk(0, *(t.expand(b, h, m, d).contiguous() for t in x), out)
-        got.append((out[b - 1, h - 1].cpu().numpy(), *ctx.d2o_cache_export(0, b - 1, h - 1, budget + m)))
+        got += [(out[i, j].cpu().numpy(), *ctx.d2o_cache_export(0, i, j, budget + m)) for i, j in full]
         ctx.close()
-    for i in (0, 1, 2, 4):  # outputs, K, V, positions
-        assert np.array_equal(got[0][i], got[1][i])
-    np.testing.assert_allclose(got[1][3], got[0][3], rtol=320 * 2.0 ** -53)  # 320 additions
+    for other in got[1:]:
+        for i in (0, 1, 2, 4):  # outputs, K, V, positions
+            assert np.array_equal(got[0][i], other[i])
+        np.testing.assert_allclose(other[3], got[0][3], rtol=m * 2.0 ** -53)  # m additions
 
 
 @pytest.mark.parametrize("positions,next_pos", [
