@@ -550,14 +550,13 @@ def test_block_append_of_few_query_tiles(dtype, d, fp8, m, G):
         _append_against_oracle(dtype, storage, d, G, m, budget, np.arange(400), 400)
 
 
-@pytest.mark.parametrize("dtype,d,fp8", [("bf16", 128, False), ("bf16", 128, True), ("f32", 64, False)])
-@pytest.mark.parametrize("value", [np.inf, 2.0 ** 127, 2.0 ** 110])
+@pytest.mark.parametrize("dtype,d,fp8,value", [
+    (dtype, d, fp8, value) for dtype, d, fp8 in (("bf16", 128, False), ("bf16", 128, True), ("f32", 64, False))
+    for value in (np.inf, 2.0 ** 127, 2.0 ** 110) if not (fp8 and np.isinf(value))])  # (an 8-bit row has no infinities)
 @pytest.mark.parametrize("m", [3, 40])  # wavefronts that share a tile, and one per tile
 def test_block_append_with_a_value_at_the_end_of_the_range(dtype, d, fp8, value, m):
     """One element of V infinite: its column of the outputs is infinite; near the end of the range: the outputs that 64
     bits give, in that column and in the others, to fp32 accuracy (300 additions; an 8-bit row keeps four bits)."""
-    if fp8 and np.isinf(value):
-        return  # (an 8-bit row has no infinities)
     n, row, col = 300, 70, 5
     g = np.random.default_rng(m)
     K, V = (ref.round_storage(g.standard_normal((n, d)), dtype) for _ in range(2))
@@ -584,7 +583,7 @@ def test_block_append_with_a_value_at_the_end_of_the_range(dtype, d, fp8, value,
         else:
             assert abs(got[i, col] - want[col]) <= 300 * 2.0 ** -24 * want[col]
         bound = 300 * 2.0 ** -24 * (p @ np.abs(vals[:n + i + 1]))
-        assert (np.abs(got[i] - want)[others] <= bound[others]).all()
+        assert (np.abs(got[i, others] - want[others]) <= bound[others]).all()
     ctx.close()
 
 
