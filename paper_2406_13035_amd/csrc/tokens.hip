@@ -672,8 +672,8 @@ __global__ __launch_bounds__(64 * kFewWaves) void match_filter_few(const uint16_
 // 32768, a tenth kept, 19.8; as a sweep in blocks of 128 rows by eight key ranges, most of them empty, 11 and 44.
 // Where many rows are flagged (repeated keys, zeros), all workgroups share what lies beyond each head's first blocks; where few
 // are, a block has a row per wavefront, as the exhaustive search is a wavefront's own.  (With the head's own workgroups only and
-// blocks of 32, one head of 32768 tokens, a tenth kept: every row tied in pairs 835 us, now 72, in nines 43.5 and 3.1 ms, a tenth
-// of the evicted keys zero 4632 and 778 us; one of 4096 with a tenth zero 111 and 37.)
+// blocks of 32, one head of 32768 tokens, a tenth kept: every row tied in pairs 835 us, now 73, in nines 43.5 and 3.1 ms, a tenth
+// of the evicted keys zero 4632 and 770 us; one of 4096 with a tenth zero 111 and 37.)
 constexpr int kFlaggedWaves = 8;
 __global__ __launch_bounds__(64 * kFlaggedWaves) void match_flagged(const uint16_t* __restrict__ K, View kv,
                                                                     const uint16_t* __restrict__ cK,
@@ -706,21 +706,30 @@ __global__ __launch_bounds__(64 * kFlaggedWaves) void match_flagged(const uint16
     for (int o = 32; o > 0; o >>= 1) least = min(least, __shfl_xor(least, o, 64));
     rounds = max(__builtin_amdgcn_readfirstlane(least) / (nblk * 32), 1);
   }
-  const int few = amb_cnt[hg.index()];
-  int group = few <= 8 * min(nblk, 256 / hg.heads) ? 8 : 32;  // rows of a block: one per wavefront where there is a CU for each
-  int head = hg.index(), e0 = hg.block() * group;
-  int at = 0, before = 0;  // the rest: the head in turn, and the blocks of the heads before it
+  // the head in work
+  int64_t bh;
+  int namb, nret;
+  const uint16_t *rk, *kb;
+  const FlaggedRow* list;
+  auto take_head = [&](int x) {
+    bh = x;
+    namb = amb_cnt[x];
+    nret = cnt[bh * 2];
+    rk = cK + (bh * slots + meta[bh * 4 + 0]) * D;
+    kb = K + x / hg.Hkv * kv.sb + x % hg.Hkv * kv.sh;
+    list = amb_list + bh * npad;
+  };
+  take_head(hg.index());
+  int group = namb <= 8 * min(nblk, 256 / hg.heads) ? 8 : 32;  // rows of a block: one per wavefront where there is a CU for each
+  int e0 = hg.block() * group;
+  int at = 0, before = 0;  // the rest: the 64 heads in turn, and the blocks of the heads before them
 #pragma unroll 1
   for (int i = blockIdx.x, round = 1;;) {
-    const int64_t bh = head;
-    const int namb = min(amb_cnt[bh], e0 + group), nret = cnt[bh * 2];
-    if (e0 < namb) {
-      const uint16_t* rk = cK + (bh * slots + meta[bh * 4 + 0]) * D;
-      const uint16_t* kb = K + head / hg.Hkv * kv.sb + head % hg.Hkv * kv.sh;
-      const FlaggedRow* list = amb_list + bh * npad;
-      const FlaggedRow fr = list[min(e0 + m, namb - 1)], own = list[min(e0 + rr, namb - 1)];
-      const float mythr = e0 + m < namb ? fr.thr : INFINITY;
-      const bool valid = e0 + rr < namb;
+    const int end = min(namb, e0 + group);
+    if (e0 < end) {
+      const FlaggedRow fr = list[min(e0 + m, end - 1)], own = list[min(e0 + rr, end - 1)];
+      const float mythr = e0 + m < end ? fr.thr : INFINITY;
+      const bool valid = e0 + rr < end;
       const uint16_t* erow = kb + int64_t(fr.pos) * kv.sn;
       bf16x8 be[8];
 #pragma unroll
@@ -827,12 +836,23 @@ __global__ __launch_bounds__(64 * kFlaggedWaves) void match_flagged(const uint16
       e0 += nblk * 32;
       continue;
     }
-    auto rest = [&](int x) { return max((amb_cnt[x] + 31) / 32 - nblk * rounds, 0); };
-    while (at < hg.heads && i - before >= rest(at)) before += rest(at++);
-    if (at == hg.heads) return;
-    head = at;
+    // the block i of what is left of the heads, of 64 heads at a time
+    int last, total;  // blocks up to and with the lane's head
+    for (;; at += 64, before += total) {
+      if (at >= hg.heads) return;
+      last = at + lane < hg.heads ? max((amb_cnt[at + lane] + 31) / 32 - nblk * rounds, 0) : 0;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(last, o, 64);
+        if (lane >= o) last += t;
+      }
+      total = __builtin_amdgcn_readlane(last, 63);
+      if (i - before < total) break;
+    }
+    const int x = __popcll(__ballot(last <= i - before));
+    take_head(at + x);
     group = 32;
-    e0 = (nblk * rounds + i - before) * 32;
+    e0 = (nblk * rounds + i - before - (x > 0 ? __builtin_amdgcn_readlane(last, max(x - 1, 0)) : 0)) * 32;
     i += gridDim.x;
   }
 }

@@ -804,7 +804,7 @@ def test_matching_of_few_and_of_many_rows(B, Hkv, n, budget):
 
 
 @pytest.mark.parametrize("copies", [2, 8, 9])  # a row's list of candidates: short, full, too long (searched exhaustively)
-@pytest.mark.parametrize("Hkv,n,budget", [(1, 300, 90), (3, 300, 90), (2, 1500, 333), (9, 1300, 90)])
+@pytest.mark.parametrize("Hkv,n,budget", [(1, 300, 90), (3, 300, 90), (2, 1500, 333), (9, 1300, 90), (70, 900, 90)])
 def test_matching_where_every_row_has_equal_candidates(Hkv, n, budget, copies):
     """Every retained key `copies` times over, so that every evicted row is flagged: launches of few and of many
     rows, more flagged rows than a launch has places for at once; a key of zeros on either side."""
