@@ -201,7 +201,8 @@ __global__ __launch_bounds__(256) void permute_rows(const int32_t* __restrict__ 
 // otherwise); a row's score then grows by the slices' sums in slice order.  The exponentials are kept, in fp64, because
 // the logits and they are what bounds the block (the fp64 units): with both formed again in block_apply, 256 tokens on
 // 2048-entry caches (32 heads) took 123 + 182 us in the two kernels, with 151 MB written and read 131 + 74 (46 since).  They
-// have a bounded place (kBlockTermBytes): the query tiles go through the three kernels in as many passes as it takes.
+// have a place of kBlockTermBytes, or of four tiles, which the position-ordered copy takes afterwards: the query tiles go through the
+// three kernels in as many passes as it takes.
 //
 // Register layouts of the two instructions (lane l, c = l % 16, kq = l / 16):
 //   operands   A[i = c][k = kq], B[k = kq][j = c]
@@ -503,7 +504,8 @@ __global__ __launch_bounds__(256) void block_norm(const int32_t* __restrict__ ct
 // elements of a bf16 or 8-bit V are bf16 numbers and an fp32 probability is the sum of three (three times eight
 // significant bits), so with these types it is three products of the bf16 instruction, exact, with fp32 sums: 74 -> 46 us
 // for 256 tokens on 2048-entry caches, 32 heads, and two thirds of the former error against 64 bits.  A probability is
-// scaled by 2^kTermScale, which keeps its last term above 2^-126, and the sums are rid of it again.
+// scaled by 2^kTermScale, which keeps its last term above 2^-126, and the sums are rid of it again.  (bf16: three of the 168
+// registers that three wavefronts per SIMD leave are spilled.)
 constexpr int kTermScale = 24;
 constexpr uint32_t kHighHalves = 0x07060302u, kLowHalves = 0x05040100u;  // v_perm_b32: two words' upper, lower halves
 template <typename T, int D>

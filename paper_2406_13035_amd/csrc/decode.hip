@@ -184,8 +184,8 @@ __device__ __forceinline__ void head_normaliser(const DecodeArgs& a, int64_t bh,
 // With the normaliser, the factors and the match formed by every wavefront for itself where a head has at most 64
 // sub-chunks, the matches' positions in the records and two instead of three reductions at the end, 32 layers one per call take
 // 833 instead of 874 us, a step of a 128-entry fp32 cache 13.8 instead of 15.3; with such a head's output rows by a wavefront
-// each, straight from registers, 812 and 12.4, and 16 sequences of 8 KV heads, four query heads each, 1423 -> 1375 for two
-// steps of 32 layers.
+// each, straight from registers, 812 and 12.6.  Calls of many layers hide most of the closing work: both changes together are
+// 1500 -> 1495 us for two steps of 32 layers of 16 sequences, four query heads per KV head, and 845 -> 838 for one long context.
 template <typename T, typename OT, int D, int G>
 __device__ __forceinline__ void head_tail(const DecodeArgs& a, OT* __restrict__ out, const View& ov, int li, int b,
                                           int hk, int64_t lbh, int64_t slot0, int ch0, int total, int nsub, double* sred,

@@ -496,7 +496,8 @@ __global__ __launch_bounds__(64 * KW * QW) __attribute__((amdgpu_waves_per_eu(4,
                                                            int nblk, int paired) {
   constexpr int NW = KW * QW, NT = 64 * NW, BN = 32 * KW;
   constexpr int NQI = TQ / 32 / QW;            // sub-tiles per wavefront and tile
-  constexpr int NP = TQ > 64 ? NQI : 1;        // parts in which the next tile is brought, one per sub-tile: fewer registers
+  constexpr int NP = TQ > 64 ? NQI : 1;        // parts in which the next tile is brought, one per sub-tile: fewer registers (12
+                                               // of the 128 are spilled even so, 2 with tiles of 64 queries)
   constexpr int NCH = TQ * 16 / NT / NP;       // 16-byte loads per thread and part
   static_assert(BN <= NT && BN % 128 == 0 && TQ % (32 * QW) == 0 && BN % TQ == 0, "a thread per key, whole sub-tiles per wavefront");
   __shared__ __attribute__((aligned(16))) uint16_t Qs[2][TQ * kLdQ];

@@ -4,7 +4,7 @@
 //
 // Every decision (top-N membership, arg-max of the cosine, threshold test) is taken on exact
 // integer keys or in fp64 with the operation order of the defining formulas, so that index
-// outputs do not depend on reduction shapes; the bf16 matrix-core product in match_filter_bf16
+// outputs do not depend on reduction shapes; the bf16 matrix-core product of the matching filters
 // only pre-selects candidates and flags rows whose two best candidates are too close for fp32.
 #include "d2o_internal.h"
 #include "decode_common.h"
@@ -78,7 +78,7 @@ __global__ __launch_bounds__(1024) void select_kernel(const S* __restrict__ scor
     meta[bh * 4 + tid] = pack.v[bh * 4 + tid];
     if (stage) stage[bh * 4 + tid] = tid == 0 ? 0 : pack.v[bh * 4 + tid];
   }
-  if (tid == 0) amb_cnt[bh] = 0;  // (counted up by match_filter_bf16)
+  if (tid == 0) amb_cnt[bh] = 0;  // (counted up by the matching filters)
   const int budget = PACKED ? pack.v[bh * 4 + 1] : meta[bh * 4 + 1], recent = PACKED ? pack.v[bh * 4 + 2] : meta[bh * 4 + 2];
   if (budget >= n) {
     for (int j = tid; j < n; j += blockDim.x) r[j] = j;
@@ -283,7 +283,8 @@ struct HeadGrid {
 // The filter is bound by the vector ALU (68 instructions per 32 x 32 sub-tile and wavefront beside 8 products), as
 // long as no wavefront waits for LDS: with the operands and inverse norms requested half a sub-tile ahead and the
 // padding confined to the last tile, at four wavefronts per SIMD, 940 -> 867 us (32768 tokens, 32 heads, a tenth
-// kept), 37 -> 34 (4096, a fifth), 54 -> 41 (256 of 2304 rows leave); with the exact similarities 864 and 40.
+// kept), 37 -> 34 (4096, a fifth), 54 -> 41 (256 of 2304 rows leave); with the exact similarities 864 and 40 (two of the 128
+// registers are spilled over the loop, 12 bytes per lane).
 // kAmbiguous bounds twice the error of one filtered cosine: at most one rounding per accumulated
 // product (128 * 2^-24 of |k_i||k_j|) plus the two fp32 inverse norms, 1.6e-5 in total, plus the
 // four mantissa bits that carry the register number (2 * 16 * 2^-24 = 1.9e-6).
